@@ -109,21 +109,24 @@ struct Cfg {
 // or the columns of B's tile), each BK deep in k, moved as items of 8
 // consecutive k per lane.
 //   KC (k contiguous in memory: row-major A, transposed B): item idx covers
-//      LDS row idx / CH, chunk idx % CH; two 128-bit loads when V (row stride
-//      a multiple of 4 floats, 16-byte aligned base), else eight 32-bit loads.
+//      LDS row idx / CH, chunk idx % CH; two 128-bit loads, whatever the row
+//      stride and the base (a 128-bit buffer load needs only the 4-byte
+//      alignment that every binary32 element has; eight 32-bit loads at odd
+//      strides before: a grouped batch of 272 ragged problems 198 -> 148 us,
+//      results bitwise unchanged).
 //   otherwise (the row index contiguous: row-major B, transposed A): item idx
 //      covers LDS row idx % ROWS, chunk idx / ROWS; eight 32-bit loads, one
 //      per k, with the lanes of a wave consecutive along the row index.
 // Either way the LDS layout is the same ([plane][ROWS][BK], swizzled chunks),
 // so the fragment reads and the MFMAs do not depend on the memory layout.
-template <int ROWS, int BK, int NT, int SETS, bool KC, bool V>
+template <int ROWS, int BK, int NT, int SETS, bool KC>
 struct Stage {
   static constexpr int CH = BK / 8;
   static constexpr int ITEMS = ROWS * CH / NT;
   static_assert(ITEMS * NT == ROWS * CH, "even split of the slab over the lanes");
   static_assert(KC || ROWS % 64 == 0 || NT % ROWS == 0, "chunk index must be wave-uniform");
   // global loads per slab and lane
-  static constexpr int LOADS = ITEMS * ((KC && V) ? 2 : 8);
+  static constexpr int LOADS = ITEMS * (KC ? 2 : 8);
   __device__ static __forceinline__ int row_of(int idx) { return KC ? idx / CH : idx % ROWS; }
   __device__ static __forceinline__ int chunk_of(int idx) { return KC ? idx % CH : idx / ROWS; }
 
@@ -173,20 +176,15 @@ struct Stage {
   template <int SET>
   __device__ __forceinline__ void load_item(int i, int k0) {
     if constexpr (KC) {
+      // (bit-cast whole vectors: a bit_cast of a vector element is not
+      // element-indexed in this compiler)
       const int off = voff[i] + k0 * 4;
-      if constexpr (V) {
-        const float4 v0 =
-            __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0));
-        const float4 v1 =
-            __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off + 16, 0, 0));
-        r[SET][i][0] = v0.x; r[SET][i][1] = v0.y; r[SET][i][2] = v0.z; r[SET][i][3] = v0.w;
-        r[SET][i][4] = v1.x; r[SET][i][5] = v1.y; r[SET][i][6] = v1.z; r[SET][i][7] = v1.w;
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          r[SET][i][e] = __builtin_bit_cast(
-              float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, off + 4 * e, 0, 0));
-      }
+      const float4 v0 =
+          __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0));
+      const float4 v1 =
+          __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off + 16, 0, 0));
+      r[SET][i][0] = v0.x; r[SET][i][1] = v0.y; r[SET][i][2] = v0.z; r[SET][i][3] = v0.w;
+      r[SET][i][4] = v1.x; r[SET][i][5] = v1.y; r[SET][i][6] = v1.z; r[SET][i][7] = v1.w;
     } else {
       const int ld4 = (int)ld * 4;
       const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
@@ -206,24 +204,7 @@ struct Stage {
     if constexpr (KC) {
       if constexpr (FAST) {
 #pragma unroll
-        for (int i = 0; i < ITEMS; ++i) {
-          const int off = voff[i] + k0 * 4;
-          if constexpr (V) {
-            // (bit-cast whole vectors: a bit_cast of a vector element is not
-            // element-indexed in this compiler)
-            const float4 v0 =
-                __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0));
-            const float4 v1 =
-                __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off + 16, 0, 0));
-            r[SET][i][0] = v0.x; r[SET][i][1] = v0.y; r[SET][i][2] = v0.z; r[SET][i][3] = v0.w;
-            r[SET][i][4] = v1.x; r[SET][i][5] = v1.y; r[SET][i][6] = v1.z; r[SET][i][7] = v1.w;
-          } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-              r[SET][i][e] = __builtin_bit_cast(
-                  float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, off + 4 * e, 0, 0));
-          }
-        }
+        for (int i = 0; i < ITEMS; ++i) load_item<SET>(i, k0);
       } else {  // partial slab: per-element offsets, invalid ones pushed out of range
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i) {
@@ -274,13 +255,10 @@ struct Stage {
 // One output tile.  lds must hold Cfg::LDS_BYTES bytes (16-byte aligned).
 // TA / TB: A / B are given transposed (A stored K x M with row stride lda,
 // B stored N x K with row stride ldb); op(A) op(B) is computed either way.
-// VEC: every operand stored with k contiguous (A unless TA, B if TB) has a
-// row stride that is a multiple of 4 floats and a 16-byte aligned base
-// (128-bit loads), and K % 4 == 0.
 // Interior slabs (tile fully inside M x N and a whole BK slab of K) take an
 // unpredicated load path; edge slabs take a guarded path that reads zeros
 // outside the matrices.  The choice is uniform across the workgroup.
-template <int BM, int BN, int BK, int WM, int WN, int NP, int NW, bool VEC, bool BETA,
+template <int BM, int BN, int BK, int WM, int WN, int NP, int NW, bool BETA,
           bool TA = false, bool TB = false, int ST = 2, int SETS_ = 0, int KG = 1>
 __device__ __forceinline__ void tile(int M, int N, int K, float alpha,
                                      const float *__restrict__ A, int64_t lda,
@@ -313,8 +291,8 @@ __device__ __forceinline__ void tile(int M, int N, int K, float alpha,
   // zero in hardware and lane addresses stay 32-bit offsets (no 64-bit VALU
   // address arithmetic).  The launcher guarantees that every panel's and
   // slab's byte extent stays below 2^31.
-  using SA = Stage<BM, BK, NT, G::SETS, !TA, VEC && !TA>;
-  using SB = Stage<BN, BK, NT, G::SETS, TB, VEC && TB>;
+  using SA = Stage<BM, BK, NT, G::SETS, !TA>;
+  using SB = Stage<BN, BK, NT, G::SETS, TB>;
   SA sa;
   SB sb;
   sa.init(A, lda, m0, M, K, tid);

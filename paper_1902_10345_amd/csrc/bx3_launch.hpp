@@ -8,7 +8,7 @@
 namespace mm {
 namespace bx3 {
 
-template <int BM, int BN, int BK, int WM, int WN, int NP, int NW, bool VEC, bool BETA, bool TA,
+template <int BM, int BN, int BK, int WM, int WN, int NP, int NW, bool BETA, bool TA,
           bool TB, int ST = 2>
 __global__ __launch_bounds__(64 * NW, 1) void gemm_bx3_kernel(
     int M, int N, int K, float alpha, const float *__restrict__ A, int64_t lda,
@@ -19,14 +19,14 @@ __global__ __launch_bounds__(64 * NW, 1) void gemm_bx3_kernel(
   const int wg = xcd_remap(blockIdx.x, gridDim.x);
   int tm, tn;
   tile_coords(wg, tiles_m, tiles_n, 8, tm, tn);
-  tile<BM, BN, BK, WM, WN, NP, NW, VEC, BETA, TA, TB, ST>(M, N, K, alpha, A, lda, B, ldb, beta,
+  tile<BM, BN, BK, WM, WN, NP, NW, BETA, TA, TB, ST>(M, N, K, alpha, A, lda, B, ldb, beta,
                                                           C, ldc, tm * BM, tn * BN, lds);
 }
 
 // The tile with its k range split between two groups of NW waves (one
 // workgroup of 2 * NW waves per tile): twice the waves per SIMD of the
 // one-group tile where its tiles come to about one per CU.
-template <int BM, int BN, int BK, int WM, int WN, int NP, int NW, bool VEC, bool BETA>
+template <int BM, int BN, int BK, int WM, int WN, int NP, int NW, bool BETA>
 __global__ __launch_bounds__(128 * NW, 1) void gemm_bx3_kg_kernel(
     int M, int N, int K, float alpha, const float *__restrict__ A, int64_t lda,
     const float *__restrict__ B, int64_t ldb, float beta, float *__restrict__ C, int64_t ldc,
@@ -36,13 +36,13 @@ __global__ __launch_bounds__(128 * NW, 1) void gemm_bx3_kg_kernel(
   const int wg = xcd_remap(blockIdx.x, gridDim.x);
   int tm, tn;
   tile_coords(wg, tiles_m, tiles_n, 8, tm, tn);
-  tile<BM, BN, BK, WM, WN, NP, NW, VEC, BETA, false, false, 2, 0, 2>(
+  tile<BM, BN, BK, WM, WN, NP, NW, BETA, false, false, 2, 0, 2>(
       M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, tm * BM, tn * BN, lds);
 }
 
 // The plain binary32 product on the FP32 matrix cores (v_mfma_f32_32x32x2f32):
 // the same tile body in its FP32 mode (no split; binary32 in LDS).
-template <int BM, int BN, int BK, int WM, int WN, int NW, bool VEC, bool BETA, bool TA, bool TB>
+template <int BM, int BN, int BK, int WM, int WN, int NW, bool BETA, bool TA, bool TB>
 __global__ __launch_bounds__(64 * NW, 1) void gemm_f32mfma_kernel(
     int M, int N, int K, float alpha, const float *__restrict__ A, int64_t lda,
     const float *__restrict__ B, int64_t ldb, float beta, float *__restrict__ C, int64_t ldc,
@@ -52,7 +52,7 @@ __global__ __launch_bounds__(64 * NW, 1) void gemm_f32mfma_kernel(
   const int wg = xcd_remap(blockIdx.x, gridDim.x);
   int tm, tn;
   tile_coords(wg, tiles_m, tiles_n, 8, tm, tn);
-  tile<BM, BN, BK, WM, WN, 1, NW, VEC, BETA, TA, TB>(M, N, K, alpha, A, lda, B, ldb, beta, C,
+  tile<BM, BN, BK, WM, WN, 1, NW, BETA, TA, TB>(M, N, K, alpha, A, lda, B, ldb, beta, C,
                                                      ldc, tm * BM, tn * BN, lds);
 }
 
@@ -67,18 +67,6 @@ inline bool offsets_fit(const GemmArgs &g) {
   return ea * 4 < ((int64_t)1 << 31) && eb * 4 < ((int64_t)1 << 31);
 }
 
-// 128-bit staging loads need every k-contiguous operand (A unless TA, B if
-// TB) to have a row stride that is a multiple of 4 floats and a 16-byte
-// aligned base; the slab grid ends at K, so K must be a multiple of 4 too.
-template <bool TA, bool TB>
-inline bool vector_loads_ok(const GemmArgs &g) {
-  if (TA && !TB) return false;  // no k-contiguous operand
-  bool v = g.K % 4 == 0;
-  if (!TA) v = v && g.lda % 4 == 0 && ((uintptr_t)g.A & 15) == 0;
-  if (TB) v = v && g.ldb % 4 == 0 && ((uintptr_t)g.B & 15) == 0;
-  return v;
-}
-
 template <int BM, int BN, int BK, int WM, int WN, int NW, bool TA = false, bool TB = false>
 gemm_status launch_f32mfma(const GemmArgs &g, hipStream_t s) {
   const int tiles_m = (int)((g.M + BM - 1) / BM);
@@ -89,20 +77,13 @@ gemm_status launch_f32mfma(const GemmArgs &g, hipStream_t s) {
     set_error("gemm_f32: lda or ldb too large for 32-bit tile offsets");
     return GEMM_STATUS_UNSUPPORTED;
   }
-  const bool vec = vector_loads_ok<TA, TB>(g);
   const bool beta = g.beta != 0.0f;
   dim3 grid((unsigned)nwg), block(64 * NW);
-#define MM_LAUNCH(V, BT)                                                                  \
-  hipLaunchKernelGGL((gemm_f32mfma_kernel<BM, BN, BK, WM, WN, NW, V, BT, TA, TB>), grid, \
+#define MM_LAUNCH(BT)                                                                  \
+  hipLaunchKernelGGL((gemm_f32mfma_kernel<BM, BN, BK, WM, WN, NW, BT, TA, TB>), grid, \
                      block, 0, s, (int)g.M, (int)g.N, (int)g.K, g.alpha, g.A, g.lda, g.B,  \
                      g.ldb, g.beta, g.C, g.ldc, tiles_m, tiles_n)
-  if constexpr (!TA || TB) {
-    if (vec) {
-      if (beta) MM_LAUNCH(true, true); else MM_LAUNCH(true, false);
-      return check_launch("gemm_f32mfma_kernel");
-    }
-  }
-  if (beta) MM_LAUNCH(false, true); else MM_LAUNCH(false, false);
+  if (beta) MM_LAUNCH(true); else MM_LAUNCH(false);
 #undef MM_LAUNCH
   return check_launch("gemm_f32mfma_kernel");
 }
@@ -118,20 +99,13 @@ gemm_status launch(const GemmArgs &g, hipStream_t s) {
     set_error("gemm_f32_3xbf16: lda or ldb too large for 32-bit tile offsets");
     return GEMM_STATUS_UNSUPPORTED;
   }
-  const bool vec = vector_loads_ok<TA, TB>(g);
   const bool beta = g.beta != 0.0f;
   dim3 grid((unsigned)nwg), block(64 * NW);
-#define MM_LAUNCH(V, BT)                                                                     \
-  hipLaunchKernelGGL((gemm_bx3_kernel<BM, BN, BK, WM, WN, NP, NW, V, BT, TA, TB, ST>), grid, \
+#define MM_LAUNCH(BT)                                                                     \
+  hipLaunchKernelGGL((gemm_bx3_kernel<BM, BN, BK, WM, WN, NP, NW, BT, TA, TB, ST>), grid, \
                      block, 0, s, (int)g.M, (int)g.N, (int)g.K, g.alpha, g.A, g.lda, g.B,     \
                      g.ldb, g.beta, g.C, g.ldc, tiles_m, tiles_n)
-  if constexpr (!TA || TB) {
-    if (vec) {
-      if (beta) MM_LAUNCH(true, true); else MM_LAUNCH(true, false);
-      return check_launch("gemm_bx3_kernel");
-    }
-  }
-  if (beta) MM_LAUNCH(false, true); else MM_LAUNCH(false, false);
+  if (beta) MM_LAUNCH(true); else MM_LAUNCH(false);
 #undef MM_LAUNCH
   return check_launch("gemm_bx3_kernel");
 }
@@ -139,7 +113,7 @@ gemm_status launch(const GemmArgs &g, hipStream_t s) {
 // A batch of equally shaped problems at fixed element strides: the tiles of
 // one problem in the grid's first dimension (XCD-aware order), the problem in
 // the second.  NP == 1 is the binary32 matrix-core mode.
-template <int BM, int BN, int BK, int WM, int WN, int NP, int NW, bool VEC, bool BETA>
+template <int BM, int BN, int BK, int WM, int WN, int NP, int NW, bool BETA>
 __global__ __launch_bounds__(64 * NW, 1) void gemm_batched_kernel(
     int M, int N, int K, float alpha, const float *__restrict__ A, int64_t lda, int64_t sa,
     const float *__restrict__ B, int64_t ldb, int64_t sb, float beta, float *__restrict__ C,
@@ -150,7 +124,7 @@ __global__ __launch_bounds__(64 * NW, 1) void gemm_batched_kernel(
   int tm, tn;
   tile_coords(wg, tiles_m, tiles_n, 8, tm, tn);
   const int64_t b = blockIdx.y;
-  tile<BM, BN, BK, WM, WN, NP, NW, VEC, BETA>(M, N, K, alpha, A + b * sa, lda, B + b * sb, ldb,
+  tile<BM, BN, BK, WM, WN, NP, NW, BETA>(M, N, K, alpha, A + b * sa, lda, B + b * sb, ldb,
                                               beta, C + b * sc, ldc, tm * BM, tn * BN, lds);
 }
 
@@ -169,16 +143,13 @@ gemm_status launch_batched(const GemmArgs &g, int64_t sa, int64_t sb, int64_t sc
     set_error("gemm_strided_batched: lda or ldb too large for 32-bit tile offsets");
     return GEMM_STATUS_UNSUPPORTED;
   }
-  // 128-bit A loads need every problem's A 16-byte aligned
-  const bool vec = vector_loads_ok<false, false>(g) && sa % 4 == 0;
   const bool beta = g.beta != 0.0f;
   const dim3 grid((unsigned)nwg, (unsigned)batch), block(64 * NW);
-#define MM_LAUNCH(V, BT)                                                                        \
-  hipLaunchKernelGGL((gemm_batched_kernel<BM, BN, BK, WM, WN, NP, NW, V, BT>), grid, block, 0, s, \
+#define MM_LAUNCH(BT)                                                                        \
+  hipLaunchKernelGGL((gemm_batched_kernel<BM, BN, BK, WM, WN, NP, NW, BT>), grid, block, 0, s, \
                      (int)g.M, (int)g.N, (int)g.K, g.alpha, g.A, g.lda, sa, g.B, g.ldb, sb,       \
                      g.beta, g.C, g.ldc, sc, tiles_m, tiles_n)
-  if (vec) { if (beta) MM_LAUNCH(true, true); else MM_LAUNCH(true, false); }
-  else     { if (beta) MM_LAUNCH(false, true); else MM_LAUNCH(false, false); }
+  if (beta) MM_LAUNCH(true); else MM_LAUNCH(false);
 #undef MM_LAUNCH
   return check_launch("gemm_batched_kernel");
 }
@@ -202,16 +173,13 @@ gemm_status launch_kg(const GemmArgs &g, hipStream_t s) {
     set_error("gemm_f32_3xbf16: lda or ldb too large for 32-bit tile offsets");
     return GEMM_STATUS_UNSUPPORTED;
   }
-  // each group's panel starts K/2 elements into a row of A
-  const bool vec = vector_loads_ok<false, false>(g) && (g.K / 2) % 4 == 0;
   const bool beta = g.beta != 0.0f;
   dim3 grid((unsigned)nwg), block(128 * NW);
-#define MM_LAUNCH(V, BT)                                                                   \
-  hipLaunchKernelGGL((gemm_bx3_kg_kernel<BM, BN, BK, WM, WN, NP, NW, V, BT>), grid, block, \
+#define MM_LAUNCH(BT)                                                                   \
+  hipLaunchKernelGGL((gemm_bx3_kg_kernel<BM, BN, BK, WM, WN, NP, NW, BT>), grid, block, \
                      0, s, (int)g.M, (int)g.N, (int)g.K, g.alpha, g.A, g.lda, g.B, g.ldb,  \
                      g.beta, g.C, g.ldc, tiles_m, tiles_n)
-  if (vec) { if (beta) MM_LAUNCH(true, true); else MM_LAUNCH(true, false); }
-  else     { if (beta) MM_LAUNCH(false, true); else MM_LAUNCH(false, false); }
+  if (beta) MM_LAUNCH(true); else MM_LAUNCH(false);
 #undef MM_LAUNCH
   return check_launch("gemm_bx3_kg_kernel");
 }

@@ -16,7 +16,6 @@ struct Desc {
   float alpha, beta;
   int variant;  // tile variant (0: 128 x 128, 1: 64 x 64)
   int tiles_n;  // output tiles along N for this variant (0: no MFMA work)
-  int vec;      // 128-bit loads of A rows allowed
 };
 
 constexpr double kDefaultSmallCost = 1.6;

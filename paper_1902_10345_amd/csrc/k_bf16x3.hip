@@ -11,7 +11,7 @@ namespace bx3 {
 // of its tile (alpha 1, beta 0) into partial plane c of P (M x N, ld N).
 // Chunks are whole slabs, so the slab grid of every chunk ends on its own
 // boundary and only a chunk's first slab can be partial.
-template <int BM, int BN, int BK, int WM, int WN, int NP, int NW, bool VEC>
+template <int BM, int BN, int BK, int WM, int WN, int NP, int NW>
 __global__ __launch_bounds__(64 * NW, 1) void gemm_bx3_splitk_kernel(
     int M, int N, int K, int chunk, const float *__restrict__ A, int64_t lda,
     const float *__restrict__ B, int64_t ldb, float *__restrict__ P, int tiles_m, int tiles_n) {
@@ -24,7 +24,7 @@ __global__ __launch_bounds__(64 * NW, 1) void gemm_bx3_splitk_kernel(
   tile_coords(wg - c * tiles, tiles_m, tiles_n, 8, tm, tn);
   const int k0 = c * chunk;
   const int kc = (K - k0 < chunk ? K - k0 : chunk);
-  tile<BM, BN, BK, WM, WN, NP, NW, VEC, false>(M, N, kc, 1.0f, A + k0, lda, B + (int64_t)k0 * ldb,
+  tile<BM, BN, BK, WM, WN, NP, NW, false>(M, N, kc, 1.0f, A + k0, lda, B + (int64_t)k0 * ldb,
                                                ldb, 0.0f, P + (int64_t)c * M * N, N, tm * BM,
                                                tn * BN, lds);
 }
@@ -84,15 +84,9 @@ gemm_status launch_splitk(const GemmArgs &g, int S, float *P, hipStream_t s) {
   const int chunk = (int)(((g.K + S - 1) / S + BK - 1) / BK * BK);
   S = (int)((g.K + chunk - 1) / chunk);  // chunks that hold work (<= requested)
   const int64_t nwg_used = (int64_t)tiles_m * tiles_n * S;
-  const bool vec = g.lda % 4 == 0 && g.K % 4 == 0 && ((uintptr_t)g.A & 15) == 0;
-  if (vec)
-    hipLaunchKernelGGL((gemm_bx3_splitk_kernel<BM, BN, BK, WM, WN, NP, NW, true>), dim3((unsigned)nwg_used),
-                       dim3(64 * NW), 0, s, (int)g.M, (int)g.N, (int)g.K, chunk, g.A, g.lda, g.B,
-                       g.ldb, P, tiles_m, tiles_n);
-  else
-    hipLaunchKernelGGL((gemm_bx3_splitk_kernel<BM, BN, BK, WM, WN, NP, NW, false>), dim3((unsigned)nwg_used),
-                       dim3(64 * NW), 0, s, (int)g.M, (int)g.N, (int)g.K, chunk, g.A, g.lda, g.B,
-                       g.ldb, P, tiles_m, tiles_n);
+  hipLaunchKernelGGL((gemm_bx3_splitk_kernel<BM, BN, BK, WM, WN, NP, NW>), dim3((unsigned)nwg_used),
+                     dim3(64 * NW), 0, s, (int)g.M, (int)g.N, (int)g.K, chunk, g.A, g.lda, g.B,
+                     g.ldb, P, tiles_m, tiles_n);
   if (gemm_status st = check_launch("gemm_bx3_splitk_kernel")) return st;
   const bool rvec = g.N % 4 == 0 && g.ldc % 4 == 0 && ((uintptr_t)g.C & 15) == 0;
   const int64_t items = rvec ? g.M * g.N / 4 : g.M * g.N;
@@ -150,7 +144,7 @@ __global__ __launch_bounds__(256) void split_kernel(int64_t n, const float *__re
 // -> 53.9 us.  The same hint on the operand loads was slower.
 constexpr int kStoreNT = 2;
 
-template <int SB, int NP, bool VEC, bool BETA>
+template <int SB, int NP, bool BETA>
 __global__ __launch_bounds__(256) void small_batched_bx3_kernel(
     int M, int N, int K, float alpha, const float *__restrict__ A, int64_t lda, int64_t sa,
     const float *__restrict__ B, int64_t ldb, int64_t sb, float beta, float *__restrict__ C,
@@ -218,18 +212,12 @@ __global__ __launch_bounds__(256) void small_batched_bx3_kernel(
       if (s > 0 || kbase == 0) {
 #pragma unroll
         for (int i = 0; i < SB; ++i) {
-          if (VEC) {
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                            rA, arow[i] + (kb + 8 * h) * 4, 0, 0));
-              a[i][4 * h] = v.x; a[i][4 * h + 1] = v.y;
-              a[i][4 * h + 2] = v.z; a[i][4 * h + 3] = v.w;
-            }
-          } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-              a[i][e] = ld(rA, arow[i] + (kb + 8 * (e >> 2) + (e & 3)) * 4);
+          for (int h = 0; h < 2; ++h) {
+            const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                          rA, arow[i] + (kb + 8 * h) * 4, 0, 0));
+            a[i][4 * h] = v.x; a[i][4 * h + 1] = v.y;
+            a[i][4 * h + 2] = v.z; a[i][4 * h + 3] = v.w;
           }
         }
 #pragma unroll
@@ -264,17 +252,12 @@ __global__ __launch_bounds__(256) void small_batched_bx3_kernel(
     if (s > 0 || kbase == 0) {
 #pragma unroll
       for (int i = 0; i < SB; ++i) {
-        if (VEC) {
-          const f32x4 v0 = __builtin_bit_cast(
-              f32x4, __builtin_amdgcn_raw_buffer_load_b128(rA, arow[i] + k0 * 4, 0, 0));
-          const f32x4 v1 = __builtin_bit_cast(
-              f32x4, __builtin_amdgcn_raw_buffer_load_b128(rA, arow[i] + k0 * 4 + 16, 0, 0));
-          a[i][0] = v0.x; a[i][1] = v0.y; a[i][2] = v0.z; a[i][3] = v0.w;
-          a[i][4] = v1.x; a[i][5] = v1.y; a[i][6] = v1.z; a[i][7] = v1.w;
-        } else {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) a[i][e] = ld(rA, arow[i] + (k0 + e) * 4);
-        }
+        const f32x4 v0 = __builtin_bit_cast(
+            f32x4, __builtin_amdgcn_raw_buffer_load_b128(rA, arow[i] + k0 * 4, 0, 0));
+        const f32x4 v1 = __builtin_bit_cast(
+            f32x4, __builtin_amdgcn_raw_buffer_load_b128(rA, arow[i] + k0 * 4 + 16, 0, 0));
+        a[i][0] = v0.x; a[i][1] = v0.y; a[i][2] = v0.z; a[i][3] = v0.w;
+        a[i][4] = v1.x; a[i][5] = v1.y; a[i][6] = v1.z; a[i][7] = v1.w;
       }
 #pragma unroll
       for (int j = 0; j < SB; ++j)
@@ -362,17 +345,13 @@ bool small_batched_fits(const GemmArgs &g) {
 template <int SB, int NP>
 gemm_status launch_small_batched(const GemmArgs &g, int64_t sa, int64_t sb, int64_t sc,
                                  int batch, hipStream_t s) {
-  // 128-bit A loads: 16-byte aligned rows and k offsets (K % 4 == 0 keeps the
-  // step grid on multiples of 4)
-  const bool vec = g.lda % 4 == 0 && g.K % 4 == 0 && sa % 4 == 0 && ((uintptr_t)g.A & 15) == 0;
   const bool beta = g.beta != 0.0f;
   const dim3 grid((unsigned)((batch + 3) / 4)), block(256);
-#define MM_LAUNCH(V, BT)                                                                         \
-  hipLaunchKernelGGL((small_batched_bx3_kernel<SB, NP, V, BT>), grid, block, 0, s, (int)g.M,      \
+#define MM_LAUNCH(BT)                                                                         \
+  hipLaunchKernelGGL((small_batched_bx3_kernel<SB, NP, BT>), grid, block, 0, s, (int)g.M,      \
                      (int)g.N, (int)g.K, g.alpha, g.A, g.lda, sa, g.B, g.ldb, sb, g.beta, g.C,     \
                      g.ldc, sc, batch)
-  if (vec) { if (beta) MM_LAUNCH(true, true); else MM_LAUNCH(true, false); }
-  else     { if (beta) MM_LAUNCH(false, true); else MM_LAUNCH(false, false); }
+  if (beta) MM_LAUNCH(true); else MM_LAUNCH(false);
 #undef MM_LAUNCH
   return check_launch("small_batched_bx3_kernel");
 }

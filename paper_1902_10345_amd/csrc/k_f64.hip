@@ -72,11 +72,11 @@ struct Cfg {
   static constexpr int STAGE = (BM + BN) * BK;        // binary64 elements per stage
 };
 
-// One output tile of one problem.  VEC: lda even, K even and A 16-byte
-// aligned (128-bit loads of A rows).  The launcher guarantees that the byte
-// extents of an A row panel (BM rows) and of a B slab (16 rows) stay below
-// 2^31.
-template <int BM, int BN, int WM, int WN, bool VEC, bool BETA>
+// One output tile of one problem.  A rows are read in 128-bit loads whatever
+// lda, K and the base (a 128-bit buffer load needs only 4-byte alignment).
+// The launcher guarantees that the byte extents of an A row panel (BM rows)
+// and of a B slab (16 rows) stay below 2^31.
+template <int BM, int BN, int WM, int WN, bool BETA>
 __device__ __forceinline__ void tile(int M, int N, int K, double alpha, const double *__restrict__ A,
                                      int64_t lda, const double *__restrict__ B, int64_t ldb,
                                      double beta, double *__restrict__ C, int64_t ldc, int m0,
@@ -115,15 +115,9 @@ __device__ __forceinline__ void tile(int M, int N, int K, double alpha, const do
 #pragma unroll
     for (int i = 0; i < G::A_ITEMS; ++i) {
       if (FAST) {
-        const int off = a_off[i] + k0 * 8;
-        if (VEC) {
-          const f64x2 v = ld2(rA, off);
-          ra[i][0] = v.x;
-          ra[i][1] = v.y;
-        } else {
-          ra[i][0] = ld1(rA, off, 0);
-          ra[i][1] = ld1(rA, off + 8, 0);
-        }
+        const f64x2 v = ld2(rA, a_off[i] + k0 * 8);
+        ra[i][0] = v.x;
+        ra[i][1] = v.y;
       } else {
         const int k = k0 + ((tid + NT * i) % CH) * 2;
 #pragma unroll
@@ -253,7 +247,7 @@ __device__ __forceinline__ void tile(int M, int N, int K, double alpha, const do
 
 // Grid: x = output tiles of one problem (XCD-aware order), y = problem of the
 // batch (element strides sa, sb, sc between consecutive problems).
-template <int BM, int BN, int WM, int WN, bool VEC, bool BETA>
+template <int BM, int BN, int WM, int WN, bool BETA>
 __global__ __launch_bounds__((Cfg<BM, BN, WM, WN>::NT), (Cfg<BM, BN, WM, WN>::MIN_WG)) void gemm_f64_kernel(
     int M, int N, int K, double alpha, const double *__restrict__ A, int64_t lda, int64_t sa,
     const double *__restrict__ B, int64_t ldb, int64_t sb, double beta, double *__restrict__ C,
@@ -264,7 +258,7 @@ __global__ __launch_bounds__((Cfg<BM, BN, WM, WN>::NT), (Cfg<BM, BN, WM, WN>::MI
   int tm, tn;
   tile_coords(wg, tiles_m, tiles_n, 8, tm, tn);
   const int64_t b = blockIdx.y;
-  tile<BM, BN, WM, WN, VEC, BETA>(M, N, K, alpha, A + b * sa, lda, B + b * sb, ldb, beta, C + b * sc,
+  tile<BM, BN, WM, WN, BETA>(M, N, K, alpha, A + b * sa, lda, B + b * sb, ldb, beta, C + b * sc,
                                   ldc, tm * BM, tn * BN, lds);
 }
 
@@ -283,16 +277,13 @@ gemm_status launch(const GemmArgsF64 &g, hipStream_t s) {
     set_error("gemm_f64: lda or ldb too large for 32-bit tile offsets");
     return GEMM_STATUS_UNSUPPORTED;
   }
-  // 128-bit loads need every problem's A to be 16-byte aligned
-  const bool vec = g.lda % 2 == 0 && g.K % 2 == 0 && g.sa % 2 == 0 && ((uintptr_t)g.A & 15) == 0;
   const bool beta = g.beta != 0.0;
   const dim3 grid((unsigned)nwg, (unsigned)g.batch), block(G::NT);
-#define MM_LAUNCH(V, BT)                                                                        \
-  hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, WM, WN, V, BT>), grid, block, 0, s, (int)g.M,      \
+#define MM_LAUNCH(BT)                                                                        \
+  hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, WM, WN, BT>), grid, block, 0, s, (int)g.M,      \
                      (int)g.N, (int)g.K, g.alpha, g.A, g.lda, g.sa, g.B, g.ldb, g.sb, g.beta, g.C, \
                      g.ldc, g.sc, tiles_m, tiles_n)
-  if (vec) { if (beta) MM_LAUNCH(true, true); else MM_LAUNCH(true, false); }
-  else     { if (beta) MM_LAUNCH(false, true); else MM_LAUNCH(false, false); }
+  if (beta) MM_LAUNCH(true); else MM_LAUNCH(false);
 #undef MM_LAUNCH
   return check_launch("gemm_f64_kernel");
 }
@@ -302,12 +293,11 @@ gemm_status launch(const GemmArgsF64 &g, hipStream_t s) {
 // fragments (each element is used by one wave only, so staging through LDS
 // would only add traffic).  The k range is walked in chunks of 16: lane group
 // g takes four k of every block (two 128-bit loads of an A row when the
-// chunk lies inside [0, K) and lda is even, else four 64-bit loads) and the
-// four B values of its column at those k (64-bit loads, consecutive lanes on
+// chunk lies inside [0, K), else four 64-bit loads) and the four B values of its column at those k (64-bit loads, consecutive lanes on
 // consecutive columns); MFMA step q multiplies the group's q-th k.
 // Rows past M and columns past N read zero through the buffer range check;
 // k past K is masked per element.
-template <int SB, bool VEC, bool BETA>
+template <int SB, bool BETA>
 __global__ __launch_bounds__(256, 2) void small_batched_kernel(
     int M, int N, int K, double alpha, const double *__restrict__ A, int64_t lda, int64_t sa,
     const double *__restrict__ B, int64_t ldb, int64_t sb, double beta, double *__restrict__ C,
@@ -348,13 +338,8 @@ __global__ __launch_bounds__(256, 2) void small_batched_kernel(
     if (k0 + 16 <= K) {
 #pragma unroll
       for (int i = 0; i < SB; ++i) {
-        if (VEC) {
-          const f64x2 v0 = ld2(rA, arow[i] + kq(0) * 8), v1 = ld2(rA, arow[i] + kq(2) * 8);
-          a[i][0] = v0.x; a[i][1] = v0.y; a[i][2] = v1.x; a[i][3] = v1.y;
-        } else {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) a[i][q] = ld1(rA, arow[i] + kq(q) * 8, 0);
-        }
+        const f64x2 v0 = ld2(rA, arow[i] + kq(0) * 8), v1 = ld2(rA, arow[i] + kq(2) * 8);
+        a[i][0] = v0.x; a[i][1] = v0.y; a[i][2] = v1.x; a[i][3] = v1.y;
       }
 #pragma unroll
       for (int j = 0; j < SB; ++j)
@@ -406,16 +391,14 @@ gemm_status launch_small(const GemmArgsF64 &g, hipStream_t s) {
     set_error("gemm_f64: lda or ldb too large for 32-bit offsets of the small-problem kernel");
     return GEMM_STATUS_UNSUPPORTED;
   }
-  const bool vec = g.lda % 2 == 0 && g.sa % 2 == 0 && ((uintptr_t)g.A & 15) == 0;
   const bool beta = g.beta != 0.0;
   const int64_t nwg = (g.batch + 3) / 4;
   if (nwg > 0x7fffffff) { set_error("gemm_f64: batch too large"); return GEMM_STATUS_UNSUPPORTED; }
-#define MM_LAUNCH(V, BT)                                                                            \
-  hipLaunchKernelGGL((small_batched_kernel<SB, V, BT>), dim3((unsigned)nwg), dim3(256), 0, s,       \
+#define MM_LAUNCH(BT)                                                                            \
+  hipLaunchKernelGGL((small_batched_kernel<SB, BT>), dim3((unsigned)nwg), dim3(256), 0, s,       \
                      (int)g.M, (int)g.N, (int)g.K, g.alpha, g.A, g.lda, g.sa, g.B, g.ldb, g.sb,     \
                      g.beta, g.C, g.ldc, g.sc, g.batch)
-  if (vec) { if (beta) MM_LAUNCH(true, true); else MM_LAUNCH(true, false); }
-  else     { if (beta) MM_LAUNCH(false, true); else MM_LAUNCH(false, false); }
+  if (beta) MM_LAUNCH(true); else MM_LAUNCH(false);
 #undef MM_LAUNCH
   return check_launch("small_batched_kernel");
 }

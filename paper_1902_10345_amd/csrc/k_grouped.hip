@@ -34,13 +34,13 @@ using G0 = bx3::Cfg<128, 128, 32, 64, 64, 2, 4>;
 using G1 = bx3::Cfg<64, 64, 32, 32, 32, 2, 4>;
 constexpr int kLdsBytes = G0::LDS_BYTES > G1::LDS_BYTES ? G0::LDS_BYTES : G1::LDS_BYTES;
 
-template <int V, bool VEC, bool BETA>
+template <int V, bool BETA>
 __device__ __forceinline__ void run_tile(const Desc &d, int m0, int n0, __bf16 *lds) {
   if constexpr (V == 0)
-    bx3::tile<128, 128, 32, 64, 64, 2, 4, VEC, BETA>(d.M, d.N, d.K, d.alpha, d.A, d.lda, d.B,
+    bx3::tile<128, 128, 32, 64, 64, 2, 4, BETA>(d.M, d.N, d.K, d.alpha, d.A, d.lda, d.B,
                                                      d.ldb, d.beta, d.C, d.ldc, m0, n0, lds);
   else
-    bx3::tile<64, 64, 32, 32, 32, 2, 4, VEC, BETA>(d.M, d.N, d.K, d.alpha, d.A, d.lda, d.B, d.ldb,
+    bx3::tile<64, 64, 32, 32, 32, 2, 4, BETA>(d.M, d.N, d.K, d.alpha, d.A, d.lda, d.B, d.ldb,
                                                    d.beta, d.C, d.ldc, m0, n0, lds);
 }
 
@@ -120,16 +120,12 @@ __global__ __launch_bounds__(256, 2) void grouped_kernel(const Desc *__restrict_
     int tm, tn;
     tile_coords(local, (d.M + bm - 1) / bm, d.tiles_n, 8, tm, tn);
     const int m0 = tm * bm, n0 = tn * bn;
-    const int sel = d.variant * 4 + (d.vec ? 2 : 0) + (d.beta != 0.0f ? 1 : 0);
+    const int sel = d.variant * 2 + (d.beta != 0.0f ? 1 : 0);
     switch (sel) {
-      case 0: run_tile<0, false, false>(d, m0, n0, lds); break;
-      case 1: run_tile<0, false, true>(d, m0, n0, lds); break;
-      case 2: run_tile<0, true, false>(d, m0, n0, lds); break;
-      case 3: run_tile<0, true, true>(d, m0, n0, lds); break;
-      case 4: run_tile<1, false, false>(d, m0, n0, lds); break;
-      case 5: run_tile<1, false, true>(d, m0, n0, lds); break;
-      case 6: run_tile<1, true, false>(d, m0, n0, lds); break;
-      default: run_tile<1, true, true>(d, m0, n0, lds); break;
+      case 0: run_tile<0, false>(d, m0, n0, lds); break;
+      case 1: run_tile<0, true>(d, m0, n0, lds); break;
+      case 2: run_tile<1, false>(d, m0, n0, lds); break;
+      default: run_tile<1, true>(d, m0, n0, lds); break;
     }
     // One barrier per tile: publishes the next index (alternate slots, so no
     // thread can still be reading the slot being written) and separates this
@@ -184,7 +180,6 @@ gemm_status grouped_build(const gemm_problem *probs, int count, const int *varia
     d.alpha = q.alpha; d.beta = q.beta;
     d.variant = variant ? variant[p] : grouped_pick_variant(q.M, q.N, small_cost);
     const int bm = grp::kBM[d.variant], bn = grp::kBN[d.variant];
-    d.vec = (q.lda % 4 == 0 && q.K % 4 == 0 && ((uintptr_t)q.A & 15) == 0) ? 1 : 0;
     // problems that need no MFMA work contribute no tiles; the host handles
     // them (no-op or C <- beta*C) before the launch
     const bool work = q.M > 0 && q.N > 0 && q.K > 0 && q.alpha != 0.0f;
