@@ -521,7 +521,8 @@ gemm_status gemm_strided_batched(int path, int64_t M, int64_t N, int64_t K, floa
     const int nb = (int)std::min<int64_t>(65535, batch - b0);
     GemmArgs g{M, N, K, alpha, beta, A + b0 * stride_a, lda, B + b0 * stride_b, ldb,
                C + b0 * stride_c, ldc};
-    if (gemm_status st = batched_run(path, cfg, g, stride_a, stride_b, stride_c, nb, stream))
+    if (gemm_status st = batched_run(path, cfg, g, n_products, stride_a, stride_b, stride_c, nb,
+                                     stream))
       return st;
   }
   return GEMM_STATUS_OK;

@@ -1,5 +1,6 @@
 // k_bf16x3.hip -- FP32-accurate split-precision GEMM on bf16 MFMA (gfx950).
 #include <algorithm>
+#include <cmath>
 
 #include "bx3_launch.hpp"
 
@@ -127,231 +128,222 @@ __global__ __launch_bounds__(256) void split_kernel(int64_t n, const float *__re
 }
 
 // ---- batched small problems --------------------------------------------------
-// M, N <= 32 SB: one wave per problem, four problems per workgroup.  The
-// operands go from memory straight into MFMA fragments (and are split in
-// registers, NP = 2 or 3 planes; NP = 1 is binary32 on the FP32 matrix
-// cores): every element is used by one wave only, so staging through LDS
-// would add traffic and barriers, and the 64 x 64 tile of four waves would
-// leave three of them on padding for a 32 x 32 problem.  A lane holds 8 k of
-// its A row (two 128-bit loads) and of its B column (eight loads, consecutive
-// lanes on consecutive columns) per 16-deep k-step: 8 consecutive k on the
-// split path, two runs of 4 in binary32 (the FP32 tile's fragment order).
+// One wave per 32 x 32 sub-tile of a problem, four waves per workgroup,
+// the sub-tiles of a problem on consecutive waves (its panels meet in the L1
+// and L2 of one CU).  The operands go from memory straight into MFMA fragments
+// (and are split in registers, NP = 2 or 3 planes; NP = 1 is binary32 on the
+// FP32 matrix cores): with so few waves per problem, staging through LDS would
+// add barriers that nothing overlaps.  A lane holds 8 k of its A row (two
+// 128-bit loads) and of its B column (eight loads, consecutive lanes on
+// consecutive columns) per 16-deep k-step: 8 consecutive k on the split path,
+// two runs of 4 in binary32 (the FP32 tile's fragment order).  With
+// enough waves to fill the machine (SETS 1: 8 waves per SIMD) they hide each
+// other's latency; a smaller batch keeps the next k-step's loads in flight
+// while one is multiplied (SETS 2: 4-5 waves per SIMD).
 // The k-steps lie on the grid that ends at K (only the first can be partial)
 // and the products come in the tile kernels' order, so every element is the
 // same sum as in the LDS-staged tile of the same arithmetic.
+// Bound: HBM for problems above about 24^3; below that the number of memory
+// instructions, so those that no lane needs (rows past M, k below 0) are
+// skipped wave by wave.
 // C stores with the non-temporal cache policy (the slc bit, NT on gfx950; a
 // hint only): 32^3 x 29 297 at beta = 0 63.2 -> 55.4 us, 48^3 x 12 000 63.6
 // -> 53.9 us.  The same hint on the operand loads was slower.
 constexpr int kStoreNT = 2;
 
-template <int SB, int NP, bool BETA>
+template <int NP, bool BETA, int SETS>
 __global__ __launch_bounds__(256) void small_batched_bx3_kernel(
     int M, int N, int K, float alpha, const float *__restrict__ A, int64_t lda, int64_t sa,
     const float *__restrict__ B, int64_t ldb, int64_t sb, float beta, float *__restrict__ C,
-    int64_t ldc, int64_t sc, int batch) {
+    int64_t ldc, int64_t sc, int batch, int tiles_m, int tiles_n) {
   const int lane = threadIdx.x & 63;
   // the wave index is uniform across the wave; saying so keeps the problem's
   // buffer resources in scalar registers
-  const int prob = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int tiles = tiles_m * tiles_n;
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  int prob = (int)blockIdx.x * 4 + wv, m0 = 0, n0 = 0;
+  if (tiles > 1) {
+    // XCD-aware order where a problem spans several waves (its panels meet in
+    // one L2: 160^2 x 16 x 1500 39 -> 26 us); one wave per problem shares
+    // nothing (32^3 x 29 297 is 6 % faster in plain order)
+    const int unit = xcd_remap(blockIdx.x, gridDim.x) * 4 + wv;
+    prob = unit / tiles;
+    const int sub = unit - prob * tiles, tm = sub / tiles_n;
+    m0 = tm * 32;
+    n0 = (sub - tm * tiles_n) * 32;
+  }
   if (prob >= batch) return;
+  const int Mr = M - m0, Nr = N - n0;  // valid rows and columns of the sub-tile (may exceed it)
   const int lr = lane & 31, lg = lane >> 5;
   // rows past M and columns past N read zero through the range check (their
   // results are never stored); k below 0 is masked per element
   const __amdgpu_buffer_rsrc_t rA = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<float *>(A + (int64_t)prob * sa), (short)0,
-      (int)(((int64_t)(M - 1) * lda + K) * 4), kBufferFlags);
+      const_cast<float *>(A + (int64_t)prob * sa + (int64_t)m0 * lda), (short)0,
+      (int)(((int64_t)(Mr - 1) * lda + K) * 4), kBufferFlags);
   const __amdgpu_buffer_rsrc_t rB = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<float *>(B + (int64_t)prob * sb), (short)0,
-      (int)(((int64_t)(K - 1) * ldb + N) * 4), kBufferFlags);
+      const_cast<float *>(B + (int64_t)prob * sb + n0), (short)0,
+      (int)(((int64_t)(K - 1) * ldb + Nr) * 4), kBufferFlags);
   const __amdgpu_buffer_rsrc_t rC = __builtin_amdgcn_make_buffer_rsrc(
-      C + (int64_t)prob * sc, (short)0, (int)(((int64_t)(M - 1) * ldc + N) * 4), kBufferFlags);
-  int arow[SB], bcol[SB];
-#pragma unroll
-  for (int i = 0; i < SB; ++i) {
-    const int r = 32 * i + lr;
-    arow[i] = r < M ? r * (int)lda * 4 : (int)0x80000000;
-  }
-#pragma unroll
-  for (int j = 0; j < SB; ++j) {
-    const int n = 32 * j + lr;
-    bcol[j] = n < N ? n * 4 : (int)0x80000000;
-  }
+      C + (int64_t)prob * sc + (int64_t)m0 * ldc + n0, (short)0,
+      (int)(((int64_t)(Mr - 1) * ldc + Nr) * 4), kBufferFlags);
+  const int arow = lr < Mr ? lr * (int)lda * 4 : (int)0x80000000;
+  const int bcol = lr < Nr ? lr * 4 : (int)0x80000000;
   const int ldb4 = (int)ldb * 4;
-  f32x16 acc[SB][SB];
+  f32x16 acc;
 #pragma unroll
-  for (int i = 0; i < SB; ++i)
-#pragma unroll
-    for (int j = 0; j < SB; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+  for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
   auto ld = [](__amdgpu_buffer_rsrc_t r, int off) {
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
   };
-  // the 8 values of one block as NP bf16 planes (plane 0 the leading part)
-  constexpr int NPL = NP > 1 ? NP : 2;
-  auto split8 = [](const float (&x)[8], bf16x8 (&pl)[NPL]) {
-#pragma unroll
-    for (int e = 0; e < 8; e += 2) {
-      bf16x2 x0, x1, x2;
-      if constexpr (NP == 2) split2(f32x2{x[e], x[e + 1]}, x0, x1);
-      else split3(f32x2{x[e], x[e + 1]}, x0, x1, x2);
-      pl[0][e] = x0.x; pl[0][e + 1] = x0.y;
-      pl[1][e] = x1.x; pl[1][e + 1] = x1.y;
-      if constexpr (NP == 3) { pl[2][e] = x2.x; pl[2][e + 1] = x2.y; }
-    }
-  };
   const int KT = (K + 15) / 16;
   const int kbase = K - KT * 16;
-  for (int s = 0; s < KT; ++s) {
-    if constexpr (NP == 1) {
-      // binary32 on v_mfma_f32_32x32x2f32, as in the FP32 tile: lane group g
-      // holds k = 4g + q and 8 + 4g + q (q < 4) of the step, and MFMA
-      // 4h + q takes element 4h + q of both groups
-      const int kb = kbase + 16 * s + 4 * lg;
-      float a[SB][8], b[SB][8];
-      if (s > 0 || kbase == 0) {
-#pragma unroll
-        for (int i = 0; i < SB; ++i) {
-#pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                          rA, arow[i] + (kb + 8 * h) * 4, 0, 0));
-            a[i][4 * h] = v.x; a[i][4 * h + 1] = v.y;
-            a[i][4 * h + 2] = v.z; a[i][4 * h + 3] = v.w;
-          }
-        }
-#pragma unroll
-        for (int j = 0; j < SB; ++j)
-#pragma unroll
-          for (int e = 0; e < 8; ++e)
-            b[j][e] = ld(rB, bcol[j] + (kb + 8 * (e >> 2) + (e & 3)) * ldb4);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int k = kb + 8 * (e >> 2) + (e & 3);
-#pragma unroll
-          for (int i = 0; i < SB; ++i)
-            a[i][e] = ld(rA, k >= 0 ? arow[i] + k * 4 : (int)0x80000000);
-#pragma unroll
-          for (int j = 0; j < SB; ++j)
-            b[j][e] = ld(rB, k >= 0 ? bcol[j] + k * ldb4 : (int)0x80000000);
-        }
-      }
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-#pragma unroll
-        for (int i = 0; i < SB; ++i)
-#pragma unroll
-          for (int j = 0; j < SB; ++j)
-            acc[i][j] =
-                __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], b[j][e], acc[i][j], 0, 0, 0);
-      continue;
-    }
-    const int k0 = kbase + 16 * s + 8 * lg;  // the lane's first k of this step
-    float a[SB][8], b[SB][8];
+  // k of a lane's element e in the step that starts at k = 0: lane group g
+  // holds k = 8g + e on the split path, 4g + e % 4 + 8 (e / 4) in binary32
+  // (as in the FP32 tile: MFMA e takes element e of both groups)
+  constexpr int kGroup = NP == 1 ? 4 : 8;       // first k of lane group 1
+  auto koff = [](int e) { return NP == 1 ? 8 * (e >> 2) + (e & 3) : e; };
+  float a[SETS][8], b[SETS][8];
+  auto load = [&](auto SET, int s) {
+    constexpr int st = decltype(SET)::value;
+    const int k0 = kbase + 16 * s + kGroup * lg;
     if (s > 0 || kbase == 0) {
 #pragma unroll
-      for (int i = 0; i < SB; ++i) {
-        const f32x4 v0 = __builtin_bit_cast(
-            f32x4, __builtin_amdgcn_raw_buffer_load_b128(rA, arow[i] + k0 * 4, 0, 0));
-        const f32x4 v1 = __builtin_bit_cast(
-            f32x4, __builtin_amdgcn_raw_buffer_load_b128(rA, arow[i] + k0 * 4 + 16, 0, 0));
-        a[i][0] = v0.x; a[i][1] = v0.y; a[i][2] = v0.z; a[i][3] = v0.w;
-        a[i][4] = v1.x; a[i][5] = v1.y; a[i][6] = v1.z; a[i][7] = v1.w;
+      for (int h = 0; h < 2; ++h) {
+        const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                      rA, arow + (k0 + koff(4 * h)) * 4, 0, 0));
+        a[st][4 * h] = v.x; a[st][4 * h + 1] = v.y;
+        a[st][4 * h + 2] = v.z; a[st][4 * h + 3] = v.w;
       }
 #pragma unroll
-      for (int j = 0; j < SB; ++j)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) b[j][e] = ld(rB, bcol[j] + (k0 + e) * ldb4);
+      for (int e = 0; e < 8; ++e) b[st][e] = ld(rB, bcol + (k0 + koff(e)) * ldb4);
     } else {
       // the partial first step: k in [kbase, kbase + 16) with kbase < 0
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        const bool kin = k0 + e >= 0;
-#pragma unroll
-        for (int i = 0; i < SB; ++i)
-          a[i][e] = ld(rA, kin ? arow[i] + (k0 + e) * 4 : (int)0x80000000);
-#pragma unroll
-        for (int j = 0; j < SB; ++j)
-          b[j][e] = ld(rB, kin ? bcol[j] + (k0 + e) * ldb4 : (int)0x80000000);
+        const int k = k0 + koff(e);
+        if (kbase + kGroup + koff(e) < 0) {  // neither lane group has a k here
+          a[st][e] = b[st][e] = 0.0f;
+        } else {
+          a[st][e] = ld(rA, k >= 0 ? arow + k * 4 : (int)0x80000000);
+          b[st][e] = ld(rB, k >= 0 ? bcol + k * ldb4 : (int)0x80000000);
+        }
       }
     }
-    bf16x8 pa[SB][NPL], pb[SB][NPL];
+  };
+  auto multiply = [&](auto SET) {
+    constexpr int st = decltype(SET)::value;
+    if constexpr (NP == 1) {
 #pragma unroll
-    for (int i = 0; i < SB; ++i) split8(a[i], pa[i]);
+      for (int e = 0; e < 8; ++e)
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[st][e], b[st][e], acc, 0, 0, 0);
+    } else {
+      // the 8 values of one block as NP bf16 planes (plane 0 the leading part)
+      auto split8 = [](const float (&x)[8], bf16x8 (&pl)[NP]) {
 #pragma unroll
-    for (int j = 0; j < SB; ++j) split8(b[j], pb[j]);
-    auto prod = [&](int qa, int qb) {
-#pragma unroll
-      for (int i = 0; i < SB; ++i)
-#pragma unroll
-        for (int j = 0; j < SB; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pa[i][qa], pb[j][qb], acc[i][j],
-                                                              0, 0, 0);
-    };
-    // small products first, the leading product last
-    if constexpr (NP == 3) {
-      prod(2, 0);
-      prod(1, 1);
-      prod(0, 2);
+        for (int e = 0; e < 8; e += 2) {
+          bf16x2 x0, x1, x2;
+          if constexpr (NP == 2) split2(f32x2{x[e], x[e + 1]}, x0, x1);
+          else split3(f32x2{x[e], x[e + 1]}, x0, x1, x2);
+          pl[0][e] = x0.x; pl[0][e + 1] = x0.y;
+          pl[1][e] = x1.x; pl[1][e + 1] = x1.y;
+          if constexpr (NP == 3) { pl[2][e] = x2.x; pl[2][e + 1] = x2.y; }
+        }
+      };
+      bf16x8 pa[NP], pb[NP];
+      split8(a[st], pa);
+      split8(b[st], pb);
+      auto prod = [&](int qa, int qb) {
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pa[qa], pb[qb], acc, 0, 0, 0);
+      };
+      // small products first, the leading product last
+      if constexpr (NP == 3) {
+        prod(2, 0);
+        prod(1, 1);
+        prod(0, 2);
+      }
+      prod(1, 0);
+      prod(0, 1);
+      prod(0, 0);
     }
-    prod(1, 0);
-    prod(0, 1);
-    prod(0, 0);
+  };
+  using S0 = std::integral_constant<int, 0>;
+  using S1 = std::integral_constant<int, 1>;
+  if constexpr (SETS == 1) {
+    for (int s = 0; s < KT; ++s) {
+      load(S0{}, s);
+      multiply(S0{});
+    }
+  } else {
+    load(S0{}, 0);
+    for (int s = 0; s < KT; s += 2) {
+      if (s + 1 < KT) load(S1{}, s + 1);
+      multiply(S0{});
+      if (s + 1 < KT) {
+        if (s + 2 < KT) load(S0{}, s + 2);
+        multiply(S1{});
+      }
+    }
   }
   // 32 x 32 block layout: lane l, element e -> row 8*(e/4) + 4*(l/32) + e%4,
   // column l%32.  Columns past N get an out-of-range offset; rows past M fall
-  // beyond the resource and their stores are dropped.  With beta != 0 every
-  // read of C is issued before the first store.
+  // beyond the resource and their stores are dropped; groups of eight rows
+  // that lie past M altogether issue nothing.  With beta != 0 every read of C
+  // is issued before the first store.
   const int ldc4 = (int)ldc * 4;
-  int vb[SB][SB];
-  float cold[SB][SB][16];
+  const int vb = lr < Nr ? 4 * lg * ldc4 + lr * 4 : (int)0x80000000;
+  float cold[16];
+  if (BETA) {
 #pragma unroll
-  for (int i = 0; i < SB; ++i)
+    for (int q = 0; q < 4; ++q)
+      if (8 * q < Mr) {
 #pragma unroll
-    for (int j = 0; j < SB; ++j) {
-      const int col = 32 * j + lr;
-      vb[i][j] = col < N ? (32 * i + 4 * lg) * ldc4 + col * 4 : (int)0x80000000;
-      if (BETA) {
+        for (int e = 4 * q; e < 4 * q + 4; ++e)
+          cold[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                  rC, vb, (8 * q + (e & 3)) * ldc4, 0));
+      }
+  }
 #pragma unroll
-        for (int e = 0; e < 16; ++e)
-          cold[i][j][e] = __builtin_bit_cast(
-              float, __builtin_amdgcn_raw_buffer_load_b32(rC, vb[i][j],
-                                                          (8 * (e >> 2) + (e & 3)) * ldc4, 0));
+  for (int q = 0; q < 4; ++q)
+    if (8 * q < Mr) {
+#pragma unroll
+      for (int e = 4 * q; e < 4 * q + 4; ++e) {
+        float v = alpha * acc[e];
+        if (BETA) v = fmaf(beta, cold[e], v);
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rC, vb,
+                                              (8 * q + (e & 3)) * ldc4, kStoreNT);
       }
     }
-#pragma unroll
-  for (int i = 0; i < SB; ++i)
-#pragma unroll
-    for (int j = 0; j < SB; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        float v = alpha * acc[i][j][e];
-        if (BETA) v = fmaf(beta, cold[i][j][e], v);
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rC, vb[i][j],
-                                              (8 * (e >> 2) + (e & 3)) * ldc4, kStoreNT);
-      }
 }
 
-// Offsets of the small-problem kernel stay below 2^31: 64 rows of A and of C,
-// K rows of B.
+// Offsets of the small-problem kernel stay below 2^31: a problem's rows of A
+// and of C (rounded up to whole sub-tiles), K rows of B.
 bool small_batched_fits(const GemmArgs &g) {
-  const int64_t lim = (int64_t)1 << 31;
-  return ((int64_t)64 * g.lda + g.K) * 4 < lim && ((int64_t)g.K * g.ldb + g.N) * 4 < lim &&
-         ((int64_t)64 * g.ldc + g.N) * 4 < lim;
+  const int64_t lim = (int64_t)1 << 31, rows = g.M + 64;
+  return (rows * g.lda + g.K) * 4 < lim && ((int64_t)g.K * g.ldb + g.N) * 4 < lim &&
+         (rows * g.ldc + g.N) * 4 < lim;
 }
 
 // At most 65535 problems per launch (the caller's chunks).
-template <int SB, int NP>
+template <int NP>
 gemm_status launch_small_batched(const GemmArgs &g, int64_t sa, int64_t sb, int64_t sc,
                                  int batch, hipStream_t s) {
+  const int64_t tiles_m = (g.M + 31) / 32, tiles_n = (g.N + 31) / 32;
+  const int64_t units = tiles_m * tiles_n * batch;
+  if (units > 0x7ffffff0) {
+    set_error("gemm_strided_batched: too many tiles for one launch");
+    return GEMM_STATUS_UNSUPPORTED;
+  }
   const bool beta = g.beta != 0.0f;
-  const dim3 grid((unsigned)((batch + 3) / 4)), block(256);
-#define MM_LAUNCH(BT)                                                                         \
-  hipLaunchKernelGGL((small_batched_bx3_kernel<SB, NP, BT>), grid, block, 0, s, (int)g.M,      \
+  const dim3 grid((unsigned)((units + 3) / 4)), block(256);
+#define MM_LAUNCH(BT, SETS)                                                                      \
+  hipLaunchKernelGGL((small_batched_bx3_kernel<NP, BT, SETS>), grid, block, 0, s, (int)g.M,       \
                      (int)g.N, (int)g.K, g.alpha, g.A, g.lda, sa, g.B, g.ldb, sb, g.beta, g.C,     \
-                     g.ldc, sc, batch)
-  if (beta) MM_LAUNCH(true); else MM_LAUNCH(false);
+                     g.ldc, sc, batch, (int)tiles_m, (int)tiles_n)
+  if (g.K <= 16 || units >= 32 * (int64_t)num_cus()) {
+    if (beta) MM_LAUNCH(true, 1); else MM_LAUNCH(false, 1);
+  } else {
+    if (beta) MM_LAUNCH(true, 2); else MM_LAUNCH(false, 2);
+  }
 #undef MM_LAUNCH
   return check_launch("small_batched_bx3_kernel");
 }
@@ -493,66 +485,68 @@ gemm_status f32mfma_run(const GemmArgs &g, int which, hipStream_t s) {
   return bx3::launch_f32mfma<128, 128, 16, 64, 64, 4>(g, s);
 }
 
-// Batched-strided products.  Small problems, one wave per problem
-// (small_batched_bx3_kernel): binary32 and six products for M, N <= 64, three
-// products while M N <= 48^2 (beyond that the 64 x 64 tile of four waves is
-// faster: 64^3 x 8000 71 against 78 us).  Otherwise the tile follows the
-// problem's size and the batch's total tile count: the single-GEMM choice for
-// a problem stacked batch times along M (binary32: 256 x 256 or 128 x 128
-// tiles on the FP32 matrix cores).
+// Batched-strided products: the tile with the least modelled time beyond the
+// operands' traffic, which every tile has in common: `fixed` ns per output
+// tile and `step` ns per tile and 16-deep k-step, whole machine, fitted on 26
+// batches whose inputs change from call to call (4 to 512 per dimension, 10 to
+// 190 MB).  The batch takes whole rounds of the workgroups that fit the
+// machine at once while there are few rounds; a round that is not full runs
+// somewhat faster.  Against the tile chosen by the stacked problem's size alone
+// (256 x 256 tiles for any large batch), binary32 / three / six products, us:
+// 100 x 72 x 90 x 2000 232 -> 70, 97 -> 54, 137 -> 55; 144 x 8 x 9 x 5403 217
+// -> 20, 153 -> 18, 236 -> 18; 300^3 x 100 162 -> 69, 50 -> 48, 75 -> 54.
+namespace {
+struct BatchTile {
+  int bm, bn, per_cu;          // output tile, tiles per compute unit at once
+  double fixed[3], step[3];    // ns: binary32, three products, six products
+};
+constexpr BatchTile kBatchTiles[kBatchedTiles] = {
+    {32, 32, 20, {0.1, 0.2, 0.2}, {0.32, 0.25, 0.26}},    // kBatchedDirect
+    {64, 64, 4, {1.5, 1.5, 2.3}, {1.1, 0.35, 0.70}},      // kBatched64
+    {128, 128, 2, {2.0, 4.4, 4.0}, {3.4, 0.95, 1.40}},    // kBatched128
+    {256, 256, 1, {8.0, 8.0, 8.0}, {12.5, 2.3, 5.0}},     // kBatched256
+};
+}  // namespace
+
 int batched_config(int path, int n_products, int64_t M, int64_t N, int64_t K, int64_t batch) {
-  if (path == GEMM_PATH_F32) {
-    if (M <= 64 && N <= 64) return kBatchedSmall1;
-    const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256);
-    if (tiles <= 0) return 1;
-    return batch >= (num_cus() + tiles - 1) / tiles ? 0 : 1;  // f32mfma 256 x 256 / 128 x 128
+  // M, N <= 64: the one-wave sub-tiles (64^3 x 4000 within 10 % of the 64 x 64
+  // tile on every path, and ahead of it below)
+  if (M <= 64 && N <= 64) return kBatchedDirect;
+  const int mode = path == GEMM_PATH_F32 ? 0 : n_products == 6 ? 2 : 1;
+  int best = kBatchedDirect;
+  double best_cost = 0.0;
+  for (int c = 0; c < kBatchedTiles; ++c) {
+    const BatchTile &t = kBatchTiles[c];
+    const double tiles = (double)((M + t.bm - 1) / t.bm) * (double)((N + t.bn - 1) / t.bn) *
+                         (double)batch;
+    const double slots = (double)num_cus() * t.per_cu;
+    const double r = tiles / slots;
+    const double rounds = r > 4.0 ? r : r >= 1.0 ? std::ceil(r) : 0.5 + 0.5 * r;
+    const double cost = rounds * slots * (t.fixed[mode] + t.step[mode] * (double)((K + 15) / 16));
+    if (c == 0 || cost < best_cost) { best = c; best_cost = cost; }
   }
-  if (M <= 64 && N <= 64) {
-    if (n_products == 6) return kBatchedSmall6;
-    return M * N <= 48 * 48 ? kBatchedSmall3 : 6;
-  }
-  // M stacked batch times (saturated: only the tile count's size matters)
-  const int64_t stacked = M <= 0 ? 0 : batch > ((int64_t)1 << 40) / M ? ((int64_t)1 << 40) : M * batch;
-  const int cfg = bx3_default_config(stacked, N, K, n_products);
-  // the small-product tiles have no batched variant: their LDS-staged
-  // counterparts of the same width take the batch
-  if (cfg >= 9) return n_products == 6 ? 5 : 6;
-  return cfg;
+  return best;
 }
 
-gemm_status batched_run(int path, int cfg, const GemmArgs &g, int64_t sa, int64_t sb, int64_t sc,
-                        int batch, hipStream_t s) {
-  if (path == GEMM_PATH_F32) {
-    if (cfg == kBatchedSmall1 && bx3::small_batched_fits(g))
-      return g.M <= 32 && g.N <= 32 ? bx3::launch_small_batched<1, 1>(g, sa, sb, sc, batch, s)
-                                    : bx3::launch_small_batched<2, 1>(g, sa, sb, sc, batch, s);
-    return cfg == 0 ? bx3::launch_batched<256, 256, 16, 128, 64, 1, 8>(g, sa, sb, sc, batch, s)
-                    : bx3::launch_batched<128, 128, 16, 64, 64, 1, 4>(g, sa, sb, sc, batch, s);
-  }
-  if (cfg == kBatchedSmall3 || cfg == kBatchedSmall6) {
-    // one wave per problem; offsets beyond 32 bits take the LDS-staged tile
-    // of the same product count (the same per-element sums)
-    const bool six = cfg == kBatchedSmall6, one = g.M <= 32 && g.N <= 32;
-    if (bx3::small_batched_fits(g)) {
-      if (six) return one ? bx3::launch_small_batched<1, 3>(g, sa, sb, sc, batch, s)
-                          : bx3::launch_small_batched<2, 3>(g, sa, sb, sc, batch, s);
-      return one ? bx3::launch_small_batched<1, 2>(g, sa, sb, sc, batch, s)
-                 : bx3::launch_small_batched<2, 2>(g, sa, sb, sc, batch, s);
-    }
-    cfg = six ? 5 : 6;
-  }
-  switch (cfg) {
-    case 0: return bx3::launch_batched<256, 256, 16, 128, 64, 2, 8>(g, sa, sb, sc, batch, s);
-    case 2: return bx3::launch_batched<256, 128, 32, 64, 64, 2, 8>(g, sa, sb, sc, batch, s);
-    case 3: return bx3::launch_batched<256, 256, 32, 128, 64, 2, 8>(g, sa, sb, sc, batch, s);
-    case 4: return bx3::launch_batched<256, 256, 16, 128, 64, 3, 8>(g, sa, sb, sc, batch, s);
-    case 5: return bx3::launch_batched<128, 128, 32, 64, 64, 3, 4>(g, sa, sb, sc, batch, s);
-    case 6: return bx3::launch_batched<64, 64, 32, 32, 32, 2, 4>(g, sa, sb, sc, batch, s);
-    case 8: return bx3::launch_batched<128, 128, 16, 64, 64, 2, 4>(g, sa, sb, sc, batch, s);
-    default:
-      set_error("gemm_strided_batched: configuration without a batched variant");
-      return GEMM_STATUS_UNSUPPORTED;
-  }
+template <int NP>
+static gemm_status batched_tile(int cfg, const GemmArgs &g, int64_t sa, int64_t sb, int64_t sc,
+                                int batch, hipStream_t s) {
+  // operands that 32-bit offsets of the chosen tile cannot reach take the
+  // 64 x 64 tile, whose panels are the smallest
+  if (cfg == kBatchedDirect && bx3::small_batched_fits(g))
+    return bx3::launch_small_batched<NP>(g, sa, sb, sc, batch, s);
+  if (cfg == kBatched256 && bx3::offsets_fit<256, 256, 32, false, false>(g))
+    return bx3::launch_batched<256, 256, 16, 128, 64, NP, 8>(g, sa, sb, sc, batch, s);
+  if (cfg == kBatched128 && bx3::offsets_fit<128, 128, 32, false, false>(g))
+    return bx3::launch_batched<128, 128, 16, 64, 64, NP, 4>(g, sa, sb, sc, batch, s);
+  return bx3::launch_batched<64, 64, 32, 32, 32, NP, 4>(g, sa, sb, sc, batch, s);
+}
+
+gemm_status batched_run(int path, int cfg, const GemmArgs &g, int n_products, int64_t sa,
+                        int64_t sb, int64_t sc, int batch, hipStream_t s) {
+  if (path == GEMM_PATH_F32) return batched_tile<1>(cfg, g, sa, sb, sc, batch, s);
+  return n_products == 6 ? batched_tile<3>(cfg, g, sa, sb, sc, batch, s)
+                         : batched_tile<2>(cfg, g, sa, sb, sc, batch, s);
 }
 
 gemm_status bx3_split(int64_t n, const float *x, uint16_t *p0, uint16_t *p1, uint16_t *p2,

@@ -201,3 +201,32 @@ def test_quick_path_scales_every_problem():
                             batch, 3)
     torch.cuda.synchronize()
     assert np.array_equal(d.cpu().numpy(), np.float32(0.5) * hC)
+
+
+@pytest.mark.parametrize("M,N,K,batch", [(65, 33, 16, 40), (65, 33, 17, 40), (32, 96, 15, 3000),
+                                         (32, 96, 33, 3000), (100, 72, 90, 600), (128, 129, 31, 90),
+                                         (200, 256, 40, 256), (257, 300, 48, 70), (7, 160, 16, 20),
+                                         (160, 8, 5, 20), (1, 65, 1, 33)])
+@pytest.mark.parametrize("n", [1, 3, 6])
+def test_tiles_of_medium_problems_exact(M, N, K, batch, n):
+    """Problems beyond 64 x 64 on whichever tile the batch gets (one-wave
+    sub-tiles with one or two register sets, 64, 128 and 256 tiles, ragged
+    edges, K at and beside the 16-deep k-step): integer inputs, every element
+    of every problem exact, C a NaN buffer with gaps that stay untouched."""
+    import torch
+    import paper_1902_10345_amd as mm
+    path = mm.PATH_F32 if n == 1 else mm.PATH_3XBF16
+    sc = M * N + 5
+    A = torch.from_numpy(si.integers((batch * M, K), K + n)).cuda().view(batch, M, K)
+    B = torch.from_numpy(si.integers((batch * K, N), K + n + 1)).cuda().view(batch, K, N)
+    C = torch.full((batch, sc), float("nan"), device="cuda")
+    mm.gemm_strided_batched(path, M, N, K, 1.0, A, K, M * K, B, N, K * N, 0.0, C, N, sc, batch,
+                            max(n, 3))
+    want = torch.matmul(A.double(), B.double()).float()
+    assert torch.equal(C[:, :M * N].view(batch, M, N), want)
+    assert bool(torch.isnan(C[:, M * N:]).all())
+    C.fill_(2.0)
+    mm.gemm_strided_batched(path, M, N, K, 1.0, A, K, M * K, B, N, K * N, -3.0, C, N, sc, batch,
+                            max(n, 3))
+    assert torch.equal(C[:, :M * N].view(batch, M, N), want - 6.0)
+    assert bool((C[:, M * N:] == 2.0).all())
