@@ -13,8 +13,8 @@
 //   ReducePeeling   alpha/beta applied once in the epilogue.
 // A batch of equally shaped problems at fixed element strides (the
 // batched-strided product of the paper's quantum-transport case study,
-// Sec. 6.4) runs the same tiles with the batch index in the grid's second
-// dimension.
+// Sec. 6.4) runs the same tiles, or sub-tiles of one wave each straight from
+// memory.
 //
 // MFMA operand layout (16x16x4, measured on gfx950): lane l supplies
 // A[l % 16][l / 16] and B[l / 16][l % 16]; accumulator element e of lane l
@@ -23,6 +23,8 @@
 // are contiguous (two 16-byte LDS reads per 16 x 16 block and slab) and every
 // k of the slab enters exactly once.
 #include <algorithm>
+#include <cmath>
+#include <type_traits>
 
 #include "common.hpp"
 #include "kernels.hpp"
@@ -245,8 +247,8 @@ __device__ __forceinline__ void tile(int M, int N, int K, double alpha, const do
     }
 }
 
-// Grid: x = output tiles of one problem (XCD-aware order), y = problem of the
-// batch (element strides sa, sb, sc between consecutive problems).
+// Grid: the output tiles of every problem of the batch (element strides sa, sb,
+// sc between consecutive problems) in one XCD-aware order.
 template <int BM, int BN, int WM, int WN, bool BETA>
 __global__ __launch_bounds__((Cfg<BM, BN, WM, WN>::NT), (Cfg<BM, BN, WM, WN>::MIN_WG)) void gemm_f64_kernel(
     int M, int N, int K, double alpha, const double *__restrict__ A, int64_t lda, int64_t sa,
@@ -255,9 +257,10 @@ __global__ __launch_bounds__((Cfg<BM, BN, WM, WN>::NT), (Cfg<BM, BN, WM, WN>::MI
   using G = Cfg<BM, BN, WM, WN>;
   __shared__ __attribute__((aligned(16))) double lds[2 * G::STAGE];
   const int wg = xcd_remap(blockIdx.x, gridDim.x);
+  const int tiles = tiles_m * tiles_n;
+  const int64_t b = wg / tiles;
   int tm, tn;
-  tile_coords(wg, tiles_m, tiles_n, 8, tm, tn);
-  const int64_t b = blockIdx.y;
+  tile_coords(wg - (int)b * tiles, tiles_m, tiles_n, 8, tm, tn);
   tile<BM, BN, WM, WN, BETA>(M, N, K, alpha, A + b * sa, lda, B + b * sb, ldb, beta, C + b * sc,
                                   ldc, tm * BM, tn * BN, lds);
 }
@@ -267,8 +270,8 @@ gemm_status launch(const GemmArgsF64 &g, hipStream_t s) {
   using G = Cfg<BM, BN, WM, WN>;
   const int tiles_m = (int)((g.M + BM - 1) / BM);
   const int tiles_n = (int)((g.N + BN - 1) / BN);
-  const int64_t nwg = (int64_t)tiles_m * tiles_n;
-  if (nwg > 0x7fffffff || g.batch > 65535) {
+  const int64_t nwg = (int64_t)tiles_m * tiles_n * g.batch;
+  if (nwg > 0x7fffffff) {
     set_error("gemm_f64: too many tiles or problems for one launch");
     return GEMM_STATUS_UNSUPPORTED;
   }
@@ -278,7 +281,7 @@ gemm_status launch(const GemmArgsF64 &g, hipStream_t s) {
     return GEMM_STATUS_UNSUPPORTED;
   }
   const bool beta = g.beta != 0.0;
-  const dim3 grid((unsigned)nwg, (unsigned)g.batch), block(G::NT);
+  const dim3 grid((unsigned)nwg), block(G::NT);
 #define MM_LAUNCH(BT)                                                                        \
   hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, WM, WN, BT>), grid, block, 0, s, (int)g.M,      \
                      (int)g.N, (int)g.K, g.alpha, g.A, g.lda, g.sa, g.B, g.ldb, g.sb, g.beta, g.C, \
@@ -288,117 +291,154 @@ gemm_status launch(const GemmArgsF64 &g, hipStream_t s) {
   return check_launch("gemm_f64_kernel");
 }
 
-// Batched small problems (M, N <= 16 SB): one wave per problem, four
-// problems per workgroup, operands loaded from memory straight into MFMA
-// fragments (each element is used by one wave only, so staging through LDS
-// would only add traffic).  The k range is walked in chunks of 16: lane group
-// g takes four k of every block (two 128-bit loads of an A row when the
-// chunk lies inside [0, K), else four 64-bit loads) and the four B values of its column at those k (64-bit loads, consecutive lanes on
-// consecutive columns); MFMA step q multiplies the group's q-th k.
-// Rows past M and columns past N read zero through the buffer range check;
-// k past K is masked per element.
-template <int SB, bool BETA>
+// Batched small problems: one wave per 16 F x 16 F sub-tile of a problem, four
+// waves per workgroup, the sub-tiles of a problem on consecutive waves.
+// Operands go from memory straight into MFMA fragments (each element is used
+// by few waves, so staging through LDS would only add traffic and barriers).
+// The k range is walked in chunks of 16: lane group g takes four k of every
+// block (two 128-bit loads of an A row when the chunk lies inside [0, K), else
+// four 64-bit loads) and the four B values of its column at those k (64-bit
+// loads, consecutive lanes on consecutive columns); MFMA step q multiplies the
+// group's q-th k.  Rows past M and columns past N read zero through the buffer
+// range check, k past K is masked per element, and memory instructions that no
+// lane needs are skipped wave by wave.
+// C stores are non-temporal (a cache hint): 32^3 x 29 297 134.2 -> 131.0 us.
+constexpr int kStoreNT = 2;
+
+template <int F, bool BETA>
 __global__ __launch_bounds__(256, 2) void small_batched_kernel(
     int M, int N, int K, double alpha, const double *__restrict__ A, int64_t lda, int64_t sa,
     const double *__restrict__ B, int64_t ldb, int64_t sb, double beta, double *__restrict__ C,
-    int64_t ldc, int64_t sc, int64_t batch) {
+    int64_t ldc, int64_t sc, int batch, int tiles_m, int tiles_n) {
   const int lane = threadIdx.x & 63;
   // the wave index is uniform across the wave; saying so keeps the problem's
   // buffer resources in scalar registers (no per-lane resource loops)
-  const int64_t prob = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int tiles = tiles_m * tiles_n;
+  int prob = (int)blockIdx.x * 4 + wv, m0 = 0, n0 = 0;
+  if (tiles > 1) {  // XCD-aware order: a problem's panels meet in one L2
+    const int unit = xcd_remap(blockIdx.x, gridDim.x) * 4 + wv;
+    prob = unit / tiles;
+    const int sub = unit - prob * tiles, tm = sub / tiles_n;
+    m0 = tm * 16 * F;
+    n0 = (sub - tm * tiles_n) * 16 * F;
+  }
   if (prob >= batch) return;
+  const int Mr = M - m0, Nr = N - n0;
   const int lr = lane & 15, lg = lane >> 4;
-  const __amdgpu_buffer_rsrc_t rA = rsrc(A + prob * sa, ((int64_t)(M - 1) * lda + K) * 8);
-  const __amdgpu_buffer_rsrc_t rB = rsrc(B + prob * sb, ((int64_t)(K - 1) * ldb + N) * 8);
-  double *Cp = C + prob * sc;
-  // column offsets of this lane's B blocks; columns past N read zero
-  int bcol[SB];
+  const __amdgpu_buffer_rsrc_t rA =
+      rsrc(A + prob * sa + m0 * lda, ((int64_t)(Mr - 1) * lda + K) * 8);
+  const __amdgpu_buffer_rsrc_t rB = rsrc(B + prob * sb + n0, ((int64_t)(K - 1) * ldb + Nr) * 8);
+  const __amdgpu_buffer_rsrc_t rC =
+      rsrc(C + prob * sc + m0 * ldc + n0, ((int64_t)(Mr - 1) * ldc + Nr) * 8);
+  int bcol[F], arow[F];
 #pragma unroll
-  for (int j = 0; j < SB; ++j) {
-    const int n = 16 * j + lr;
-    bcol[j] = n < N ? n * 8 : (int)0x80000000;
+  for (int i = 0; i < F; ++i) {
+    const int x = 16 * i + lr;
+    bcol[i] = x < Nr ? x * 8 : (int)0x80000000;
+    arow[i] = x < Mr ? x * (int)lda * 8 : (int)0x80000000;
   }
-  int arow[SB];
+  const int ldb8 = (int)ldb * 8;
+  f64x4 acc[F][F];
 #pragma unroll
-  for (int i = 0; i < SB; ++i) {
-    const int r = 16 * i + lr;
-    arow[i] = r < M ? r * (int)lda * 8 : (int)0x80000000;
-  }
-  f64x4 acc[SB][SB];
+  for (int i = 0; i < F; ++i)
 #pragma unroll
-  for (int i = 0; i < SB; ++i)
-#pragma unroll
-    for (int j = 0; j < SB; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    // lane group g takes k = k0 + 2g, +1 (q = 0, 1) and k0 + 8 + 2g, +1
-    // (q = 2, 3): one 128-bit load of the four groups reads 64 contiguous
-    // bytes of each A row
+    for (int j = 0; j < F; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
+  double a[F][4], b[F][4];
+  // lane group g takes k = k0 + 2g, +1 (q = 0, 1) and k0 + 8 + 2g, +1
+  // (q = 2, 3): one 128-bit load of the four groups reads 64 contiguous
+  // bytes of each A row
+  auto load = [&](int k0) {
     auto kq = [&](int q) { return k0 + 2 * lg + (q & 1) + 8 * (q >> 1); };
-    double a[SB][4], b[SB][4];
     if (k0 + 16 <= K) {
 #pragma unroll
-      for (int i = 0; i < SB; ++i) {
+      for (int i = 0; i < F; ++i) {
         const f64x2 v0 = ld2(rA, arow[i] + kq(0) * 8), v1 = ld2(rA, arow[i] + kq(2) * 8);
         a[i][0] = v0.x; a[i][1] = v0.y; a[i][2] = v1.x; a[i][3] = v1.y;
       }
 #pragma unroll
-      for (int j = 0; j < SB; ++j)
+      for (int j = 0; j < F; ++j)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) b[j][q] = ld1(rB, bcol[j] + kq(q) * (int)ldb * 8, 0);
+        for (int q = 0; q < 4; ++q) b[j][q] = ld1(rB, bcol[j] + kq(q) * ldb8, 0);
     } else {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
+        const bool any = k0 + (q & 1) + 8 * (q >> 1) < K;  // some lane group has a k here
         const bool kin = kq(q) < K;
 #pragma unroll
-        for (int i = 0; i < SB; ++i) a[i][q] = ld1(rA, kin ? arow[i] + kq(q) * 8 : (int)0x80000000, 0);
+        for (int i = 0; i < F; ++i)
+          a[i][q] = any ? ld1(rA, kin ? arow[i] + kq(q) * 8 : (int)0x80000000, 0) : 0.0;
 #pragma unroll
-        for (int j = 0; j < SB; ++j)
-          b[j][q] = ld1(rB, kin ? bcol[j] + kq(q) * (int)ldb * 8 : (int)0x80000000, 0);
+        for (int j = 0; j < F; ++j)
+          b[j][q] = any ? ld1(rB, kin ? bcol[j] + kq(q) * ldb8 : (int)0x80000000, 0) : 0.0;
       }
     }
+  };
+  for (int k0 = 0; k0 < K; k0 += 16) {
+    load(k0);
 #pragma unroll
     for (int q = 0; q < 4; ++q)
 #pragma unroll
-      for (int i = 0; i < SB; ++i)
+      for (int i = 0; i < F; ++i)
 #pragma unroll
-        for (int j = 0; j < SB; ++j)
+        for (int j = 0; j < F; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i][q], b[j][q], acc[i][j], 0, 0, 0);
   }
+  // element e of lane l is row lg + 4 e, column lr of its block; columns past
+  // N get an out-of-range offset, rows past M fall beyond the resource.  With
+  // beta != 0 every read of C is issued before the first store.
+  const int ldc8 = (int)ldc * 8;
+  int vb[F];
 #pragma unroll
-  for (int i = 0; i < SB; ++i)
+  for (int j = 0; j < F; ++j) {
+    const int col = 16 * j + lr;
+    vb[j] = col < Nr ? lg * ldc8 + col * 8 : (int)0x80000000;
+  }
+  double cold[F][F][4];
+  if (BETA) {
 #pragma unroll
-    for (int j = 0; j < SB; ++j) {
-      const int col = 16 * j + lr;
-      if (col >= N) continue;
+    for (int i = 0; i < F; ++i)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int row = 16 * i + lg + 4 * e;
-        if (row < M) {
-          double *p = Cp + (int64_t)row * ldc + col;
-          const double v = alpha * acc[i][j][e];
-          // non-temporal store (a cache hint): 32^3 x 29 297 134.2 -> 131.0
-          // us, 48^3 x 12 000 135.1 -> 125.9 us at beta = 0
-          __builtin_nontemporal_store(BETA ? fma(beta, *p, v) : v, p);
+      for (int e = 0; e < 4; ++e)
+        if (16 * i + 4 * e < Mr) {
+#pragma unroll
+          for (int j = 0; j < F; ++j) cold[i][j][e] = ld1(rC, vb[j], (16 * i + 4 * e) * ldc8);
+        }
+  }
+#pragma unroll
+  for (int i = 0; i < F; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (16 * i + 4 * e < Mr) {
+#pragma unroll
+        for (int j = 0; j < F; ++j) {
+          double v = alpha * acc[i][j][e];
+          if (BETA) v = fma(beta, cold[i][j][e], v);
+          __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rC, vb[j],
+                                                (16 * i + 4 * e) * ldc8, kStoreNT);
         }
       }
-    }
 }
 
-template <int SB>
+// 32-bit offsets of the small-problem kernel: a problem's rows of A and of C
+// (rounded up to whole sub-tiles), K rows of B.
+static bool small_fits(const GemmArgsF64 &g) {
+  const int64_t lim = (int64_t)1 << 31, rows = g.M + 64;
+  return (rows * g.lda + g.K) * 8 < lim && (g.K * g.ldb + g.N) * 8 < lim &&
+         (rows * g.ldc + g.N) * 8 < lim;
+}
+
+template <int F>
 gemm_status launch_small(const GemmArgsF64 &g, hipStream_t s) {
-  if (((int64_t)(16 * SB) * g.lda + g.K) * 8 >= ((int64_t)1 << 31) ||
-      ((int64_t)g.K * g.ldb + g.N) * 8 >= ((int64_t)1 << 31)) {
-    set_error("gemm_f64: lda or ldb too large for 32-bit offsets of the small-problem kernel");
-    return GEMM_STATUS_UNSUPPORTED;
-  }
-  const bool beta = g.beta != 0.0;
-  const int64_t nwg = (g.batch + 3) / 4;
-  if (nwg > 0x7fffffff) { set_error("gemm_f64: batch too large"); return GEMM_STATUS_UNSUPPORTED; }
-#define MM_LAUNCH(BT)                                                                            \
-  hipLaunchKernelGGL((small_batched_kernel<SB, BT>), dim3((unsigned)nwg), dim3(256), 0, s,       \
-                     (int)g.M, (int)g.N, (int)g.K, g.alpha, g.A, g.lda, g.sa, g.B, g.ldb, g.sb,     \
-                     g.beta, g.C, g.ldc, g.sc, g.batch)
-  if (beta) MM_LAUNCH(true); else MM_LAUNCH(false);
+  const int64_t tiles_m = (g.M + 16 * F - 1) / (16 * F), tiles_n = (g.N + 16 * F - 1) / (16 * F);
+  const int64_t units = tiles_m * tiles_n * g.batch;
+  if (units > 0x7ffffff0) { set_error("gemm_f64: batch too large"); return GEMM_STATUS_UNSUPPORTED; }
+#define MM_LAUNCH(BT)                                                                               \
+  hipLaunchKernelGGL((small_batched_kernel<F, BT>), dim3((unsigned)((units + 3) / 4)),        \
+                     dim3(256), 0, s, (int)g.M, (int)g.N, (int)g.K, g.alpha, g.A, g.lda, g.sa, g.B, \
+                     g.ldb, g.sb, g.beta, g.C, g.ldc, g.sc, (int)g.batch, (int)tiles_m,             \
+                     (int)tiles_n)
+  if (g.beta != 0.0) MM_LAUNCH(true); else MM_LAUNCH(false);
 #undef MM_LAUNCH
   return check_launch("small_batched_kernel");
 }
@@ -436,36 +476,81 @@ static const F64Config kF64Configs[] = {
 int f64_num_configs() { return (int)(sizeof(kF64Configs) / sizeof(kF64Configs[0])); }
 const TileConfig &f64_config(int i) { return kF64Configs[i].t; }
 
+// Sub-tile codes of a batch (beyond the configurations): one wave per 16 x 16,
+// 32 x 32 or 64 x 64 outputs.
+constexpr int kDirect16 = 100, kDirect32 = 101, kDirect64 = 102;
+
+// A batch: the tile with the least modelled time beyond the operands' traffic
+// (`fixed` ns per output tile, `step` ns per tile and 16 k, whole machine;
+// fitted on 26 batches whose inputs change from call to call).  LDS tiles only
+// when they fill the machine.  Against one wave per problem up to 64 x 64 and
+// 128 x 128 LDS tiles beyond, us at beta = 0: 76 x 48 x 32 x 1134 36 -> 16, 9 x
+// 112 x 48 x 770 33 -> 9, 159 x 112 x 64 x 429 52 -> 33, 96^3 x 700 58 -> 43.
+static int f64_batch_config(int64_t M, int64_t N, int64_t K, int64_t batch) {
+  // 64 x 64 per wave only for batches of nearly full 64 x 64 problems that
+  // fill the machine (64^3 x 2000 41 us against 45 for 32 x 32)
+  if (M > 48 && N > 48 && M <= 64 && N <= 64 && K >= 32 && batch >= 6 * (int64_t)num_cus())
+    return kDirect64;
+  struct Tile {
+    int cfg, b, per_cu;
+    double fixed, step;
+  };
+  constexpr Tile kTiles[] = {{kDirect16, 16, 20, 0.05, 0.22},
+                             {kDirect32, 32, 12, 0.10, 0.45},
+                             {2, 64, 3, 1.0, 1.55},
+                             {0, 128, 2, 4.0, 6.0}};
+  int best = 2;
+  double best_cost = -1.0;
+  for (const Tile &t : kTiles) {
+    const bool lds = t.cfg < kDirect16;
+    const double tiles = (double)((M + t.b - 1) / t.b) * (double)((N + t.b - 1) / t.b) * (double)batch;
+    const double slots = (double)num_cus() * t.per_cu, r = tiles / slots;
+    // the sub-tiles re-read their panels too often in problems beyond 256
+    if (lds ? (r < 1.0 && M <= 256 && N <= 256) : (M > 256 || N > 256)) continue;
+    const double rounds = r > 4.0 ? r : r >= 1.0 ? std::ceil(r) : 0.7 + 0.3 * r;
+    const double cost = rounds * slots * (t.fixed + t.step * (double)((K + 15) / 16));
+    if (best_cost < 0.0 || cost < best_cost) { best = t.cfg; best_cost = cost; }
+  }
+  return best;
+}
+
 int f64_default_config(int64_t M, int64_t N, int64_t K, int64_t batch) {
-  (void)K;
-  // batches of small problems: one wave per problem
-  if (batch > 1 && M <= 64 && N <= 64) return M <= 16 && N <= 16 ? 3 : (M <= 32 && N <= 32 ? 4 : 5);
+  if (batch > 1) return f64_batch_config(M, N, K, batch);
   // 128 x 128 tiles once there are two per CU; 64 x 64 below that.  Measured
   // on one box: the kernel is matrix-core bound and the tiles tie within 1 %
   // at 4096^3, but 64 x 64 tiles read 10x the minimum HBM bytes there (5.3
   // against 1.9 GB per launch), which costs clock under the power limit; at
   // 2048^3 (one 128 x 128 tile per CU) 64 x 64 tiles are 11 % faster.
   const int64_t t = ((M + 127) / 128) * ((N + 127) / 128);
-  const int64_t need = (2 * (int64_t)num_cus() + t - 1) / (t > 0 ? t : 1);  // problems needed
-  return batch >= need ? 0 : 2;
+  return t >= 2 * (int64_t)num_cus() ? 0 : 2;
 }
 
 gemm_status f64_run(const GemmArgsF64 &g, int cfg, hipStream_t s) {
+  if (cfg >= 3 && cfg <= 5) {
+    const int lim = cfg == 3 ? 16 : cfg == 4 ? 32 : 64;
+    if (g.M > lim || g.N > lim) {
+      set_error("gemm_f64: problem larger than the small-problem configuration");
+      return GEMM_STATUS_UNSUPPORTED;
+    }
+    cfg = kDirect16 + (cfg - 3);
+  }
+  if (cfg >= kDirect16) {
+    const int lim = cfg == kDirect16 ? 16 : cfg == kDirect32 ? 32 : 64;
+    if (g.M <= 64 && g.N <= 64 &&
+        ((lim * g.lda + g.K) * 8 >= ((int64_t)1 << 31) || (g.K * g.ldb + g.N) * 8 >= ((int64_t)1 << 31))) {
+      set_error("gemm_f64: lda or ldb too large for 32-bit offsets of the small-problem kernel");
+      return GEMM_STATUS_UNSUPPORTED;
+    }
+    // other operands that 32-bit offsets cannot reach take the 64 x 64 tile
+    if (!f64::small_fits(g)) cfg = 2;
+  }
   switch (cfg) {
     case 0: return f64::launch<128, 128, 64, 64>(g, s);
     case 1: return f64::launch<256, 128, 64, 64>(g, s);
     case 2: return f64::launch<64, 64, 32, 32>(g, s);
-    case 3:
-    case 4:
-    case 5: {
-      const int lim = cfg == 3 ? 16 : cfg == 4 ? 32 : 64;
-      if (g.M > lim || g.N > lim) {
-        set_error("gemm_f64: problem larger than the small-problem configuration");
-        return GEMM_STATUS_UNSUPPORTED;
-      }
-      return cfg == 3 ? f64::launch_small<1>(g, s)
-                      : cfg == 4 ? f64::launch_small<2>(g, s) : f64::launch_small<4>(g, s);
-    }
+    case kDirect16: return f64::launch_small<1>(g, s);
+    case kDirect32: return f64::launch_small<2>(g, s);
+    case kDirect64: return f64::launch_small<4>(g, s);
     default: set_error("gemm_f64: bad tile config"); return GEMM_STATUS_UNSUPPORTED;
   }
 }

@@ -253,3 +253,27 @@ def test_batched_strided_more_problems_than_one_launch():
     mm.gemm_f64_strided_batched(M, N, K, 2.0, dA, K, M * K, dB, N, K * N, -1.0, dC, N, M * N, batch)
     torch.cuda.synchronize()
     assert np.array_equal(dC.cpu().numpy(), 2.0 * np.matmul(hA, hB) - hC)
+
+
+@pytest.mark.parametrize("M,N,K,batch", [(17, 16, 15, 50), (16, 33, 16, 50), (65, 31, 17, 600),
+                                         (50, 64, 33, 1600), (64, 49, 40, 1600), (100, 72, 90, 90),
+                                         (128, 128, 18, 300), (130, 250, 7, 70), (300, 260, 33, 5),
+                                         (7, 160, 3, 20), (1, 1, 1, 3)])
+def test_tiles_of_batched_problems_exact(M, N, K, batch):
+    """Batches on whichever tile they get (one-wave 16, 32 or 64 sub-tiles, LDS
+    tiles): integer inputs, every element of every problem exact, gaps
+    between the outputs untouched, beta == 0 never reads C."""
+    import torch
+    import paper_1902_10345_amd as mm
+    sc = M * N + 3
+    A = torch.from_numpy(si.integers((batch * M, K), K, -1000, 1000)).cuda().double().view(batch, M, K)
+    B = torch.from_numpy(si.integers((batch * K, N), K + 1, -1000, 1000)).cuda().double().view(batch, K, N)
+    want = torch.matmul(A, B)
+    C = torch.full((batch, sc), float("nan"), dtype=torch.float64, device="cuda")
+    mm.gemm_f64_strided_batched(M, N, K, 1.0, A, K, M * K, B, N, K * N, 0.0, C, N, sc, batch)
+    assert torch.equal(C[:, :M * N].view(batch, M, N), want)
+    assert bool(torch.isnan(C[:, M * N:]).all())
+    C.fill_(2.0)
+    mm.gemm_f64_strided_batched(M, N, K, 2.0, A, K, M * K, B, N, K * N, -3.0, C, N, sc, batch)
+    assert torch.equal(C[:, :M * N].view(batch, M, N), 2 * want - 6.0)
+    assert bool((C[:, M * N:] == 2.0).all())
