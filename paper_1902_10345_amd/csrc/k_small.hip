@@ -1,11 +1,11 @@
 // k_small.hip -- products too small to fill the machine with output tiles.
 //
 // One BM x BN output tile per workgroup of KW waves.  The tile's k range is
-// cut into KW consecutive chunks of whole k-steps, one per wave: every wave
-// accumulates the whole tile over its own chunk on the matrix cores, with its
-// MFMA fragments loaded straight from global memory into registers (no LDS
-// staging: a wave touches each element it loads once).  The KW partial tiles
-// are then summed in wave order through LDS and the epilogue applies alpha
+// cut into KW consecutive ranges of whole chunks, one per wave: every wave
+// accumulates the whole tile over its own range on the matrix cores, with its
+// own loads (a wave touches each element it loads once; nothing is shared
+// between waves, so the k loop has no barrier).  The KW partial tiles are then
+// summed in wave order through LDS and the epilogue applies alpha
 // and beta.  This is the k-reduction of the matrix product split into
 // independent partial reductions whose write conflict on C is resolved by a
 // sum (Sec. 3.3, write-conflict resolution; App. A, the wcr attribute), here
@@ -28,64 +28,244 @@ using bx3::bf16x2;
 using bx3::f32x2;
 using bx3::kBufferFlags;
 
-constexpr int KW = 8;  // waves per workgroup (k chunks per output tile)
+constexpr int KW = 8;  // waves per workgroup (k ranges per output tile)
 
-// Per lane and k-step: E consecutive k of one row of op(A) and of one column
-// of op(B) per 32 x 32 block (k-step 8 in binary32: lanes 0-31 hold k 0..3,
-// lanes 32-63 k 4..7; k-step 16 in bf16: 8 k per half-wave).
-template <int NP>
-struct Mode {
-  static constexpr int KSTEP = NP == 1 ? 8 : 16;
-  static constexpr int E = NP == 1 ? 4 : 8;
+// One operand of a wave: NF blocks of 32 rows of op(A) (columns of op(B)), CK
+// k per chunk (the unit of loading), SETS chunks of loads in flight, E
+// consecutive k per lane and MFMA k-step (a k-step is 2E deep: lanes 0-31 hold
+// its first E k, lanes 32-63 the others).  A row index outside the matrix reads
+// as zero: its lane offset lies beyond the resource.  Lane offsets are fixed
+// for the whole product and the chunk moves in the wave-uniform offset, so a
+// chunk costs no vector address arithmetic.  How it is read:
+enum class Read {
+  // row index contiguous in memory (row-major B, transposed A): one 32-bit
+  // load per k, consecutive lanes on consecutive addresses
+  kRows,
+  // k contiguous (row-major A, transposed B): 128-bit loads, at any alignment,
+  // each lane from its own row
+  kDirect,
+  // k contiguous, long products: a direct read touches 32 rows per
+  // instruction, which the L1 serves one row at a time.  Instead consecutive
+  // lanes read consecutive 16-byte pieces of a row (CK k per row: 8 or 4
+  // lanes), and the wave turns the chunk through an LDS area of its own
+  // (pieces XOR-swizzled by the row; no barrier: one wave's LDS instructions
+  // execute in order)
+  kStaged,
 };
 
-// Loads the lane's E values of one row (A) or column (B) of the operand at
-// k = k0 .. k0 + E - 1.  idx: the row of op(A) / column of op(B); valid: idx
-// inside the matrix.  KC: the operand is stored with k contiguous (row-major
-// A, transposed B); then VEC allows 128-bit loads (row stride a multiple of
-// 4 floats, 16-byte aligned base, K % 4 == 0).  Elements outside the matrix
-// read as zero: their offset is pushed past the resource.
-template <int E, bool KC, bool VEC>
-__device__ __forceinline__ void load_frag(__amdgpu_buffer_rsrc_t rs, int64_t ld, int idx,
-                                          bool valid, int k0, int K, float (&v)[E]) {
-  constexpr int kOut = (int)0x80000000;
-  if constexpr (KC && VEC) {
+template <Read R, int NF, int CK, int SETS, int E>
+struct Operand;
+
+template <int NF, int CK, int SETS, int E>
+struct Operand<Read::kStaged, NF, CK, SETS, E> {
+  static constexpr int NI = NF * CK / 8;        // 128-bit loads per chunk
+  static constexpr int LPR = CK / 4;            // lanes (16-byte pieces) per row
+  static constexpr int LDS_FLOATS = NF * 32 * CK;
+  __amdgpu_buffer_rsrc_t rs;
+  int voff[NI];
+  f32x4 raw[SETS][NI];
+  float *lds;
+  int lane;
+  __device__ static __forceinline__ int swz(int r) { return LPR == 8 ? r & 7 : (r >> 1) & 3; }
+  __device__ __forceinline__ int row(int j) const { return j * (64 / LPR) + lane / LPR; }
+  __device__ __forceinline__ void init(const float *P, int bytes, int ld, int i0, int lim, int lane_,
+                                       float *lds_) {
+    rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(P), (short)0, bytes, kBufferFlags);
+    lane = lane_;
+    lds = lds_;
 #pragma unroll
-    for (int q = 0; q < E / 4; ++q) {
-      const int k = k0 + 4 * q;
-      const int off = (valid && k < K) ? (int)(((unsigned)idx * (unsigned)ld + k) * 4u) : kOut;
-      const float4 x =
-          __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
-      v[4 * q + 0] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
-    }
-  } else {
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int k = k0 + e;
-      const unsigned el = KC ? (unsigned)idx * (unsigned)ld + k : (unsigned)k * (unsigned)ld + idx;
-      const int off = (valid && k < K) ? (int)(el * 4u) : kOut;
-      v[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0));
+    for (int j = 0; j < NI; ++j) {
+      const int i = i0 + row(j);
+      voff[j] = i < lim ? (int)(((unsigned)i * (unsigned)ld + (lane % LPR) * 4) * 4u) : (int)0x80000000;
     }
   }
+  template <int S>
+  __device__ __forceinline__ void load(int k0) {
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+      raw[S][j] = __builtin_bit_cast(
+          f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff[j], k0 * 4, 0));
+  }
+  // the chunk that begins before k = 0
+  template <int S>
+  __device__ __forceinline__ void load_masked(int k0) {
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bool in = voff[j] >= 0 && k0 + (lane % LPR) * 4 + e >= 0;
+        const int off = in ? voff[j] + (k0 + e) * 4 : (int)0x80000000;
+        raw[S][j][e] =
+            __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0));
+      }
+  }
+  template <int S>
+  __device__ __forceinline__ void stage() {
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      const int r = row(j);
+      *reinterpret_cast<f32x4 *>(lds + r * CK + (((lane % LPR) ^ swz(r)) << 2)) = raw[S][j];
+    }
+  }
+  template <int S>
+  __device__ __forceinline__ void frag(float (&v)[NF][E], int u) const {
+    const int lr = lane & 31, lg = lane >> 5;
+#pragma unroll
+    for (int i = 0; i < NF; ++i)
+#pragma unroll
+      for (int q = 0; q < E / 4; ++q) {
+        const int r = 32 * i + lr;
+        const f32x4 x = *reinterpret_cast<const f32x4 *>(
+            lds + r * CK + ((((2 * u + lg) * (E / 4) + q) ^ swz(r)) << 2));
+        v[i][4 * q] = x.x; v[i][4 * q + 1] = x.y; v[i][4 * q + 2] = x.z; v[i][4 * q + 3] = x.w;
+      }
+  }
+};
+
+template <int NF, int CK, int SETS, int E>
+struct Operand<Read::kRows, NF, CK, SETS, E> {
+  static constexpr int LDS_FLOATS = 0;
+  __amdgpu_buffer_rsrc_t rs;
+  int voff[NF];
+  float raw[SETS][NF][CK / 2];  // element x: k-step x / E, k x % E of the lane's E
+  int ld, lg;
+  __device__ __forceinline__ void init(const float *P, int bytes, int ld_, int i0, int lim, int lane,
+                                       float *) {
+    rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(P), (short)0, bytes, kBufferFlags);
+    ld = ld_;
+    lg = lane >> 5;
+#pragma unroll
+    for (int i = 0; i < NF; ++i) {
+      const int n = i0 + 32 * i + (lane & 31);
+      voff[i] = n < lim ? n * 4 : (int)0x80000000;
+    }
+  }
+  template <int S>
+  __device__ __forceinline__ void load(int k0) {
+#pragma unroll
+    for (int i = 0; i < NF; ++i) {
+      const int off = voff[i] + lg * E * ld * 4;
+#pragma unroll
+      for (int x = 0; x < CK / 2; ++x)
+        raw[S][i][x] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                     rs, off, (k0 + x / E * 2 * E + x % E) * ld * 4, 0));
+    }
+  }
+  template <int S>
+  __device__ __forceinline__ void load_masked(int k0) {
+#pragma unroll
+    for (int i = 0; i < NF; ++i)
+#pragma unroll
+      for (int x = 0; x < CK / 2; ++x) {
+        const int k = k0 + x / E * 2 * E + lg * E + x % E;
+        const int off = voff[i] >= 0 && k >= 0 ? voff[i] + k * ld * 4 : (int)0x80000000;
+        raw[S][i][x] =
+            __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0));
+      }
+  }
+  template <int S>
+  __device__ __forceinline__ void stage() {}
+  template <int S>
+  __device__ __forceinline__ void frag(float (&v)[NF][E], int u) const {
+#pragma unroll
+    for (int i = 0; i < NF; ++i)
+#pragma unroll
+      for (int e = 0; e < E; ++e) v[i][e] = raw[S][i][u * E + e];
+  }
+};
+
+template <int NF, int CK, int SETS, int E>
+struct Operand<Read::kDirect, NF, CK, SETS, E> {
+  static constexpr int LDS_FLOATS = 0;
+  __amdgpu_buffer_rsrc_t rs;
+  int voff[NF];
+  float raw[SETS][NF][CK / 2];
+  int lg;
+  __device__ __forceinline__ void init(const float *P, int bytes, int ld, int i0, int lim, int lane,
+                                       float *) {
+    rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(P), (short)0, bytes, kBufferFlags);
+    lg = lane >> 5;
+#pragma unroll
+    for (int i = 0; i < NF; ++i) {
+      const int m = i0 + 32 * i + (lane & 31);
+      voff[i] = m < lim ? (int)(((unsigned)m * (unsigned)ld + lg * E) * 4u) : (int)0x80000000;
+    }
+  }
+  template <int S>
+  __device__ __forceinline__ void load(int k0) {
+#pragma unroll
+    for (int i = 0; i < NF; ++i)
+#pragma unroll
+      for (int q = 0; q < CK / 8; ++q) {
+        const float4 x = __builtin_bit_cast(
+            float4, __builtin_amdgcn_raw_buffer_load_b128(
+                        rs, voff[i], (k0 + 4 * q / E * 2 * E + 4 * q % E) * 4, 0));
+        raw[S][i][4 * q + 0] = x.x; raw[S][i][4 * q + 1] = x.y;
+        raw[S][i][4 * q + 2] = x.z; raw[S][i][4 * q + 3] = x.w;
+      }
+  }
+  template <int S>
+  __device__ __forceinline__ void load_masked(int k0) {
+#pragma unroll
+    for (int i = 0; i < NF; ++i)
+#pragma unroll
+      for (int x = 0; x < CK / 2; ++x) {
+        const int kr = k0 + x / E * 2 * E + x % E;  // the k of lane group 0
+        const int off = voff[i] >= 0 && kr + lg * E >= 0 ? voff[i] + kr * 4 : (int)0x80000000;
+        raw[S][i][x] =
+            __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0));
+      }
+  }
+  template <int S>
+  __device__ __forceinline__ void stage() {}
+  template <int S>
+  __device__ __forceinline__ void frag(float (&v)[NF][E], int u) const {
+#pragma unroll
+    for (int i = 0; i < NF; ++i)
+#pragma unroll
+      for (int e = 0; e < E; ++e) v[i][e] = raw[S][i][u * E + e];
+  }
+};
+
+template <int NP>
+constexpr int kE = NP == 1 ? 4 : 8;
+
+// k per chunk: one MFMA k-step, or staged 32 (16 for 64 x 64 tiles, whose
+// blocks need the registers).
+template <int BM, int NP>
+constexpr int chunk_k(bool staged) {
+  return staged ? (BM == 32 ? 32 : 16) : 2 * kE<NP>;
 }
 
-template <int BM, int BN, int NP, bool TA, bool TB, bool VA, bool VB, bool BETA>
+// Bound: a wave's chain of chunks (two to four waves per SIMD), each wanting
+// its loads to arrive and its share of the L1's address rate; SETS - 1 chunks
+// of loads are in flight while one is multiplied.
+template <int BM, int BN, int NP, bool STAGED, bool TA, bool TB, bool BETA>
 __global__ __launch_bounds__(64 * KW) void gemm_small_kernel(
-    int M, int N, int K, float alpha, const float *__restrict__ A, int64_t lda, int bytes_a,
-    const float *__restrict__ B, int64_t ldb, int bytes_b, float beta, float *__restrict__ C,
-    int64_t ldc, int tiles_n, int steps_per_wave) {
+    int M, int N, int K, float alpha, const float *__restrict__ A, int lda, int bytes_a,
+    const float *__restrict__ B, int ldb, int bytes_b, float beta, float *__restrict__ C,
+    int64_t ldc, int tiles_n, int chunks_per_wave) {
   constexpr int FM = BM / 32, FN = BN / 32;
-  constexpr int KSTEP = Mode<NP>::KSTEP, E = Mode<NP>::E;
+  constexpr int E = kE<NP>;
+  constexpr int CK = chunk_k<BM, NP>(STAGED);
+  constexpr int KS = CK / (2 * E);              // MFMA k-steps per chunk
+  constexpr int SETS = STAGED ? (BM == 32 ? 2 : 3) : (FM * CK > 16 ? 3 : 4);
   constexpr int BLK = 16 * 64;  // floats of one 32 x 32 accumulator block
-  __shared__ float red[KW * FM * FN * BLK];
+  constexpr Read kc = STAGED ? Read::kStaged : Read::kDirect;
+  using OpA = Operand<TA ? Read::kRows : kc, FM, CK, SETS, E>;
+  using OpB = Operand<TB ? kc : Read::kRows, FN, CK, SETS, E>;
+  constexpr int TOT = FM * FN * BLK;            // floats of a partial tile
+  constexpr int STG = OpA::LDS_FLOATS + OpB::LDS_FLOATS;
+  constexpr int PERW = TOT > STG ? TOT : STG;   // a wave's LDS: staging, then its partial tile
+  __shared__ __attribute__((aligned(16))) float smem[KW * PERW];
 
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int lr = lane & 31, lg = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m0 = (blockIdx.x / tiles_n) * BM, n0 = (blockIdx.x % tiles_n) * BN;
-  const __amdgpu_buffer_rsrc_t ra =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(A), (short)0, bytes_a, kBufferFlags);
-  const __amdgpu_buffer_rsrc_t rb =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(B), (short)0, bytes_b, kBufferFlags);
+  OpA opa;
+  OpB opb;
+  opa.init(A, bytes_a, lda, m0, M, lane, smem + w * PERW);
+  opb.init(B, bytes_b, ldb, n0, N, lane, smem + w * PERW + OpA::LDS_FLOATS);
 
   f32x16 acc[FM][FN];
 #pragma unroll
@@ -95,110 +275,142 @@ __global__ __launch_bounds__(64 * KW) void gemm_small_kernel(
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
 
-  const int ks_total = (K + KSTEP - 1) / KSTEP;
-  const int ks0 = w * steps_per_wave;
-  const int ks1 = ks0 + steps_per_wave < ks_total ? ks0 + steps_per_wave : ks_total;
+  // the grid of chunks ends at K: only chunk 0 can be partial
+  const int total = (K + CK - 1) / CK;
+  const int kbase = K - total * CK;
+  const int c0 = w * chunks_per_wave;
+  const int n = (c0 + chunks_per_wave < total ? c0 + chunks_per_wave : total) - c0;
 
-  float fa[2][FM][E], fb[2][FN][E];
-  auto load = [&](int set, int ks) {
-    const int k0 = ks * KSTEP + lg * E;
-#pragma unroll
-    for (int i = 0; i < FM; ++i) {
-      const int m = m0 + i * 32 + lr;
-      load_frag<E, !TA, VA>(ra, lda, m, m < M, k0, K, fa[set][i]);
-    }
-#pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      const int n = n0 + j * 32 + lr;
-      load_frag<E, TB, VB>(rb, ldb, n, n < N, k0, K, fb[set][j]);
-    }
+  auto load = [&](auto SET, int c) {
+    constexpr int S = decltype(SET)::value;
+    const int k0 = kbase + c * CK;
+    opa.template load<S>(k0);
+    opb.template load<S>(k0);
   };
-  auto mfma = [&](int set) {
-    if constexpr (NP == 1) {
-      // MFMA q sums k = q of the lower half-wave's four and of the upper
-      // half-wave's four: every k of the step exactly once
+  auto load_masked = [&](auto SET) {
+    constexpr int S = decltype(SET)::value;
+    opa.template load_masked<S>(kbase);
+    opb.template load_masked<S>(kbase);
+  };
+  auto multiply = [&](auto SET) {
+    constexpr int S = decltype(SET)::value;
+    if constexpr (STG > 0) {
+      // the previous chunk's reads are done before its area is rewritten, and
+      // this chunk's writes before its reads (order within the wave)
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      opa.template stage<S>();
+      opb.template stage<S>();
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
+    for (int u = 0; u < KS; ++u) {
+      float fa[FM][E], fb[FN][E];
+      opa.template frag<S>(fa, u);
+      opb.template frag<S>(fb, u);
+      if constexpr (NP == 1) {
+        // MFMA q sums k = q of the lower half-wave's four and of the upper
+        // half-wave's four: every k of the step exactly once
 #pragma unroll
-        for (int i = 0; i < FM; ++i)
+        for (int q = 0; q < 4; ++q)
 #pragma unroll
-          for (int j = 0; j < FN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[set][i][q], fb[set][j][q],
-                                                             acc[i][j], 0, 0, 0);
-    } else {
-      bf16x8 a[NP][FM], b[NP][FN];
-      // split of E = 8 binary32 values into NP bf16 planes, two at a time
-      auto split8 = [&](const float (&x)[E], bf16x8 &p0, bf16x8 &p1, bf16x8 &p2) {
+          for (int i = 0; i < FM; ++i)
 #pragma unroll
-        for (int e = 0; e < 8; e += 2) {
-          bf16x2 x0, x1, x2;
-          if constexpr (NP == 2) bx3::split2(f32x2{x[e], x[e + 1]}, x0, x1);
-          else bx3::split3(f32x2{x[e], x[e + 1]}, x0, x1, x2);
-          p0[e] = x0.x; p0[e + 1] = x0.y;
-          p1[e] = x1.x; p1[e + 1] = x1.y;
-          if constexpr (NP == 3) { p2[e] = x2.x; p2[e + 1] = x2.y; }
+            for (int j = 0; j < FN; ++j)
+              acc[i][j] =
+                  __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][q], fb[j][q], acc[i][j], 0, 0, 0);
+      } else {
+        bf16x8 a[NP][FM], b[NP][FN];
+        // split of E = 8 binary32 values into NP bf16 planes, two at a time
+        auto split8 = [&](const float (&x)[E], bf16x8 &p0, bf16x8 &p1, bf16x8 &p2) {
+#pragma unroll
+          for (int e = 0; e < 8; e += 2) {
+            bf16x2 x0, x1, x2;
+            if constexpr (NP == 2) bx3::split2(f32x2{x[e], x[e + 1]}, x0, x1);
+            else bx3::split3(f32x2{x[e], x[e + 1]}, x0, x1, x2);
+            p0[e] = x0.x; p0[e + 1] = x0.y;
+            p1[e] = x1.x; p1[e + 1] = x1.y;
+            if constexpr (NP == 3) { p2[e] = x2.x; p2[e + 1] = x2.y; }
+          }
+        };
+#pragma unroll
+        for (int i = 0; i < FM; ++i) split8(fa[i], a[0][i], a[1][i], a[NP - 1][i]);
+#pragma unroll
+        for (int j = 0; j < FN; ++j) split8(fb[j], b[0][j], b[1][j], b[NP - 1][j]);
+        auto prod = [&](int qa, int qb) {
+#pragma unroll
+          for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[qa][i], b[qb][j], acc[i][j],
+                                                                  0, 0, 0);
+        };
+        // small products first, the leading product last
+        if constexpr (NP == 3) {
+          prod(2, 0);
+          prod(1, 1);
+          prod(0, 2);
         }
-      };
-#pragma unroll
-      for (int i = 0; i < FM; ++i) split8(fa[set][i], a[0][i], a[1][i], a[NP - 1][i]);
-#pragma unroll
-      for (int j = 0; j < FN; ++j) split8(fb[set][j], b[0][j], b[1][j], b[NP - 1][j]);
-      auto prod = [&](int qa, int qb) {
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[qa][i], b[qb][j], acc[i][j],
-                                                                0, 0, 0);
-      };
-      // small products first, the leading product last
-      if constexpr (NP == 3) {
-        prod(2, 0);
-        prod(1, 1);
-        prod(0, 2);
+        prod(1, 0);
+        prod(0, 1);
+        prod(0, 0);
       }
-      prod(1, 0);
-      prod(0, 1);
-      prod(0, 0);
     }
   };
 
-  // two register sets: the loads of step ks+1 are in flight while step ks
-  // is multiplied
-  if (ks0 < ks1) {
-    load(0, ks0);
-    int ks = ks0;
-    for (; ks + 2 <= ks1; ks += 2) {
-      load(1, ks + 1);
-      mfma(0);
-      if (ks + 2 < ks1) load(0, ks + 2);
-      mfma(1);
-    }
-    if (ks < ks1) mfma(0);
+  if (n > 0) {
+    if (c0 == 0 && kbase < 0) load_masked(std::integral_constant<int, 0>{});
+    else load(std::integral_constant<int, 0>{}, c0);
+    bx3::static_for<SETS - 2>([&](auto I) {
+      constexpr int i = decltype(I)::value + 1;
+      if (i < n) load(std::integral_constant<int, i>{}, c0 + i);
+    });
+    for (int s = 0; s < n; s += SETS)
+      bx3::static_for<SETS>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        if (s + i < n) {
+          if (s + i + SETS - 1 < n)
+            load(std::integral_constant<int, (i + SETS - 1) % SETS>{}, c0 + s + i + SETS - 1);
+          multiply(I);
+        }
+      });
   }
 
-  // partial tiles to LDS (lane-contiguous: no bank conflicts), then the
-  // ordered sum over the waves and the epilogue
+  // partial tiles to LDS (lane-contiguous: no bank conflicts; each wave's own
+  // area, after its staging), then the ordered sum over the waves and the
+  // epilogue (every read of C before the first store)
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
     for (int j = 0; j < FN; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) red[((w * FM + i) * FN + j) * BLK + e * 64 + lane] = acc[i][j][e];
-  __syncthreads();
-  constexpr int TOT = FM * FN * BLK;
-  for (int idx = tid; idx < TOT; idx += 64 * KW) {
-    float s = red[idx];
+      for (int e = 0; e < 16; ++e)
+        smem[w * PERW + (i * FN + j) * BLK + e * 64 + lane] = acc[i][j][e];
+  constexpr int PER = TOT / (64 * KW);
+  float cold[PER];
+  float *p[PER];
 #pragma unroll
-    for (int v = 1; v < KW; ++v) s += red[v * TOT + idx];
+  for (int r = 0; r < PER; ++r) {
+    const int idx = tid + r * 64 * KW;
     const int l = idx & 63, e = (idx >> 6) & 15, blk = idx >> 10;
     const int row = m0 + (blk / FN) * 32 + 8 * (e >> 2) + 4 * (l >> 5) + (e & 3);
     const int col = n0 + (blk % FN) * 32 + (l & 31);
-    if (row < M && col < N) {
-      float *p = C + (int64_t)row * ldc + col;
-      const float v = alpha * s;
-      *p = BETA ? fmaf(beta, *p, v) : v;
-    }
+    p[r] = row < M && col < N ? C + (int64_t)row * ldc + col : nullptr;
+    if (BETA) cold[r] = p[r] ? *p[r] : 0.0f;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < PER; ++r) {
+    const int idx = tid + r * 64 * KW;
+    float s = smem[idx];
+#pragma unroll
+    for (int v = 1; v < KW; ++v) s += smem[v * PERW + idx];
+    const float v = alpha * s;
+    if (p[r]) *p[r] = BETA ? fmaf(beta, cold[r], v) : v;
   }
 }
 
@@ -218,30 +430,29 @@ gemm_status launch(const GemmArgs &g, hipStream_t s) {
     set_error("small-product configuration: operands too large for 32-bit offsets");
     return GEMM_STATUS_UNSUPPORTED;
   }
-  const int ks_total = (int)((g.K + Mode<NP>::KSTEP - 1) / Mode<NP>::KSTEP);
-  const int spw = (ks_total + KW - 1) / KW;
-  const bool va = !g.ta && g.lda % 4 == 0 && g.K % 4 == 0 && ((uintptr_t)g.A & 15) == 0;
-  const bool vb = g.tb && g.ldb % 4 == 0 && g.K % 4 == 0 && ((uintptr_t)g.B & 15) == 0;
+  // Staged where a wave's range is long (direct -> staged, us): 32 x 32 tiles
+  // NN K 3761 16.1 -> 12.6, 1689 12.3 -> 10.2, 1369 8.8 -> 9.2, 349 8.1 -> 10.1;
+  // TT K 1440 11.0 -> 9.7, 571 13.7 -> 14.4; 64 x 64 tiles K 3712 84 -> 75, 2480
+  // 57 -> 55.  The rule looks at K alone: the ranges of the waves, and with
+  // them the bits of the result, are the same for every transpose flag (TN,
+  // which has nothing to turn, takes the same chunks).
+  const bool staged = g.K >= 1280;
+  const int ck = chunk_k<BM, NP>(staged);
+  const int chunks = (int)((g.K + ck - 1) / ck);
+  const int cpw = (chunks + KW - 1) / KW;
   const bool beta = g.beta != 0.0f;
   const dim3 grid((unsigned)(tiles_m * tiles_n)), block(64 * KW);
-#define MM_SMALL(TA, TB, VA, VB, BT)                                                           \
-  hipLaunchKernelGGL((gemm_small_kernel<BM, BN, NP, TA, TB, VA, VB, BT>), grid, block, 0, s,   \
-                     (int)g.M, (int)g.N, (int)g.K, g.alpha, g.A, g.lda, (int)ea, g.B, g.ldb,    \
-                     (int)eb, g.beta, g.C, g.ldc, (int)tiles_n, spw)
-#define MM_SMALL_BETA(TA, TB, VA, VB) \
-  do { if (beta) MM_SMALL(TA, TB, VA, VB, true); else MM_SMALL(TA, TB, VA, VB, false); } while (0)
-  if (!g.ta && !g.tb) {
-    if (va) MM_SMALL_BETA(false, false, true, false);
-    else MM_SMALL_BETA(false, false, false, false);
-  } else if (!g.ta && g.tb) {
-    if (va && vb) MM_SMALL_BETA(false, true, true, true);
-    else MM_SMALL_BETA(false, true, false, false);
-  } else if (g.ta && !g.tb) {
-    MM_SMALL_BETA(true, false, false, false);
-  } else {
-    if (vb) MM_SMALL_BETA(true, true, false, true);
-    else MM_SMALL_BETA(true, true, false, false);
-  }
+#define MM_SMALL(ST, TA, TB, BT)                                                                   \
+  hipLaunchKernelGGL((gemm_small_kernel<BM, BN, NP, ST, TA, TB, BT>), grid, block, 0, s, (int)g.M, \
+                     (int)g.N, (int)g.K, g.alpha, g.A, (int)g.lda, (int)ea, g.B, (int)g.ldb,       \
+                     (int)eb, g.beta, g.C, g.ldc, (int)tiles_n, cpw)
+#define MM_SMALL_BETA(ST, TA, TB) \
+  do { if (beta) MM_SMALL(ST, TA, TB, true); else MM_SMALL(ST, TA, TB, false); } while (0)
+#define MM_SMALL_ST(TA, TB) \
+  do { if (staged) MM_SMALL_BETA(true, TA, TB); else MM_SMALL_BETA(false, TA, TB); } while (0)
+  if (g.ta) { if (g.tb) MM_SMALL_ST(true, true); else MM_SMALL_ST(true, false); }
+  else      { if (g.tb) MM_SMALL_ST(false, true); else MM_SMALL_ST(false, false); }
+#undef MM_SMALL_ST
 #undef MM_SMALL_BETA
 #undef MM_SMALL
   return check_launch("gemm_small_kernel");

@@ -146,3 +146,27 @@ def test_transposed_operands_on_small_shapes(ta, tb):
             _check_f32(A, B, C0, C, 1.5, 0.5)
         else:
             check_split_result(oracle, A, B, C0, C, 1.5, 0.5, 3)
+
+
+@pytest.mark.parametrize("M,N,K", [(70, 45, 1279), (70, 45, 1283), (33, 100, 4099)])
+@pytest.mark.parametrize("path,n", [("f32", 3), ("3xbf16", 3), ("3xbf16", 6)])
+def test_transpose_flags_return_the_same_bits(M, N, K, path, n):
+    """Every transpose flag combination of one product sums the same k ranges
+    in the same order, below and above the length from which operands are
+    turned through LDS."""
+    import torch
+    import paper_1902_10345_amd as mm
+    code = mm.PATH_F32 if path == "f32" else mm.PATH_3XBF16
+    A, B = si.uniform((M, K), K), si.uniform((K, N), K + 1)
+    dA, dB = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+    dAt, dBt = dA.t().contiguous(), dB.t().contiguous()
+    outs = []
+    for ta in (False, True):
+        for tb in (False, True):
+            C = torch.empty((M, N), device="cuda")
+            mm.gemm_ex(mm.ROW_MAJOR, mm.TRANS if ta else mm.NO_TRANS,
+                       mm.TRANS if tb else mm.NO_TRANS, M, N, K, 1.5, dAt if ta else dA,
+                       M if ta else K, dBt if tb else dB, K if tb else N, 0.0, C, N, code, n)
+            outs.append(C)
+    for C in outs[1:]:
+        assert torch.equal(C, outs[0])
