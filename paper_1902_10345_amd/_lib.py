@@ -13,6 +13,8 @@ from __future__ import annotations
 import ctypes
 import os
 
+import torch
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libgemm_mi355x.so")
 
@@ -39,9 +41,8 @@ def _load():
         raise ImportError(
             "HIP library %s is not built; run `python -c 'import __graft_entry__ as g; g.build()'`"
             % LIB_PATH)
-    # torch must own the HIP runtime: load it first so that the library's
-    # libamdhip64 dependency resolves to the runtime torch already mapped.
-    import torch  # noqa: F401
+    # torch owns the HIP runtime: it is imported first (above), so that the
+    # library's libamdhip64 dependency resolves to the runtime it mapped.
     return ctypes.CDLL(LIB_PATH)
 
 
@@ -131,20 +132,26 @@ _sig("err_norm_f64", _int, _i64, _i64, _vp, _i64, _vp, _vp, _vp, _vp, _sz, _vp)
 
 def ptr(x) -> int | None:
     """Device (or host) address of a tensor / int / None."""
-    if x is None:
-        return None
-    if isinstance(x, int):
+    if x is None or isinstance(x, int):
         return x
-    if hasattr(x, "data_ptr"):
+    try:
         return x.data_ptr()
+    except AttributeError:
+        pass
     if hasattr(x, "ctypes"):
         return x.ctypes.data
     raise TypeError("cannot take the address of %r" % type(x))
 
 
+# The current stream's handle without building a Stream object around it (0.3
+# against 2.8 us, of the 7.2 us that a small product's call took on the host).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def stream_handle(stream=None) -> int:
-    import torch
     if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream

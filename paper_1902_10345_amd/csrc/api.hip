@@ -5,9 +5,8 @@
 // has been checked.  Argument rules follow the BLAS-style call of the paper's
 // external-code example (Sec. 2.1), read as row-major with no transposes.
 #include <algorithm>
-#include <mutex>
+#include <atomic>
 #include <string>
-#include <vector>
 
 #include "common.hpp"
 #include "kernels.hpp"
@@ -35,20 +34,21 @@ gemm_status bad_arg(int index, const char *fn, const char *why) {
   return -index;
 }
 
+// Asked on every call: the count of each of the first devices is cached in an
+// atomic (0: not asked yet; a race stores the same value twice).
 int num_cus() {
-  static std::mutex mu;
-  static std::vector<int> cache;
+  static std::atomic<int> cache[64];
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 256;
-  std::lock_guard<std::mutex> lock(mu);
-  if ((int)cache.size() <= dev) cache.resize(dev + 1, 0);
-  if (cache[dev] == 0) {
-    int n = 0;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
-      n = 256;
-    cache[dev] = n;
+  if (dev >= 0 && dev < 64) {
+    const int c = cache[dev].load(std::memory_order_relaxed);
+    if (c > 0) return c;
   }
-  return cache[dev];
+  int n = 0;
+  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
+    n = 256;
+  if (dev >= 0 && dev < 64) cache[dev].store(n, std::memory_order_relaxed);
+  return n;
 }
 
 // Shared checks of the (M,N,K,alpha,A,lda,B,ldb,beta,C,ldc) prefix.

@@ -7,6 +7,7 @@
 // every configuration of a path on real operands and records the fastest per
 // power-of-two size bucket; grouped_autotune picks the per-problem tile
 // shapes of a grouped batch.  The table persists as a small JSON file.
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -26,6 +27,9 @@ namespace {
 using Key = std::tuple<int, int, int, int, int>;  // path, n_products, log2 buckets of M, N, K
 std::mutex g_mu;
 std::map<Key, int> g_table;
+// Entries of g_table, readable without the lock: every call asks the table, and
+// most programs tune nothing.
+std::atomic<size_t> g_entries{0};
 double g_small_cost = kDefaultSmallCost;
 
 int bucket(int64_t x) {
@@ -54,6 +58,7 @@ int cfg_count(int path) {
 }  // namespace
 
 int tuned_config(int path, int n_products, int64_t M, int64_t N, int64_t K) {
+  if (g_entries.load(std::memory_order_acquire) == 0) return -1;
   std::lock_guard<std::mutex> lk(g_mu);
   auto it = g_table.find(key(path, n_products, M, N, K));
   return it == g_table.end() ? -1 : it->second;
@@ -124,6 +129,7 @@ gemm_status gemm_autotune(int path, int64_t M, int64_t N, int64_t K, float alpha
   {
     std::lock_guard<std::mutex> lk(g_mu);
     g_table[key(path, n_products, M, N, K)] = best;
+    g_entries.store(g_table.size(), std::memory_order_release);
   }
   *best_cfg = best;
   return GEMM_STATUS_OK;
@@ -248,6 +254,7 @@ gemm_status gemm_tuner_load(const char *json_path) {
   std::fclose(f);
   std::lock_guard<std::mutex> lk(g_mu);
   g_table = table;
+  g_entries.store(g_table.size(), std::memory_order_release);
   g_small_cost = small;
   return GEMM_STATUS_OK;
 }
@@ -255,6 +262,7 @@ gemm_status gemm_tuner_load(const char *json_path) {
 void gemm_tuner_clear(void) {
   std::lock_guard<std::mutex> lk(g_mu);
   g_table.clear();
+  g_entries.store(0, std::memory_order_release);
   g_small_cost = kDefaultSmallCost;
 }
 
