@@ -339,7 +339,7 @@ gemm_status launch_small_batched(const GemmArgs &g, int64_t sa, int64_t sb, int6
   hipLaunchKernelGGL((small_batched_bx3_kernel<NP, BT, SETS>), grid, block, 0, s, (int)g.M,       \
                      (int)g.N, (int)g.K, g.alpha, g.A, g.lda, sa, g.B, g.ldb, sb, g.beta, g.C,     \
                      g.ldc, sc, batch, (int)tiles_m, (int)tiles_n)
-  if (g.K <= 16 || units >= 32 * (int64_t)num_cus()) {
+  if (g.K <= 16 || units > 16 * (int64_t)num_cus()) {
     if (beta) MM_LAUNCH(true, 1); else MM_LAUNCH(false, 1);
   } else {
     if (beta) MM_LAUNCH(true, 2); else MM_LAUNCH(false, 2);

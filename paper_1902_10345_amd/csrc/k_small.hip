@@ -244,7 +244,7 @@ template <int BM, int BN, int NP, bool STAGED, bool TA, bool TB, bool BETA>
 __global__ __launch_bounds__(64 * KW) void gemm_small_kernel(
     int M, int N, int K, float alpha, const float *__restrict__ A, int lda, int bytes_a,
     const float *__restrict__ B, int ldb, int bytes_b, float beta, float *__restrict__ C,
-    int64_t ldc, int tiles_n, int chunks_per_wave) {
+    int64_t ldc, int tiles_m, int tiles_n, int chunks_per_wave, bool deal) {
   constexpr int FM = BM / 32, FN = BN / 32;
   constexpr int E = kE<NP>;
   constexpr int CK = chunk_k<BM, NP>(STAGED);
@@ -261,7 +261,27 @@ __global__ __launch_bounds__(64 * KW) void gemm_small_kernel(
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int m0 = (blockIdx.x / tiles_n) * BM, n0 = (blockIdx.x % tiles_n) * BN;
+  // XCD-aware order, groups of 8 tile rows walked down a column of tiles: the
+  // tiles that share an operand panel, and the cache lines that unaligned
+  // neighbours have in common, meet in one L2 (900^2 x 3000 73 -> 58 us in
+  // binary32, 48 x 2993 x 5248 38 -> 25).  `deal`: the columns of tiles go to
+  // the XCDs one by one instead -- rows of B that lie a multiple of 4 KB apart
+  // put the 8-column run of one XCD on few of its L2 channels (64 x 4096 x
+  // 4096 19.4 us in runs, 17.2 dealt).
+  int tm, tn;
+  const int w0 = blockIdx.x, dealt = tiles_n / 8 * 8;
+  if (deal && w0 < dealt * tiles_m) {
+    const int c = (w0 >> 3) / tiles_m;
+    tm = (w0 >> 3) - c * tiles_m;
+    tn = c * 8 + (w0 & 7);
+  } else if (deal) {
+    const int r = w0 - dealt * tiles_m;
+    tm = r % tiles_m;
+    tn = dealt + r / tiles_m;
+  } else {
+    tile_coords(xcd_remap(w0, gridDim.x), tiles_m, tiles_n, 8, tm, tn);
+  }
+  const int m0 = tm * BM, n0 = tn * BN;
   OpA opa;
   OpB opb;
   opa.init(A, bytes_a, lda, m0, M, lane, smem + w * PERW);
@@ -431,12 +451,13 @@ gemm_status launch(const GemmArgs &g, hipStream_t s) {
     return GEMM_STATUS_UNSUPPORTED;
   }
   // Staged where a wave's range is long (direct -> staged, us): 32 x 32 tiles
-  // NN K 3761 16.1 -> 12.6, 1689 12.3 -> 10.2, 1369 8.8 -> 9.2, 349 8.1 -> 10.1;
-  // TT K 1440 11.0 -> 9.7, 571 13.7 -> 14.4; 64 x 64 tiles K 3712 84 -> 75, 2480
-  // 57 -> 55.  The rule looks at K alone: the ranges of the waves, and with
+  // NN K 3761 16.1 -> 12.6, 1500 12.2 -> 11.1, 1100 8.8 -> 8.2, 349 8.1 -> 10.1;
+  // TT K 1440 11.0 -> 9.7, 571 13.7 -> 14.4; 64 x 64 tiles K 3712 84 -> 75, 1500
+  // 24.4 -> 23.6.  The rule looks at K alone: the ranges of the waves, and with
   // them the bits of the result, are the same for every transpose flag (TN,
   // which has nothing to turn, takes the same chunks).
-  const bool staged = g.K >= 1280;
+  const bool staged = g.K >= 1024;
+  const bool deal = tiles_m <= 8 && !g.tb && g.ldb % 1024 == 0;
   const int ck = chunk_k<BM, NP>(staged);
   const int chunks = (int)((g.K + ck - 1) / ck);
   const int cpw = (chunks + KW - 1) / KW;
@@ -445,7 +466,7 @@ gemm_status launch(const GemmArgs &g, hipStream_t s) {
 #define MM_SMALL(ST, TA, TB, BT)                                                                   \
   hipLaunchKernelGGL((gemm_small_kernel<BM, BN, NP, ST, TA, TB, BT>), grid, block, 0, s, (int)g.M, \
                      (int)g.N, (int)g.K, g.alpha, g.A, (int)g.lda, (int)ea, g.B, (int)g.ldb,       \
-                     (int)eb, g.beta, g.C, g.ldc, (int)tiles_n, cpw)
+                     (int)eb, g.beta, g.C, g.ldc, (int)tiles_m, (int)tiles_n, cpw, deal)
 #define MM_SMALL_BETA(ST, TA, TB) \
   do { if (beta) MM_SMALL(ST, TA, TB, true); else MM_SMALL(ST, TA, TB, false); } while (0)
 #define MM_SMALL_ST(TA, TB) \

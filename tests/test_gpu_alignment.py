@@ -10,10 +10,10 @@ import seeded_inputs as si
 
 pytestmark = pytest.mark.gpu
 
-# K 1279 and 1283: around the length from which the small-product tiles turn
+# K 1023 and 1027: around the length from which the small-product tiles turn
 # their operands through LDS
-SHAPES = [(65, 33, 17), (257, 130, 97), (300, 70, 255), (40, 300, 1001), (33, 65, 1279),
-          (45, 70, 1283)]
+SHAPES = [(65, 33, 17), (257, 130, 97), (300, 70, 255), (40, 300, 1001), (33, 65, 1023),
+          (45, 70, 1027), (70, 45, 1283)]
 
 
 def _placed(x, off, ld, dtype="float32"):
