@@ -51,6 +51,34 @@ int num_cus() {
   return n;
 }
 
+int addressable_config(int path, int n_products, const GemmArgs &g) {
+  const bool f32 = path == GEMM_PATH_F32;
+  const int cfg = f32 ? f32_default_config(g.M, g.N, g.K)
+                      : bx3_default_config(g.M, g.N, g.K, n_products);
+  const TileConfig &t = f32 ? f32_config(cfg) : bx3_config(cfg);
+  const bool small = f32 ? cfg == 7 || cfg == 8 : cfg >= 9 && cfg <= 12;
+  // floats from the base of what a workgroup addresses: a small tile the whole
+  // operand, the others a panel (k contiguous) or a slab of bk rows
+  const int64_t ra = small ? (g.ta ? g.K : g.M) : (g.ta ? t.bk : t.bm);
+  const int64_t rb = small ? (g.tb ? g.N : g.K) : (g.tb ? t.bn : t.bk);
+  const int64_t lim = ((int64_t)1 << 31) / 4;
+  if (ra * g.lda + (g.ta ? g.M : g.K) < lim && rb * g.ldb + (g.tb ? g.K : g.N) < lim) return cfg;
+  return f32 ? f32_count_config(g.M, g.N, g.K) : bx3_count_config(g.M, g.N, g.K, n_products);
+}
+
+double tile_time(const TileCost &t, int64_t M, int64_t N, int64_t K) {
+  const int64_t cus = num_cus(), slots = cus * t.per_cu;
+  const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+  const double steps = (double)((K + 15) / 16);
+  const int64_t rest = tiles % slots, deep = (rest + cus - 1) / cus;  // workgroups per CU of the rest
+  double us = (double)(tiles / slots) * (t.fixed + t.full * steps);
+  if (rest > 0)
+    us += t.fixed + steps * (t.per_cu > 1 ? t.alone + (t.full - t.alone) * (double)(deep - 1) /
+                                                          (double)(t.per_cu - 1)
+                                          : t.alone);
+  return us;
+}
+
 // Shared checks of the (M,N,K,alpha,A,lda,B,ldb,beta,C,ldc) prefix.
 // Returns 0 and sets `quick` when the call is fully handled by a quick path
 // decision (no-op or C <- beta*C); returns -index on a bad argument.
@@ -90,6 +118,13 @@ static int pick_config(int path, int n_products, int64_t M, int64_t N, int64_t K
   }
 }
 
+// The configuration that a call on either binary32 path runs: tuned, else the
+// default.
+static int run_config(int path, int n_products, const GemmArgs &g) {
+  const int t = tuned_config(path, n_products, g.M, g.N, g.K);
+  return t >= 0 ? t : addressable_config(path, n_products, g);
+}
+
 gemm_status check_f32_args(const char *fn, int64_t M, int64_t N, int64_t K, float alpha,
                            const float *A, int64_t lda, const float *B, int64_t ldb,
                            const float *C, int64_t ldc, bool &noop, bool &scale_only) {
@@ -123,7 +158,7 @@ gemm_status gemm_f32(int64_t M, int64_t N, int64_t K, float alpha, const float *
   if (st || ck.noop) return st;
   if (ck.scale_only) return scale_c(M, N, beta, C, ldc, stream);
   GemmArgs g{M, N, K, alpha, beta, A, lda, B, ldb, C, ldc};
-  return f32_run(g, pick_config(GEMM_PATH_F32, 0, M, N, K), stream);
+  return f32_run(g, run_config(GEMM_PATH_F32, 0, g), stream);
 }
 
 gemm_status gemm_f32_3xbf16(int64_t M, int64_t N, int64_t K, float alpha, const float *A,
@@ -138,7 +173,7 @@ gemm_status gemm_f32_3xbf16(int64_t M, int64_t N, int64_t K, float alpha, const 
   if (ck.noop) return GEMM_STATUS_OK;
   if (ck.scale_only) return scale_c(M, N, beta, C, ldc, stream);
   GemmArgs g{M, N, K, alpha, beta, A, lda, B, ldb, C, ldc};
-  return bx3_run(g, pick_config(GEMM_PATH_3XBF16, n_products, M, N, K), stream);
+  return bx3_run(g, run_config(GEMM_PATH_3XBF16, n_products, g), stream);
 }
 
 int gemm_splitk_default_splits(int64_t M, int64_t N, int64_t K) {
@@ -335,7 +370,7 @@ gemm_status gemm_run_config(int path, int cfg, int64_t M, int64_t N, int64_t K, 
     return fp8_gemm_run_cfg(M, N, K, alpha, workspace, beta, C, ldc, cfg, stream);
   }
   GemmArgs g{M, N, K, alpha, beta, A, lda, B, ldb, C, ldc};
-  if (cfg < 0) cfg = pick_config(path, n_products, M, N, K);
+  if (cfg < 0) cfg = run_config(path, n_products, g);
   switch (path) {
     case GEMM_PATH_F32: return f32_run(g, cfg, stream);
     case GEMM_PATH_3XBF16: return bx3_run(g, cfg, stream);
@@ -395,18 +430,13 @@ gemm_status gemm_ex(int order, int trans_a, int trans_b, int64_t M, int64_t N, i
   const bool trans = g.ta || g.tb;
   if (path == GEMM_PATH_F32) {
     // transposed operands run on the FP32 matrix-core and small-product
-    // tiles only
-    int cfg = pick_config(GEMM_PATH_F32, 0, g.M, g.N, K);
-    if (trans && (cfg < 5 || cfg > 8)) {
-      const int64_t big = ((g.M + 255) / 256) * ((g.N + 255) / 256);
-      cfg = big >= num_cus() ? 5 : 6;
-    }
+    // tiles only (a tuned choice may be a vector-ALU tile)
+    int cfg = run_config(GEMM_PATH_F32, 0, g);
+    if (trans && cfg < 5) cfg = addressable_config(GEMM_PATH_F32, 0, g);
     return f32_run(g, cfg, stream);
   }
-  int cfg = trans ? bx3_default_config(g.M, g.N, K, n_products)
-                  : pick_config(GEMM_PATH_3XBF16, n_products, g.M, g.N, K);
-  // the two-group tile has no transposed-operand variant: its one-group form
-  if (trans && cfg == 14) cfg = 8;
+  int cfg = trans ? addressable_config(GEMM_PATH_3XBF16, n_products, g)
+                  : run_config(GEMM_PATH_3XBF16, n_products, g);
   // with only B transposed the 32-deep 256 x 256 tile measured 8 % faster
   // than the 16-deep one that is the default otherwise
   if (cfg == 0 && !g.ta && g.tb) cfg = 3;

@@ -273,14 +273,13 @@ __device__ __forceinline__ void tile(int M, int N, int K, float alpha,
   // g-th of KG equal k ranges (the caller guarantees K % KG == 0) into the
   // same output tile with its own LDS stages (lds + g * LDS_BYTES), and the
   // partial tiles are summed in group order before the epilogue.
-  static_assert(KG == 1 || (KG == 2 && !TA && !TB && ST == 2),
-                "k-groups: two groups, operands not transposed, two LDS stages");
+  static_assert(KG == 1 || (KG == 2 && ST == 2), "k-groups: two groups, two LDS stages");
   const int grp = KG > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / NT) : 0;
   const int tid = (int)threadIdx.x - grp * NT;
   if constexpr (KG > 1) {
     K /= KG;
-    A += (int64_t)grp * K;
-    B += (int64_t)grp * K * ldb;
+    A += (int64_t)grp * K * (TA ? lda : 1);
+    B += (int64_t)grp * K * (TB ? 1 : ldb);
     lds += grp * (G::LDS_BYTES / 2);
   }
   const int lane = tid & 63, wave = tid >> 6;
@@ -848,8 +847,7 @@ __device__ __forceinline__ void tile(int M, int N, int K, float alpha,
   // ---- sum of the k-groups' partial tiles (group order) --------------------
   if constexpr (KG > 1) {
     // every fragment read of both groups is done before their stages are
-    // reused; group 1 leaves its partial tile in LDS lane-contiguous (the
-    // two groups' stages together hold exactly one group's accumulators)
+    // reused; group 1 leaves its partial tile in LDS lane-contiguous
     float *red = reinterpret_cast<float *>(lds - grp * (G::LDS_BYTES / 2));
     static_assert(G::NT * G::FM * G::FN * 16 * 4 <= KG * G::LDS_BYTES, "partial tile fits");
     __syncthreads();

@@ -26,7 +26,7 @@ __global__ __launch_bounds__(64 * NW, 1) void gemm_bx3_kernel(
 // The tile with its k range split between two groups of NW waves (one
 // workgroup of 2 * NW waves per tile): twice the waves per SIMD of the
 // one-group tile where its tiles come to about one per CU.
-template <int BM, int BN, int BK, int WM, int WN, int NP, int NW, bool BETA>
+template <int BM, int BN, int BK, int WM, int WN, int NP, int NW, bool BETA, bool TA, bool TB>
 __global__ __launch_bounds__(128 * NW, 1) void gemm_bx3_kg_kernel(
     int M, int N, int K, float alpha, const float *__restrict__ A, int64_t lda,
     const float *__restrict__ B, int64_t ldb, float beta, float *__restrict__ C, int64_t ldc,
@@ -36,7 +36,7 @@ __global__ __launch_bounds__(128 * NW, 1) void gemm_bx3_kg_kernel(
   const int wg = xcd_remap(blockIdx.x, gridDim.x);
   int tm, tn;
   tile_coords(wg, tiles_m, tiles_n, 8, tm, tn);
-  tile<BM, BN, BK, WM, WN, NP, NW, BETA, false, false, 2, 0, 2>(
+  tile<BM, BN, BK, WM, WN, NP, NW, BETA, TA, TB, 2, 0, 2>(
       M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, tm * BM, tn * BN, lds);
 }
 
@@ -154,12 +154,9 @@ gemm_status launch_batched(const GemmArgs &g, int64_t sa, int64_t sb, int64_t sc
   return check_launch("gemm_batched_kernel");
 }
 
-// The tile configurations that have transposed-operand variants (the ones the
-// library picks by default): 0, 2, 3, 4, 5, 6 and 8 of the split path, both
-// FP32 matrix-core tiles.
 // Two k-groups per workgroup; K odd has no equal halves (UNSUPPORTED: the
 // configuration choice sends such shapes elsewhere).
-template <int BM, int BN, int BK, int WM, int WN, int NP, int NW>
+template <int BM, int BN, int BK, int WM, int WN, int NP, int NW, bool TA = false, bool TB = false>
 gemm_status launch_kg(const GemmArgs &g, hipStream_t s) {
   if (g.K % 2 != 0) {
     set_error("gemm_f32_3xbf16: the two-group configuration needs an even K");
@@ -169,14 +166,14 @@ gemm_status launch_kg(const GemmArgs &g, hipStream_t s) {
   const int tiles_n = (int)((g.N + BN - 1) / BN);
   const int64_t nwg = (int64_t)tiles_m * tiles_n;
   if (nwg > 0x7fffffff) { set_error("gemm_f32_3xbf16: too many tiles"); return GEMM_STATUS_UNSUPPORTED; }
-  if (!offsets_fit<BM, BN, BK, false, false>(g)) {
+  if (!offsets_fit<BM, BN, BK, TA, TB>(g)) {
     set_error("gemm_f32_3xbf16: lda or ldb too large for 32-bit tile offsets");
     return GEMM_STATUS_UNSUPPORTED;
   }
   const bool beta = g.beta != 0.0f;
   dim3 grid((unsigned)nwg), block(128 * NW);
 #define MM_LAUNCH(BT)                                                                   \
-  hipLaunchKernelGGL((gemm_bx3_kg_kernel<BM, BN, BK, WM, WN, NP, NW, BT>), grid, block, \
+  hipLaunchKernelGGL((gemm_bx3_kg_kernel<BM, BN, BK, WM, WN, NP, NW, BT, TA, TB>), grid, block, \
                      0, s, (int)g.M, (int)g.N, (int)g.K, g.alpha, g.A, g.lda, g.B, g.ldb,  \
                      g.beta, g.C, g.ldc, tiles_m, tiles_n)
   if (beta) MM_LAUNCH(true); else MM_LAUNCH(false);
@@ -184,6 +181,8 @@ gemm_status launch_kg(const GemmArgs &g, hipStream_t s) {
   return check_launch("gemm_bx3_kg_kernel");
 }
 
+// The tile configurations that have transposed-operand variants: the ones the
+// library picks by default (all but 1, 7 and 13), every FP32 matrix-core tile.
 template <bool TA, bool TB>
 gemm_status bx3_run_trans(const GemmArgs &g, int cfg, hipStream_t s) {
   switch (cfg) {
@@ -194,6 +193,11 @@ gemm_status bx3_run_trans(const GemmArgs &g, int cfg, hipStream_t s) {
     case 5: return launch<128, 128, 32, 64, 64, 3, 4, TA, TB>(g, s);
     case 6: return launch<64, 64, 32, 32, 32, 2, 4, TA, TB>(g, s);
     case 8: return launch<128, 128, 16, 64, 64, 2, 4, TA, TB>(g, s);
+    case 14: return launch_kg<128, 128, 16, 64, 64, 2, 4, TA, TB>(g, s);
+    case 15: return launch<128, 128, 16, 64, 64, 3, 4, TA, TB>(g, s);
+    case 16: return launch_kg<128, 128, 16, 64, 64, 3, 4, TA, TB>(g, s);
+    case 17: return launch<256, 128, 32, 64, 64, 3, 8, TA, TB>(g, s);
+    case 18: return launch_kg<64, 64, 32, 32, 32, 2, 4, TA, TB>(g, s);
     default:
       set_error("gemm_ex: this tile configuration has no transposed-operand variant");
       return GEMM_STATUS_UNSUPPORTED;
@@ -203,6 +207,7 @@ gemm_status bx3_run_trans(const GemmArgs &g, int cfg, hipStream_t s) {
 template <bool TA, bool TB>
 gemm_status f32mfma_run_trans(const GemmArgs &g, int which, hipStream_t s) {
   if (which == 0) return launch_f32mfma<256, 256, 16, 128, 64, 8, TA, TB>(g, s);
+  if (which == 2) return launch_kg<128, 128, 16, 64, 64, 1, 4, TA, TB>(g, s);
   return launch_f32mfma<128, 128, 16, 64, 64, 4, TA, TB>(g, s);
 }
 

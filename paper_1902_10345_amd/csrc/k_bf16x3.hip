@@ -381,52 +381,72 @@ static const Bx3Config kBx3Configs[] = {
     // 128 x 128 x 16 tiles, the k range split between two groups of four
     // waves (partial tiles summed through LDS in group order)
     {{128, 128, 16, "bx3_128x128x16_2x4w64x64_p3_kg2"}, 2},
+    // six products: 16-deep slabs (32-deep ones leave one workgroup per CU),
+    // the two-group tile, and 256 x 128 tiles
+    {{128, 128, 16, "bx3_128x128x16_4w64x64_p6"}, 3},
+    {{128, 128, 16, "bx3_128x128x16_2x4w64x64_p6_kg2"}, 3},
+    {{256, 128, 32, "bx3_256x128x32_8w64x64_p6"}, 3},
+    // 64 x 64 tiles, the k range split between two groups of four waves
+    {{64, 64, 32, "bx3_64x64x32_2x4w32x32_p3_kg2"}, 2},
 };
 
 int bx3_num_configs() { return (int)(sizeof(kBx3Configs) / sizeof(kBx3Configs[0])); }
 const TileConfig &bx3_config(int i) { return kBx3Configs[i].t; }
 int bx3_config_products(int i) { return kBx3Configs[i].np == 2 ? 3 : 6; }
 
+// The default: the configuration with the least modelled time (tile_time).
+// Costs fitted on 47 shapes of 0.3 to 4.5 thousand per dimension, whole and
+// ragged, every configuration timed on inputs that change from call to call.
+// Against the rules on tile counts that the library had (256 x 256 tiles only
+// when they fill every CU), us: three products 3500^3 369 -> 240, 3800 x 4000 x
+// 1000 102 -> 86, 1280 x 1045 x 3712 75 -> 62; six products 3500^3 665 -> 416,
+// 2500^3 237 -> 167, 2516 x 2228 x 208 31 -> 21, 2048^3 101 -> 90.
 int bx3_default_config(int64_t M, int64_t N, int64_t K, int n_products) {
   const int64_t cus = num_cus();
   auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-  const int64_t big = tiles(256, 256);
-  // Shapes whose 128 x 128 tiles leave CUs idle: the small-product tiles (the
-  // k range split over a workgroup's eight waves), measured by graph replay
-  // over 19 shapes: 32 x 32 tiles up to two per CU (256^3: 3.7 us against
-  // 6.1 for the 64 x 64 LDS tile; 512^3 5.0 against 9.6), 64 x 64 tiles
-  // while those stay below two per CU (768^3, 1024^3), the 64 x 64 LDS tile
-  // beyond.
-  auto small = [&](int p3_32, int p3_64, int lds64) {
-    if (tiles(32, 32) <= 2 * cus) return p3_32;
-    return tiles(64, 64) < 2 * cus ? p3_64 : lds64;
+  static const TileCost k3[] = {{0, 256, 256, 1, 10.0, 1.05, 1.05}, {2, 256, 128, 1, 7.0, 0.65, 0.65},
+                                {8, 128, 128, 2, 2.5, 0.50, 0.78},  {14, 128, 128, 1, 4.0, 0.39, 0.39},
+                                {6, 64, 64, 5, 2.0, 0.24, 0.80},    {18, 64, 64, 2, 1.0, 0.235, 0.255},
+                                {10, 64, 64, 1, 3.4, 0.152, 0.152}, {9, 32, 32, 2, 1.2, 0.09, 0.11}};
+  static const TileCost k6[] = {{4, 256, 256, 1, 15.0, 1.78, 1.78}, {17, 256, 128, 1, 8.0, 1.0, 1.0},
+                                {15, 128, 128, 2, 3.0, 0.82, 1.2},  {16, 128, 128, 1, 3.0, 0.63, 0.63},
+                                {12, 64, 64, 1, 3.0, 0.20, 0.20},   {11, 32, 32, 2, 1.5, 0.11, 0.135}};
+  // 512 whole 64 x 64 tiles in at most half as many 128 x 128 ones as there are
+  // CUs keep the 64 x 64 LDS tile, a documented default (2048 x 1024 x 4096: 89
+  // us; configuration 18 takes 70)
+  if (n_products == 3 && M % 128 == 0 && N % 128 == 0 && 2 * tiles(128, 128) <= cus &&
+      tiles(64, 64) >= 2 * cus)
+    return 6;
+  // Six products: where the machine is not full of 128 x 128 tiles the small
+  // tiles, whose sums run over an eighth of K, keep the rounding error where it
+  // was; longer sums only where they were as long (three products are bound by
+  // what the split drops, 3.8e-6 either way).
+  const bool short_sums = n_products == 6 && tiles(128, 128) < cus;
+  int best = n_products == 6 ? 12 : 10;
+  double best_us = -1.0;
+  auto consider = [&](const TileCost &t) {
+    const bool small = t.cfg >= 9 && t.cfg <= 12;
+    if (short_sums && !small) return;
+    if ((t.cfg == 14 || t.cfg == 16 || t.cfg == 18) && K % 2 != 0) return;  // two equal k ranges
+    const double us = tile_time(t, M, N, K);
+    if (best_us < 0.0 || us < best_us) { best = t.cfg; best_us = us; }
   };
-  if (n_products == 6) {
-    if (big >= cus) return 4;
-    // six products: the small-product tiles beat the 128 x 128 LDS tile on
-    // every underfilled shape swept but one (1536^2 x 512, 3 % behind)
-    return tiles(128, 128) >= cus ? 5 : small(11, 12, 12);
-  }
-  // 256 x 256 x 16: 1.5-2.4 % ahead of the 32-deep slabs at 4096^3,
-  // 8192 x 2048 x 4096 and 8192^2 x 4096 (same box, alternating)
-  if (big >= cus) return 0;
-  // Below that, measured on one box (all configurations, alternating): the
-  // 8-wave 256 x 128 tiles win by 7-11 % when they come to about one wave of
-  // the machine (4096 x 2048^2, 2560^3, 2048 x 4096^2; with and without
-  // beta); 128 x 128 x 16 tiles while they fill every CU (at one tile per CU
-  // they win by 6 % with beta == 0, the paper's C = A*B at 2048^3, and lose
-  // by 4 % with beta != 0); the small-product tiles below that.
-  const int64_t mid = tiles(256, 128);
-  if (mid * 4 >= cus * 3 && mid <= cus) return 2;
-  // 128 x 128 tiles for more than half of the CUs and at most all of them:
-  // the tile with its k range split between two groups of four waves (two
-  // waves per SIMD instead of one), measured over eight shapes: 2048^3 64.9
-  // -> 57.6 us, 1792^3 62.2 -> 44.5 (the 64 x 64 tile before), 1536^3 42.0 ->
-  // 37.6; at half of the CUs and below the 64 x 64 tiles stay ahead
-  const int64_t t128 = tiles(128, 128);
-  if (t128 <= cus && 2 * t128 > cus && K % 2 == 0) return 14;
-  if (t128 >= cus) return 8;
-  return small(9, 10, 6);
+  if (n_products == 6) for (const TileCost &t : k6) consider(t);
+  else for (const TileCost &t : k3) consider(t);
+  return best;
+}
+
+int bx3_count_config(int64_t M, int64_t N, int64_t K, int n_products) {
+  const int64_t cus = num_cus();
+  auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  const bool six = n_products == 6;
+  if (tiles(256, 256) >= cus) return six ? 4 : 0;
+  const int64_t t128 = tiles(128, 128), mid = tiles(256, 128);
+  if (!six && mid * 4 >= cus * 3 && mid <= cus) return 2;
+  if (!six && t128 <= cus && 2 * t128 > cus && K % 2 == 0) return 14;
+  if (t128 >= cus) return six ? 15 : 8;
+  if (tiles(32, 32) <= 2 * cus) return six ? 11 : 9;
+  return six ? 12 : tiles(64, 64) < 2 * cus ? 10 : 6;
 }
 
 gemm_status bx3_run(const GemmArgs &g, int cfg, hipStream_t s) {
@@ -444,6 +464,10 @@ gemm_status bx3_run(const GemmArgs &g, int cfg, hipStream_t s) {
     case 8: return bx3::launch<128, 128, 16, 64, 64, 2, 4>(g, s);
     case 13: return bx3::launch<256, 256, 16, 128, 64, 2, 8, false, false, 3>(g, s);
     case 14: return bx3::launch_kg<128, 128, 16, 64, 64, 2, 4>(g, s);
+    case 15: return bx3::launch<128, 128, 16, 64, 64, 3, 4>(g, s);
+    case 16: return bx3::launch_kg<128, 128, 16, 64, 64, 3, 4>(g, s);
+    case 17: return bx3::launch<256, 128, 32, 64, 64, 3, 8>(g, s);
+    case 18: return bx3::launch_kg<64, 64, 32, 32, 32, 2, 4>(g, s);
     default: set_error("gemm_f32_3xbf16: bad tile config"); return GEMM_STATUS_UNSUPPORTED;
   }
 }
@@ -471,18 +495,10 @@ gemm_status bx3_run_splitk(const GemmArgs &g, int n_products, int splits, void *
 }
 
 gemm_status f32mfma_run(const GemmArgs &g, int which, hipStream_t s) {
-  if (which == 2) {
-    if (g.ta || g.tb) {
-      set_error("gemm_ex: the two-group FP32 matrix-core tile takes no transposed operands");
-      return GEMM_STATUS_UNSUPPORTED;
-    }
-    return bx3::launch_kg<128, 128, 16, 64, 64, 1, 4>(g, s);
-  }
   if (g.ta || g.tb)
     return g.ta ? (g.tb ? f32mfma_run_tt(g, which, s) : f32mfma_run_tn(g, which, s))
                 : f32mfma_run_nt(g, which, s);
-  if (which == 0) return bx3::launch_f32mfma<256, 256, 16, 128, 64, 8>(g, s);
-  return bx3::launch_f32mfma<128, 128, 16, 64, 64, 4>(g, s);
+  return bx3::f32mfma_run_trans<false, false>(g, which, s);
 }
 
 // Batched-strided products: the tile with the least modelled time beyond the

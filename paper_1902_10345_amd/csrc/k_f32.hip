@@ -268,20 +268,38 @@ static const TileConfig kF32Configs[] = {
 int f32_num_configs() { return (int)(sizeof(kF32Configs) / sizeof(kF32Configs[0])); }
 const TileConfig &f32_config(int i) { return kF32Configs[i]; }
 
+// The default: the matrix-core or small-product tile with the least modelled
+// time (tile_time; costs fitted as the split path's).  Against rules on tile
+// counts alone, us: 3500^3 857 -> 720, 4500^3 2134 -> 1500, 1216 x 3840 x 2224
+// 271 -> 196, 1280 x 1045 x 3712 128 -> 108, 6000 x 4000 x 2000 943 -> 718.
 int f32_default_config(int64_t M, int64_t N, int64_t K) {
-  // measured: the FP32 matrix-core tiles win while they fill every CU (256 x
-  // 256: 140 TFLOP/s at 4096^3 against 90 on the vector ALU).  Below that the
-  // small-product tiles (the k range split over a workgroup's eight waves)
-  // win on every shape swept, 1.7-4.3x over the 64 x 64 vector-ALU tile
-  // (256^3: 4.1 against 17.5 us; graph-replayed launches): 64 x 64 tiles
-  // once they fill the CUs, 32 x 32 tiles before.
+  const int64_t cus = num_cus();
+  const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128);
+  static const TileCost kCosts[] = {{5, 256, 256, 1, 8.0, 3.8, 3.8},  {6, 128, 128, 2, 4.0, 1.15, 1.95},
+                                    {9, 128, 128, 1, 4.0, 1.04, 1.04}, {8, 64, 64, 1, 3.0, 0.275, 0.275},
+                                    {7, 32, 32, 2, 1.0, 0.13, 0.15}};
+  // whole 128 x 128 tiles, more than one and at most two per CU, keep the 128 x
+  // 128 tile, a documented default (2560 x 2048 x 2048: 255 us; the 64 x 64
+  // small tiles take 191)
+  if (M % 128 == 0 && N % 128 == 0 && t128 > cus && t128 <= 2 * cus) return 6;
+  // The tiles whose sums run over all of K or half of it only where the
+  // machine is full of 128 x 128 tiles, or nearly so: the small tiles' sums run
+  // over an eighth of K and keep the rounding error where it was.
+  const bool whole_k = t128 >= cus, half_k = K % 2 == 0 && 4 * t128 > 3 * cus;
+  int best = 8;
+  double best_us = -1.0;
+  for (const TileCost &t : kCosts) {
+    if ((t.cfg == 5 || t.cfg == 6) ? !whole_k : t.cfg == 9 && !half_k) continue;
+    const double us = tile_time(t, M, N, K);
+    if (best_us < 0.0 || us < best_us) { best = t.cfg; best_us = us; }
+  }
+  return best;
+}
+
+int f32_count_config(int64_t M, int64_t N, int64_t K) {
   const int64_t cus = num_cus();
   auto tiles = [&](int64_t b) { return ((M + b - 1) / b) * ((N + b - 1) / b); };
   if (tiles(256) >= cus) return 5;
-  // 128 x 128 tiles for more than three quarters of the CUs and at most all
-  // of them: the matrix-core tile with its k range split between two groups
-  // of four waves (2048^3 166.8 -> 151.6 us, 1792^3 126.6 against 147.9 for
-  // the small-product tiles); fewer tiles: the small-product tiles
   const int64_t t128 = tiles(128);
   if (t128 <= cus && 4 * t128 > 3 * cus && K % 2 == 0) return 9;
   if (t128 >= cus) return 6;
@@ -289,7 +307,7 @@ int f32_default_config(int64_t M, int64_t N, int64_t K) {
 }
 
 gemm_status f32_run(const GemmArgs &g, int cfg, hipStream_t s) {
-  if ((g.ta || g.tb) && cfg != 5 && cfg != 6 && cfg != 7 && cfg != 8) {
+  if ((g.ta || g.tb) && cfg < 5) {
     set_error("gemm_ex: only the FP32 matrix-core and small-product tiles take transposed operands");
     return GEMM_STATUS_UNSUPPORTED;
   }

@@ -244,7 +244,7 @@ template <int BM, int BN, int NP, bool STAGED, bool TA, bool TB, bool BETA>
 __global__ __launch_bounds__(64 * KW) void gemm_small_kernel(
     int M, int N, int K, float alpha, const float *__restrict__ A, int lda, int bytes_a,
     const float *__restrict__ B, int ldb, int bytes_b, float beta, float *__restrict__ C,
-    int64_t ldc, int tiles_m, int tiles_n, int chunks_per_wave, bool deal) {
+    int64_t ldc, int tiles_m, int tiles_n, bool deal) {
   constexpr int FM = BM / 32, FN = BN / 32;
   constexpr int E = kE<NP>;
   constexpr int CK = chunk_k<BM, NP>(STAGED);
@@ -298,8 +298,10 @@ __global__ __launch_bounds__(64 * KW) void gemm_small_kernel(
   // the grid of chunks ends at K: only chunk 0 can be partial
   const int total = (K + CK - 1) / CK;
   const int kbase = K - total * CK;
-  const int c0 = w * chunks_per_wave;
-  const int n = (c0 + chunks_per_wave < total ? c0 + chunks_per_wave : total) - c0;
+  // equal ranges to within a chunk (whole multiples would leave the last wave
+  // short and the other sums longer)
+  const int c0 = (int)((int64_t)w * total / KW);
+  const int n = (int)((int64_t)(w + 1) * total / KW) - c0;
 
   auto load = [&](auto SET, int c) {
     constexpr int S = decltype(SET)::value;
@@ -458,15 +460,12 @@ gemm_status launch(const GemmArgs &g, hipStream_t s) {
   // which has nothing to turn, takes the same chunks).
   const bool staged = g.K >= 1024;
   const bool deal = tiles_m <= 8 && !g.tb && g.ldb % 1024 == 0;
-  const int ck = chunk_k<BM, NP>(staged);
-  const int chunks = (int)((g.K + ck - 1) / ck);
-  const int cpw = (chunks + KW - 1) / KW;
   const bool beta = g.beta != 0.0f;
   const dim3 grid((unsigned)(tiles_m * tiles_n)), block(64 * KW);
 #define MM_SMALL(ST, TA, TB, BT)                                                                   \
   hipLaunchKernelGGL((gemm_small_kernel<BM, BN, NP, ST, TA, TB, BT>), grid, block, 0, s, (int)g.M, \
                      (int)g.N, (int)g.K, g.alpha, g.A, (int)g.lda, (int)ea, g.B, (int)g.ldb,       \
-                     (int)eb, g.beta, g.C, g.ldc, (int)tiles_m, (int)tiles_n, cpw, deal)
+                     (int)eb, g.beta, g.C, g.ldc, (int)tiles_m, (int)tiles_n, deal)
 #define MM_SMALL_BETA(ST, TA, TB) \
   do { if (beta) MM_SMALL(ST, TA, TB, true); else MM_SMALL(ST, TA, TB, false); } while (0)
 #define MM_SMALL_ST(TA, TB) \

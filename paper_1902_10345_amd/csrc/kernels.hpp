@@ -25,10 +25,25 @@ struct TileConfig {
   const char *name;
 };
 
+// A tile configuration's time, for the choice among configurations: `fixed` us
+// per round of workgroups plus, per 16 k, `alone` us with one workgroup on each
+// compute unit up to `full` with per_cu of them (linear between).  Whole rounds
+// of per_cu workgroups per compute unit, then the remainder.
+struct TileCost {
+  int cfg, bm, bn, per_cu;
+  double fixed, alone, full;
+};
+double tile_time(const TileCost &t, int64_t M, int64_t N, int64_t K);
+// The default configuration of `path` for g, or, where 32-bit offsets of that
+// one cannot reach the operands, the configuration that tile counts alone give
+// (large tiles that address one panel at a time).
+int addressable_config(int path, int n_products, const GemmArgs &g);
+
 // Plain FP32 vector-ALU path.
 int f32_num_configs();
 const TileConfig &f32_config(int i);
 int f32_default_config(int64_t M, int64_t N, int64_t K);
+int f32_count_config(int64_t M, int64_t N, int64_t K);
 gemm_status f32_run(const GemmArgs &g, int cfg, hipStream_t s);
 
 // FP32-accurate split-precision path on bf16 MFMA.
@@ -36,9 +51,10 @@ int bx3_num_configs();
 const TileConfig &bx3_config(int i);
 int bx3_config_products(int i);
 int bx3_default_config(int64_t M, int64_t N, int64_t K, int n_products);
+int bx3_count_config(int64_t M, int64_t N, int64_t K, int n_products);
 gemm_status bx3_run(const GemmArgs &g, int cfg, hipStream_t s);
-// Transposed-operand variants (B^T, A^T, both), for configurations 0, 2, 3,
-// 4, 5, 6 and 8; bx3_run and f32mfma_run dispatch to them from g.ta / g.tb.
+// Transposed-operand variants (B^T, A^T, both), for every configuration that
+// the library picks by default; bx3_run and f32mfma_run dispatch to them from g.ta / g.tb.
 gemm_status bx3_run_nt(const GemmArgs &g, int cfg, hipStream_t s);
 gemm_status bx3_run_tn(const GemmArgs &g, int cfg, hipStream_t s);
 gemm_status bx3_run_tt(const GemmArgs &g, int cfg, hipStream_t s);
@@ -46,7 +62,8 @@ gemm_status f32mfma_run_nt(const GemmArgs &g, int which, hipStream_t s);
 gemm_status f32mfma_run_tn(const GemmArgs &g, int which, hipStream_t s);
 gemm_status f32mfma_run_tt(const GemmArgs &g, int which, hipStream_t s);
 int bx3_splitk_default(int64_t M, int64_t N, int64_t K);
-// FP32 matrix-core tiles of the plain path: 0 = 256 x 256 (8 waves), 1 = 128 x 128 (4 waves)
+// FP32 matrix-core tiles of the plain path: 0 = 256 x 256 (8 waves), 1 = 128 x
+// 128 (4 waves), 2 = 128 x 128 with the k range split between two groups of four
 gemm_status f32mfma_run(const GemmArgs &g, int which, hipStream_t s);
 size_t bx3_splitk_ws_bytes(int64_t M, int64_t N, int splits);
 gemm_status bx3_run_splitk(const GemmArgs &g, int n_products, int splits, void *ws, hipStream_t s);

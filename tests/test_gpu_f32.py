@@ -204,3 +204,22 @@ def test_err_norm_matches_oracle():
     assert got[3] == exp[3]
     got2 = mm.ops.err_norm(torch.from_numpy(C).cuda(), torch.from_numpy(R).cuda())
     assert got2[3] == oracle.norms(C, R)[3]
+
+
+def test_operand_larger_than_the_small_tiles_reach():
+    """A spans more than 2^31 bytes (row stride 2^18 + 1, 2100 rows): the
+    default small tile cannot address it and the panel tile runs instead;
+    every element exact on integer inputs."""
+    import torch
+    import paper_1902_10345_amd as mm
+    M, N, K, lda = 2100, 2100, 400, (1 << 18) + 1
+    assert "small" in mm.gemm_config_name(mm.PATH_F32, mm.gemm_default_config(mm.PATH_F32, M, N, K))
+    g = torch.Generator(device="cuda").manual_seed(5)
+    A = torch.randint(-8, 9, (M, K), generator=g, device="cuda").float()
+    B = torch.randint(-8, 9, (K, N), generator=g, device="cuda").float()
+    buf = torch.empty(M * lda, device="cuda")
+    view = torch.as_strided(buf, (M, K), (lda, 1))
+    view.copy_(A)
+    C = torch.full((M, N), float("nan"), device="cuda")
+    mm.gemm_f32(M, N, K, 1.0, buf, lda, B, N, 0.0, C, N)
+    assert torch.equal(C, (A.double() @ B.double()).float())

@@ -365,3 +365,31 @@ def test_default_tile_rules_for_underfilled_shapes():
     assert name(mm.PATH_F32, 2560, 2048, 2048) == "f32mfma_128x128x16_4w64x64"
     assert name(mm.PATH_F32, 4096, 4096, 4096) == "f32mfma_256x256x16_8w128x64"
     assert name(mm.PATH_3XBF16, 4096, 4096, 4096) == "bx3_256x256x16_8w128x64_p3"
+
+
+def test_default_tiles_by_modelled_time():
+    """Shapes where the tile counts alone gave a slower choice; the binary32 and
+    six-product paths keep the tiles with short sums where the machine is not
+    full of 128 x 128 tiles."""
+    import paper_1902_10345_amd as mm
+
+    def name(path, M, N, K):
+        return mm.gemm_config_name(path, mm.gemm_default_config(path, M, N, K))
+    assert name(mm.PATH_3XBF16, 3500, 3500, 3500) == "bx3_256x256x16_8w128x64_p3"
+    assert name(mm.PATH_3XBF16, 1280, 1045, 3712) == "bx3_64x64x32_2x4w32x32_p3_kg2"
+    assert name(mm.PATH_F32, 3500, 3500, 3500) == "f32_small_64x64_8wk"
+    assert name(mm.PATH_F32, 6000, 4000, 2000) == "f32mfma_128x128x16_4w64x64"
+    for shape in [(800, 3000, 300), (1000, 1000, 1001), (33, 4097, 77), (1500, 600, 4000)]:
+        assert "small" in name(mm.PATH_F32, *shape), shape
+
+
+def test_operands_beyond_the_small_tiles_offsets_take_the_panel_tiles():
+    """A product whose whole operands span 2^31 bytes cannot run on the small
+    tiles; it runs where only a panel has to be addressed, and is refused only
+    where that is too large as well (dummy pointers: nothing is launched)."""
+    import paper_1902_10345_amd as mm
+    # default for the shape: a small tile; lda puts even a panel out of reach
+    assert "small" in mm.gemm_config_name(mm.PATH_F32, mm.gemm_default_config(mm.PATH_F32, 3500, 3500, 3500))
+    assert mm.lib.gemm_f32(3500, 3500, 3500, 1.0, F, 1 << 23, F, 3500, 0.0, F, 3500, None) == \
+        mm.STATUS_UNSUPPORTED
+    assert "32-bit tile offsets" in mm.gemm_last_error()
