@@ -136,10 +136,11 @@ __global__ __launch_bounds__(256) void split_kernel(int64_t n, const float *__re
 // add barriers that nothing overlaps.  A lane holds 8 k of its A row (two
 // 128-bit loads) and of its B column (eight loads, consecutive lanes on
 // consecutive columns) per 16-deep k-step: 8 consecutive k on the split path,
-// two runs of 4 in binary32 (the FP32 tile's fragment order).  With
-// enough waves to fill the machine (SETS 1: 8 waves per SIMD) they hide each
-// other's latency; a smaller batch keeps the next k-step's loads in flight
-// while one is multiplied (SETS 2: 4-5 waves per SIMD).
+// two runs of 4 in binary32 (the FP32 tile's fragment order).  Eight
+// waves per SIMD hide each other's latency; keeping the next k-step's loads in
+// flight as well costs a third of the waves and was level or slower (20 x 20 x
+// 100 x 5000 17.7 -> 17.6 us, 40 x 20 x 33 x 700 5.6 -> 5.6, 60 x 60 x 59 x
+// 3000 45 -> 51).
 // The k-steps lie on the grid that ends at K (only the first can be partial)
 // and the products come in the tile kernels' order, so every element is the
 // same sum as in the LDS-staged tile of the same arithmetic.
@@ -151,7 +152,7 @@ __global__ __launch_bounds__(256) void split_kernel(int64_t n, const float *__re
 // -> 53.9 us.  The same hint on the operand loads was slower.
 constexpr int kStoreNT = 2;
 
-template <int NP, bool BETA, int SETS>
+template <int NP, bool BETA, bool TILED>
 __global__ __launch_bounds__(256) void small_batched_bx3_kernel(
     int M, int N, int K, float alpha, const float *__restrict__ A, int64_t lda, int64_t sa,
     const float *__restrict__ B, int64_t ldb, int64_t sb, float beta, float *__restrict__ C,
@@ -159,13 +160,13 @@ __global__ __launch_bounds__(256) void small_batched_bx3_kernel(
   const int lane = threadIdx.x & 63;
   // the wave index is uniform across the wave; saying so keeps the problem's
   // buffer resources in scalar registers
-  const int tiles = tiles_m * tiles_n;
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   int prob = (int)blockIdx.x * 4 + wv, m0 = 0, n0 = 0;
-  if (tiles > 1) {
+  if constexpr (TILED) {
     // XCD-aware order where a problem spans several waves (its panels meet in
     // one L2: 160^2 x 16 x 1500 39 -> 26 us); one wave per problem shares
     // nothing (32^3 x 29 297 is 6 % faster in plain order)
+    const int tiles = tiles_m * tiles_n;
     const int unit = xcd_remap(blockIdx.x, gridDim.x) * 4 + wv;
     prob = unit / tiles;
     const int sub = unit - prob * tiles, tm = sub / tiles_n;
@@ -186,56 +187,64 @@ __global__ __launch_bounds__(256) void small_batched_bx3_kernel(
   const __amdgpu_buffer_rsrc_t rC = __builtin_amdgcn_make_buffer_rsrc(
       C + (int64_t)prob * sc + (int64_t)m0 * ldc + n0, (short)0,
       (int)(((int64_t)(Mr - 1) * ldc + Nr) * 4), kBufferFlags);
-  const int arow = lr < Mr ? lr * (int)lda * 4 : (int)0x80000000;
-  const int bcol = lr < Nr ? lr * 4 : (int)0x80000000;
   const int ldb4 = (int)ldb * 4;
+  // k of a lane's element e in the step that starts at k = 0: lane group g
+  // holds k = 8g + e on the split path, 4g + e % 4 + 8 (e / 4) in binary32
+  // (as in the FP32 tile: MFMA e takes element e of both groups).  The group's
+  // part is in the lane's offset, the rest in the wave-uniform offset.
+  constexpr int kGroup = NP == 1 ? 4 : 8;       // first k of lane group 1
+  auto koff = [](int e) { return NP == 1 ? 8 * (e >> 2) + (e & 3) : e; };
+  const int arow = lr < Mr ? (lr * (int)lda + kGroup * lg) * 4 : (int)0x80000000;
+  const int bcol = lr < Nr ? lr * 4 + kGroup * lg * ldb4 : (int)0x80000000;
   f32x16 acc;
 #pragma unroll
   for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
-  auto ld = [](__amdgpu_buffer_rsrc_t r, int off) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+  auto ld = [](__amdgpu_buffer_rsrc_t r, int off, int soff) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, soff, 0));
   };
   const int KT = (K + 15) / 16;
   const int kbase = K - KT * 16;
-  // k of a lane's element e in the step that starts at k = 0: lane group g
-  // holds k = 8g + e on the split path, 4g + e % 4 + 8 (e / 4) in binary32
-  // (as in the FP32 tile: MFMA e takes element e of both groups)
-  constexpr int kGroup = NP == 1 ? 4 : 8;       // first k of lane group 1
-  auto koff = [](int e) { return NP == 1 ? 8 * (e >> 2) + (e & 3) : e; };
-  float a[SETS][8], b[SETS][8];
-  auto load = [&](auto SET, int s) {
-    constexpr int st = decltype(SET)::value;
-    const int k0 = kbase + 16 * s + kGroup * lg;
+  float a[8], b[8];
+  auto load = [&](int s) {
+    const int k0 = kbase + 16 * s;
     if (s > 0 || kbase == 0) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                      rA, arow + (k0 + koff(4 * h)) * 4, 0, 0));
-        a[st][4 * h] = v.x; a[st][4 * h + 1] = v.y;
-        a[st][4 * h + 2] = v.z; a[st][4 * h + 3] = v.w;
+                                                      rA, arow, (k0 + koff(4 * h)) * 4, 0));
+        a[4 * h] = v.x; a[4 * h + 1] = v.y;
+        a[4 * h + 2] = v.z; a[4 * h + 3] = v.w;
       }
 #pragma unroll
-      for (int e = 0; e < 8; ++e) b[st][e] = ld(rB, bcol + (k0 + koff(e)) * ldb4);
+      for (int e = 0; e < 8; ++e) b[e] = ld(rB, bcol, (k0 + koff(e)) * ldb4);
     } else {
       // the partial first step: k in [kbase, kbase + 16) with kbase < 0
+      auto element = [&](int e) {
+        const int kk = kbase + koff(e);  // the k of lane group 0
+        const bool in = kk + kGroup * lg >= 0;
+        a[e] = ld(rA, in && lr < Mr ? arow + kk * 4 : (int)0x80000000, 0);
+        b[e] = ld(rB, in && lr < Nr ? bcol + kk * ldb4 : (int)0x80000000, 0);
+      };
+      // branches around loads that neither lane group needs: worth their cost
+      // only where they save several of the eight (at K = 59, where they save
+      // none, 32 x 32 x 6798 with three products 43 -> 36 us without them)
+      if (K > (NP == 1 ? 10 : 6)) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int k = k0 + koff(e);
-        if (kbase + kGroup + koff(e) < 0) {  // neither lane group has a k here
-          a[st][e] = b[st][e] = 0.0f;
-        } else {
-          a[st][e] = ld(rA, k >= 0 ? arow + k * 4 : (int)0x80000000);
-          b[st][e] = ld(rB, k >= 0 ? bcol + k * ldb4 : (int)0x80000000);
+        for (int e = 0; e < 8; ++e) element(e);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          a[e] = b[e] = 0.0f;
+          if (kbase + koff(e) + kGroup >= 0) element(e);
         }
       }
     }
   };
-  auto multiply = [&](auto SET) {
-    constexpr int st = decltype(SET)::value;
+  auto multiply = [&]() {
     if constexpr (NP == 1) {
 #pragma unroll
       for (int e = 0; e < 8; ++e)
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[st][e], b[st][e], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[e], acc, 0, 0, 0);
     } else {
       // the 8 values of one block as NP bf16 planes (plane 0 the leading part)
       auto split8 = [](const float (&x)[8], bf16x8 (&pl)[NP]) {
@@ -250,8 +259,8 @@ __global__ __launch_bounds__(256) void small_batched_bx3_kernel(
         }
       };
       bf16x8 pa[NP], pb[NP];
-      split8(a[st], pa);
-      split8(b[st], pb);
+      split8(a, pa);
+      split8(b, pb);
       auto prod = [&](int qa, int qb) {
         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pa[qa], pb[qb], acc, 0, 0, 0);
       };
@@ -266,23 +275,13 @@ __global__ __launch_bounds__(256) void small_batched_bx3_kernel(
       prod(0, 0);
     }
   };
-  using S0 = std::integral_constant<int, 0>;
-  using S1 = std::integral_constant<int, 1>;
-  if constexpr (SETS == 1) {
-    for (int s = 0; s < KT; ++s) {
-      load(S0{}, s);
-      multiply(S0{});
-    }
-  } else {
-    load(S0{}, 0);
-    for (int s = 0; s < KT; s += 2) {
-      if (s + 1 < KT) load(S1{}, s + 1);
-      multiply(S0{});
-      if (s + 1 < KT) {
-        if (s + 2 < KT) load(S0{}, s + 2);
-        multiply(S1{});
-      }
-    }
+  for (int s = 0; s < KT; ++s) {
+    load(s);
+    // all loads of a step in flight before its first product: left alone, the
+    // compiler moves each load of B behind the previous binary32 product and
+    // waits for it (32^3 x 29 297 in binary32 97 -> 63 us)
+    __builtin_amdgcn_sched_barrier(0);
+    multiply();
   }
   // 32 x 32 block layout: lane l, element e -> row 8*(e/4) + 4*(l/32) + e%4,
   // column l%32.  Columns past N get an out-of-range offset; rows past M fall
@@ -335,15 +334,12 @@ gemm_status launch_small_batched(const GemmArgs &g, int64_t sa, int64_t sb, int6
   }
   const bool beta = g.beta != 0.0f;
   const dim3 grid((unsigned)((units + 3) / 4)), block(256);
-#define MM_LAUNCH(BT, SETS)                                                                      \
-  hipLaunchKernelGGL((small_batched_bx3_kernel<NP, BT, SETS>), grid, block, 0, s, (int)g.M,       \
-                     (int)g.N, (int)g.K, g.alpha, g.A, g.lda, sa, g.B, g.ldb, sb, g.beta, g.C,     \
-                     g.ldc, sc, batch, (int)tiles_m, (int)tiles_n)
-  if (g.K <= 16 || units > 16 * (int64_t)num_cus()) {
-    if (beta) MM_LAUNCH(true, 1); else MM_LAUNCH(false, 1);
-  } else {
-    if (beta) MM_LAUNCH(true, 2); else MM_LAUNCH(false, 2);
-  }
+#define MM_LAUNCH(BT, TILED)                                                                     \
+  hipLaunchKernelGGL((small_batched_bx3_kernel<NP, BT, TILED>), grid, block, 0, s,                 \
+                     (int)g.M, (int)g.N, (int)g.K, g.alpha, g.A, g.lda, sa, g.B, g.ldb, sb,        \
+                     g.beta, g.C, g.ldc, sc, batch, (int)tiles_m, (int)tiles_n)
+  if (tiles_m * tiles_n > 1) { if (beta) MM_LAUNCH(true, true); else MM_LAUNCH(false, true); }
+  else                       { if (beta) MM_LAUNCH(true, false); else MM_LAUNCH(false, false); }
 #undef MM_LAUNCH
   return check_launch("small_batched_bx3_kernel");
 }
@@ -503,31 +499,28 @@ gemm_status f32mfma_run(const GemmArgs &g, int which, hipStream_t s) {
 
 // Batched-strided products: the tile with the least modelled time beyond the
 // operands' traffic, which every tile has in common: `fixed` ns per output
-// tile and `step` ns per tile and 16-deep k-step, whole machine, fitted on 26
+// tile and `step` ns per tile and 16-deep k-step, whole machine, fitted on 46
 // batches whose inputs change from call to call (4 to 512 per dimension, 10 to
 // 190 MB).  The batch takes whole rounds of the workgroups that fit the
 // machine at once while there are few rounds; a round that is not full runs
 // somewhat faster.  Against the tile chosen by the stacked problem's size alone
 // (256 x 256 tiles for any large batch), binary32 / three / six products, us:
 // 100 x 72 x 90 x 2000 232 -> 70, 97 -> 54, 137 -> 55; 144 x 8 x 9 x 5403 217
-// -> 20, 153 -> 18, 236 -> 18; 300^3 x 100 162 -> 69, 50 -> 48, 75 -> 54.
+// -> 20, 153 -> 18, 236 -> 18; 300^3 x 100 162 -> 67, 50 -> 48, 75 -> 55, 60 x 60 x 59 x 3000 58 -> 39 at beta = 0.5.
 namespace {
 struct BatchTile {
   int bm, bn, per_cu;          // output tile, tiles per compute unit at once
   double fixed[3], step[3];    // ns: binary32, three products, six products
 };
 constexpr BatchTile kBatchTiles[kBatchedTiles] = {
-    {32, 32, 20, {0.1, 0.2, 0.2}, {0.32, 0.25, 0.26}},    // kBatchedDirect
-    {64, 64, 4, {1.5, 1.5, 2.3}, {1.1, 0.35, 0.70}},      // kBatched64
-    {128, 128, 2, {2.0, 4.4, 4.0}, {3.4, 0.95, 1.40}},    // kBatched128
+    {32, 32, 20, {0.1, 0.2, 0.1}, {0.30, 0.14, 0.21}},    // kBatchedDirect
+    {64, 64, 4, {1.5, 2.5, 5.0}, {1.25, 0.28, 0.42}},     // kBatched64
+    {128, 128, 2, {2.0, 6.0, 4.0}, {3.25, 0.55, 1.40}},   // kBatched128
     {256, 256, 1, {8.0, 8.0, 8.0}, {12.5, 2.3, 5.0}},     // kBatched256
 };
 }  // namespace
 
 int batched_config(int path, int n_products, int64_t M, int64_t N, int64_t K, int64_t batch) {
-  // M, N <= 64: the one-wave sub-tiles (64^3 x 4000 within 10 % of the 64 x 64
-  // tile on every path, and ahead of it below)
-  if (M <= 64 && N <= 64) return kBatchedDirect;
   const int mode = path == GEMM_PATH_F32 ? 0 : n_products == 6 ? 2 : 1;
   int best = kBatchedDirect;
   double best_cost = 0.0;
