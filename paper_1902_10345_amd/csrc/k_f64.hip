@@ -482,8 +482,7 @@ constexpr int kDirect16 = 100, kDirect32 = 101, kDirect64 = 102;
 
 // A batch: the tile with the least modelled time beyond the operands' traffic
 // (`fixed` ns per output tile, `step` ns per tile and 16 k, whole machine;
-// fitted on 26 batches whose inputs change from call to call).  LDS tiles only
-// when they fill the machine.  Against one wave per problem up to 64 x 64 and
+// fitted on 26 batches whose inputs change from call to call).   Against one wave per problem up to 64 x 64 and
 // 128 x 128 LDS tiles beyond, us at beta = 0: 76 x 48 x 32 x 1134 36 -> 16, 9 x
 // 112 x 48 x 770 33 -> 9, 159 x 112 x 64 x 429 52 -> 33, 96^3 x 700 58 -> 43.
 static int f64_batch_config(int64_t M, int64_t N, int64_t K, int64_t batch) {
@@ -497,7 +496,7 @@ static int f64_batch_config(int64_t M, int64_t N, int64_t K, int64_t batch) {
   };
   constexpr Tile kTiles[] = {{kDirect16, 16, 20, 0.05, 0.22},
                              {kDirect32, 32, 12, 0.10, 0.45},
-                             {2, 64, 3, 1.0, 1.55},
+                             {2, 64, 3, 2.5, 1.30},
                              {0, 128, 2, 4.0, 6.0}};
   int best = 2;
   double best_cost = -1.0;
@@ -505,9 +504,13 @@ static int f64_batch_config(int64_t M, int64_t N, int64_t K, int64_t batch) {
     const bool lds = t.cfg < kDirect16;
     const double tiles = (double)((M + t.b - 1) / t.b) * (double)((N + t.b - 1) / t.b) * (double)batch;
     const double slots = (double)num_cus() * t.per_cu, r = tiles / slots;
-    // the sub-tiles re-read their panels too often in problems beyond 256
-    if (lds ? (r < 1.0 && M <= 256 && N <= 256) : (M > 256 || N > 256)) continue;
-    const double rounds = r > 4.0 ? r : r >= 1.0 ? std::ceil(r) : 0.7 + 0.3 * r;
+    // the sub-tiles re-read their panels too often in problems beyond 256, and
+    // three waves of an LDS tile idle in problems up to 32 x 32 (32 x 32 x 512
+    // x 300 43 us, 32 with sub-tiles)
+    if (lds ? M <= 32 && N <= 32 : M > 256 || N > 256) continue;
+    // LDS tiles that do not fill the machine come one or two to a CU
+    const double part = lds ? 0.58 + 0.42 * std::ceil(r * t.per_cu) / t.per_cu : 0.7 + 0.3 * r;
+    const double rounds = r > 4.0 ? r : r >= 1.0 ? std::ceil(r) : part;
     const double cost = rounds * slots * (t.fixed + t.step * (double)((K + 15) / 16));
     if (best_cost < 0.0 || cost < best_cost) { best = t.cfg; best_cost = cost; }
   }
