@@ -277,7 +277,7 @@ int f32_default_config(int64_t M, int64_t N, int64_t K) {
   const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128);
   static const TileCost kCosts[] = {{5, 256, 256, 1, 8.0, 3.8, 3.8},  {6, 128, 128, 2, 4.0, 1.15, 1.95},
                                     {9, 128, 128, 1, 4.0, 1.04, 1.04}, {8, 64, 64, 1, 3.0, 0.275, 0.275},
-                                    {7, 32, 32, 2, 1.0, 0.13, 0.15}};
+                                    {7, 32, 32, 2, 1.3, 0.14, 0.165}};
   // whole 128 x 128 tiles, more than one and at most two per CU, keep the 128 x
   // 128 tile, a documented default (2560 x 2048 x 2048: 255 us; the 64 x 64
   // small tiles take 191)
