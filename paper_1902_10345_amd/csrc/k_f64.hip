@@ -60,7 +60,7 @@ __device__ __forceinline__ f64x2 ld2(__amdgpu_buffer_rsrc_t r, int voff) {
 
 template <int BM, int BN, int WM, int WN>
 struct Cfg {
-  static constexpr int NW = (BM / WM) * (BN / WN);
+  static constexpr int NW = (BM / WM) * (BN / WN);   // waves of one k group
   static constexpr int NT = 64 * NW;
   static constexpr int WAVES_N = BN / WN;
   static constexpr int FM = WM / 16, FN = WN / 16;   // 16 x 16 blocks per wave
@@ -78,14 +78,25 @@ struct Cfg {
 // lda, K and the base (a 128-bit buffer load needs only 4-byte alignment).
 // The launcher guarantees that the byte extents of an A row panel (BM rows)
 // and of a B slab (16 rows) stay below 2^31.
-template <int BM, int BN, int WM, int WN, bool BETA>
+//
+// KG = 2: two groups of NW waves share the workgroup, each with its own half
+// of the slabs and its own LDS stages; the second group's partial tile is
+// added to the first's through LDS, and two slabs of global loads are in flight
+// per lane instead of one.  For products with one tile per CU at most, where
+// nothing else hides a workgroup's latency (64 x 64 tiles, 1024^3: 50 -> 43 us;
+// one of the two changes alone 48).  With more tiles per CU it is slower
+// (1999 x 1501 x 1003: 106 -> 112).
+template <int BM, int BN, int WM, int WN, int KG, bool BETA>
 __device__ __forceinline__ void tile(int M, int N, int K, double alpha, const double *__restrict__ A,
                                      int64_t lda, const double *__restrict__ B, int64_t ldb,
                                      double beta, double *__restrict__ C, int64_t ldc, int m0,
                                      int n0, double *lds) {
   using G = Cfg<BM, BN, WM, WN>;
   constexpr int NT = G::NT;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int group = KG > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / NT) : 0;
+  const int tid = KG > 1 ? (int)threadIdx.x % NT : (int)threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  lds += group * 2 * G::STAGE;
   const int Mr = M - m0, Nr = N - n0;
   const bool interior = Mr >= BM && Nr >= BN;
   const int rowsA = Mr < BM ? Mr : BM;
@@ -110,10 +121,13 @@ __device__ __forceinline__ void tile(int M, int N, int K, double alpha, const do
     b_row[i] = __builtin_amdgcn_readfirstlane(2 * (idx / BN)) * ldb8;
   }
 
-  double ra[G::A_ITEMS][2], rb[G::B_ITEMS][2];
+  constexpr int DEPTH = KG;  // slabs of global loads in flight
+  double ra_[DEPTH][G::A_ITEMS][2], rb_[DEPTH][G::B_ITEMS][2];
   // FAST: the slab lies inside [0, K); otherwise k outside [0, K) read as 0.
-  auto gload = [&](auto F, int k0) {
+  auto gload = [&](auto F, auto SET, int k0) {
     constexpr bool FAST = decltype(F)::value;
+    auto &ra = ra_[decltype(SET)::value];
+    auto &rb = rb_[decltype(SET)::value];
 #pragma unroll
     for (int i = 0; i < G::A_ITEMS; ++i) {
       if (FAST) {
@@ -148,7 +162,9 @@ __device__ __forceinline__ void tile(int M, int N, int K, double alpha, const do
       }
     }
   };
-  auto sstore = [&](int stage) {
+  auto sstore = [&](auto SET, int stage) {
+    auto &ra = ra_[decltype(SET)::value];
+    auto &rb = rb_[decltype(SET)::value];
     double *sA = lds + stage * G::STAGE;
     double *sB = sA + BM * BK;
 #pragma unroll
@@ -205,67 +221,112 @@ __device__ __forceinline__ void tile(int M, int N, int K, double alpha, const do
   // kbase = K - KT*16 <= 0, so only slab 0 can be partial (loaded masked in
   // the prologue).  Loads past the last slab are clamped to it (in bounds,
   // never consumed), so both halves of the loop issue the same instructions.
+  // With KG = 2 the second group starts at slab ceil(KT / 2); an odd slab
+  // count leaves it one slab short, which it does not multiply.
   using Fast = std::true_type;
   using Masked = std::false_type;
-  const int KT = (K + BK - 1) / BK;
-  const int kbase = K - KT * BK;
-  auto kslab = [&](int s) { return kbase + (s < KT ? s : KT - 1) * BK; };
-  gload(Masked{}, kbase);
-  sstore(0);
+  using R0 = std::integral_constant<int, 0>;
+  using R1 = std::integral_constant<int, DEPTH - 1>;
+  const int KA = (K + BK - 1) / BK;
+  const int KT = (KA + KG - 1) / KG;            // slabs of the first group
+  const int own = KG > 1 && group ? KA - KT : KT;
+  const int kbase = K - KA * BK + group * KT * BK;
+  auto kslab = [&](int s) {
+    const int k = kbase + (s < own ? s : own - 1) * BK;
+    return KG > 1 && k < 0 ? 0 : k;  // (a group without slabs reads some slab unused)
+  };
+  if (group == 0) gload(Masked{}, R0{}, kbase);
+  else gload(Fast{}, R0{}, kslab(0));
+  if (DEPTH == 2) gload(Fast{}, R1{}, kslab(1));
+  sstore(R0{}, 0);
   __syncthreads();
   int t = 0;
   for (; t + 2 <= KT; t += 2) {
-    gload(Fast{}, kslab(t + 1));
+    gload(Fast{}, R0{}, kslab(t + DEPTH));
     __builtin_amdgcn_sched_barrier(0);
     mfma_stage(0);
-    sstore(1);
+    sstore(R1{}, 1);
     __syncthreads();
-    gload(Fast{}, kslab(t + 2));
+    gload(Fast{}, R1{}, kslab(t + 1 + DEPTH));
     __builtin_amdgcn_sched_barrier(0);
-    mfma_stage(1);
-    sstore(0);
+    if (KG == 1 || t + 1 < own) mfma_stage(1);
+    sstore(R0{}, 0);
     __syncthreads();
   }
-  if (t < KT) mfma_stage(0);
+  if (t < KT && (KG == 1 || t < own)) mfma_stage(0);
+
+  if constexpr (KG > 1) {
+    double *part = lds - group * 2 * G::STAGE;
+    __syncthreads();  // the last fragment reads
+    if (group) {
+#pragma unroll
+      for (int i = 0; i < G::FM; ++i)
+#pragma unroll
+        for (int j = 0; j < G::FN; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) part[((i * G::FN + j) * 4 + e) * NT + tid] = acc[i][j][e];
+    }
+    __syncthreads();
+    if (group) return;
+#pragma unroll
+    for (int i = 0; i < G::FM; ++i)
+#pragma unroll
+      for (int j = 0; j < G::FN; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[i][j][e] += part[((i * G::FN + j) * 4 + e) * NT + tid];
+  }
 
   // Epilogue: element e of lane l is row lg + 4 e, column lr of its block.
+  // With beta != 0 a row of blocks of C is read in one go, ahead of the stores
+  // of the row before it: element by element each read waited for its
+  // predecessor's store (1999 x 1501 x 1003 108 -> 103 us).
+  auto inside = [&](int i, int j, int e) {
+    return interior || (wn0 + 16 * j + lr < Nr && wm0 + 16 * i + lg + 4 * e < Mr);
+  };
+  double *const cp = C + (int64_t)(m0 + wm0 + lg) * ldc + (n0 + wn0 + lr);
+  double cold[2][G::FN][4];
+  auto cread = [&](int i) {
 #pragma unroll
-  for (int i = 0; i < G::FM; ++i)
+    for (int j = 0; j < G::FN; ++j)
 #pragma unroll
-    for (int j = 0; j < G::FN; ++j) {
-      const int col = wn0 + 16 * j + lr;
-      if (!interior && col >= Nr) continue;
+      for (int e = 0; e < 4; ++e)
+        cold[i & 1][j][e] = inside(i, j, e) ? cp[(int64_t)(16 * i + 4 * e) * ldc + 16 * j] : 0.0;
+  };
+  if (BETA) cread(0);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int row = wm0 + 16 * i + lg + 4 * e;
-        if (interior || row < Mr) {
-          double *p = C + (int64_t)(m0 + row) * ldc + (n0 + col);
+  for (int i = 0; i < G::FM; ++i) {
+    if (BETA && i + 1 < G::FM) cread(i + 1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < G::FN; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (inside(i, j, e)) {
           const double v = alpha * acc[i][j][e];
-          *p = BETA ? fma(beta, *p, v) : v;
+          cp[(int64_t)(16 * i + 4 * e) * ldc + 16 * j] = BETA ? fma(beta, cold[i & 1][j][e], v) : v;
         }
-      }
-    }
+  }
 }
 
 // Grid: the output tiles of every problem of the batch (element strides sa, sb,
 // sc between consecutive problems) in one XCD-aware order.
-template <int BM, int BN, int WM, int WN, bool BETA>
-__global__ __launch_bounds__((Cfg<BM, BN, WM, WN>::NT), (Cfg<BM, BN, WM, WN>::MIN_WG)) void gemm_f64_kernel(
+template <int BM, int BN, int WM, int WN, int KG, bool BETA>
+__global__ __launch_bounds__((KG * Cfg<BM, BN, WM, WN>::NT), (Cfg<BM, BN, WM, WN>::MIN_WG)) void gemm_f64_kernel(
     int M, int N, int K, double alpha, const double *__restrict__ A, int64_t lda, int64_t sa,
     const double *__restrict__ B, int64_t ldb, int64_t sb, double beta, double *__restrict__ C,
     int64_t ldc, int64_t sc, int tiles_m, int tiles_n) {
   using G = Cfg<BM, BN, WM, WN>;
-  __shared__ __attribute__((aligned(16))) double lds[2 * G::STAGE];
+  __shared__ __attribute__((aligned(16))) double lds[KG * 2 * G::STAGE];
   const int wg = xcd_remap(blockIdx.x, gridDim.x);
   const int tiles = tiles_m * tiles_n;
   const int64_t b = wg / tiles;
   int tm, tn;
   tile_coords(wg - (int)b * tiles, tiles_m, tiles_n, 8, tm, tn);
-  tile<BM, BN, WM, WN, BETA>(M, N, K, alpha, A + b * sa, lda, B + b * sb, ldb, beta, C + b * sc,
+  tile<BM, BN, WM, WN, KG, BETA>(M, N, K, alpha, A + b * sa, lda, B + b * sb, ldb, beta, C + b * sc,
                                   ldc, tm * BM, tn * BN, lds);
 }
 
-template <int BM, int BN, int WM, int WN>
+template <int BM, int BN, int WM, int WN, int KG = 1>
 gemm_status launch(const GemmArgsF64 &g, hipStream_t s) {
   using G = Cfg<BM, BN, WM, WN>;
   const int tiles_m = (int)((g.M + BM - 1) / BM);
@@ -281,9 +342,9 @@ gemm_status launch(const GemmArgsF64 &g, hipStream_t s) {
     return GEMM_STATUS_UNSUPPORTED;
   }
   const bool beta = g.beta != 0.0;
-  const dim3 grid((unsigned)nwg), block(G::NT);
+  const dim3 grid((unsigned)nwg), block(KG * G::NT);
 #define MM_LAUNCH(BT)                                                                        \
-  hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, WM, WN, BT>), grid, block, 0, s, (int)g.M,      \
+  hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, WM, WN, KG, BT>), grid, block, 0, s, (int)g.M,      \
                      (int)g.N, (int)g.K, g.alpha, g.A, g.lda, g.sa, g.B, g.ldb, g.sb, g.beta, g.C, \
                      g.ldc, g.sc, tiles_m, tiles_n)
   if (beta) MM_LAUNCH(true); else MM_LAUNCH(false);
@@ -443,6 +504,165 @@ gemm_status launch_small(const GemmArgsF64 &g, hipStream_t s) {
   return check_launch("small_batched_kernel");
 }
 
+// Products with too few output tiles to fill the machine: one 16 F x 16 F tile
+// per workgroup of eight waves, each accumulating the whole tile over its own
+// run of 16-deep chunks (two chunks of operands in flight per wave, straight
+// from memory into MFMA fragments as in the batched kernel; no barrier in the
+// k loop); the eight partial tiles are added in wave order through LDS.
+// Bound: a wave's chain of loads while CUs are idle (0.5 us a chunk for F = 1,
+// 1.45 for F = 2), the L2 beyond that (about 11 TB/s at 2048^3, where LDS tiles
+// are 1.5 times as fast).  Against 64 x 64 tiles, us: 160 x 48 x 1888 84 -> 13,
+// 32 x 2016 x 759 37 -> 7, 166 x 1036 x 1857 84 -> 24, 576 x 1136 x 1512 71 ->
+// 51.  Three chunks in flight were no faster (13.6, 7.5; F = 2: 26, 56).
+constexpr int KW = 8;
+
+template <int F, bool BETA>
+__global__ __launch_bounds__(64 * KW) void split_kernel(
+    int M, int N, int K, double alpha, const double *__restrict__ A, int64_t lda, int64_t sa,
+    const double *__restrict__ B, int64_t ldb, int64_t sb, double beta, double *__restrict__ C,
+    int64_t ldc, int64_t sc, int tiles_m, int tiles_n) {
+  constexpr int OUT = 16 * F * 16 * F;
+  __shared__ double part[KW][OUT];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int wg = xcd_remap(blockIdx.x, gridDim.x), tiles = tiles_m * tiles_n;
+  const int64_t prob = wg / tiles;
+  int tm, tn;
+  tile_coords(wg - (int)prob * tiles, tiles_m, tiles_n, 8, tm, tn);
+  const int m0 = tm * 16 * F, n0 = tn * 16 * F;
+  const int Mr = M - m0, Nr = N - n0;
+  const int lr = lane & 15, lg = lane >> 4;
+  const __amdgpu_buffer_rsrc_t rA =
+      rsrc(A + prob * sa + (int64_t)m0 * lda, ((int64_t)(Mr - 1) * lda + K) * 8);
+  const __amdgpu_buffer_rsrc_t rB = rsrc(B + prob * sb + n0, ((int64_t)(K - 1) * ldb + Nr) * 8);
+  // lane group g takes k = 2g, 2g + 1, 8 + 2g, 9 + 2g of a chunk; its part of
+  // the offsets is fixed, the chunk's is wave-uniform
+  const int ldb8 = (int)ldb * 8;
+  int arow[F], bcol[F];
+#pragma unroll
+  for (int i = 0; i < F; ++i) {
+    const int x = 16 * i + lr;
+    arow[i] = x < Mr ? (x * (int)lda + 2 * lg) * 8 : (int)0x80000000;
+    bcol[i] = x < Nr ? x * 8 + 2 * lg * ldb8 : (int)0x80000000;
+  }
+  f64x4 acc[F][F];
+#pragma unroll
+  for (int i = 0; i < F; ++i)
+#pragma unroll
+    for (int j = 0; j < F; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
+  // the chunk grid ends at K: only chunk 0 can be partial
+  const int KC = (K + 15) / 16, kbase = K - 16 * KC;
+  const int c0 = wave * KC / KW, c1 = (wave + 1) * KC / KW;
+  double a[2][F][4], b[2][F][4];
+  auto load = [&](auto S, int c) {
+    constexpr int st = decltype(S)::value;
+    // chunks past the wave's last are read again at an offset in range, unused
+    const int k = kbase + 16 * (c < c1 ? c : c1 - 1), k0 = k > 0 ? k : 0;
+#pragma unroll
+    for (int i = 0; i < F; ++i)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const f64x2 v = __builtin_bit_cast(
+            f64x2, __builtin_amdgcn_raw_buffer_load_b128(rA, arow[i], (k0 + 8 * h) * 8, 0));
+        a[st][i][2 * h] = v.x;
+        a[st][i][2 * h + 1] = v.y;
+      }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int j = 0; j < F; ++j) b[st][j][q] = ld1(rB, bcol[j], (k0 + (q & 1) + 8 * (q >> 1)) * ldb8);
+  };
+  auto load_partial = [&]() {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = kbase + (q & 1) + 8 * (q >> 1);  // of lane group 0
+      const bool in = k + 2 * lg >= 0;
+#pragma unroll
+      for (int i = 0; i < F; ++i)
+        a[0][i][q] = ld1(rA, in && arow[i] >= 0 ? arow[i] + k * 8 : (int)0x80000000, 0);
+#pragma unroll
+      for (int j = 0; j < F; ++j)
+        b[0][j][q] = ld1(rB, in && bcol[j] >= 0 ? bcol[j] + k * ldb8 : (int)0x80000000, 0);
+    }
+  };
+  auto multiply = [&](auto S) {
+    constexpr int st = decltype(S)::value;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int i = 0; i < F; ++i)
+#pragma unroll
+        for (int j = 0; j < F; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[st][i][q], b[st][j][q], acc[i][j], 0, 0, 0);
+  };
+  using S0 = std::integral_constant<int, 0>;
+  using S1 = std::integral_constant<int, 1>;
+  if (c0 < c1) {
+    if (c0 == 0 && kbase < 0) load_partial();
+    else load(S0{}, c0);
+    for (int c = c0;;) {
+      load(S1{}, c + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(S0{});
+      if (++c >= c1) break;
+      load(S0{}, c + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(S1{});
+      if (++c >= c1) break;
+    }
+  }
+  // element e of lane l is row lg + 4 e, column lr of its block
+#pragma unroll
+  for (int i = 0; i < F; ++i)
+#pragma unroll
+    for (int j = 0; j < F; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) part[wave][((i * F + j) * 4 + e) * 64 + lane] = acc[i][j][e];
+  double *const Cb = C + prob * sc + (int64_t)m0 * ldc + n0;
+  double cold[(OUT + 64 * KW - 1) / (64 * KW)];
+  auto at = [&](int idx, int &row, int &col) {
+    const int blk = idx >> 8, e = (idx >> 6) & 3, l = idx & 63;
+    row = 16 * (blk / F) + (l >> 4) + 4 * e;
+    col = 16 * (blk % F) + (l & 15);
+  };
+  int row, col;
+  if (BETA) {
+#pragma unroll
+    for (int x = 0; x * 64 * KW < OUT; ++x) {
+      const int idx = x * 64 * KW + (int)threadIdx.x;
+      at(idx, row, col);
+      cold[x] = idx < OUT && row < Mr && col < Nr ? Cb[(int64_t)row * ldc + col] : 0.0;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int x = 0; x * 64 * KW < OUT; ++x) {
+    const int idx = x * 64 * KW + (int)threadIdx.x;
+    at(idx, row, col);
+    if (idx < OUT && row < Mr && col < Nr) {
+      double v = part[0][idx];
+#pragma unroll
+      for (int w = 1; w < KW; ++w) v += part[w][idx];
+      v *= alpha;
+      Cb[(int64_t)row * ldc + col] = BETA ? fma(beta, cold[x], v) : v;
+    }
+  }
+}
+
+template <int F>
+gemm_status launch_split(const GemmArgsF64 &g, hipStream_t s) {
+  const int64_t tiles_m = (g.M + 16 * F - 1) / (16 * F), tiles_n = (g.N + 16 * F - 1) / (16 * F);
+  const int64_t units = tiles_m * tiles_n * g.batch;
+  if (units > 0x7ffffff0) { set_error("gemm_f64: batch too large"); return GEMM_STATUS_UNSUPPORTED; }
+#define MM_LAUNCH(BT)                                                                                \
+  hipLaunchKernelGGL((split_kernel<F, BT>), dim3((unsigned)units), dim3(64 * KW), 0, s,        \
+                     (int)g.M, (int)g.N, (int)g.K, g.alpha, g.A, g.lda, g.sa, g.B, g.ldb, g.sb,      \
+                     g.beta, g.C, g.ldc, g.sc, (int)tiles_m, (int)tiles_n)
+  if (g.beta != 0.0) MM_LAUNCH(true); else MM_LAUNCH(false);
+#undef MM_LAUNCH
+  return check_launch("split_kernel");
+}
+
 // C <- beta*C over a batch (alpha == 0 or K == 0).
 template <bool BETA>
 __global__ __launch_bounds__(256) void scale_kernel(int64_t M, int64_t N, double beta,
@@ -471,6 +691,11 @@ static const F64Config kF64Configs[] = {
     {{16, 16, 16, "f64_small_16"}},
     {{32, 32, 16, "f64_small_32"}},
     {{64, 64, 16, "f64_small_64"}},
+    // one tile per workgroup of 8 waves, its k range split over the waves
+    {{16, 16, 16, "f64_16x16x16_8wk"}},
+    {{32, 32, 16, "f64_32x32x16_8wk"}},
+    // 64 x 64 tiles, the k range split between two groups of four waves
+    {{64, 64, 16, "f64_64x64x16_2x4w32x32_kg2"}},
 };
 
 int f64_num_configs() { return (int)(sizeof(kF64Configs) / sizeof(kF64Configs[0])); }
@@ -479,6 +704,15 @@ const TileConfig &f64_config(int i) { return kF64Configs[i].t; }
 // Sub-tile codes of a batch (beyond the configurations): one wave per 16 x 16,
 // 32 x 32 or 64 x 64 outputs.
 constexpr int kDirect16 = 100, kDirect32 = 101, kDirect64 = 102;
+
+// The split kernels' modelled time in us (fitted on 33 products from 32 to 2048
+// per dimension): the chain of one wave's chunks, or a cost per tile and per
+// tile and chunk, whichever is longer.
+static double split_time(int f, double tiles, double kc) {
+  const double chain = std::ceil(kc / 8.0);
+  return f == 1 ? std::max(1.5 + 0.5 * chain, 3.0 + tiles * (0.0022 + 0.00029 * kc))
+                : std::max(1.5 + 1.45 * chain, 3.0 + tiles * (0.008 + 0.00073 * kc));
+}
 
 // A batch: the tile with the least modelled time beyond the operands' traffic
 // (`fixed` ns per output tile, `step` ns per tile and 16 k, whole machine;
@@ -514,18 +748,40 @@ static int f64_batch_config(int64_t M, int64_t N, int64_t K, int64_t batch) {
     const double cost = rounds * slots * (t.fixed + t.step * (double)((K + 15) / 16));
     if (best_cost < 0.0 || cost < best_cost) { best = t.cfg; best_cost = cost; }
   }
+  // few long problems: the k range split over a workgroup's waves (64 x 64 x 512
+  // x 100 26 -> 19 us, 64 x 64 x 256 x 50 15 -> 7.5)
+  for (int f = 1; f <= 2; ++f) {
+    const int b = 16 * f;
+    const double tiles = (double)((M + b - 1) / b) * (double)((N + b - 1) / b) * (double)batch;
+    const double cost = 1e3 * (2.0 + split_time(f, tiles, (double)((K + 15) / 16)));
+    if (cost < best_cost) { best = 5 + f; best_cost = cost; }
+  }
   return best;
 }
 
 int f64_default_config(int64_t M, int64_t N, int64_t K, int64_t batch) {
   if (batch > 1) return f64_batch_config(M, N, K, batch);
-  // 128 x 128 tiles once there are two per CU; 64 x 64 below that.  Measured
-  // on one box: the kernel is matrix-core bound and the tiles tie within 1 %
-  // at 4096^3, but 64 x 64 tiles read 10x the minimum HBM bytes there (5.3
-  // against 1.9 GB per launch), which costs clock under the power limit; at
-  // 2048^3 (one 128 x 128 tile per CU) 64 x 64 tiles are 11 % faster.
-  const int64_t t = ((M + 127) / 128) * ((N + 127) / 128);
-  return t >= 2 * (int64_t)num_cus() ? 0 : 2;
+  // 128 x 128 tiles once there are two per CU.  Measured on one box: the kernel
+  // is matrix-core bound and the tiles tie within 1 % at 4096^3, but 64 x 64
+  // tiles read 10x the minimum HBM bytes there (5.3 against 1.9 GB per launch),
+  // which costs clock under the power limit; at 2048^3 (one 128 x 128 tile per
+  // CU) 64 x 64 tiles are 11 % faster.
+  const double cus = num_cus();
+  auto tiles = [&](int b) { return (double)((M + b - 1) / b) * (double)((N + b - 1) / b); };
+  if (tiles(128) >= 2 * cus) return 0;
+  // Below that the least modelled time in us.  64 x 64 tiles: a CU with n of
+  // them takes 0.25 + 0.46 n per slab (the matrix cores' own time is 0.48 n);
+  // the two-group form where n is 1.
+  const double kc = (double)((K + 15) / 16), r = tiles(64) / cus, n = std::ceil(r);
+  const struct { int cfg; double us; } c[] = {
+      {2, 3.5 + kc * (n <= 1.0 ? 0.71 : n <= 4.0 ? 0.25 + 0.46 * n : 0.5 * r)},
+      {8, n <= 1.0 ? 4.5 + 0.6 * kc : 1e30},
+      {6, split_time(1, tiles(16), kc)},
+      {7, split_time(2, tiles(32), kc)}};
+  int best = 0;
+  for (int i = 1; i < 4; ++i)
+    if (c[i].us < c[best].us) best = i;
+  return c[best].cfg;
 }
 
 gemm_status f64_run(const GemmArgsF64 &g, int cfg, hipStream_t s) {
@@ -544,13 +800,16 @@ gemm_status f64_run(const GemmArgsF64 &g, int cfg, hipStream_t s) {
       set_error("gemm_f64: lda or ldb too large for 32-bit offsets of the small-problem kernel");
       return GEMM_STATUS_UNSUPPORTED;
     }
-    // other operands that 32-bit offsets cannot reach take the 64 x 64 tile
-    if (!f64::small_fits(g)) cfg = 2;
   }
+  // other operands that 32-bit offsets cannot reach take the 64 x 64 tile
+  if ((cfg >= kDirect16 || cfg == 6 || cfg == 7) && !f64::small_fits(g)) cfg = 2;
   switch (cfg) {
     case 0: return f64::launch<128, 128, 64, 64>(g, s);
     case 1: return f64::launch<256, 128, 64, 64>(g, s);
     case 2: return f64::launch<64, 64, 32, 32>(g, s);
+    case 6: return f64::launch_split<1>(g, s);
+    case 7: return f64::launch_split<2>(g, s);
+    case 8: return f64::launch<64, 64, 32, 32, 2>(g, s);
     case kDirect16: return f64::launch_small<1>(g, s);
     case kDirect32: return f64::launch_small<2>(g, s);
     case kDirect64: return f64::launch_small<4>(g, s);

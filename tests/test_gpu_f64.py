@@ -277,3 +277,35 @@ def test_tiles_of_batched_problems_exact(M, N, K, batch):
     mm.gemm_f64_strided_batched(M, N, K, 2.0, A, K, M * K, B, N, K * N, -3.0, C, N, sc, batch)
     assert torch.equal(C[:, :M * N].view(batch, M, N), 2 * want - 6.0)
     assert bool((C[:, M * N:] == 2.0).all())
+
+
+@pytest.mark.parametrize("K", [1, 15, 16, 17, 100, 127, 128, 129, 300])
+@pytest.mark.parametrize("M,N", [(16, 16), (33, 47), (65, 70), (1, 130)])
+def test_k_split_configs_exact(M, N, K):
+    """The configurations that cut the k range between waves or wave groups,
+    with fewer chunks than waves, partial chunks and an odd number of slabs;
+    integer inputs, so every order of the sum gives the exact result."""
+    import paper_1902_10345_amd as mm
+    A = si.integers((M, K), 3, -1000, 1000).astype(np.float64)
+    B = si.integers((K, N), 4, -1000, 1000).astype(np.float64)
+    C0 = si.integers((M, N), 5, -1000, 1000).astype(np.float64)
+    exact = oracle.dgemm(A, B, alpha=2.0, beta=-3.0, C0=C0)
+    ran = 0
+    for cfg in range(mm.gemm_num_configs(mm.PATH_F64)):
+        if not mm.gemm_config_name(mm.PATH_F64, cfg).endswith(("_8wk", "_kg2")):
+            continue
+        _, C = _run(mm, A, B, C0, 2.0, -3.0, cfg=cfg)
+        assert np.array_equal(C, exact), mm.gemm_config_name(mm.PATH_F64, cfg)
+        ran += 1
+    assert ran == 3
+
+
+@pytest.mark.parametrize("M,N,K,batch", [(64, 64, 500, 5), (40, 17, 777, 3), (16, 16, 2000, 2)])
+def test_few_long_batched_problems_exact(M, N, K, batch):
+    import torch
+    import paper_1902_10345_amd as mm
+    A = torch.randint(-9, 10, (batch, M, K), device="cuda").double()
+    B = torch.randint(-9, 10, (batch, K, N), device="cuda").double()
+    C = torch.ones((batch, M, N), device="cuda", dtype=torch.float64)
+    mm.gemm_f64_strided_batched(M, N, K, 2.0, A, K, M * K, B, N, K * N, -3.0, C, N, M * N, batch)
+    assert torch.equal(C, 2 * torch.stack([a @ b for a, b in zip(A.cpu(), B.cpu())]).cuda() - 3.0)
