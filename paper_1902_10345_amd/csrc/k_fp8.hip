@@ -10,6 +10,7 @@
 // qbT is B's code matrix transposed (column j contiguous), so both operands are
 // k-contiguous and stage into LDS without a transpose.  Codes in [K, Kp) are 0.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "common.hpp"
@@ -227,57 +228,6 @@ __global__ __launch_bounds__(256) void quant_rows_reg_kernel(int M, int K, int64
   with_mode(s, nan, emit);
 }
 
-// One wave per row (four rows per workgroup) for rows of at most 256 * CH
-// padded elements: lane t holds elements 4t + 256j (j < CH) in registers, the amax
-// is a wave reduction (no LDS, no barrier), and each lane stores the 4 codes
-// of each of its groups as one 32-bit word.  VEC: ld % 4 == 0 and the base
-// 16-byte aligned.
-template <int CH, bool VEC>
-__global__ __launch_bounds__(256) void quant_rows_wave_kernel(int M, int K, int64_t Kp,
-                                                              const float *__restrict__ A,
-                                                              int64_t lda, uint8_t *__restrict__ qa,
-                                                              float *__restrict__ sa,
-                                                              uint32_t *__restrict__ zero,
-                                                              int64_t nzero) {
-  clear_words(zero, nzero);
-  const int lane = threadIdx.x & 63;
-  const int i = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (i >= M) return;
-  const float *row = A + (int64_t)i * lda;
-  float v[CH][4];
-  float m = 0.0f;
-  bool nan = false;
-#pragma unroll
-  for (int j = 0; j < CH; ++j) {
-    const int k = 4 * lane + 256 * j;
-    if (VEC && k + 3 < K) {
-      const float4 x = *reinterpret_cast<const float4 *>(row + k);
-      v[j][0] = x.x; v[j][1] = x.y; v[j][2] = x.z; v[j][3] = x.w;
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[j][e] = k + e < K ? row[k + e] : 0.0f;
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      m = fmaxf(m, fabsf(v[j][e]));
-      nan |= v[j][e] != v[j][e];
-    }
-  }
-  m = warp_max(m);
-  const float s = (m == 0.0f) ? 1.0f : m / 448.0f;
-  if (lane == 0) sa[i] = s;
-  const float r = 1.0f / s;
-  uint8_t *q = qa + (int64_t)i * Kp;
-  auto emit = [&](auto mode) {
-#pragma unroll
-    for (int j = 0; j < CH; ++j) {
-      const int k = 4 * lane + 256 * j;
-      if (k < Kp) *reinterpret_cast<uint32_t *>(q + k) = codes4<decltype(mode)::value>(v[j], s, r);
-    }
-  };
-  with_mode(s, nan, emit);
-}
-
 __global__ __launch_bounds__(256) void fill_u32_kernel(uint32_t *__restrict__ p, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
     p[i] = 0u;
@@ -370,27 +320,88 @@ __global__ __launch_bounds__(256) void quant_cols_t_kernel(int K, int N, int64_t
   }
 }
 
-// One-pass column quantisation for K <= 1024 * CQ: a workgroup of 1024 lanes
-// holds a stripe of 16 columns of the K x Nc matrix in registers between the
-// amax reduction and the encoding, so the matrix is read from HBM once (the
-// two-pass path reads it for the amax and again for the codes).  Lane (tx, ty)
-// = (tid & 3, tid >> 2) holds columns j0 + 4 tx .. + 3 of rows 4 (ty + 256 i)
-// .. + 3 (i < CQ): 4 consecutive k of each of its 4 columns, so each column's
-// codes come out as 32-bit words of 4 consecutive k, stored straight into the
-// transposed layout (row j of qT holds column j, k contiguous) -- the 16 lanes
-// of a wave with one tx write 64 contiguous bytes of each of their columns.
-// Stripes are remapped so that the two stripes of one 128-byte row segment
-// run on one XCD (their shared lines meet in its L2).  VEC: ld % 4 == 0 and
-// the base 16-byte aligned.
-template <int CQ, bool VEC>
-__global__ __launch_bounds__(1024) void quant_cols_reg_kernel(int K, int Nc, int64_t Kp,
-                                                              const float *__restrict__ B,
-                                                              int64_t ldb,
-                                                              uint8_t *__restrict__ qT,
-                                                              float *__restrict__ scales) {
-  __shared__ float red[16][16];
-  const int tid = threadIdx.x, tx = tid & 3, ty = tid >> 2;
-  const int stripe = xcd_remap(blockIdx.x, gridDim.x);
+// Both operands' quantisation in one launch, for rows (columns) of at most 4096
+// padded elements, each held in registers between its amax and its codes (one
+// read from HBM).  A job is one operand: R vectors of K elements, by rows
+// (R x K, row stride ld) or by columns (K x R); the first blocks0 workgroups of
+// the grid take the first job.  One launch instead of one per operand: a small
+// product's time is its launches (427 x 240 x 240, quantisation included, 20 ->
+// 17.7 us; 4096^3 quantised in 41 us, 48 in two launches).
+struct QuantJob {
+  const float *P;
+  int64_t ld;
+  uint8_t *q;
+  float *scales;
+  int R, cols;
+};
+
+// four binary32 values in one 128-bit load at any 4-byte alignment
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// Rows.  WAVE: one wave per row, K <= 256 * CH, lane t holds elements 4t +
+// 256j (j < CH); the amax is a wave reduction without a barrier.  Else four
+// waves per row, K <= 1024 * CH, lane t of the four holds elements 4t + 1024j.
+// Each lane stores the 4 codes of each of its groups as one 32-bit word.
+template <bool WAVE, int CH>
+__device__ __forceinline__ void quant_rows(const QuantJob &job, int block, int K, int64_t Kp,
+                                           float *red) {
+  constexpr int NT = WAVE ? 64 : 256;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int g = WAVE ? wave : wave >> 2, t = (int)threadIdx.x & (NT - 1);
+  const int i = block * (1024 / NT) + g;
+  const float *row = job.P + (int64_t)(i < job.R ? i : 0) * job.ld;
+  float v[CH][4];
+  float m = 0.0f;
+  bool nan = false;
+#pragma unroll
+  for (int j = 0; j < CH; ++j) {
+    const int k = 4 * t + 4 * NT * j;
+    if (k + 3 < K) {
+      const f32x4u x = *reinterpret_cast<const f32x4u *>(row + k);
+      v[j][0] = x.x; v[j][1] = x.y; v[j][2] = x.z; v[j][3] = x.w;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[j][e] = k + e < K ? row[k + e] : 0.0f;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      m = fmaxf(m, fabsf(v[j][e]));
+      nan |= v[j][e] != v[j][e];
+    }
+  }
+  m = warp_max(m);
+  if constexpr (!WAVE) {
+    if ((threadIdx.x & 63) == 0) red[wave] = m;
+    __syncthreads();
+    m = fmaxf(fmaxf(red[4 * g], red[4 * g + 1]), fmaxf(red[4 * g + 2], red[4 * g + 3]));
+  }
+  if (i >= job.R) return;
+  const float s = (m == 0.0f) ? 1.0f : m / 448.0f;
+  if (t == 0) job.scales[i] = s;
+  const float r = 1.0f / s;
+  uint8_t *q = job.q + (int64_t)i * Kp;
+  auto emit = [&](auto mode) {
+#pragma unroll
+    for (int j = 0; j < CH; ++j) {
+      const int k = 4 * t + 4 * NT * j;
+      if (k < Kp) *reinterpret_cast<uint32_t *>(q + k) = codes4<decltype(mode)::value>(v[j], s, r);
+    }
+  };
+  with_mode(s, nan, emit);
+}
+
+// Columns, K <= 1024 * CQ: the workgroup holds a stripe of 16 columns.  Lane
+// (tx, ty) = (tid & 3, tid >> 2) holds columns j0 + 4 tx .. + 3 of rows
+// 4 (ty + 256 i) .. + 3 (i < CQ): 4 consecutive k of each of its 4 columns, so
+// each column's codes come out as 32-bit words of 4 consecutive k, stored
+// straight into the transposed layout (row j of q holds column j, k
+// contiguous) -- the 16 lanes of a wave with one tx write 64 contiguous bytes
+// of each of their columns.  Stripes are remapped so that the two stripes of
+// one 128-byte row segment run on one XCD (their shared lines meet in its L2).
+template <int CQ>
+__device__ __forceinline__ void quant_cols(const QuantJob &job, int stripe, int K, int64_t Kp,
+                                           float *red) {
+  const int tid = threadIdx.x, tx = tid & 3, ty = tid >> 2, Nc = job.R;
   const int j0 = stripe * 16 + tx * 4;  // the lane's first column
   float x[CQ][4][4];                    // [block i][row e][column c]
   float m[4] = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -400,9 +411,9 @@ __global__ __launch_bounds__(1024) void quant_cols_reg_kernel(int K, int Nc, int
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int k = 4 * (ty + 256 * i) + e;
-      const float *p = B + (int64_t)k * ldb + j0;
-      if (VEC && k < K && j0 + 3 < Nc) {
-        const float4 v = *reinterpret_cast<const float4 *>(p);
+      const float *p = job.P + (int64_t)k * job.ld + j0;
+      if (k < K && j0 + 3 < Nc) {
+        const f32x4u v = *reinterpret_cast<const f32x4u *>(p);
         x[i][e][0] = v.x; x[i][e][1] = v.y; x[i][e][2] = v.z; x[i][e][3] = v.w;
       } else {
 #pragma unroll
@@ -423,23 +434,23 @@ __global__ __launch_bounds__(1024) void quant_cols_reg_kernel(int K, int Nc, int
   const int wave = tid >> 6;
   if ((tid & 63) < 4) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) red[wave][tx * 4 + c] = m[c];
+    for (int c = 0; c < 4; ++c) red[wave * 16 + tx * 4 + c] = m[c];
   }
   __syncthreads();
   float sc[4], rc[4];
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
-    float a = red[0][tx * 4 + c];
+    float a = red[tx * 4 + c];
 #pragma unroll
-    for (int w = 1; w < 16; ++w) a = fmaxf(a, red[w][tx * 4 + c]);
+    for (int w = 1; w < 16; ++w) a = fmaxf(a, red[w * 16 + tx * 4 + c]);
     sc[c] = (a == 0.0f) ? 1.0f : a / 448.0f;
     rc[c] = 1.0f / sc[c];
-    if (ty == 0 && j0 + c < Nc) scales[j0 + c] = sc[c];
+    if (ty == 0 && j0 + c < Nc) job.scales[j0 + c] = sc[c];
   }
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
     if (j0 + c >= Nc) continue;
-    uint8_t *q = qT + (int64_t)(j0 + c) * Kp;
+    uint8_t *q = job.q + (int64_t)(j0 + c) * Kp;
     auto emit = [&](auto mode) {
 #pragma unroll
       for (int i = 0; i < CQ; ++i) {
@@ -450,6 +461,18 @@ __global__ __launch_bounds__(1024) void quant_cols_reg_kernel(int K, int Nc, int
     };
     with_mode(sc[c], nan[c], emit);  // per column: lanes may take different modes
   }
+}
+
+template <bool WAVE, int CH, int CQ>
+__global__ __launch_bounds__(1024) void quant_pair_kernel(QuantJob job0, QuantJob job1, int blocks0,
+                                                          int K, int64_t Kp) {
+  __shared__ float red[256];
+  const bool first = (int)blockIdx.x < blocks0;
+  const QuantJob job = first ? job0 : job1;
+  const int block = first ? (int)blockIdx.x : (int)blockIdx.x - blocks0;
+  const int blocks = first ? blocks0 : (int)gridDim.x - blocks0;
+  if (job.cols) quant_cols<CQ>(job, xcd_remap(block, blocks), K, Kp, red);
+  else quant_rows<WAVE, CH>(job, block, K, Kp, red);
 }
 
 // ---------------------------------------------------------------- GEMM ----
@@ -982,7 +1005,7 @@ __global__ __launch_bounds__(256) void encode_kernel(int64_t n, const float *__r
 size_t fp8_ws_bytes(int64_t M, int64_t N, int64_t K) { return fp8::layout(M, N, K).total; }
 int64_t fp8_kp(int64_t K) { return fp8::layout(0, 0, K).Kp; }
 
-// Row quantisation: R rows of K binary32 values (row stride ld) -> per-row
+// Row quantisation (Kp > 4096): R rows of K binary32 values (row stride ld) -> per-row
 // scales and codes in rows of Kp bytes (k contiguous).  zero: nzero words that
 // the launch also clears when its grid has a thread for each (for a later
 // quant_cols on the same stream); *cleared tells whether it did.
@@ -991,30 +1014,9 @@ static gemm_status quant_rows(int64_t R, int64_t K, int64_t Kp, const float *P, 
                               uint32_t *zero = nullptr, int64_t nzero = 0,
                               bool *cleared = nullptr) {
   const bool vec = ld % 4 == 0 && ((uintptr_t)P & 15) == 0;
-  const int chw = (int)((Kp + 255) / 256);
-  const int64_t threads = 256 * (chw <= 2 ? (R + 3) / 4 : R);
+  const int64_t threads = 256 * R;
   if (zero == nullptr || nzero > threads) nzero = 0;
   if (cleared) *cleared = nzero > 0;
-  // Short rows (at most 512 padded elements): one wave per row.  Measured on
-  // 4096-row operands, 7 % faster than a workgroup per row at K = 300 and
-  // 16 % slower at K = 4096, where four rows per workgroup keep too few bytes
-  // in flight per CU.
-  if (chw <= 2) {
-    const unsigned grid = (unsigned)((R + 3) / 4);
-#define MM_QWAVE(CH)                                                                               \
-  do {                                                                                             \
-    if (vec)                                                                                       \
-      hipLaunchKernelGGL((fp8::quant_rows_wave_kernel<CH, true>), dim3(grid), dim3(256), 0, s,      \
-                         (int)R, (int)K, Kp, P, ld, q, scales, zero, nzero);                       \
-    else                                                                                           \
-      hipLaunchKernelGGL((fp8::quant_rows_wave_kernel<CH, false>), dim3(grid), dim3(256), 0, s,     \
-                         (int)R, (int)K, Kp, P, ld, q, scales, zero, nzero);                       \
-  } while (0)
-    if (chw == 1) MM_QWAVE(1);
-    else MM_QWAVE(2);
-#undef MM_QWAVE
-    return check_launch("quant_rows_wave_kernel");
-  }
   const int ch = (int)((Kp + 1023) / 1024);
 #define MM_QROWS(CH)                                                                             \
   do {                                                                                           \
@@ -1026,10 +1028,6 @@ static gemm_status quant_rows(int64_t R, int64_t K, int64_t Kp, const float *P, 
                          0, s, (int)R, (int)K, Kp, P, ld, q, scales, zero, nzero);               \
   } while (0)
   switch (ch) {
-    case 1: MM_QROWS(1); break;
-    case 2: MM_QROWS(2); break;
-    case 3: MM_QROWS(3); break;
-    case 4: MM_QROWS(4); break;
     case 5: MM_QROWS(5); break;
     case 6: MM_QROWS(6); break;
     case 7: MM_QROWS(7); break;
@@ -1042,32 +1040,12 @@ static gemm_status quant_rows(int64_t R, int64_t K, int64_t Kp, const float *P, 
   return check_launch("quant_rows_kernel");
 }
 
-// Column quantisation: a K x Nc matrix (row stride ld) -> per-column scales
+// Column quantisation (Kp > 4096): a K x Nc matrix (row stride ld) -> per-column scales
 // and the codes of each column in a row of Kp bytes (transposed, k
 // contiguous).  amax: Nc words of scratch, already zero when amax_clear.
 static gemm_status quant_cols(int64_t K, int64_t Nc, int64_t Kp, const float *P, int64_t ld,
                               uint32_t *amax, uint8_t *q, float *scales, hipStream_t s,
                               bool amax_clear = false) {
-  // up to 4096 rows: one pass, the stripe held in registers
-  if (Kp <= 4096) {
-    const bool vec1 = ld % 4 == 0 && ((uintptr_t)P & 15) == 0;
-    const dim3 grid((unsigned)((Nc + 15) / 16));
-#define MM_QCOLS(CQ)                                                                             \
-  do {                                                                                           \
-    if (vec1)                                                                                    \
-      hipLaunchKernelGGL((fp8::quant_cols_reg_kernel<CQ, true>), grid, dim3(1024), 0, s, (int)K, \
-                         (int)Nc, Kp, P, ld, q, scales);                                         \
-    else                                                                                         \
-      hipLaunchKernelGGL((fp8::quant_cols_reg_kernel<CQ, false>), grid, dim3(1024), 0, s,        \
-                         (int)K, (int)Nc, Kp, P, ld, q, scales);                                 \
-  } while (0)
-    if (Kp <= 1024) MM_QCOLS(1);
-    else if (Kp <= 2048) MM_QCOLS(2);
-    else if (Kp <= 3072) MM_QCOLS(3);
-    else MM_QCOLS(4);
-#undef MM_QCOLS
-    return check_launch("quant_cols_reg_kernel");
-  }
   if (!amax_clear) {
     const unsigned fg = (unsigned)std::min<int64_t>((Nc + 255) / 256, 1024);
     hipLaunchKernelGGL(fp8::fill_u32_kernel, dim3(fg), dim3(256), 0, s, amax, Nc);
@@ -1098,6 +1076,30 @@ gemm_status fp8_quantize_run(int64_t M, int64_t N, int64_t K, const float *A, in
   float *sa = reinterpret_cast<float *>(base + L.sa);
   float *sb = reinterpret_cast<float *>(base + L.sb);
   uint32_t *amax = reinterpret_cast<uint32_t *>(base + L.amax);
+  if (L.Kp <= 4096) {
+    // column stripes first: they take longer
+    fp8::QuantJob ja{A, lda, qa, sa, (int)M, ta}, jb{B, ldb, qb, sb, (int)N, !tb};
+    if (ja.cols < jb.cols) std::swap(ja, jb);
+    auto blocks = [&](const fp8::QuantJob &j) {
+      const int per = j.cols ? 16 : L.Kp <= 512 ? 16 : 4;
+      return (j.R + per - 1) / per;
+    };
+    const int blocks0 = blocks(ja), total = blocks0 + blocks(jb);
+    if (total == 0) return GEMM_STATUS_OK;
+#define MM_QPAIR(WAVE, CH, CQ)                                                                     \
+  hipLaunchKernelGGL((fp8::quant_pair_kernel<WAVE, CH, CQ>), dim3((unsigned)total), dim3(1024), 0, \
+                     s, ja, jb, blocks0, (int)K, L.Kp)
+    // one wave per row up to 512 (7 % faster than four at 4096 rows of 300,
+    // 16 % slower at rows of 4096)
+    if (L.Kp <= 256) MM_QPAIR(true, 1, 1);
+    else if (L.Kp <= 512) MM_QPAIR(true, 2, 1);
+    else if (L.Kp <= 1024) MM_QPAIR(false, 1, 1);
+    else if (L.Kp <= 2048) MM_QPAIR(false, 2, 2);
+    else if (L.Kp <= 3072) MM_QPAIR(false, 3, 3);
+    else MM_QPAIR(false, 4, 4);
+#undef MM_QPAIR
+    return check_launch("quant_pair_kernel");
+  }
   // When A goes by rows and B by columns, A's launch clears B's amax words.
   bool amax_clear = false;
   if (M > 0) {
@@ -1167,7 +1169,7 @@ static gemm_status fp8_launch_ring(int64_t M, int64_t N, const fp8::Layout &L, f
   return check_launch("gemm_fp8_ring_kernel");
 }
 
-int fp8_num_configs() { return 7; }
+int fp8_num_configs() { return 9; }
 const char *fp8_config_name(int cfg) {
   switch (cfg) {
     case 0: return "fp8_256x256x128_8w128x64";
@@ -1176,6 +1178,8 @@ const char *fp8_config_name(int cfg) {
     case 4: return "fp8_256x128x128_8w64x64_dma";
     case 5: return "fp8_256x256x128_4w128x128_dma";
     case 6: return "fp8_256x256x64_8w128x64_dma_ring4";
+    case 7: return "fp8_64x64x128_4w32x32_dma";
+    case 8: return "fp8_64x64x64_4w32x32_dma_ring4";
     default: return "fp8_256x256x128_8w128x64_dma";
   }
 }
@@ -1190,15 +1194,26 @@ gemm_status fp8_gemm_run_cfg(int64_t M, int64_t N, int64_t K, float alpha, const
   if (cfg == 4) return fp8_launch<256, 128, 64, 64, true>(M, N, L, alpha, base, beta, C, ldc, s);
   if (cfg == 5) return fp8_launch<256, 256, 128, 128, true>(M, N, L, alpha, base, beta, C, ldc, s);
   if (cfg == 6) return fp8_launch_ring<256, 256, 128, 64>(M, N, L, alpha, base, beta, C, ldc, s);
+  if (cfg == 7) return fp8_launch<64, 64, 32, 32, true>(M, N, L, alpha, base, beta, C, ldc, s);
+  if (cfg == 8) return fp8_launch_ring<64, 64, 32, 32>(M, N, L, alpha, base, beta, C, ldc, s);
   return fp8_launch<256, 256, 128, 64, false>(M, N, L, alpha, base, beta, C, ldc, s);
 }
 
-// Direct-to-LDS kernels: 256 x 256 tiles while they fill every compute unit
-// (measured best at 4096^3 and above), 128 x 128 tiles -- two workgroups per
-// compute unit -- below that (1.9x at 2048^3 and at 1024 x 4096 x 4096).
-int fp8_default_config(int64_t M, int64_t N, int64_t) {
-  const int64_t big = ((M + 255) / 256) * ((N + 255) / 256);
-  return big >= num_cus() ? 2 : 3;
+// Direct-to-LDS kernels.  256 x 256 tiles take 1.75 us per 128-deep slab and
+// round of one tile per CU, 64 x 64 tiles 0.8 ns per tile and slab and a shorter
+// prologue and epilogue (a lane's 16 results instead of 128): the smaller sum
+// (us without quantisation, 256 / 128 / 64: 4096^3 54 / 60 / 88, 3000^3 47 / 55
+// / 47, 2048^3 31 / 18 / 16, 1474 x 1051 x 96 15 / 9 / 5).  With at most three
+// 64 x 64 tiles for two CUs, the ring of four stages (512^3 5.1 -> 4.5 us, 800 x
+// 800 x 4000 17 -> 12); beyond, other workgroups hide a slab's latency and the
+// two-stage form is ahead (2048^3 15 us, ring 19).
+int fp8_default_config(int64_t M, int64_t N, int64_t K) {
+  const double cus = num_cus(), slabs = (double)((K + 127) / 128);
+  auto tiles = [&](int b) { return (double)((M + b - 1) / b) * (double)((N + b - 1) / b); };
+  const double big = 6.0 + 1.75 * slabs * std::ceil(tiles(256) / cus);
+  const double small = 3.0 + 0.0008 * slabs * tiles(64);
+  if (big < small) return 2;
+  return tiles(64) <= 1.5 * cus ? 8 : 7;
 }
 
 gemm_status fp8_encode_run(int64_t n, const float *x, uint8_t *out, hipStream_t s) {

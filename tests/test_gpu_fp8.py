@@ -95,6 +95,36 @@ def test_column_quantiser_register_blocks_are_bitwise_the_oracle(K):
     assert not qbT[:, K:].any()
 
 
+@pytest.mark.parametrize("M,N,K", [(17, 33, 255), (16, 16, 256), (1, 1, 257), (15, 5, 513),
+                                   (4, 17, 1023), (3, 18, 2047), (9, 31, 4095)])
+def test_quantiser_of_unaligned_operands_is_bitwise_the_oracle(M, N, K):
+    """Row strides that are no multiple of 16 bytes, bases at 4-byte alignment
+    and NaN in the padding, at the edges of the row and column blocks of the
+    one-launch quantiser."""
+    import torch
+    import paper_1902_10345_amd as mm
+    A, B, _ = si.fp8_workload(M, N, K, seed=K, outliers="none")
+    dA = torch.full((M * (K + 1) + 1,), float("nan"), device="cuda")
+    dB = torch.full((K * (N + 3) + 1,), float("nan"), device="cuda")
+    vA = dA[1:].view(M, K + 1)[:, :K]
+    vB = dB[1:].view(K, N + 3)[:, :N]
+    vA.copy_(torch.from_numpy(A))
+    vB.copy_(torch.from_numpy(B))
+    nbytes = mm.gemm_fp8_workspace_bytes(M, N, K)
+    ws = torch.zeros(nbytes, dtype=torch.uint8, device="cuda")
+    mm.fp8_quantize(M, N, K, vA, K + 1, vB, N + 3, ws, nbytes)
+    L = mm.fp8_workspace_layout(M, N, K)
+    h = ws.cpu().numpy()
+    rsa, rsb = oracle.fp8_scales_rows(A), oracle.fp8_scales_cols(B)
+    assert np.array_equal(h[L["sa"]:L["sa"] + 4 * M].view(np.float32), rsa)
+    assert np.array_equal(h[L["sb"]:L["sb"] + 4 * N].view(np.float32), rsb)
+    qa = h[L["qa"]:L["qa"] + M * L["Kp"]].reshape(M, L["Kp"])
+    qbT = h[L["qb"]:L["qb"] + N * L["Kp"]].reshape(N, L["Kp"])
+    assert np.array_equal(qa[:, :K], oracle.fp8_quantize_rows(A, rsa))
+    assert np.array_equal(qbT[:, :K].T, oracle.fp8_quantize_cols(B, rsb))
+    assert not qa[:, K:].any() and not qbT[:, K:].any()
+
+
 @pytest.mark.parametrize("M,N,K", [(40, 36, 200), (40, 36, 1000), (12, 20, 9000)])
 def test_quantiser_special_values_are_bitwise_the_oracle(M, N, K):
     """Rows and columns with NaN, infinities, signed zeros and scales of
