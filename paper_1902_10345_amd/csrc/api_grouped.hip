@@ -93,7 +93,7 @@ gemm_status grouped_gemm(const gemm_problem *problems, int count, int path,
   if ((st = enqueue_scale_only(problems, count, stream))) return st;
   if (count == 0) return GEMM_STATUS_OK;
   if ((st = grouped_upload(workspace, descs, starts, stream))) return st;
-  return grouped_enqueue(workspace, count, total, grouped_grid(total), stream);
+  return grouped_enqueue(workspace, count, total, stream);
 }
 
 gemm_status grouped_graph_create(const gemm_problem *problems, int count, int path,
@@ -122,7 +122,7 @@ gemm_status grouped_graph_create(const gemm_problem *problems, int count, int pa
     return hip_fail("grouped_graph_create: begin capture", e);
   }
   st = enqueue_scale_only(problems, count, cap);
-  if (!st && count > 0) st = grouped_enqueue(workspace, count, total, grouped_grid(total), cap);
+  if (!st && count > 0) st = grouped_enqueue(workspace, count, total, cap);
   e = hipStreamEndCapture(cap, &g->graph);
   hipStreamDestroy(cap);
   if (st || e != hipSuccess) {

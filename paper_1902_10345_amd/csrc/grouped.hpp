@@ -30,7 +30,6 @@ gemm_status grouped_upload(void *ws, const std::vector<Desc> &descs, const std::
                            hipStream_t s);
 gemm_status grouped_upload_pinned(void *ws, void *pinned, const std::vector<Desc> &descs,
                                   const std::vector<int> &starts, hipStream_t s);
-gemm_status grouped_enqueue(void *ws, int count, int total, int grid, hipStream_t s);
-int grouped_grid(int total);
+gemm_status grouped_enqueue(void *ws, int count, int total, hipStream_t s);
 
 }  // namespace mm

@@ -2,17 +2,16 @@
 // uneven sizes on the 3xBF16 split-precision MFMA path.
 //
 // The batch is flattened into one list of output tiles (problem p owns tiles
-// [start[p], start[p+1])).  A grid sized to the machine's resident capacity
-// takes tile indices from an atomic counter -- the mechanism behind the
+// [start[p], start[p+1])), one workgroup per tile, in an order that hands out
+// the longest tiles first: the hardware's dispatcher then plays the part of the
 // paper's consume scopes (Sec. 3.3), where workers take elements off a shared
-// stream with atomic operations -- finds the
-// owning problem by binary search over the prefix of tile counts and runs the
-// same tile body as the single-GEMM kernel.  Each problem carries its own tile
-// shape, chosen per problem (library heuristic or the autotuner).
+// stream -- a workgroup starts as soon as a CU has room.  A workgroup finds its
+// problem by a search over the prefix of tile counts and runs the same tile
+// body as the single-GEMM kernel.  Each problem carries its own tile shape,
+// chosen per problem (library heuristic or the autotuner).
 //
-// The counter lives in the caller's workspace and is cleared by a fill kernel
-// launched before the persistent kernel on the same stream, so the pair can be
-// captured into a HIP graph and replayed (no memset nodes).
+// Nothing in the workspace is written on the device, so a launch can be
+// captured into a HIP graph and replayed.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -25,114 +24,75 @@
 namespace mm {
 namespace grp {
 
-// Tile variants of the grouped kernel (all 256 lanes, 2 bf16 planes, BK 32).
-//   0: 128 x 128 (2 x 2 waves of 64 x 64)     1: 64 x 64 (2 x 2 waves of 32 x 32)
+// Tile variants of the grouped kernel (256 lanes, 2 bf16 planes).
+//   0: 128 x 128 x 16 (2 x 2 waves of 64 x 64)   1: 64 x 64 x 32 (2 x 2 of 32 x 32)
 constexpr int kVariants = 2;
 constexpr int kBM[kVariants] = {128, 64};
 constexpr int kBN[kVariants] = {128, 64};
-using G0 = bx3::Cfg<128, 128, 32, 64, 64, 2, 4>;
+using G0 = bx3::Cfg<128, 128, 16, 64, 64, 2, 4>;
 using G1 = bx3::Cfg<64, 64, 32, 32, 32, 2, 4>;
 constexpr int kLdsBytes = G0::LDS_BYTES > G1::LDS_BYTES ? G0::LDS_BYTES : G1::LDS_BYTES;
 
 template <int V, bool BETA>
 __device__ __forceinline__ void run_tile(const Desc &d, int m0, int n0, __bf16 *lds) {
   if constexpr (V == 0)
-    bx3::tile<128, 128, 32, 64, 64, 2, 4, BETA>(d.M, d.N, d.K, d.alpha, d.A, d.lda, d.B,
+    bx3::tile<128, 128, 16, 64, 64, 2, 4, BETA>(d.M, d.N, d.K, d.alpha, d.A, d.lda, d.B,
                                                      d.ldb, d.beta, d.C, d.ldc, m0, n0, lds);
   else
     bx3::tile<64, 64, 32, 32, 32, 2, 4, BETA>(d.M, d.N, d.K, d.alpha, d.A, d.lda, d.B, d.ldb,
                                                    d.beta, d.C, d.ldc, m0, n0, lds);
 }
 
-__device__ __forceinline__ int starts_at(bool in_lds, const int *s_starts, const int *starts,
-                                         int p) {
-  return in_lds ? s_starts[p] : starts[p];
+// Workgroups are dispatched round robin over the 8 XCDs.  Within each run of
+// kRun * 8 consecutive ids, an XCD gets kRun consecutive tiles: neighbouring
+// tiles of a problem -- which share A row panels and B column panels -- meet in
+// one L2, and every XCD sees the list from its long end to its short one (512
+// problems of 32 to 1024 per dimension: runs of 1 tile 167 us, 4 155, 16 152,
+// 64 160; 204 unaligned problems 96, 91, 91, 104).
+constexpr int kRun = 16;
+__device__ __forceinline__ int dealt_tile(int wg, int total) {
+  const int base = wg - wg % (8 * kRun);
+  if (base + 8 * kRun > total) return base + xcd_remap(wg - base, total - base);
+  const int in = wg - base;
+  return base + (in % 8) * kRun + in / 8;
 }
 
-__global__ __launch_bounds__(64) void clear_counter_kernel(unsigned *counter) {
-  if (threadIdx.x == 0) counter[0] = 0u;
-}
-
-// Tile prefixes of batches up to this size are searched in LDS.
-constexpr int kLdsStarts = 3072;
-
-__global__ __launch_bounds__(256, 2) void grouped_kernel(const Desc *__restrict__ descs,
-                                                         const int *__restrict__ starts, int count,
-                                                         int total_tiles, int static_tiles,
-                                                         unsigned *__restrict__ counter) {
+// Bound: HBM and the matrix cores' wait for it (a tile is 2 to 64 k-slabs, then
+// done).  Three workgroups per CU (16-deep slabs: 32 KB of LDS, 142 registers
+// per lane) overlap their start, loads and stores: 512 problems of
+// 32 to 1024 per dimension 165 -> 152 us against two persistent workgroups per CU
+// that took tiles from an atomic counter (cleared by a launch of its own); 204
+// unaligned problems 139 -> 90.
+__global__ __launch_bounds__(256, 3) void grouped_kernel(
+    const Desc *__restrict__ descs, const int *__restrict__ starts, int count, int first) {
   __shared__ __attribute__((aligned(16))) __bf16 lds[kLdsBytes / 2];
-  __shared__ int s_starts[kLdsStarts];
-  __shared__ int s_tile[2];
-  const bool in_lds = count < kLdsStarts;
-  if (in_lds)
-    for (int i = threadIdx.x; i <= count; i += 256) s_starts[i] = starts[i];
-  // Tiles [0, static_tiles) are dealt round-robin (tile t to slot t mod G):
-  // the list is sorted longest first, so each round hands every
-  // workgroup a tile of similar cost and needs no atomics.  The remaining
-  // tiles are dequeued from the counter (first come, first served), which
-  // evens out the tail; a whole grid's worth of simultaneous same-address
-  // atomics would otherwise serialise at the start of every launch.
-  // Workgroup ids are dispatched round robin over the 8 XCDs; the slot
-  // permutation hands each XCD a run of G/8 consecutive tiles per round, so
-  // neighbouring tiles of a problem -- which share A row panels and B column
-  // panels -- run on one XCD and meet in its L2 instead of being fetched from
-  // HBM once per XCD.
-  const int G = gridDim.x;
-  const int w = (int)blockIdx.x;
-  const int slot = G % 8 == 0 ? (w % 8) * (G / 8) + w / 8 : w;
-  if (threadIdx.x == 0)
-    s_tile[0] = slot < static_tiles ? slot : static_tiles + (int)atomicAdd(counter, 1u);
-  __syncthreads();
-  // Values read from LDS are per-lane to the compiler; the tile index is
-  // wave-uniform by construction, and saying so keeps everything derived
-  // from it (tile origin, buffer resources) in scalar registers -- a per-lane
-  // buffer resource turns every buffer load into a readfirstlane loop.
-  int t = __builtin_amdgcn_readfirstlane(s_tile[0]);
-  for (int it = 1; t < total_tiles; ++it) {
-    // Dequeue the next tile now: the atomic's round trip overlaps this tile's
-    // work, and its result is only read after the tile.
-    unsigned next = 0u;
-    if (threadIdx.x == 0)
-      next = (t + G < static_tiles || static_tiles >= total_tiles)
-                 ? (unsigned)(t + G)
-                 : (unsigned)static_tiles + atomicAdd(counter, 1u);
-    // owning problem: the last p with starts[p] <= t
-    int lo = 0, hi = count - 1;
-    if (in_lds) {
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (s_starts[mid] <= t) lo = mid;
-        else hi = mid - 1;
-      }
-    } else {
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (starts[mid] <= t) lo = mid;
-        else hi = mid - 1;
-      }
-    }
-    lo = __builtin_amdgcn_readfirstlane(lo);
-    const Desc d = descs[lo];
-    const int local = t - __builtin_amdgcn_readfirstlane(starts_at(in_lds, s_starts, starts, lo));
-    const int bm = d.variant == 0 ? 128 : 64, bn = bm;
-    // tiles of a problem in groups of 8 tile rows, as in the single-GEMM
-    // kernels: consecutive dequeues share A row panels and B column panels
-    int tm, tn;
-    tile_coords(local, (d.M + bm - 1) / bm, d.tiles_n, 8, tm, tn);
-    const int m0 = tm * bm, n0 = tn * bn;
-    const int sel = d.variant * 2 + (d.beta != 0.0f ? 1 : 0);
-    switch (sel) {
-      case 0: run_tile<0, false>(d, m0, n0, lds); break;
-      case 1: run_tile<0, true>(d, m0, n0, lds); break;
-      case 2: run_tile<1, false>(d, m0, n0, lds); break;
-      default: run_tile<1, true>(d, m0, n0, lds); break;
-    }
-    // One barrier per tile: publishes the next index (alternate slots, so no
-    // thread can still be reading the slot being written) and separates this
-    // tile's last LDS reads from the next tile's first LDS writes.
-    if (threadIdx.x == 0) s_tile[it & 1] = (int)next;
-    __syncthreads();
-    t = __builtin_amdgcn_readfirstlane(s_tile[it & 1]);
+  const int t = first + dealt_tile((int)blockIdx.x, (int)gridDim.x);
+  // owning problem: the last p with starts[p] <= t, a search by 64 lanes (two
+  // dependent loads for up to 4096 problems)
+  const int lane = threadIdx.x & 63;
+  int lo = 0, n = count;
+  while (n > 1) {
+    const int step = (n + 63) / 64, at = lane * step;
+    const bool le = at < n && starts[lo + (at < n ? at : 0)] <= t;
+    const int seg = __builtin_popcountll(__ballot(le)) - 1;
+    lo += seg * step;
+    n = min(step, n - seg * step);
+  }
+  lo = __builtin_amdgcn_readfirstlane(lo);
+  const Desc d = descs[lo];
+  const int local = t - starts[lo];
+  const int bm = d.variant == 0 ? 128 : 64, bn = bm;
+  // tiles of a problem in groups of 8 tile rows, as in the single-GEMM
+  // kernels: consecutive tiles share A row panels and B column panels
+  int tm, tn;
+  tile_coords(local, (d.M + bm - 1) / bm, d.tiles_n, 8, tm, tn);
+  const int m0 = tm * bm, n0 = tn * bn;
+  if (d.beta != 0.0f) {
+    if (d.variant == 0) run_tile<0, true>(d, m0, n0, lds);
+    else run_tile<1, true>(d, m0, n0, lds);
+  } else {
+    if (d.variant == 0) run_tile<0, false>(d, m0, n0, lds);
+    else run_tile<1, false>(d, m0, n0, lds);
   }
 }
 
@@ -194,22 +154,21 @@ gemm_status grouped_build(const gemm_problem *probs, int count, const int *varia
   return GEMM_STATUS_OK;
 }
 
-gemm_status grouped_enqueue(void *ws, int count, int total, int grid, hipStream_t s) {
-  uint8_t *base = static_cast<uint8_t *>(ws);
-  unsigned *counter = reinterpret_cast<unsigned *>(base);
+gemm_status grouped_enqueue(void *ws, int count, int total, hipStream_t s) {
+  if (total == 0) return GEMM_STATUS_OK;
+  const uint8_t *base = static_cast<const uint8_t *>(ws);
   const Desc *descs = reinterpret_cast<const Desc *>(base + 256);
   const int *starts = reinterpret_cast<const int *>(
       base + 256 + ((sizeof(Desc) * (size_t)count + 255) / 256) * 256);
-  hipLaunchKernelGGL(grp::clear_counter_kernel, dim3(1), dim3(64), 0, s, counter);
-  if (gemm_status st = check_launch("clear_counter_kernel")) return st;
-  if (total == 0) return GEMM_STATUS_OK;
-  // all but the last two rounds are dealt statically, and at least the first
-  // round (a batch of at most one round needs no atomics at all)
-  const int rounds = total / grid;
-  const int static_tiles = rounds > 2 ? (rounds - 2) * grid : std::min(total, grid);
-  hipLaunchKernelGGL(grp::grouped_kernel, dim3(grid), dim3(256), 0, s, descs, starts, count, total,
-                     static_tiles, counter);
-  return check_launch("grouped_kernel");
+  // (a launch holds less than 2^32 lanes)
+  constexpr int kMaxGrid = 1 << 23;
+  for (int first = 0; first < total; first += kMaxGrid) {
+    const dim3 grid((unsigned)std::min(kMaxGrid, total - first));
+    hipLaunchKernelGGL(grp::grouped_kernel, grid, dim3(256), 0, s, descs, starts, count, first);
+    if (gemm_status st = check_launch("grouped_kernel")) return st;
+    if (total - first <= kMaxGrid) break;
+  }
+  return GEMM_STATUS_OK;
 }
 
 gemm_status grouped_upload(void *ws, const std::vector<Desc> &descs, const std::vector<int> &starts,
@@ -240,11 +199,6 @@ gemm_status grouped_upload_pinned(void *ws, void *pinned, const std::vector<Desc
                                 hipMemcpyHostToDevice, s);
   if (e != hipSuccess) return hip_fail("grouped: descriptor upload", e);
   return GEMM_STATUS_OK;
-}
-
-int grouped_grid(int total) {
-  const int resident = num_cus() * 2;  // two 256-lane workgroups per CU
-  return std::max(1, std::min(total, resident));
 }
 
 }  // namespace mm

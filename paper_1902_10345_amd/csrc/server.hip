@@ -235,7 +235,7 @@ static void launch_step(gemm_server *s, StreamCtx &sc) {
       lib(scale_c(q.M, q.N, q.beta, q.C, q.ldc, sc.stream));
   }
   if (!status) lib(grouped_upload_pinned(sc.ws, sc.pinned, descs, starts, sc.stream));
-  if (!status) lib(grouped_enqueue(sc.ws, (int)probs.size(), total, grouped_grid(total), sc.stream));
+  if (!status) lib(grouped_enqueue(sc.ws, (int)probs.size(), total, sc.stream));
   if (!status) hip(hipEventRecord(sc.kernel_done, sc.stream), "server: record kernel event");
   for (size_t i = 0; !status && i < st->tickets.size(); ++i) {
     Request &r = s->reqs[st->tickets[i]];

@@ -174,11 +174,10 @@ gemm_status grouped_autotune(const gemm_problem *problems, int count, int path, 
     int total = 0;
     if ((st = grouped_build(problems, count, var.data(), descs, starts, total))) break;
     if ((st = grouped_upload(workspace, descs, starts, stream))) break;
-    const int grid = grouped_grid(total);
-    if ((st = grouped_enqueue(workspace, count, total, grid, stream))) break;  // warm-up
+    if ((st = grouped_enqueue(workspace, count, total, stream))) break;  // warm-up
     he = hipEventRecord(e0, stream);
     for (int r = 0; !st && he == hipSuccess && r < reps; ++r)
-      st = grouped_enqueue(workspace, count, total, grid, stream);
+      st = grouped_enqueue(workspace, count, total, stream);
     if (!st && he == hipSuccess) he = hipEventRecord(e1, stream);
     if (!st && he == hipSuccess) he = hipEventSynchronize(e1);
     float ms = 0.0f;

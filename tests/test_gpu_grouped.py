@@ -174,3 +174,32 @@ def test_large_batch_prefix_search_in_global_memory_and_mixed_schedule():
             got = d[7].cpu().numpy().astype(np.float64)
             # integer inputs in [-8, 8]: exact on both split planes
             assert np.array_equal(got, oracle.gemm(A, B, alpha=2.0, beta=-1.0, C0=C0)), (M, N, K, rep)
+
+
+@pytest.mark.parametrize("count", [1, 2, 63, 64, 65, 129, 4097])
+def test_problem_search_and_tile_order_at_their_edges(count):
+    """Counts around the 64 lanes of the problem search (and past its second
+    level), with problems that own no tile in between and tile totals that are
+    no multiple of the dealing's runs; integer inputs, so the results are exact."""
+    import torch
+    import paper_1902_10345_amd as mm
+    g = np.random.default_rng(count)
+    pool = torch.randint(-4, 5, (1 << 14,), device="cuda").float()
+    out = torch.full((count * 1024 + 300 * 300,), 7.0, device="cuda")
+    probs, at, want = [], 0, []
+    for p in range(count):
+        M, N, K = (int(v) for v in g.integers(0 if p % 5 == 4 else 1, 32, 3))
+        if p == count // 2:
+            M, N, K = 300, 257, 20
+        A, B = pool[:M * K].view(M, K), pool[100:100 + K * N].view(K, N)
+        C = out[at:at + M * N].view(M, N)
+        at += M * N
+        probs.append((M, N, K, A if M * K else pool, max(K, 1), B if K * N else pool, max(N, 1),
+                      C if M * N else out, max(N, 1), 1.0, 0.5))
+        want.append((A.cpu().double() @ B.cpu().double() + 3.5).reshape(-1))
+    arr = mm.problem_array(probs)
+    ws = torch.empty(mm.grouped_gemm_workspace_bytes(count), dtype=torch.uint8, device="cuda")
+    mm.grouped_gemm(arr, count, mm.PATH_3XBF16, None, ws, ws.numel())
+    got = out.cpu().double()
+    assert torch.equal(got[:at], torch.cat(want))
+    assert bool((got[at:] == 7.0).all())
