@@ -102,7 +102,7 @@ gemm_status gemm_f32_3xbf16(int64_t M, int64_t N, int64_t K, float alpha,
 /* Split-K form of gemm_f32_3xbf16, for shapes whose output tiles alone leave
  * compute units idle (few or thin tiles, deep K).  The reduction over k is cut
  * into `splits` chunks of whole 16-deep (32-deep for 6 products) slabs; each
- * (chunk, 128 x 128 output tile) pair is one workgroup that writes its partial
+ * (chunk, output tile) pair is one workgroup that writes its partial
  * product to the workspace, and a second kernel resolves the write conflict of
  * the chunks on C -- the write-conflict resolution of a reduction (Sec. 3.3,
  * write-conflict resolution memlets; App. A, the wcr attribute), here an

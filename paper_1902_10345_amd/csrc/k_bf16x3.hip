@@ -10,8 +10,9 @@ namespace bx3 {
 // ---- split-K ----------------------------------------------------------------
 // Workgroup (chunk c, output tile) multiplies K range [c*chunk, min(K, (c+1)*chunk))
 // of its tile (alpha 1, beta 0) into partial plane c of P (M x N, ld N).
-// Chunks are whole slabs, so the slab grid of every chunk ends on its own
-// boundary and only a chunk's first slab can be partial.
+// Chunks are whole units of 16 k (32 with six products), whatever the tile: the
+// slab grid of every chunk ends on its own boundary, only a chunk's first slab
+// can be partial, and every tile gives the same partial products.
 template <int BM, int BN, int BK, int WM, int WN, int NP, int NW>
 __global__ __launch_bounds__(64 * NW, 1) void gemm_bx3_splitk_kernel(
     int M, int N, int K, int chunk, const float *__restrict__ A, int64_t lda,
@@ -32,8 +33,9 @@ __global__ __launch_bounds__(64 * NW, 1) void gemm_bx3_splitk_kernel(
 
 // The write-conflict resolution of the chunks: C = alpha * (P_0 + P_1 + ...)
 // + beta * C, summed in chunk order (deterministic), the same epilogue
-// arithmetic as the single-pass kernel.  VEC: N, ldc multiples of 4 and C
-// 16-byte aligned.
+// arithmetic as the single-pass kernel.  Eight planes are read ahead of their
+// additions: with so few elements a chain of S dependent reads is the kernel's
+// time (57 x 1856 x 6046 in 23 chunks, with the 128 x 128 tile, 24.8 -> 21.9 us).  VEC: N, ldc multiples of 4 and C 16-byte aligned.
 template <bool VEC, bool BETA>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(int M, int N, int S,
                                                             const float *__restrict__ P,
@@ -44,9 +46,14 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(int M, int N, int S,
     const int64_t n4 = plane / 4;
     for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < n4; q += (int64_t)gridDim.x * 256) {
       float4 acc = reinterpret_cast<const float4 *>(P)[q];
-      for (int c = 1; c < S; ++c) {
-        const float4 v = reinterpret_cast<const float4 *>(P + c * plane)[q];
-        acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+      for (int c = 1; c < S; c += 8) {
+        float4 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          v[u] = reinterpret_cast<const float4 *>(P + (c + u < S ? c + u : S - 1) * plane)[q];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (c + u < S) { acc.x += v[u].x; acc.y += v[u].y; acc.z += v[u].z; acc.w += v[u].w; }
       }
       const int64_t e = 4 * q;
       const int64_t i = e / N, j = e - i * N;
@@ -62,7 +69,14 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(int M, int N, int S,
   } else {
     for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < plane; e += (int64_t)gridDim.x * 256) {
       float acc = P[e];
-      for (int c = 1; c < S; ++c) acc += P[c * plane + e];
+      for (int c = 1; c < S; c += 8) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = P[(c + u < S ? c + u : S - 1) * plane + e];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (c + u < S) acc += v[u];
+      }
       const int64_t i = e / N, j = e - i * N;
       float *cp = C + i * ldc + j;
       const float v = alpha * acc;
@@ -72,7 +86,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(int M, int N, int S,
 }
 
 template <int BM, int BN, int BK, int WM, int WN, int NP, int NW>
-gemm_status launch_splitk(const GemmArgs &g, int S, float *P, hipStream_t s) {
+gemm_status launch_splitk(const GemmArgs &g, int S, int unit, float *P, hipStream_t s) {
   const int tiles_m = (int)((g.M + BM - 1) / BM);
   const int tiles_n = (int)((g.N + BN - 1) / BN);
   const int64_t nwg = (int64_t)tiles_m * tiles_n * S;
@@ -82,7 +96,7 @@ gemm_status launch_splitk(const GemmArgs &g, int S, float *P, hipStream_t s) {
     set_error("gemm_f32_3xbf16_splitk: lda or ldb too large for 32-bit tile offsets");
     return GEMM_STATUS_UNSUPPORTED;
   }
-  const int chunk = (int)(((g.K + S - 1) / S + BK - 1) / BK * BK);
+  const int chunk = (int)(((g.K + S - 1) / S + unit - 1) / unit * unit);
   S = (int)((g.K + chunk - 1) / chunk);  // chunks that hold work (<= requested)
   const int64_t nwg_used = (int64_t)tiles_m * tiles_n * S;
   hipLaunchKernelGGL((gemm_bx3_splitk_kernel<BM, BN, BK, WM, WN, NP, NW>), dim3((unsigned)nwg_used),
@@ -468,8 +482,7 @@ gemm_status bx3_run(const GemmArgs &g, int cfg, hipStream_t s) {
   }
 }
 
-// Split-K uses the 128 x 128 tiles (16-deep slabs for three products,
-// 32-deep for six); a chunk is at least 256 deep.
+// Split counts for the 128 x 128 tiles; a chunk is at least 256 deep.
 int bx3_splitk_default(int64_t M, int64_t N, int64_t K) {
   const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128);
   int64_t s = (2 * (int64_t)num_cus() + tiles - 1) / tiles;
@@ -485,9 +498,23 @@ size_t bx3_splitk_ws_bytes(int64_t M, int64_t N, int splits) {
 
 gemm_status bx3_run_splitk(const GemmArgs &g, int n_products, int splits, void *ws, hipStream_t s) {
   float *P = static_cast<float *>(ws);
-  if (splits <= 1) return bx3_run(g, n_products == 6 ? 5 : 8, s);  // same tile, one pass
-  if (n_products == 6) return bx3::launch_splitk<128, 128, 32, 64, 64, 3, 4>(g, splits, P, s);
-  return bx3::launch_splitk<128, 128, 16, 64, 64, 2, 4>(g, splits, P, s);
+  if (splits <= 1) return bx3_run(g, n_products == 6 ? 15 : 8, s);  // same tile, one pass
+  const int unit = n_products == 6 ? 32 : 16;
+  // 64 x 64 tiles where half of a 128 x 128 tile would be padding (three / six
+  // products, us, 128 -> 64: 14 x 3595 x 1168 15.1 -> 12.5, 21 -> 14; 64 x 4096
+  // x 4096 22.5 -> 22, 29 -> 27) or operands are small and a chunk's chain of
+  // slabs is the time (512 x 512 x 2048 18.5 -> 15.8, 23 -> 18).  Larger operands
+  // stream from HBM, three products as fast as that goes: 128-wide tiles read
+  // longer pieces of B's rows (64 x 8192 x 8192 70 -> 65, 100 x 4096 x 4096 32 ->
+  // 25, 120 x 1100 x 7000 22 -> 20).
+  const int64_t bytes = 4 * (g.M + g.N) * g.K;
+  const bool small = (g.M <= 64 ? n_products == 6 || bytes <= 80000000 : bytes <= 24000000) &&
+                     bx3::offsets_fit<64, 64, 32, false, false>(g);
+  if (n_products == 6)
+    return small ? bx3::launch_splitk<64, 64, 32, 32, 32, 3, 4>(g, splits, unit, P, s)
+                 : bx3::launch_splitk<128, 128, 16, 64, 64, 3, 4>(g, splits, unit, P, s);
+  return small ? bx3::launch_splitk<64, 64, 32, 32, 32, 2, 4>(g, splits, unit, P, s)
+               : bx3::launch_splitk<128, 128, 16, 64, 64, 2, 4>(g, splits, unit, P, s);
 }
 
 gemm_status f32mfma_run(const GemmArgs &g, int which, hipStream_t s) {

@@ -127,3 +127,32 @@ def test_full_size_sampled_rows(M, N, K, seed):
     torch.cuda.synchronize()
     rows = sample_rows(M, 32, seed)
     check_split_result(oracle, A[rows], B, C0[rows], dC.cpu().numpy()[rows], 1.5, 0.5, 3)
+
+
+@pytest.mark.parametrize("M,N,K,splits", [(64, 70, 1100, 3), (1, 65, 777, 2), (33, 129, 2049, 7),
+                                          (65, 64, 530, 5), (130, 70, 3000, 12)])
+@pytest.mark.parametrize("n", [3, 6])
+def test_chunks_are_the_single_tile_products_bitwise(M, N, K, splits, n):
+    """Every chunk's partial product is the 128 x 128 tile's product of the
+    chunk's k range, whichever tile the entry point picks, and they are summed
+    in chunk order: one chunk at a time through gemm_run_config, added here."""
+    import torch
+    import paper_1902_10345_amd as mm
+    A, B = si.uniform((M, K), 3), si.uniform((K, N), 4)
+    C0 = np.zeros((M, N), np.float32)
+    _, C = _run(mm, A, B, C0, 1.0, 0.0, n, splits)
+    unit = 16 if n == 3 else 32
+    chunk = -(-(-(-K // splits)) // unit) * unit
+    name = "bx3_128x128x16_4w64x64_p3" if n == 3 else "bx3_128x128x32_4w64x64_p6"
+    cfg = [c for c in range(mm.gemm_num_configs(mm.PATH_3XBF16))
+           if mm.gemm_config_name(mm.PATH_3XBF16, c) == name][0]
+    want = None
+    for k0 in range(0, K, chunk):
+        a = torch.from_numpy(np.ascontiguousarray(A[:, k0:k0 + chunk])).cuda()
+        b = torch.from_numpy(np.ascontiguousarray(B[k0:k0 + chunk])).cuda()
+        c = torch.empty((M, N), device="cuda")
+        kc = a.shape[1]
+        mm.gemm_run_config(mm.PATH_3XBF16, cfg, M, N, kc, 1.0, a, kc, b, N, 0.0, c, N, n)
+        c = c.cpu().numpy()
+        want = c if want is None else want + c
+    assert np.array_equal(C, want)
