@@ -164,7 +164,7 @@ def _source_sha(files):
 
 def run_grouped(torch, mm, steps, warmup):
     """512 problems, M, N, K log-uniform in [32, 1024] (multiples of 16), one
-    persistent launch captured in a HIP graph, tile shapes from the autotuner."""
+    launch captured in a HIP graph, tile shapes from the autotuner."""
     import numpy as np
     import seeded_inputs as si
     probs = si.grouped_problems(512, seed=5)
@@ -194,7 +194,7 @@ def run_grouped(torch, mm, steps, warmup):
             "tflops": round(tf, 1), "frac_3product_ceiling": round(tf * 3 / PEAK_BF16_MFMA, 4),
             "hbm_gbs_of_min_bytes": round(gbs, 1), "frac_hbm": round(gbs / PEAK_HBM_GBS, 4),
             "tiles_128x128": n128, "tiles_64x64": len(dev) - n128,
-            "launch": "hipGraph replay (counter clear + persistent kernel)", **_stats(per)}
+            "launch": "hipGraph replay (one kernel)", **_stats(per)}
 
 
 def run_serving(torch, mm, seconds, rate=2000.0):

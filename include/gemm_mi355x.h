@@ -64,11 +64,12 @@ const char *gemm_version(void);
 /* ------------------------------------------------------------------------
  * Plain FP32 path: binary32 products and binary32 sums, no split.
  * C <- alpha*A*B + beta*C.  The library picks the tile configuration per
- * shape (gemm_default_config): where 256 x 256 or 128 x 128 tiles fill the
- * compute units, the binary32 matrix-core tile (v_mfma_f32_32x32x2_f32: each
- * product and sum in binary32); below that the small-product tiles (32 x 32
- * or 64 x 64 outputs per workgroup, the k range split over its eight waves
- * on the same matrix-core instruction, partial tiles summed in wave order).
+ * shape (gemm_default_config), by modelled time: a binary32 matrix-core tile
+ * (256 x 256 or 128 x 128 outputs, v_mfma_f32_32x32x2_f32: each product and
+ * sum in binary32), or where those would leave compute units idle the
+ * small-product tiles (32 x 32 or 64 x 64 outputs per workgroup, the k range
+ * split over its eight waves on the same matrix-core instruction, partial
+ * tiles summed in wave order).
  * The vector-ALU tiles (fused multiply-add accumulation in per-lane register
  * micro-tiles) remain configurations of the path: gemm_run_config selects
  * any of them.
@@ -197,7 +198,9 @@ gemm_status fp8_e4m3_encode(int64_t n, const float *x, uint8_t *codes, hipStream
  * the quantum-transport case study, Sec. 6.4 and table "Strided Matrix
  * Multiplication Performance", are double precision by the peak they are
  * measured against).  Layout, quick returns, status codes and determinism as
- * gemm_f32.  Arguments: 1 M, 2 N, 3 K, 4 alpha, 5 A, 6 lda, 7 B, 8 ldb,
+ * gemm_f32.  Products of few output tiles split the k range over a
+ * workgroup's waves (partial sums added in wave order).
+ * Arguments: 1 M, 2 N, 3 K, 4 alpha, 5 A, 6 lda, 7 B, 8 ldb,
  * 9 beta, 10 C, 11 ldc, 12 stream.
  * ---------------------------------------------------------------------- */
 gemm_status gemm_f64(int64_t M, int64_t N, int64_t K, double alpha,
@@ -226,7 +229,7 @@ gemm_status gemm_f64_strided_batched(int64_t M, int64_t N, int64_t K, double alp
  * (n_products 3 or 6, as gemm_f32_3xbf16).  Output matrices must not
  * overlap: stride_c >= (M-1)*ldc + N when batch > 1.  Layout and quick
  * returns as gemm_f32; up to 65535 problems per launch.  Problems run as 32 x
- * 32 sub-tiles of one wave each (no LDS staging; always for M, N <= 64) or on
+ * 32 sub-tiles of one wave each (no LDS staging) or on
  * the LDS-staged tiles, whichever is modelled faster, with results bitwise
  * those of the library's matrix-core tiles of the same arithmetic either way.
  * Arguments: 1 path,
@@ -314,10 +317,11 @@ gemm_status gemm_ex(int order, int trans_a, int trans_b, int64_t M, int64_t N, i
                     void *workspace, size_t ws_bytes, hipStream_t stream);
 
 /* ------------------------------------------------------------------------
- * Grouped GEMM: many independent problems of uneven sizes in ONE persistent
- * launch on the 3xBF16 path (3 products).  Workgroups dequeue output tiles
- * from an atomic counter, the batch-dequeue mechanism the paper uses for
- * consume scopes (Sec. 3.3), and each problem runs with its own tile shape.
+ * Grouped GEMM: many independent problems of uneven sizes in ONE launch
+ * on the 3xBF16 path (3 products).  One workgroup per output tile, longest
+ * tiles first, started by the dispatcher as compute units have room -- the
+ * dynamic work distribution of the paper's consume scopes (Sec. 3.3) -- and
+ * each problem runs with its own tile shape.
  *
  * gemm_problem: one C <- alpha*A*B + beta*C with the conventions above
  * (device pointers owned by the caller).  A problem with M == 0 or N == 0 is
@@ -328,17 +332,16 @@ gemm_status gemm_ex(int order, int trans_a, int trans_b, int64_t M, int64_t N, i
  * (grouped_autotune) returns such an array.
  *
  * workspace: device memory of at least grouped_gemm_workspace_bytes(count)
- * bytes, 256-byte aligned, owned by the caller; it holds the tile counter and
- * the descriptor table.  Calls that share a workspace must not overlap.
+ * bytes, 256-byte aligned, owned by the caller; it holds the descriptor
+ * table.  Calls that share a workspace must not overlap.
  *
  * grouped_gemm uploads the descriptor table with a stream synchronisation
  * (the host table is released on return) and then enqueues the launch.
  * Arguments: 1 problems (host array), 2 count, 3 path (GEMM_PATH_3XBF16),
  * 4 tile_variant (host array or NULL), 5 workspace, 6 ws_bytes, 7 stream.
  *
- * grouped_graph_create uploads the table once and captures the launch (a
- * counter-clearing kernel and the persistent kernel, no memset nodes) into
- * an executable HIP graph; grouped_graph_launch replays it on a stream with
+ * grouped_graph_create uploads the table once and captures the launch (no
+ * memset nodes) into an executable HIP graph; grouped_graph_launch replays it on a stream with
  * no host work; the workspace and the problems' buffers must stay valid until
  * grouped_graph_destroy.  Arguments of create: 1..6 as grouped_gemm,
  * 7 stream used for the upload, 8 graph (out).

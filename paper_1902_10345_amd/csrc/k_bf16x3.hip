@@ -293,7 +293,7 @@ __global__ __launch_bounds__(256) void small_batched_bx3_kernel(
     load(s);
     // all loads of a step in flight before its first product: left alone, the
     // compiler moves each load of B behind the previous binary32 product and
-    // waits for it (32^3 x 29 297 in binary32 97 -> 63 us)
+    // waits for it (32 x 32 x 64 x 6798 in binary32 37 -> 33 us)
     __builtin_amdgcn_sched_barrier(0);
     multiply();
   }
@@ -533,7 +533,7 @@ gemm_status f32mfma_run(const GemmArgs &g, int which, hipStream_t s) {
 // somewhat faster.  Against the tile chosen by the stacked problem's size alone
 // (256 x 256 tiles for any large batch), binary32 / three / six products, us:
 // 100 x 72 x 90 x 2000 232 -> 70, 97 -> 54, 137 -> 55; 144 x 8 x 9 x 5403 217
-// -> 20, 153 -> 18, 236 -> 18; 300^3 x 100 162 -> 67, 50 -> 48, 75 -> 55, 60 x 60 x 59 x 3000 58 -> 39 at beta = 0.5.
+// -> 20, 153 -> 18, 236 -> 18; 300^3 x 100 162 -> 67, 50 -> 48, 75 -> 55.
 namespace {
 struct BatchTile {
   int bm, bn, per_cu;          // output tile, tiles per compute unit at once

@@ -1212,7 +1212,8 @@ int fp8_default_config(int64_t M, int64_t N, int64_t K) {
   auto tiles = [&](int b) { return (double)((M + b - 1) / b) * (double)((N + b - 1) / b); };
   const double big = 6.0 + 1.75 * slabs * std::ceil(tiles(256) / cus);
   const double small = 3.0 + 0.0008 * slabs * tiles(64);
-  if (big < small) return 2;
+  // (a 256-row panel of codes stays below 2^31 bytes)
+  if (big < small && K <= ((int64_t)1 << 23) - 256) return 2;
   return tiles(64) <= 1.5 * cus ? 8 : 7;
 }
 

@@ -1,4 +1,4 @@
-// k_grouped.hip -- one persistent launch for a batch of independent GEMMs of
+// k_grouped.hip -- one launch for a batch of independent GEMMs of
 // uneven sizes on the 3xBF16 split-precision MFMA path.
 //
 // The batch is flattened into one list of output tiles (problem p owns tiles

@@ -4,7 +4,7 @@
 // FIFO.  A scheduler thread admits the head of the queue whenever a slot and
 // room in the caller's HBM arena are free (first-fit allocator), copies the
 // operands into the arena, and groups everything admitted since the last
-// launch into one step: one grouped persistent launch on the next idle stream.
+// launch into one step: one grouped launch on the next idle stream.
 // Steps on different streams overlap on the device, so requests that arrive
 // while others run are admitted and computed without waiting for them -- the
 // concurrency of independent connected components on separate streams that
