@@ -542,8 +542,8 @@ struct BatchTile {
 constexpr BatchTile kBatchTiles[kBatchedTiles] = {
     {32, 32, 20, {0.1, 0.2, 0.1}, {0.30, 0.14, 0.21}},    // kBatchedDirect
     {64, 64, 4, {1.5, 2.5, 5.0}, {1.25, 0.28, 0.42}},     // kBatched64
-    {128, 128, 2, {2.0, 6.0, 4.0}, {3.25, 0.55, 1.40}},   // kBatched128
-    {256, 256, 1, {8.0, 8.0, 8.0}, {12.5, 2.3, 5.0}},     // kBatched256
+    {128, 128, 2, {3.7, 6.0, 4.0}, {3.05, 0.55, 1.40}},   // kBatched128
+    {256, 256, 1, {8.0, 8.0, 8.0}, {12.3, 2.3, 5.0}},     // kBatched256
 };
 }  // namespace
 
