@@ -27,6 +27,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "f64_slabs.hpp"
 #include "kernels.hpp"
 
 namespace mm {
@@ -37,7 +38,6 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int BK = 16;       // k per slab
 constexpr int CH = BK / 2;   // 16-byte chunks (two binary64) per LDS row
 constexpr int kBufferFlags = 0x00020000;
 
@@ -123,7 +123,8 @@ __device__ __forceinline__ void tile(int M, int N, int K, double alpha, const do
 
   constexpr int DEPTH = KG;  // slabs of global loads in flight
   double ra_[DEPTH][G::A_ITEMS][2], rb_[DEPTH][G::B_ITEMS][2];
-  // FAST: the slab lies inside [0, K); otherwise k outside [0, K) read as 0.
+  // FAST: the slab lies inside [0, K), or begins before k = 0 and is not
+  // multiplied; otherwise k outside [0, K) read as 0.
   auto gload = [&](auto F, auto SET, int k0) {
     constexpr bool FAST = decltype(F)::value;
     auto &ra = ra_[decltype(SET)::value];
@@ -142,7 +143,10 @@ __device__ __forceinline__ void tile(int M, int N, int K, double alpha, const do
       }
     }
     if (FAST) {
-      const __amdgpu_buffer_rsrc_t rB = rsrc(B + (int64_t)k0 * ldb + n0, ((int64_t)(BK - 1) * ldb + colsB) * 8);
+      // (one group: k0 >= 0, its only partial slab is loaded masked)
+      const int kb = KG == 1 || k0 > 0 ? k0 : 0;
+      const __amdgpu_buffer_rsrc_t rB =
+          rsrc(B + (int64_t)kb * ldb + n0, slab_extent(KG == 1 ? kb : k0, ldb, colsB) * 8);
 #pragma unroll
       for (int i = 0; i < G::B_ITEMS; ++i)
 #pragma unroll
@@ -217,37 +221,26 @@ __device__ __forceinline__ void tile(int M, int N, int K, double alpha, const do
     }
   };
 
-  // The slab grid ends exactly at K: slab s covers [kbase + 16 s, +16) with
-  // kbase = K - KT*16 <= 0, so only slab 0 can be partial (loaded masked in
-  // the prologue).  Loads past the last slab are clamped to it (in bounds,
-  // never consumed), so both halves of the loop issue the same instructions.
-  // With KG = 2 the second group starts at slab ceil(KT / 2); an odd slab
-  // count leaves it one slab short, which it does not multiply.
+  // Slab 0 of the first group is loaded masked in the prologue.
   using Fast = std::true_type;
   using Masked = std::false_type;
   using R0 = std::integral_constant<int, 0>;
   using R1 = std::integral_constant<int, DEPTH - 1>;
-  const int KA = (K + BK - 1) / BK;
-  const int KT = (KA + KG - 1) / KG;            // slabs of the first group
-  const int own = KG > 1 && group ? KA - KT : KT;
-  const int kbase = K - KA * BK + group * KT * BK;
-  auto kslab = [&](int s) {
-    const int k = kbase + (s < own ? s : own - 1) * BK;
-    return KG > 1 && k < 0 ? 0 : k;  // (a group without slabs reads some slab unused)
-  };
-  if (group == 0) gload(Masked{}, R0{}, kbase);
-  else gload(Fast{}, R0{}, kslab(0));
-  if (DEPTH == 2) gload(Fast{}, R1{}, kslab(1));
+  const Slabs sl(K, KG, group);
+  const int KT = sl.turns, own = sl.own;
+  if (group == 0) gload(Masked{}, R0{}, sl.base);
+  else gload(Fast{}, R0{}, sl.k(0));
+  if (DEPTH == 2) gload(Fast{}, R1{}, sl.k(1));
   sstore(R0{}, 0);
   __syncthreads();
   int t = 0;
   for (; t + 2 <= KT; t += 2) {
-    gload(Fast{}, R0{}, kslab(t + DEPTH));
+    gload(Fast{}, R0{}, sl.k(t + DEPTH));
     __builtin_amdgcn_sched_barrier(0);
     mfma_stage(0);
     sstore(R1{}, 1);
     __syncthreads();
-    gload(Fast{}, R1{}, kslab(t + 1 + DEPTH));
+    gload(Fast{}, R1{}, sl.k(t + 1 + DEPTH));
     __builtin_amdgcn_sched_barrier(0);
     if (KG == 1 || t + 1 < own) mfma_stage(1);
     sstore(R0{}, 0);

@@ -393,3 +393,59 @@ def test_operands_beyond_the_small_tiles_offsets_take_the_panel_tiles():
     assert mm.lib.gemm_f32(3500, 3500, 3500, 1.0, F, 1 << 23, F, 3500, 0.0, F, 3500, None) == \
         mm.STATUS_UNSUPPORTED
     assert "32-bit tile offsets" in mm.gemm_last_error()
+
+
+_SLABS_MAIN = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "f64_slabs.hpp"
+using namespace mm::f64;
+// every full-slab load that the tiles issue: (K, groups, group, first row,
+// last row of B addressed or -1), then the slabs that each group multiplies
+int main() {
+  for (int K = 1; K <= 200; ++K)
+    for (int kg = 1; kg <= 2; ++kg)
+      for (int group = 0; group < kg; ++group) {
+        const Slabs s(K, kg, group);
+        std::printf("G %d %d %d %d %d %d\n", K, kg, group, s.turns, s.own, s.base);
+        // the first group's slab 0 goes through the masked load
+        for (int i = group == 0 ? 1 : 0; i < s.turns + 4; ++i) {
+          if (kg == 1 && s.turns < 2) break;  // no full-slab load is issued
+          const long long ldb = 1000, e = slab_extent(s.k(i), ldb, 7);
+          std::printf("L %d %d %d %d %lld\n", K, kg, group, s.k(i), e > 0 ? (e - 7) / ldb : -1);
+        }
+      }
+}
+"""
+
+
+def test_f64_slab_loads_stay_inside_the_matrix(tmp_path):
+    """Every unmasked slab load of the binary64 tiles addresses rows of B in
+    [0, K) or nothing at all, for one and two wave groups, also where a group
+    owns no slab; the groups' slabs cover every k once."""
+    import subprocess
+    src, exe = tmp_path / "slabs.cpp", tmp_path / "slabs"
+    src.write_text(_SLABS_MAIN)
+    csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                        "paper_1902_10345_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-I", csrc, str(src), "-o", str(exe)], check=True)
+    covered, empty = {}, 0
+    for line in subprocess.run([str(exe)], check=True, capture_output=True,
+                               text=True).stdout.splitlines():
+        kind, *v = line.split()
+        if kind == "L":
+            K, kg, group, k0, rows = map(int, v)
+            if rows < 0:
+                assert k0 < 0, line
+                empty += 1
+            else:
+                assert 0 <= k0 and k0 + rows < K, line
+        else:
+            K, kg, group, turns, own, base = map(int, v)
+            assert own <= turns and turns - own <= 1, line
+            for k in range(base, base + 16 * own):
+                if k >= 0:
+                    covered.setdefault((K, kg), []).append(k)
+    assert empty > 0
+    for (K, kg), ks in covered.items():
+        assert sorted(ks) == list(range(K)), (K, kg)
