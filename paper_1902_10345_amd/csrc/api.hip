@@ -51,18 +51,28 @@ int num_cus() {
   return n;
 }
 
+// Whether configuration cfg of a binary32 path can run g: two equal k ranges of
+// a two-group tile, transposed operands, and 32-bit offsets from the base of
+// what a workgroup addresses (a small tile the whole operand, the others a panel
+// where k is contiguous, else a slab of bk rows).
+static bool config_runs(int path, int cfg, const GemmArgs &g) {
+  const bool f32 = path == GEMM_PATH_F32;
+  const TileConfig &t = f32 ? f32_config(cfg) : bx3_config(cfg);
+  const bool small = f32 ? cfg == 7 || cfg == 8 : cfg >= 9 && cfg <= 12;
+  const bool two_groups = f32 ? cfg == 9 : cfg == 14 || cfg == 16 || cfg == 18;
+  if (two_groups && g.K % 2 != 0) return false;
+  if ((g.ta || g.tb) && (f32 ? cfg < 5 : cfg == 1 || cfg == 7 || cfg == 13)) return false;
+  const int64_t ra = small ? (g.ta ? g.K : g.M) : (g.ta ? t.bk : t.bm);
+  const int64_t rb = small ? (g.tb ? g.N : g.K) : (g.tb ? t.bn : t.bk);
+  const int64_t lim = ((int64_t)1 << 31) / 4;
+  return ra * g.lda + (g.ta ? g.M : g.K) < lim && rb * g.ldb + (g.tb ? g.K : g.N) < lim;
+}
+
 int addressable_config(int path, int n_products, const GemmArgs &g) {
   const bool f32 = path == GEMM_PATH_F32;
   const int cfg = f32 ? f32_default_config(g.M, g.N, g.K)
                       : bx3_default_config(g.M, g.N, g.K, n_products);
-  const TileConfig &t = f32 ? f32_config(cfg) : bx3_config(cfg);
-  const bool small = f32 ? cfg == 7 || cfg == 8 : cfg >= 9 && cfg <= 12;
-  // floats from the base of what a workgroup addresses: a small tile the whole
-  // operand, the others a panel (k contiguous) or a slab of bk rows
-  const int64_t ra = small ? (g.ta ? g.K : g.M) : (g.ta ? t.bk : t.bm);
-  const int64_t rb = small ? (g.tb ? g.N : g.K) : (g.tb ? t.bn : t.bk);
-  const int64_t lim = ((int64_t)1 << 31) / 4;
-  if (ra * g.lda + (g.ta ? g.M : g.K) < lim && rb * g.ldb + (g.tb ? g.K : g.N) < lim) return cfg;
+  if (config_runs(path, cfg, g)) return cfg;
   return f32 ? f32_count_config(g.M, g.N, g.K) : bx3_count_config(g.M, g.N, g.K, n_products);
 }
 
@@ -118,11 +128,12 @@ static int pick_config(int path, int n_products, int64_t M, int64_t N, int64_t K
   }
 }
 
-// The configuration that a call on either binary32 path runs: tuned, else the
-// default.
+// The configuration that a call on either binary32 path runs: the tuned one
+// where it can run the problem (an entry holds for a bucket of sizes, of either
+// parity of K and any row stride), else the default.
 static int run_config(int path, int n_products, const GemmArgs &g) {
   const int t = tuned_config(path, n_products, g.M, g.N, g.K);
-  return t >= 0 ? t : addressable_config(path, n_products, g);
+  return t >= 0 && config_runs(path, t, g) ? t : addressable_config(path, n_products, g);
 }
 
 gemm_status check_f32_args(const char *fn, int64_t M, int64_t N, int64_t K, float alpha,
@@ -429,11 +440,8 @@ gemm_status gemm_ex(int order, int trans_a, int trans_b, int64_t M, int64_t N, i
   }
   const bool trans = g.ta || g.tb;
   if (path == GEMM_PATH_F32) {
-    // transposed operands run on the FP32 matrix-core and small-product
-    // tiles only (a tuned choice may be a vector-ALU tile)
-    int cfg = run_config(GEMM_PATH_F32, 0, g);
-    if (trans && cfg < 5) cfg = addressable_config(GEMM_PATH_F32, 0, g);
-    return f32_run(g, cfg, stream);
+    // (transposed operands: the FP32 matrix-core and small-product tiles only)
+    return f32_run(g, run_config(GEMM_PATH_F32, 0, g), stream);
   }
   int cfg = trans ? addressable_config(GEMM_PATH_3XBF16, n_products, g)
                   : run_config(GEMM_PATH_3XBF16, n_products, g);

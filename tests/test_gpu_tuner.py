@@ -147,3 +147,36 @@ def test_grouped_autotune_variants_are_correct_and_become_the_default():
                                N, 0.0, solo, N, n_products=3)
             torch.cuda.synchronize()
             assert np.array_equal(solo.cpu().numpy(), C), (t, M, N, K)
+
+
+@pytest.mark.parametrize("trans", [False, True])
+@pytest.mark.parametrize("kind,n,config", [("f32", 0, "f32mfma_128x128x16_2x4w64x64_kg2"),
+                                           ("3xbf16", 3, "bx3_64x64x32_2x4w32x32_p3_kg2"),
+                                           ("3xbf16", 6, "bx3_128x128x16_2x4w64x64_p6_kg2"),
+                                           ("f32", 0, "f32_128x64x32_r8x4")])
+def test_tuned_entry_that_cannot_run_the_problem_is_passed_over(tmp_path, kind, n, config, trans):
+    """A tuned entry holds for a bucket of sizes: a two-group tile (two equal k
+    ranges) recorded there leaves an odd K to the default, and a vector-ALU tile
+    leaves transposed operands to it."""
+    import torch
+    import paper_1902_10345_amd as mm
+    path = _path(mm, kind)
+    f = tmp_path / "tuner.json"
+    f.write_text('{"arch": "gfx950", "grouped_small_cost": 1.6, "entries": [\n'
+                 '{"path": %d, "n_products": %d, "log2_m": 8, "log2_n": 8, "log2_k": 7, '
+                 '"config": "%s"}\n]}\n' % (path, n, config))
+    mm.gemm_tuner_load(str(f))
+    M, N, K = 200, 150, 101
+    A, B, C0 = si.uniform((M, K), 41), si.uniform((K, N), 42), si.uniform((M, N), 43)
+    dA = torch.from_numpy(np.ascontiguousarray(A.T) if trans else A).cuda()
+    dB, dC = torch.from_numpy(B).cuda(), torch.from_numpy(C0).cuda()
+    mm.gemm_ex(mm.ROW_MAJOR, mm.TRANS if trans else mm.NO_TRANS, mm.NO_TRANS, M, N, K, 1.5, dA,
+               M if trans else K, dB, N, 0.5, dC, N, path, max(n, 3))
+    torch.cuda.synchronize()
+    C = dC.cpu().numpy()
+    if kind == "3xbf16":
+        check_split_result(oracle, A, B, C0, C, 1.5, 0.5, n)
+    else:
+        ref = oracle.gemm(A, B, alpha=1.5, beta=0.5, C0=C0)
+        den = oracle.gemm_abs(A, B, alpha=1.5, beta=0.5, C0=C0)
+        assert oracle.norms(C, ref, den)[3] <= 2 * 1.01 * gamma(K)
