@@ -258,8 +258,12 @@ struct Stage {
 // Interior slabs (tile fully inside M x N and a whole BK slab of K) take an
 // unpredicated load path; edge slabs take a guarded path that reads zeros
 // outside the matrices.  The choice is uniform across the workgroup.
+// FOLD: every accumulator is added to a running total, and cleared, after each
+// quarter of the slabs (at least one slab), so that a rounding happens against
+// the sum of that quarter instead of all of the range before it.
 template <int BM, int BN, int BK, int WM, int WN, int NP, int NW, bool BETA,
-          bool TA = false, bool TB = false, int ST = 2, int SETS_ = 0, int KG = 1>
+          bool TA = false, bool TB = false, int ST = 2, int SETS_ = 0, int KG = 1,
+          bool FOLD = false>
 __device__ __forceinline__ void tile(int M, int N, int K, float alpha,
                                      const float *__restrict__ A, int64_t lda,
                                      const float *__restrict__ B, int64_t ldb, float beta,
@@ -360,6 +364,14 @@ __device__ __forceinline__ void tile(int M, int N, int K, float alpha,
     for (int j = 0; j < G::FN; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+  static_assert(!FOLD || G::SETS == 1, "folding is built into the one-register-set loop");
+  f32x16 total[FOLD ? G::FM : 1][FOLD ? G::FN : 1];
+  if constexpr (FOLD) {
+#pragma unroll
+    for (int i = 0; i < G::FM; ++i)
+#pragma unroll
+      for (int j = 0; j < G::FN; ++j) total[i][j] = acc[i][j];
+  }
 
   // Fragments of one 16-deep k-step: the lane's 8 consecutive k of its A row
   // (per block i and plane p) and of its B column (per block j and plane p).
@@ -495,17 +507,37 @@ __device__ __forceinline__ void tile(int M, int N, int K, float alpha,
   if constexpr (G::SETS == 1) {
     // One register set: slab t+1 is loaded at the top of the step that
     // multiplies slab t and written to the other stage at its end.
+    const int quarter = KT >= 4 ? KT / 4 : 1;
+    int left = quarter;
+    auto fold = [&]() {  // one more slab is in acc
+      if constexpr (FOLD) {
+        if (--left == 0) {
+          left = quarter;
+#pragma unroll
+          for (int i = 0; i < G::FM; ++i)
+#pragma unroll
+            for (int j = 0; j < G::FN; ++j)
+#pragma unroll
+              for (int e = 0; e < 16; ++e) {
+                total[i][j][e] += acc[i][j][e];
+                acc[i][j][e] = 0.0f;
+              }
+        }
+      }
+    };
     __syncthreads();
     for (; t + 2 <= KT; t += 2) {
       gload(S0{}, Fast{}, kslab(t + 1));
       __builtin_amdgcn_sched_barrier(0);
       mfma_stage(0);
       sstore(S0{}, 1);
+      fold();
       __syncthreads();
       gload(S0{}, Fast{}, kslab(t + 2));
       __builtin_amdgcn_sched_barrier(0);
       mfma_stage(1);
       sstore(S0{}, 0);
+      fold();
       __syncthreads();
     }
   } else if constexpr (ST == 3) {
@@ -842,6 +874,14 @@ __device__ __forceinline__ void tile(int M, int N, int K, float alpha,
     if (t < KT) {  // odd slab count: the last slab sits in stage 0
       mfma_stage(0);
     }
+  }
+  if constexpr (FOLD) {
+#pragma unroll
+    for (int i = 0; i < G::FM; ++i)
+#pragma unroll
+      for (int j = 0; j < G::FN; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][j][e] += total[i][j][e];
   }
 
   // ---- sum of the k-groups' partial tiles (group order) --------------------

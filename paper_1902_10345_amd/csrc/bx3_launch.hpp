@@ -25,7 +25,10 @@ __global__ __launch_bounds__(64 * NW, 1) void gemm_bx3_kernel(
 
 // The tile with its k range split between two groups of NW waves (one
 // workgroup of 2 * NW waves per tile): twice the waves per SIMD of the
-// one-group tile where its tiles come to about one per CU.
+// one-group tile where its tiles come to about one per CU.  The 64 x 64 tile
+// folds its sums by quarters of a group's range: it takes products that the
+// small tiles, whose sums run over an eighth of K, would take otherwise, and has
+// the registers for a second set of its 16 accumulators per lane.
 template <int BM, int BN, int BK, int WM, int WN, int NP, int NW, bool BETA, bool TA, bool TB>
 __global__ __launch_bounds__(128 * NW, 1) void gemm_bx3_kg_kernel(
     int M, int N, int K, float alpha, const float *__restrict__ A, int64_t lda,
@@ -36,7 +39,7 @@ __global__ __launch_bounds__(128 * NW, 1) void gemm_bx3_kg_kernel(
   const int wg = xcd_remap(blockIdx.x, gridDim.x);
   int tm, tn;
   tile_coords(wg, tiles_m, tiles_n, 8, tm, tn);
-  tile<BM, BN, BK, WM, WN, NP, NW, BETA, TA, TB, 2, 0, 2>(
+  tile<BM, BN, BK, WM, WN, NP, NW, BETA, TA, TB, 2, 0, 2, BM == 64>(
       M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, tm * BM, tn * BN, lds);
 }
 

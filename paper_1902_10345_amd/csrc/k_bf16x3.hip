@@ -427,16 +427,23 @@ int bx3_default_config(int64_t M, int64_t N, int64_t K, int n_products) {
   if (n_products == 3 && M % 128 == 0 && N % 128 == 0 && 2 * tiles(128, 128) <= cus &&
       tiles(64, 64) >= 2 * cus)
     return 6;
-  // Six products: where the machine is not full of 128 x 128 tiles the small
-  // tiles, whose sums run over an eighth of K, keep the rounding error where it
-  // was; longer sums only where they were as long (three products are bound by
-  // what the split drops, 3.8e-6 either way).
-  const bool short_sums = n_products == 6 && tiles(128, 128) < cus;
+  // No longer sums than the rules on tile counts gave, in parts of K: the small
+  // tiles' run over an eighth each, the two-group tiles' over a half, or (the 64
+  // x 64 one, whose sums are folded) an eighth; folding goes by whole slabs of
+  // 32, so that below K = 96 its parts would be the longer ones.  Operands of one
+  // sign show the difference, the split's own error averages out there: uniform
+  // in [0, 1), 1280 x 1045 x 3712, 1.13e-7 with the small tile, 1.09e-7 folded
+  // (65 us), 2.7e-7 over K / 2 unfolded (65 us), 5.3e-7 over K.
+  auto parts = [&](int cfg) {
+    if (cfg >= 9 && cfg <= 12) return 8;
+    if (cfg == 18) return K >= 96 ? 8 : 2;
+    return cfg == 14 || cfg == 16 ? 2 : 1;
+  };
+  const int at_least = parts(bx3_count_config(M, N, K, n_products));
   int best = n_products == 6 ? 12 : 10;
   double best_us = -1.0;
   auto consider = [&](const TileCost &t) {
-    const bool small = t.cfg >= 9 && t.cfg <= 12;
-    if (short_sums && !small) return;
+    if (parts(t.cfg) < at_least) return;
     if ((t.cfg == 14 || t.cfg == 16 || t.cfg == 18) && K % 2 != 0) return;  // two equal k ranges
     const double us = tile_time(t, M, N, K);
     if (best_us < 0.0 || us < best_us) { best = t.cfg; best_us = us; }

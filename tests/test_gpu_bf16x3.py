@@ -227,3 +227,31 @@ def test_full_size_sampled_rows(M, N, K, seed, n):
     C = dC.cpu().numpy()[rows]
     rel = _check(A[rows], B, C0[rows], C, 1.5, 0.5, n)
     print("n=%d %dx%dx%d sampled rel_fro %.3e" % (n, M, N, K, rel))
+
+
+@pytest.mark.parametrize("M,N,K", [(1280, 1045, 3712), (1552, 741, 4079), (1000, 1200, 96),
+                                   (1100, 1000, 130), (1200, 1200, 200), (1264, 874, 173)])
+def test_default_rounds_no_more_than_the_small_tile(M, N, K):
+    """Operands of one sign, where accumulation shows beside the split's own
+    error: the default tile's error is that of the small tile, whose sums run
+    over an eighth of K.  Rounding errors of a chain of n steps grow as n^1.5 and
+    the eight partial sums add the same few either way, so sums over K / 2 would
+    give twice the accumulation error; 10 % allow for a different order."""
+    import torch
+    import paper_1902_10345_amd as mm
+    g = torch.Generator(device="cuda")
+    g.manual_seed(K)
+    A = torch.rand(M, K, generator=g, device="cuda")
+    B = torch.rand(K, N, generator=g, device="cuda")
+    a0, b0 = A.bfloat16().float(), B.bfloat16().float()
+    a1, b1 = (A - a0).bfloat16().double(), (B - b0).bfloat16().double()
+    a0, b0 = a0.double(), b0.double()
+    exact = a0 @ b0 + a0 @ b1 + a1 @ b0
+    small = [mm.gemm_config_name(mm.PATH_3XBF16, c)
+             for c in range(mm.gemm_num_configs(mm.PATH_3XBF16))].index("bx3_small_64x64_8wk_p3")
+    err = []
+    for cfg in (-1, small):
+        C = torch.empty(M, N, device="cuda")
+        mm.gemm_run_config(mm.PATH_3XBF16, cfg, M, N, K, 1.0, A, K, B, N, 0.0, C, N, n_products=3)
+        err.append(float((C.double() - exact).norm() / exact.norm()))
+    assert err[0] <= 1.1 * err[1], err

@@ -449,3 +449,21 @@ def test_f64_slab_loads_stay_inside_the_matrix(tmp_path):
     assert empty > 0
     for (K, kg), ks in covered.items():
         assert sorted(ks) == list(range(K)), (K, kg)
+
+
+def test_default_sums_of_three_products_no_longer_than_an_eighth():
+    """Three products with few 64 x 64 tiles (at most half of the 128 x 128 tiles
+    that the compute units hold): the default's sums run over an eighth of K --
+    the small tiles, or the folded two-group tile from K = 96 on."""
+    import random
+
+    import paper_1902_10345_amd as mm
+    r, seen = random.Random(8), set()
+    while len(seen) < 2 or r.random() > 1e-3:
+        M, N, K = (int(2 ** r.uniform(0, 12.5)) for _ in range(3))
+        if 2 * -(-M // 128) * -(-N // 128) > 256 or -(-M // 64) * -(-N // 64) >= 512:
+            continue
+        name = mm.gemm_config_name(mm.PATH_3XBF16, mm.gemm_default_config(mm.PATH_3XBF16, M, N, K))
+        small = name in ("bx3_small_32x32_8wk_p3", "bx3_small_64x64_8wk_p3")
+        assert small or (name == "bx3_64x64x32_2x4w32x32_p3_kg2" and K >= 96), (M, N, K, name)
+        seen.add(small)
