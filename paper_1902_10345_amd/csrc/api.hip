@@ -52,15 +52,15 @@ int num_cus() {
 }
 
 // Whether configuration cfg of a binary32 path can run g: two equal k ranges of
-// a two-group tile, transposed operands, and 32-bit offsets from the base of
-// what a workgroup addresses (a small tile the whole operand, the others a panel
-// where k is contiguous, else a slab of bk rows).
+// a two-group tile, transposed operands, a launch's lanes, and 32-bit offsets from
+// the base of what a workgroup addresses (a small tile the whole operand, the
+// others a panel where k is contiguous, else a slab of bk rows).
 static bool config_runs(int path, int cfg, const GemmArgs &g) {
   const bool f32 = path == GEMM_PATH_F32;
   const TileConfig &t = f32 ? f32_config(cfg) : bx3_config(cfg);
   const bool small = f32 ? cfg == 7 || cfg == 8 : cfg >= 9 && cfg <= 12;
   const bool two_groups = f32 ? cfg == 9 : cfg == 14 || cfg == 16 || cfg == 18;
-  if (two_groups && g.K % 2 != 0) return false;
+  if ((two_groups && g.K % 2 != 0) || t.per_launch(g.M, g.N) < 1) return false;
   if ((g.ta || g.tb) && (f32 ? cfg < 5 : cfg == 1 || cfg == 7 || cfg == 13)) return false;
   const int64_t ra = small ? (g.ta ? g.K : g.M) : (g.ta ? t.bk : t.bm);
   const int64_t rb = small ? (g.tb ? g.N : g.K) : (g.tb ? t.bn : t.bk);

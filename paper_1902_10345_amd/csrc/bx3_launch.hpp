@@ -75,7 +75,7 @@ gemm_status launch_f32mfma(const GemmArgs &g, hipStream_t s) {
   const int tiles_m = (int)((g.M + BM - 1) / BM);
   const int tiles_n = (int)((g.N + BN - 1) / BN);
   const int64_t nwg = (int64_t)tiles_m * tiles_n;
-  if (nwg > 0x7fffffff) { set_error("gemm_f32: too many tiles"); return GEMM_STATUS_UNSUPPORTED; }
+  if (nwg > kMaxLanes / (64 * NW)) { set_error("gemm_f32: too many tiles"); return GEMM_STATUS_UNSUPPORTED; }
   if (!offsets_fit<BM, BN, BK, TA, TB>(g)) {
     set_error("gemm_f32: lda or ldb too large for 32-bit tile offsets");
     return GEMM_STATUS_UNSUPPORTED;
@@ -97,7 +97,7 @@ gemm_status launch(const GemmArgs &g, hipStream_t s) {
   const int tiles_m = (int)((g.M + BM - 1) / BM);
   const int tiles_n = (int)((g.N + BN - 1) / BN);
   const int64_t nwg = (int64_t)tiles_m * tiles_n;
-  if (nwg > 0x7fffffff) { set_error("gemm_f32_3xbf16: too many tiles"); return GEMM_STATUS_UNSUPPORTED; }
+  if (nwg > kMaxLanes / (64 * NW)) { set_error("gemm_f32_3xbf16: too many tiles"); return GEMM_STATUS_UNSUPPORTED; }
   if (!offsets_fit<BM, BN, BK, TA, TB>(g)) {
     set_error("gemm_f32_3xbf16: lda or ldb too large for 32-bit tile offsets");
     return GEMM_STATUS_UNSUPPORTED;
@@ -138,7 +138,7 @@ gemm_status launch_batched(const GemmArgs &g, int64_t sa, int64_t sb, int64_t sc
   const int tiles_m = (int)((g.M + BM - 1) / BM);
   const int tiles_n = (int)((g.N + BN - 1) / BN);
   const int64_t nwg = (int64_t)tiles_m * tiles_n * batch;
-  if (nwg > 0x7fffffff) {
+  if (nwg > kMaxLanes / (64 * NW)) {
     set_error("gemm_strided_batched: too many tiles or problems for one launch");
     return GEMM_STATUS_UNSUPPORTED;
   }
@@ -168,7 +168,7 @@ gemm_status launch_kg(const GemmArgs &g, hipStream_t s) {
   const int tiles_m = (int)((g.M + BM - 1) / BM);
   const int tiles_n = (int)((g.N + BN - 1) / BN);
   const int64_t nwg = (int64_t)tiles_m * tiles_n;
-  if (nwg > 0x7fffffff) { set_error("gemm_f32_3xbf16: too many tiles"); return GEMM_STATUS_UNSUPPORTED; }
+  if (nwg > kMaxLanes / (128 * NW)) { set_error("gemm_f32_3xbf16: too many tiles"); return GEMM_STATUS_UNSUPPORTED; }
   if (!offsets_fit<BM, BN, BK, TA, TB>(g)) {
     set_error("gemm_f32_3xbf16: lda or ldb too large for 32-bit tile offsets");
     return GEMM_STATUS_UNSUPPORTED;

@@ -25,6 +25,10 @@ gemm_status bad_arg(int index, const char *fn, const char *why);
 // Number of compute units of the current device (cached per device).
 int num_cus();
 
+// One dimension of a launch holds less than 2^32 lanes (whole workgroups of up
+// to 1024).
+constexpr int64_t kMaxLanes = ((int64_t)1 << 32) - 1024;
+
 // ------------------------------------------------------- device helpers --
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));

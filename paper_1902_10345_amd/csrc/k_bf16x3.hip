@@ -90,7 +90,7 @@ gemm_status launch_splitk(const GemmArgs &g, int S, int unit, float *P, hipStrea
   const int tiles_m = (int)((g.M + BM - 1) / BM);
   const int tiles_n = (int)((g.N + BN - 1) / BN);
   const int64_t nwg = (int64_t)tiles_m * tiles_n * S;
-  if (nwg > 0x7fffffff) { set_error("gemm_f32_3xbf16_splitk: too many workgroups"); return GEMM_STATUS_UNSUPPORTED; }
+  if (nwg > kMaxLanes / (64 * NW)) { set_error("gemm_f32_3xbf16_splitk: too many workgroups"); return GEMM_STATUS_UNSUPPORTED; }
   if (((int64_t)BM * g.lda + g.K) * 4 >= (int64_t)1 << 31 ||
       ((int64_t)BK * g.ldb + g.N) * 4 >= ((int64_t)1 << 31)) {
     set_error("gemm_f32_3xbf16_splitk: lda or ldb too large for 32-bit tile offsets");
@@ -342,7 +342,7 @@ gemm_status launch_small_batched(const GemmArgs &g, int64_t sa, int64_t sb, int6
                                  int batch, hipStream_t s) {
   const int64_t tiles_m = (g.M + 31) / 32, tiles_n = (g.N + 31) / 32;
   const int64_t units = tiles_m * tiles_n * batch;
-  if (units > 0x7ffffff0) {
+  if (units > kMaxLanes / 64) {
     set_error("gemm_strided_batched: too many tiles for one launch");
     return GEMM_STATUS_UNSUPPORTED;
   }
@@ -369,35 +369,35 @@ struct Bx3Config {
   int np;
 };
 static const Bx3Config kBx3Configs[] = {
-    {{256, 256, 16, "bx3_256x256x16_8w128x64_p3"}, 2},
-    {{128, 128, 32, "bx3_128x128x32_4w64x64_p3"}, 2},
-    {{256, 128, 32, "bx3_256x128x32_8w64x64_p3"}, 2},
-    {{256, 256, 32, "bx3_256x256x32_8w128x64_p3"}, 2},
-    {{256, 256, 16, "bx3_256x256x16_8w128x64_p6"}, 3},
-    {{128, 128, 32, "bx3_128x128x32_4w64x64_p6"}, 3},
-    {{64, 64, 32, "bx3_64x64x32_4w32x32_p3"}, 2},
-    {{256, 256, 16, "bx3_256x256x16_4w128x128_p3"}, 2},
-    {{128, 128, 16, "bx3_128x128x16_4w64x64_p3"}, 2},
+    {{256, 256, 16, "bx3_256x256x16_8w128x64_p3", 512}, 2},
+    {{128, 128, 32, "bx3_128x128x32_4w64x64_p3", 256}, 2},
+    {{256, 128, 32, "bx3_256x128x32_8w64x64_p3", 512}, 2},
+    {{256, 256, 32, "bx3_256x256x32_8w128x64_p3", 512}, 2},
+    {{256, 256, 16, "bx3_256x256x16_8w128x64_p6", 512}, 3},
+    {{128, 128, 32, "bx3_128x128x32_4w64x64_p6", 256}, 3},
+    {{64, 64, 32, "bx3_64x64x32_4w32x32_p3", 256}, 2},
+    {{256, 256, 16, "bx3_256x256x16_4w128x128_p3", 256}, 2},
+    {{128, 128, 16, "bx3_128x128x16_4w64x64_p3", 256}, 2},
     // small products: one tile per workgroup of 8 waves, its k range split
     // over the waves (fragments straight from global memory, ordered sum
     // through LDS)
-    {{32, 32, 16, "bx3_small_32x32_8wk_p3"}, 2},
-    {{64, 64, 16, "bx3_small_64x64_8wk_p3"}, 2},
-    {{32, 32, 16, "bx3_small_32x32_8wk_p6"}, 3},
-    {{64, 64, 16, "bx3_small_64x64_8wk_p6"}, 3},
+    {{32, 32, 16, "bx3_small_32x32_8wk_p3", 512}, 2},
+    {{64, 64, 16, "bx3_small_64x64_8wk_p3", 512}, 2},
+    {{32, 32, 16, "bx3_small_32x32_8wk_p6", 512}, 3},
+    {{64, 64, 16, "bx3_small_64x64_8wk_p6", 512}, 3},
     // the 256 x 256 x 16 tile with a ring of three LDS stages: the first
     // product's fragments of the next slab are read before the barrier
-    {{256, 256, 16, "bx3_256x256x16_8w128x64_p3_ring3"}, 2},
+    {{256, 256, 16, "bx3_256x256x16_8w128x64_p3_ring3", 512}, 2},
     // 128 x 128 x 16 tiles, the k range split between two groups of four
     // waves (partial tiles summed through LDS in group order)
-    {{128, 128, 16, "bx3_128x128x16_2x4w64x64_p3_kg2"}, 2},
+    {{128, 128, 16, "bx3_128x128x16_2x4w64x64_p3_kg2", 512}, 2},
     // six products: 16-deep slabs (32-deep ones leave one workgroup per CU),
     // the two-group tile, and 256 x 128 tiles
-    {{128, 128, 16, "bx3_128x128x16_4w64x64_p6"}, 3},
-    {{128, 128, 16, "bx3_128x128x16_2x4w64x64_p6_kg2"}, 3},
-    {{256, 128, 32, "bx3_256x128x32_8w64x64_p6"}, 3},
+    {{128, 128, 16, "bx3_128x128x16_4w64x64_p6", 256}, 3},
+    {{128, 128, 16, "bx3_128x128x16_2x4w64x64_p6_kg2", 512}, 3},
+    {{256, 128, 32, "bx3_256x128x32_8w64x64_p6", 512}, 3},
     // 64 x 64 tiles, the k range split between two groups of four waves
-    {{64, 64, 32, "bx3_64x64x32_2x4w32x32_p3_kg2"}, 2},
+    {{64, 64, 32, "bx3_64x64x32_2x4w32x32_p3_kg2", 512}, 2},
 };
 
 int bx3_num_configs() { return (int)(sizeof(kBx3Configs) / sizeof(kBx3Configs[0])); }
@@ -443,7 +443,7 @@ int bx3_default_config(int64_t M, int64_t N, int64_t K, int n_products) {
   int best = n_products == 6 ? 12 : 10;
   double best_us = -1.0;
   auto consider = [&](const TileCost &t) {
-    if (parts(t.cfg) < at_least) return;
+    if (parts(t.cfg) < at_least || kBx3Configs[t.cfg].t.per_launch(M, N) < 1) return;
     if ((t.cfg == 14 || t.cfg == 16 || t.cfg == 18) && K % 2 != 0) return;  // two equal k ranges
     const double us = tile_time(t, M, N, K);
     if (best_us < 0.0 || us < best_us) { best = t.cfg; best_us = us; }
@@ -543,14 +543,15 @@ gemm_status f32mfma_run(const GemmArgs &g, int which, hipStream_t s) {
 // -> 20, 153 -> 18, 236 -> 18; 300^3 x 100 162 -> 67, 50 -> 48, 75 -> 55.
 namespace {
 struct BatchTile {
-  int bm, bn, per_cu;          // output tile, tiles per compute unit at once
+  TileConfig t;                // output tile
+  int per_cu;                  // tiles per compute unit at once
   double fixed[3], step[3];    // ns: binary32, three products, six products
 };
 constexpr BatchTile kBatchTiles[kBatchedTiles] = {
-    {32, 32, 20, {0.1, 0.2, 0.1}, {0.30, 0.14, 0.21}},    // kBatchedDirect
-    {64, 64, 4, {1.5, 2.5, 5.0}, {1.25, 0.28, 0.42}},     // kBatched64
-    {128, 128, 2, {3.7, 6.0, 4.0}, {3.05, 0.55, 1.40}},   // kBatched128
-    {256, 256, 1, {8.0, 8.0, 8.0}, {12.3, 2.3, 5.0}},     // kBatched256
+    {{32, 32, 16, "direct", 64}, 20, {0.1, 0.2, 0.1}, {0.30, 0.14, 0.21}},    // kBatchedDirect
+    {{64, 64, 32, "lds64", 256}, 4, {1.5, 2.5, 5.0}, {1.25, 0.28, 0.42}},     // kBatched64
+    {{128, 128, 16, "lds128", 256}, 2, {3.7, 6.0, 4.0}, {3.05, 0.55, 1.40}},   // kBatched128
+    {{256, 256, 16, "lds256", 512}, 1, {8.0, 8.0, 8.0}, {12.3, 2.3, 5.0}},     // kBatched256
 };
 }  // namespace
 
@@ -560,7 +561,7 @@ int batched_config(int path, int n_products, int64_t M, int64_t N, int64_t K, in
   double best_cost = 0.0;
   for (int c = 0; c < kBatchedTiles; ++c) {
     const BatchTile &t = kBatchTiles[c];
-    const double tiles = (double)((M + t.bm - 1) / t.bm) * (double)((N + t.bn - 1) / t.bn) *
+    const double tiles = (double)((M + t.t.bm - 1) / t.t.bm) * (double)((N + t.t.bn - 1) / t.t.bn) *
                          (double)batch;
     const double slots = (double)num_cus() * t.per_cu;
     const double r = tiles / slots;
@@ -574,22 +575,39 @@ int batched_config(int path, int n_products, int64_t M, int64_t N, int64_t K, in
 template <int NP>
 static gemm_status batched_tile(int cfg, const GemmArgs &g, int64_t sa, int64_t sb, int64_t sc,
                                 int batch, hipStream_t s) {
-  // operands that 32-bit offsets of the chosen tile cannot reach take the
-  // 64 x 64 tile, whose panels are the smallest
-  if (cfg == kBatchedDirect && bx3::small_batched_fits(g))
-    return bx3::launch_small_batched<NP>(g, sa, sb, sc, batch, s);
-  if (cfg == kBatched256 && bx3::offsets_fit<256, 256, 32, false, false>(g))
-    return bx3::launch_batched<256, 256, 16, 128, 64, NP, 8>(g, sa, sb, sc, batch, s);
-  if (cfg == kBatched128 && bx3::offsets_fit<128, 128, 32, false, false>(g))
-    return bx3::launch_batched<128, 128, 16, 64, 64, NP, 4>(g, sa, sb, sc, batch, s);
-  return bx3::launch_batched<64, 64, 32, 32, 32, NP, 4>(g, sa, sb, sc, batch, s);
+  switch (cfg) {
+    case kBatchedDirect: return bx3::launch_small_batched<NP>(g, sa, sb, sc, batch, s);
+    case kBatched128: return bx3::launch_batched<128, 128, 16, 64, 64, NP, 4>(g, sa, sb, sc, batch, s);
+    case kBatched256: return bx3::launch_batched<256, 256, 16, 128, 64, NP, 8>(g, sa, sb, sc, batch, s);
+    default: return bx3::launch_batched<64, 64, 32, 32, 32, NP, 4>(g, sa, sb, sc, batch, s);
+  }
 }
 
 gemm_status batched_run(int path, int cfg, const GemmArgs &g, int n_products, int64_t sa,
                         int64_t sb, int64_t sc, int batch, hipStream_t s) {
-  if (path == GEMM_PATH_F32) return batched_tile<1>(cfg, g, sa, sb, sc, batch, s);
-  return n_products == 6 ? batched_tile<3>(cfg, g, sa, sb, sc, batch, s)
-                         : batched_tile<2>(cfg, g, sa, sb, sc, batch, s);
+  // operands that 32-bit offsets of the chosen tile cannot reach take the
+  // 64 x 64 tile, whose panels are the smallest, and problems with more 64 x 64
+  // tiles than a launch has room for the 256 x 256 one
+  const bool fits256 = bx3::offsets_fit<256, 256, 32, false, false>(g);
+  if ((cfg == kBatchedDirect && !bx3::small_batched_fits(g)) ||
+      (cfg == kBatched128 && !bx3::offsets_fit<128, 128, 32, false, false>(g)) ||
+      (cfg == kBatched256 && !fits256))
+    cfg = kBatched64;
+  if (kBatchTiles[cfg].t.per_launch(g.M, g.N) < 1 && fits256) cfg = kBatched256;
+  // as many problems to a launch as its lanes allow
+  const int64_t most = std::max<int64_t>(1, kBatchTiles[cfg].t.per_launch(g.M, g.N));
+  for (int64_t b = 0; b < batch; b += most) {
+    GemmArgs part = g;
+    part.A += b * sa;
+    part.B += b * sb;
+    part.C += b * sc;
+    const int n = (int)std::min<int64_t>(most, batch - b);
+    const gemm_status st = path == GEMM_PATH_F32 ? batched_tile<1>(cfg, part, sa, sb, sc, n, s)
+                           : n_products == 6     ? batched_tile<3>(cfg, part, sa, sb, sc, n, s)
+                                                 : batched_tile<2>(cfg, part, sa, sb, sc, n, s);
+    if (st) return st;
+  }
+  return GEMM_STATUS_OK;
 }
 
 gemm_status bx3_split(int64_t n, const float *x, uint16_t *p0, uint16_t *p1, uint16_t *p2,

@@ -222,7 +222,7 @@ gemm_status launch(const GemmArgs &g, hipStream_t s) {
   const int tiles_m = (int)((g.M + BM - 1) / BM);
   const int tiles_n = (int)((g.N + BN - 1) / BN);
   const int64_t nwg = (int64_t)tiles_m * tiles_n;
-  if (nwg > 0x7fffffff) { set_error("gemm_f32: too many tiles"); return GEMM_STATUS_UNSUPPORTED; }
+  if (nwg > kMaxLanes / 256) { set_error("gemm_f32: too many tiles"); return GEMM_STATUS_UNSUPPORTED; }
   if (((int64_t)BM * g.lda + g.K) * 4 >= ((int64_t)1 << 31) ||
       ((int64_t)BK * g.ldb + BN) * 4 >= ((int64_t)1 << 31)) {
     set_error("gemm_f32: leading dimension too large for 32-bit tile offsets");
@@ -247,22 +247,22 @@ gemm_status launch(const GemmArgs &g, hipStream_t s) {
 
 // Tile configurations of the FP32 path (index = config id).
 static const TileConfig kF32Configs[] = {
-    {128, 128, 32, "f32_128x128x32_r8x8"},
-    {64, 64, 32, "f32_64x64x32_r4x4"},
-    {128, 64, 32, "f32_128x64x32_r8x4"},
-    {128, 128, 32, "f32_128x128x32_r8x8_u2"},
-    {128, 64, 32, "f32_128x64x32_r8x4_u2"},
+    {128, 128, 32, "f32_128x128x32_r8x8", 256},
+    {64, 64, 32, "f32_64x64x32_r4x4", 256},
+    {128, 64, 32, "f32_128x64x32_r8x4", 256},
+    {128, 128, 32, "f32_128x128x32_r8x8_u2", 256},
+    {128, 64, 32, "f32_128x64x32_r8x4_u2", 256},
     // binary32 products on the FP32 matrix cores (same arithmetic; the tile
     // body of the split-precision path in its FP32 mode)
-    {256, 256, 16, "f32mfma_256x256x16_8w128x64"},
-    {128, 128, 16, "f32mfma_128x128x16_4w64x64"},
+    {256, 256, 16, "f32mfma_256x256x16_8w128x64", 512},
+    {128, 128, 16, "f32mfma_128x128x16_4w64x64", 256},
     // small products: one tile per workgroup of 8 waves, its k range split
     // over the waves (binary32 matrix cores, ordered sum through LDS)
-    {32, 32, 8, "f32_small_32x32_8wk"},
-    {64, 64, 8, "f32_small_64x64_8wk"},
+    {32, 32, 8, "f32_small_32x32_8wk", 512},
+    {64, 64, 8, "f32_small_64x64_8wk", 512},
     // the FP32 matrix-core 128 x 128 tile with its k range split between two
     // groups of four waves (partial tiles summed through LDS in group order)
-    {128, 128, 16, "f32mfma_128x128x16_2x4w64x64_kg2"},
+    {128, 128, 16, "f32mfma_128x128x16_2x4w64x64_kg2", 512},
 };
 
 int f32_num_configs() { return (int)(sizeof(kF32Configs) / sizeof(kF32Configs[0])); }
@@ -290,6 +290,7 @@ int f32_default_config(int64_t M, int64_t N, int64_t K) {
   double best_us = -1.0;
   for (const TileCost &t : kCosts) {
     if ((t.cfg == 5 || t.cfg == 6) ? !whole_k : t.cfg == 9 && !half_k) continue;
+    if (kF32Configs[t.cfg].per_launch(M, N) < 1) continue;
     const double us = tile_time(t, M, N, K);
     if (best_us < 0.0 || us < best_us) { best = t.cfg; best_us = us; }
   }

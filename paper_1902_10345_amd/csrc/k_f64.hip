@@ -325,7 +325,7 @@ gemm_status launch(const GemmArgsF64 &g, hipStream_t s) {
   const int tiles_m = (int)((g.M + BM - 1) / BM);
   const int tiles_n = (int)((g.N + BN - 1) / BN);
   const int64_t nwg = (int64_t)tiles_m * tiles_n * g.batch;
-  if (nwg > 0x7fffffff) {
+  if (nwg > kMaxLanes / (KG * G::NT)) {
     set_error("gemm_f64: too many tiles or problems for one launch");
     return GEMM_STATUS_UNSUPPORTED;
   }
@@ -486,7 +486,7 @@ template <int F>
 gemm_status launch_small(const GemmArgsF64 &g, hipStream_t s) {
   const int64_t tiles_m = (g.M + 16 * F - 1) / (16 * F), tiles_n = (g.N + 16 * F - 1) / (16 * F);
   const int64_t units = tiles_m * tiles_n * g.batch;
-  if (units > 0x7ffffff0) { set_error("gemm_f64: batch too large"); return GEMM_STATUS_UNSUPPORTED; }
+  if (units > kMaxLanes / 64) { set_error("gemm_f64: batch too large"); return GEMM_STATUS_UNSUPPORTED; }
 #define MM_LAUNCH(BT)                                                                               \
   hipLaunchKernelGGL((small_batched_kernel<F, BT>), dim3((unsigned)((units + 3) / 4)),        \
                      dim3(256), 0, s, (int)g.M, (int)g.N, (int)g.K, g.alpha, g.A, g.lda, g.sa, g.B, \
@@ -646,7 +646,7 @@ template <int F>
 gemm_status launch_split(const GemmArgsF64 &g, hipStream_t s) {
   const int64_t tiles_m = (g.M + 16 * F - 1) / (16 * F), tiles_n = (g.N + 16 * F - 1) / (16 * F);
   const int64_t units = tiles_m * tiles_n * g.batch;
-  if (units > 0x7ffffff0) { set_error("gemm_f64: batch too large"); return GEMM_STATUS_UNSUPPORTED; }
+  if (units > kMaxLanes / (64 * KW)) { set_error("gemm_f64: batch too large"); return GEMM_STATUS_UNSUPPORTED; }
 #define MM_LAUNCH(BT)                                                                                \
   hipLaunchKernelGGL((split_kernel<F, BT>), dim3((unsigned)units), dim3(64 * KW), 0, s,        \
                      (int)g.M, (int)g.N, (int)g.K, g.alpha, g.A, g.lda, g.sa, g.B, g.ldb, g.sb,      \
@@ -677,18 +677,19 @@ struct F64Config {
   TileConfig t;
 };
 static const F64Config kF64Configs[] = {
-    {{128, 128, 16, "f64_128x128x16_4w64x64"}},
-    {{256, 128, 16, "f64_256x128x16_8w64x64"}},
-    {{64, 64, 16, "f64_64x64x16_4w32x32"}},
-    // one wave per problem, operands straight into MFMA fragments (M, N <= 16 / 32 / 64)
-    {{16, 16, 16, "f64_small_16"}},
-    {{32, 32, 16, "f64_small_32"}},
-    {{64, 64, 16, "f64_small_64"}},
+    {{128, 128, 16, "f64_128x128x16_4w64x64", 256}},
+    {{256, 128, 16, "f64_256x128x16_8w64x64", 512}},
+    {{64, 64, 16, "f64_64x64x16_4w32x32", 256}},
+    // one wave per output tile, operands straight into MFMA fragments (as a
+    // configuration: problems of one tile, M, N <= 16 / 32 / 64)
+    {{16, 16, 16, "f64_small_16", 64}},
+    {{32, 32, 16, "f64_small_32", 64}},
+    {{64, 64, 16, "f64_small_64", 64}},
     // one tile per workgroup of 8 waves, its k range split over the waves
-    {{16, 16, 16, "f64_16x16x16_8wk"}},
-    {{32, 32, 16, "f64_32x32x16_8wk"}},
+    {{16, 16, 16, "f64_16x16x16_8wk", 512}},
+    {{32, 32, 16, "f64_32x32x16_8wk", 512}},
     // 64 x 64 tiles, the k range split between two groups of four waves
-    {{64, 64, 16, "f64_64x64x16_2x4w32x32_kg2"}},
+    {{64, 64, 16, "f64_64x64x16_2x4w32x32_kg2", 512}},
 };
 
 int f64_num_configs() { return (int)(sizeof(kF64Configs) / sizeof(kF64Configs[0])); }
@@ -735,6 +736,7 @@ static int f64_batch_config(int64_t M, int64_t N, int64_t K, int64_t batch) {
     // three waves of an LDS tile idle in problems up to 32 x 32 (32 x 32 x 512
     // x 300 43 us, 32 with sub-tiles)
     if (lds ? M <= 32 && N <= 32 : M > 256 || N > 256) continue;
+    if (lds && kF64Configs[t.cfg].t.per_launch(M, N) < 1) continue;
     // LDS tiles that do not fill the machine come one or two to a CU
     const double part = lds ? 0.58 + 0.42 * std::ceil(r * t.per_cu) / t.per_cu : 0.7 + 0.3 * r;
     const double rounds = r > 4.0 ? r : r >= 1.0 ? std::ceil(r) : part;
@@ -777,6 +779,21 @@ int f64_default_config(int64_t M, int64_t N, int64_t K, int64_t batch) {
   return c[best].cfg;
 }
 
+static gemm_status f64_launch(const GemmArgsF64 &g, int cfg, hipStream_t s) {
+  switch (cfg) {
+    case 0: return f64::launch<128, 128, 64, 64>(g, s);
+    case 1: return f64::launch<256, 128, 64, 64>(g, s);
+    case 2: return f64::launch<64, 64, 32, 32>(g, s);
+    case 6: return f64::launch_split<1>(g, s);
+    case 7: return f64::launch_split<2>(g, s);
+    case 8: return f64::launch<64, 64, 32, 32, 2>(g, s);
+    case kDirect16: return f64::launch_small<1>(g, s);
+    case kDirect32: return f64::launch_small<2>(g, s);
+    case kDirect64: return f64::launch_small<4>(g, s);
+    default: set_error("gemm_f64: bad tile config"); return GEMM_STATUS_UNSUPPORTED;
+  }
+}
+
 gemm_status f64_run(const GemmArgsF64 &g, int cfg, hipStream_t s) {
   if (cfg >= 3 && cfg <= 5) {
     const int lim = cfg == 3 ? 16 : cfg == 4 ? 32 : 64;
@@ -796,18 +813,22 @@ gemm_status f64_run(const GemmArgsF64 &g, int cfg, hipStream_t s) {
   }
   // other operands that 32-bit offsets cannot reach take the 64 x 64 tile
   if ((cfg >= kDirect16 || cfg == 6 || cfg == 7) && !f64::small_fits(g)) cfg = 2;
-  switch (cfg) {
-    case 0: return f64::launch<128, 128, 64, 64>(g, s);
-    case 1: return f64::launch<256, 128, 64, 64>(g, s);
-    case 2: return f64::launch<64, 64, 32, 32>(g, s);
-    case 6: return f64::launch_split<1>(g, s);
-    case 7: return f64::launch_split<2>(g, s);
-    case 8: return f64::launch<64, 64, 32, 32, 2>(g, s);
-    case kDirect16: return f64::launch_small<1>(g, s);
-    case kDirect32: return f64::launch_small<2>(g, s);
-    case kDirect64: return f64::launch_small<4>(g, s);
-    default: set_error("gemm_f64: bad tile config"); return GEMM_STATUS_UNSUPPORTED;
+  // as many problems to a launch as its lanes allow
+  const int tile = cfg >= kDirect16 ? cfg - kDirect16 + 3 : cfg;
+  if (tile < 0 || tile >= f64_num_configs()) {
+    set_error("gemm_f64: bad tile config");
+    return GEMM_STATUS_UNSUPPORTED;
   }
+  const int64_t most = std::max<int64_t>(1, kF64Configs[tile].t.per_launch(g.M, g.N));
+  for (int64_t b = 0; b < g.batch; b += most) {
+    GemmArgsF64 part = g;
+    part.A += b * g.sa;
+    part.B += b * g.sb;
+    part.C += b * g.sc;
+    part.batch = std::min(most, g.batch - b);
+    if (gemm_status st = f64_launch(part, cfg, s)) return st;
+  }
+  return GEMM_STATUS_OK;
 }
 
 gemm_status scale_c_f64(int64_t M, int64_t N, double beta, double *C, int64_t ldc, int64_t sc,

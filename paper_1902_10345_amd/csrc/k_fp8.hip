@@ -1125,6 +1125,10 @@ static gemm_status fp8_launch(int64_t M, int64_t N, const fp8::Layout &L, float 
     return GEMM_STATUS_UNSUPPORTED;
   }
   const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (int)((N + BN - 1) / BN);
+  if ((int64_t)tiles_m * tiles_n > kMaxLanes / (64 * (BM / WM) * (BN / WN))) {
+    set_error("gemm_fp8: too many tiles for one launch");
+    return GEMM_STATUS_UNSUPPORTED;
+  }
   const dim3 grid((unsigned)((int64_t)tiles_m * tiles_n)), block(64 * (BM / WM) * (BN / WN));
   const uint8_t *qa = base + L.qa, *qb = base + L.qb;
   const float *sa = reinterpret_cast<const float *>(base + L.sa);
@@ -1156,6 +1160,10 @@ static gemm_status fp8_launch_ring(int64_t M, int64_t N, const fp8::Layout &L, f
     return GEMM_STATUS_UNSUPPORTED;
   }
   const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (int)((N + BN - 1) / BN);
+  if ((int64_t)tiles_m * tiles_n > kMaxLanes / (64 * (BM / WM) * (BN / WN))) {
+    set_error("gemm_fp8: too many tiles for one launch");
+    return GEMM_STATUS_UNSUPPORTED;
+  }
   const dim3 grid((unsigned)((int64_t)tiles_m * tiles_n)), block(64 * (BM / WM) * (BN / WN));
   const uint8_t *qa = base + L.qa, *qb = base + L.qb;
   const float *sa = reinterpret_cast<const float *>(base + L.sa);
@@ -1212,8 +1220,9 @@ int fp8_default_config(int64_t M, int64_t N, int64_t K) {
   auto tiles = [&](int b) { return (double)((M + b - 1) / b) * (double)((N + b - 1) / b); };
   const double big = 6.0 + 1.75 * slabs * std::ceil(tiles(256) / cus);
   const double small = 3.0 + 0.0008 * slabs * tiles(64);
-  // (a 256-row panel of codes stays below 2^31 bytes)
-  if (big < small && K <= ((int64_t)1 << 23) - 256) return 2;
+  // (a 256-row panel of codes stays below 2^31 bytes, a launch below 2^32 lanes)
+  const bool too_many = tiles(64) > (double)(kMaxLanes / 256);
+  if ((big < small || too_many) && K <= ((int64_t)1 << 23) - 256) return 2;
   return tiles(64) <= 1.5 * cus ? 8 : 7;
 }
 

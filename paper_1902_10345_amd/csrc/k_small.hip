@@ -448,8 +448,8 @@ gemm_status launch(const GemmArgs &g, hipStream_t s) {
   const int64_t ea = g.ta ? extent_bytes(g.K, g.lda, g.M) : extent_bytes(g.M, g.lda, g.K);
   const int64_t eb = g.tb ? extent_bytes(g.N, g.ldb, g.K) : extent_bytes(g.K, g.ldb, g.N);
   // every element offset (and the out-of-range marker) must fit in 31 bits
-  if (tiles_m * tiles_n > 0x7fffffff || ea >= ((int64_t)1 << 31) || eb >= ((int64_t)1 << 31)) {
-    set_error("small-product configuration: operands too large for 32-bit offsets");
+  if (tiles_m * tiles_n > kMaxLanes / (64 * KW) || ea >= ((int64_t)1 << 31) || eb >= ((int64_t)1 << 31)) {
+    set_error("small-product configuration: operands too large for 32-bit offsets or one launch");
     return GEMM_STATUS_UNSUPPORTED;
   }
   // Staged where a wave's range is long (direct -> staged, us): 32 x 32 tiles

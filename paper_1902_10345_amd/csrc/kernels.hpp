@@ -23,6 +23,12 @@ struct GemmArgs {
 struct TileConfig {
   int bm, bn, bk;
   const char *name;
+  int lanes;  // per output tile
+  // problems of M x N that one launch holds
+  int64_t per_launch(int64_t M, int64_t N) const {
+    const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+    return tiles > 0 ? kMaxLanes / lanes / tiles : kMaxLanes;
+  }
 };
 
 // A tile configuration's time, for the choice among configurations: `fixed` us

@@ -467,3 +467,26 @@ def test_default_sums_of_three_products_no_longer_than_an_eighth():
         small = name in ("bx3_small_32x32_8wk_p3", "bx3_small_64x64_8wk_p3")
         assert small or (name == "bx3_64x64x32_2x4w32x32_p3_kg2" and K >= 96), (M, N, K, name)
         seen.add(small)
+
+
+def test_default_tiles_of_very_long_operands_fit_one_launch():
+    """The default of a path launches less than 2^32 lanes: few rows or columns
+    of up to 2^30 are no reason for tiles that one launch does not hold."""
+    import re
+
+    import paper_1902_10345_amd as mm
+
+    def lanes(name):
+        waves = re.search(r"_(?:(\d)x)?(\d)w(?:\d|k)", name)
+        return 64 * int(waves.group(1) or 1) * int(waves.group(2))
+    assert lanes("bx3_64x64x32_2x4w32x32_p3_kg2") == 512 and lanes("f32_small_32x32_8wk") == 512
+    assert lanes("fp8_64x64x128_4w32x32_dma") == 256
+    for path in (mm.PATH_F32, mm.PATH_3XBF16, mm.PATH_FP8, mm.PATH_F64):
+        for long in [1 << 26, (1 << 28) - 1, 1 << 28, (1 << 29) + 3, 1 << 30]:
+            for short, K in [(1, 1), (1, 64), (33, 1), (70, 16)]:
+                for M, N in [(long, short), (short, long)]:
+                    name = mm.gemm_config_name(path, mm.gemm_default_config(path, M, N, K))
+                    bm, bn = map(int, re.search(r"_(\d+)x(\d+)", name).groups())
+                    tiles = -(-M // bm) * -(-N // bn)
+                    if M * N <= 1 << 30:
+                        assert tiles * lanes(name) < 1 << 32, (path, M, N, K, name)
