@@ -1082,23 +1082,33 @@ gemm_status fp8_quantize_run(int64_t M, int64_t N, int64_t K, const float *A, in
     if (ja.cols < jb.cols) std::swap(ja, jb);
     auto blocks = [&](const fp8::QuantJob &j) {
       const int per = j.cols ? 16 : L.Kp <= 512 ? 16 : 4;
-      return (j.R + per - 1) / per;
+      return ((int64_t)j.R + per - 1) / per;
     };
-    const int blocks0 = blocks(ja), total = blocks0 + blocks(jb);
-    if (total == 0) return GEMM_STATUS_OK;
-#define MM_QPAIR(WAVE, CH, CQ)                                                                     \
-  hipLaunchKernelGGL((fp8::quant_pair_kernel<WAVE, CH, CQ>), dim3((unsigned)total), dim3(1024), 0, \
-                     s, ja, jb, blocks0, (int)K, L.Kp)
-    // one wave per row up to 512 (7 % faster than four at 4096 rows of 300,
-    // 16 % slower at rows of 4096)
-    if (L.Kp <= 256) MM_QPAIR(true, 1, 1);
-    else if (L.Kp <= 512) MM_QPAIR(true, 2, 1);
-    else if (L.Kp <= 1024) MM_QPAIR(false, 1, 1);
-    else if (L.Kp <= 2048) MM_QPAIR(false, 2, 2);
-    else if (L.Kp <= 3072) MM_QPAIR(false, 3, 3);
-    else MM_QPAIR(false, 4, 4);
+    const int64_t blocks0 = blocks(ja), blocks1 = blocks(jb);
+    auto launch = [&](int64_t b0, int64_t b1) -> gemm_status {
+      if (b0 + b1 == 0) return GEMM_STATUS_OK;
+      if (b0 + b1 > kMaxLanes / 1024) {
+        set_error("fp8_quantize: too many rows or columns for one launch");
+        return GEMM_STATUS_UNSUPPORTED;
+      }
+#define MM_QPAIR(WAVE, CH, CQ)                                                              \
+  hipLaunchKernelGGL((fp8::quant_pair_kernel<WAVE, CH, CQ>), dim3((unsigned)(b0 + b1)),     \
+                     dim3(1024), 0, s, ja, jb, (int)b0, (int)K, L.Kp)
+      // one wave per row up to 512 (7 % faster than four at 4096 rows of 300,
+      // 16 % slower at rows of 4096)
+      if (L.Kp <= 256) MM_QPAIR(true, 1, 1);
+      else if (L.Kp <= 512) MM_QPAIR(true, 2, 1);
+      else if (L.Kp <= 1024) MM_QPAIR(false, 1, 1);
+      else if (L.Kp <= 2048) MM_QPAIR(false, 2, 2);
+      else if (L.Kp <= 3072) MM_QPAIR(false, 3, 3);
+      else MM_QPAIR(false, 4, 4);
 #undef MM_QPAIR
-    return check_launch("quant_pair_kernel");
+      return check_launch("quant_pair_kernel");
+    };
+    // (a launch each where one does not hold both)
+    if (blocks0 + blocks1 <= kMaxLanes / 1024) return launch(blocks0, blocks1);
+    if (gemm_status st = launch(blocks0, 0)) return st;
+    return launch(0, blocks1);
   }
   // When A goes by rows and B by columns, A's launch clears B's amax words.
   bool amax_clear = false;

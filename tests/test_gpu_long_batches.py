@@ -43,3 +43,25 @@ def test_long_single_column_product():
     C = torch.zeros(M, device="cuda")
     mm.gemm_f32(M, 1, 1, 1.0, a, 1, b, 1, 0.0, C, 1)
     assert torch.equal(C, 3.0 * a)
+
+
+def test_fp8_quantisation_of_more_lanes_than_a_launch():
+    """2^25 rows and as many columns (and a few) of one element: 2^31 lanes each."""
+    import torch
+    import paper_1902_10345_amd as mm
+    R = (1 << 25) + 40
+    a = (torch.arange(R, device="cuda", dtype=torch.int32) % 127 - 63).float()
+    b = (torch.arange(R, device="cuda", dtype=torch.int32) % 101 - 50).float()
+    nbytes = mm.gemm_fp8_workspace_bytes(R, R, 1)
+    ws = torch.full((nbytes,), 0x55, dtype=torch.uint8, device="cuda")
+    mm.fp8_quantize(R, R, 1, a, 1, b, R, ws, nbytes)
+    L = mm.fp8_workspace_layout(R, R, 1)
+    for x, q, s in ((a, "qa", "sa"), (b, "qb", "sb")):
+        codes = ws[L[q]:L[q] + R * L["Kp"]].view(R, L["Kp"])
+        # one element per row: its code is that of +-448, of 0 where it is zero
+        want = torch.where(x == 0, 0x00, torch.where(x < 0, 0xFE, 0x7E)).to(torch.uint8)
+        assert torch.equal(codes[:, 0], want), q
+        assert not bool(codes[:, 1:].any()), q
+        scale = ws[L[s]:L[s] + 4 * R].view(torch.float32)
+        assert torch.equal(scale, torch.where(x == 0, torch.ones_like(x),
+                                              x.abs() / torch.full_like(x, 448.0))), s
