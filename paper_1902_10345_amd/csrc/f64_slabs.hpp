@@ -29,9 +29,10 @@ struct Slabs {
 
 // Binary64 elements of B, from its row max(k0, 0), that the unmasked load of the
 // slab at k0 may address (cols columns, row stride ldb): a whole slab, which lies
-// in [0, K), or nothing where it would begin before k = 0.
+// in [0, K), or nothing where it would begin before k = 0 (a mask: the compiler
+// makes a branch of a conditional here).
 constexpr long long slab_extent(int k0, long long ldb, int cols) {
-  return k0 >= 0 ? (BK - 1) * ldb + cols : 0;
+  return ((BK - 1) * ldb + cols) & ~((long long)k0 >> 63);
 }
 
 }  // namespace f64

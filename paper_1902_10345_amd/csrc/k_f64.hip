@@ -40,6 +40,7 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int CH = BK / 2;   // 16-byte chunks (two binary64) per LDS row
 constexpr int kBufferFlags = 0x00020000;
+enum { kFast, kGuarded, kMasked };  // how a tile loads a slab
 
 // 128-byte rows: 16 consecutive rows at one logical chunk occupy 16 distinct
 // 16-byte bank groups.
@@ -123,10 +124,10 @@ __device__ __forceinline__ void tile(int M, int N, int K, double alpha, const do
 
   constexpr int DEPTH = KG;  // slabs of global loads in flight
   double ra_[DEPTH][G::A_ITEMS][2], rb_[DEPTH][G::B_ITEMS][2];
-  // FAST: the slab lies inside [0, K), or begins before k = 0 and is not
+  // FAST: the slab lies inside [0, K) or, GUARD, begins before k = 0 and is not
   // multiplied; otherwise k outside [0, K) read as 0.
   auto gload = [&](auto F, auto SET, int k0) {
-    constexpr bool FAST = decltype(F)::value;
+    constexpr bool FAST = decltype(F)::value != kMasked, GUARD = decltype(F)::value == kGuarded;
     auto &ra = ra_[decltype(SET)::value];
     auto &rb = rb_[decltype(SET)::value];
 #pragma unroll
@@ -143,10 +144,9 @@ __device__ __forceinline__ void tile(int M, int N, int K, double alpha, const do
       }
     }
     if (FAST) {
-      // (one group: k0 >= 0, its only partial slab is loaded masked)
-      const int kb = KG == 1 || k0 > 0 ? k0 : 0;
       const __amdgpu_buffer_rsrc_t rB =
-          rsrc(B + (int64_t)kb * ldb + n0, slab_extent(KG == 1 ? kb : k0, ldb, colsB) * 8);
+          rsrc(B + (int64_t)(unsigned)(GUARD && k0 < 0 ? 0 : k0) * ldb + n0,
+               (GUARD ? slab_extent(k0, ldb, colsB) : (int64_t)(BK - 1) * ldb + colsB) * 8);
 #pragma unroll
       for (int i = 0; i < G::B_ITEMS; ++i)
 #pragma unroll
@@ -221,16 +221,18 @@ __device__ __forceinline__ void tile(int M, int N, int K, double alpha, const do
     }
   };
 
-  // Slab 0 of the first group is loaded masked in the prologue.
-  using Fast = std::true_type;
-  using Masked = std::false_type;
+  // Slab 0 of the first group is loaded masked in the prologue; the loads of the
+  // loop, which takes two turns, lie inside [0, K).
+  using Fast = std::integral_constant<int, kFast>;
+  using Guarded = std::integral_constant<int, kGuarded>;
+  using Masked = std::integral_constant<int, kMasked>;
   using R0 = std::integral_constant<int, 0>;
   using R1 = std::integral_constant<int, DEPTH - 1>;
   const Slabs sl(K, KG, group);
   const int KT = sl.turns, own = sl.own;
   if (group == 0) gload(Masked{}, R0{}, sl.base);
-  else gload(Fast{}, R0{}, sl.k(0));
-  if (DEPTH == 2) gload(Fast{}, R1{}, sl.k(1));
+  else gload(Guarded{}, R0{}, sl.k(0));
+  if (DEPTH == 2) gload(Guarded{}, R1{}, sl.k(1));
   sstore(R0{}, 0);
   __syncthreads();
   int t = 0;

@@ -400,20 +400,24 @@ _SLABS_MAIN = r"""
 #include <cstdlib>
 #include "f64_slabs.hpp"
 using namespace mm::f64;
-// every full-slab load that the tiles issue: (K, groups, group, first row,
-// last row of B addressed or -1), then the slabs that each group multiplies
+// every full-slab load that the tiles issue: (K, groups, group, first k, rows of
+// B addressed); with two groups the prologue's are guarded, the loop's, which
+// needs two turns, never
 int main() {
   for (int K = 1; K <= 200; ++K)
     for (int kg = 1; kg <= 2; ++kg)
       for (int group = 0; group < kg; ++group) {
         const Slabs s(K, kg, group);
         std::printf("G %d %d %d %d %d %d\n", K, kg, group, s.turns, s.own, s.base);
+        const long long ldb = 1000;
         // the first group's slab 0 goes through the masked load
-        for (int i = group == 0 ? 1 : 0; i < s.turns + 4; ++i) {
-          if (kg == 1 && s.turns < 2) break;  // no full-slab load is issued
-          const long long ldb = 1000, e = slab_extent(s.k(i), ldb, 7);
+        for (int i = group == 0 ? 1 : 0; kg == 2 && i < 2; ++i) {
+          const long long e = slab_extent(s.k(i), ldb, 7);
           std::printf("L %d %d %d %d %lld\n", K, kg, group, s.k(i), e > 0 ? (e - 7) / ldb : -1);
         }
+        for (int t = 0; t + 2 <= s.turns; t += 2)
+          for (int i = t + kg; i < t + kg + 2; ++i)
+            std::printf("L %d %d %d %d %d\n", K, kg, group, s.k(i), BK - 1);
       }
 }
 """
