@@ -460,7 +460,7 @@ gemm_status gemm_f64(int64_t M, int64_t N, int64_t K, double alpha, const double
   if (st || ck.noop) return st;
   if (ck.scale_only) return scale_c_f64(M, N, beta, C, ldc, 0, 1, stream);
   GemmArgsF64 g{M, N, K, alpha, beta, A, lda, 0, B, ldb, 0, C, ldc, 0, 1};
-  return f64_run(g, f64_default_config(M, N, K, 1), stream);
+  return f64_run(g, f64_default_config(M, N, K, 1), false, stream);
 }
 
 gemm_status gemm_f64_run_config(int cfg, int64_t M, int64_t N, int64_t K, double alpha,
@@ -478,7 +478,7 @@ gemm_status gemm_f64_run_config(int cfg, int64_t M, int64_t N, int64_t K, double
   if (ck.noop) return GEMM_STATUS_OK;
   if (ck.scale_only) return scale_c_f64(M, N, beta, C, ldc, 0, 1, stream);
   GemmArgsF64 g{M, N, K, alpha, beta, A, lda, 0, B, ldb, 0, C, ldc, 0, 1};
-  return f64_run(g, cfg < 0 ? f64_default_config(M, N, K, 1) : cfg, stream);
+  return f64_run(g, cfg < 0 ? f64_default_config(M, N, K, 1) : cfg, false, stream);
 }
 
 gemm_status gemm_f64_strided_batched(int64_t M, int64_t N, int64_t K, double alpha,
@@ -520,7 +520,7 @@ gemm_status gemm_f64_strided_batched(int64_t M, int64_t N, int64_t K, double alp
     const int64_t nb = std::min<int64_t>(65535, batch - b0);
     GemmArgsF64 g{M, N, K, alpha, beta, A + b0 * stride_a, lda, stride_a, B + b0 * stride_b, ldb,
                   stride_b, C + b0 * stride_c, ldc, stride_c, nb};
-    if (gemm_status st = f64_run(g, cfg, stream)) return st;
+    if (gemm_status st = f64_run(g, cfg, true, stream)) return st;
   }
   return GEMM_STATUS_OK;
 }

@@ -89,8 +89,6 @@ template <int BM, int BN, int BK, int WM, int WN, int NP, int NW>
 gemm_status launch_splitk(const GemmArgs &g, int S, int unit, float *P, hipStream_t s) {
   const int tiles_m = (int)((g.M + BM - 1) / BM);
   const int tiles_n = (int)((g.N + BN - 1) / BN);
-  const int64_t nwg = (int64_t)tiles_m * tiles_n * S;
-  if (nwg > kMaxLanes / (64 * NW)) { set_error("gemm_f32_3xbf16_splitk: too many workgroups"); return GEMM_STATUS_UNSUPPORTED; }
   if (((int64_t)BM * g.lda + g.K) * 4 >= (int64_t)1 << 31 ||
       ((int64_t)BK * g.ldb + g.N) * 4 >= ((int64_t)1 << 31)) {
     set_error("gemm_f32_3xbf16_splitk: lda or ldb too large for 32-bit tile offsets");
@@ -98,8 +96,12 @@ gemm_status launch_splitk(const GemmArgs &g, int S, int unit, float *P, hipStrea
   }
   const int chunk = (int)(((g.K + S - 1) / S + unit - 1) / unit * unit);
   S = (int)((g.K + chunk - 1) / chunk);  // chunks that hold work (<= requested)
-  const int64_t nwg_used = (int64_t)tiles_m * tiles_n * S;
-  hipLaunchKernelGGL((gemm_bx3_splitk_kernel<BM, BN, BK, WM, WN, NP, NW>), dim3((unsigned)nwg_used),
+  const int64_t nwg = (int64_t)tiles_m * tiles_n * S;
+  if (nwg > kMaxLanes / (64 * NW)) {
+    set_error("gemm_f32_3xbf16_splitk: too many workgroups");
+    return GEMM_STATUS_UNSUPPORTED;
+  }
+  hipLaunchKernelGGL((gemm_bx3_splitk_kernel<BM, BN, BK, WM, WN, NP, NW>), dim3((unsigned)nwg),
                      dim3(64 * NW), 0, s, (int)g.M, (int)g.N, (int)g.K, chunk, g.A, g.lda, g.B,
                      g.ldb, P, tiles_m, tiles_n);
   if (gemm_status st = check_launch("gemm_bx3_splitk_kernel")) return st;
@@ -328,11 +330,12 @@ __global__ __launch_bounds__(256) void small_batched_bx3_kernel(
     }
 }
 
-// Offsets of the small-problem kernel stay below 2^31: a problem's rows of A
-// and of C (rounded up to whole sub-tiles), K rows of B.
+// Offsets of the small-problem kernel stay below 2^31: M rows of A, K rows of B,
+// the rows of C in whole groups of eight (those past M are dropped by the range
+// check).
 bool small_batched_fits(const GemmArgs &g) {
-  const int64_t lim = (int64_t)1 << 31, rows = g.M + 64;
-  return (rows * g.lda + g.K) * 4 < lim && ((int64_t)g.K * g.ldb + g.N) * 4 < lim &&
+  const int64_t lim = (int64_t)1 << 31, rows = (g.M + 7) / 8 * 8;
+  return (g.M * g.lda + g.K) * 4 < lim && (g.K * g.ldb + g.N) * 4 < lim &&
          (rows * g.ldc + g.N) * 4 < lim;
 }
 
@@ -516,7 +519,8 @@ gemm_status bx3_run_splitk(const GemmArgs &g, int n_products, int splits, void *
   // 25, 120 x 1100 x 7000 22 -> 20).
   const int64_t bytes = 4 * (g.M + g.N) * g.K;
   const bool small = (g.M <= 64 ? n_products == 6 || bytes <= 80000000 : bytes <= 24000000) &&
-                     bx3::offsets_fit<64, 64, 32, false, false>(g);
+                     bx3::offsets_fit<64, 64, 32, false, false>(g) &&
+                     kBx3Configs[6].t.per_launch(g.M, g.N) >= splits;
   if (n_products == 6)
     return small ? bx3::launch_splitk<64, 64, 32, 32, 32, 3, 4>(g, splits, unit, P, s)
                  : bx3::launch_splitk<128, 128, 16, 64, 64, 3, 4>(g, splits, unit, P, s);
@@ -585,15 +589,20 @@ static gemm_status batched_tile(int cfg, const GemmArgs &g, int64_t sa, int64_t 
 
 gemm_status batched_run(int path, int cfg, const GemmArgs &g, int n_products, int64_t sa,
                         int64_t sb, int64_t sc, int batch, hipStream_t s) {
-  // operands that 32-bit offsets of the chosen tile cannot reach take the
-  // 64 x 64 tile, whose panels are the smallest, and problems with more 64 x 64
-  // tiles than a launch has room for the 256 x 256 one
-  const bool fits256 = bx3::offsets_fit<256, 256, 32, false, false>(g);
-  if ((cfg == kBatchedDirect && !bx3::small_batched_fits(g)) ||
-      (cfg == kBatched128 && !bx3::offsets_fit<128, 128, 32, false, false>(g)) ||
-      (cfg == kBatched256 && !fits256))
-    cfg = kBatched64;
-  if (kBatchTiles[cfg].t.per_launch(g.M, g.N) < 1 && fits256) cfg = kBatched256;
+  // a tile whose 32-bit offsets cannot reach the operands, or with more tiles in a
+  // problem than a launch has room for, leaves them to the next that can: the 64 x
+  // 64 one has the smallest panels of A, the larger ones the smaller slabs of B
+  auto runs = [&](int c) {
+    if (kBatchTiles[c].t.per_launch(g.M, g.N) < 1) return false;
+    switch (c) {
+      case kBatchedDirect: return bx3::small_batched_fits(g);
+      case kBatched128: return bx3::offsets_fit<128, 128, 16, false, false>(g);
+      case kBatched256: return bx3::offsets_fit<256, 256, 16, false, false>(g);
+      default: return bx3::offsets_fit<64, 64, 32, false, false>(g);
+    }
+  };
+  for (int c : {kBatched64, kBatched128, kBatched256})
+    if (!runs(cfg)) cfg = c;
   // as many problems to a launch as its lanes allow
   const int64_t most = std::max<int64_t>(1, kBatchTiles[cfg].t.per_launch(g.M, g.N));
   for (int64_t b = 0; b < batch; b += most) {

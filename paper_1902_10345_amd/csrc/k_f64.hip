@@ -77,8 +77,8 @@ struct Cfg {
 
 // One output tile of one problem.  A rows are read in 128-bit loads whatever
 // lda, K and the base (a 128-bit buffer load needs only 4-byte alignment).
-// The launcher guarantees that the byte extents of an A row panel (BM rows)
-// and of a B slab (16 rows) stay below 2^31.
+// The launcher guarantees that the byte extents of an A row panel (BM rows, or M
+// where that is less) and of a B slab (16 rows, or K) stay below 2^31.
 //
 // KG = 2: two groups of NW waves share the workgroup, each with its own half
 // of the slabs and its own LDS stages; the second group's partial tile is
@@ -108,7 +108,7 @@ __device__ __forceinline__ void tile(int M, int N, int K, double alpha, const do
 #pragma unroll
   for (int i = 0; i < G::A_ITEMS; ++i) {
     const int idx = tid + NT * i;
-    a_off[i] = ((idx / CH) * (int)lda + (idx % CH) * 2) * 8;
+    a_off[i] = idx / CH < rowsA ? ((idx / CH) * (int)lda + (idx % CH) * 2) * 8 : (int)0x80000000;
   }
   // B: this lane's column (out-of-range columns get an offset past any slab)
   // and the item's first k row (wave-uniform)
@@ -321,6 +321,11 @@ __global__ __launch_bounds__((KG * Cfg<BM, BN, WM, WN>::NT), (Cfg<BM, BN, WM, WN
                                   ldc, tm * BM, tn * BN, lds);
 }
 
+static bool tile_reaches(const GemmArgsF64 &g, int64_t bm) {
+  const int64_t lim = ((int64_t)1 << 31) / 8;
+  return std::min(bm, g.M) * g.lda + g.K < lim && std::min<int64_t>(BK, g.K) * g.ldb + g.N < lim;
+}
+
 template <int BM, int BN, int WM, int WN, int KG = 1>
 gemm_status launch(const GemmArgsF64 &g, hipStream_t s) {
   using G = Cfg<BM, BN, WM, WN>;
@@ -331,8 +336,7 @@ gemm_status launch(const GemmArgsF64 &g, hipStream_t s) {
     set_error("gemm_f64: too many tiles or problems for one launch");
     return GEMM_STATUS_UNSUPPORTED;
   }
-  if (((int64_t)BM * g.lda + g.K) * 8 >= ((int64_t)1 << 31) ||
-      ((int64_t)BK * g.ldb + g.N) * 8 >= ((int64_t)1 << 31)) {
+  if (!tile_reaches(g, BM)) {
     set_error("gemm_f64: lda or ldb too large for 32-bit tile offsets");
     return GEMM_STATUS_UNSUPPORTED;
   }
@@ -476,11 +480,11 @@ __global__ __launch_bounds__(256, 2) void small_batched_kernel(
       }
 }
 
-// 32-bit offsets of the small-problem kernel: a problem's rows of A and of C
-// (rounded up to whole sub-tiles), K rows of B.
+// 32-bit offsets of the small-problem kernel: M rows of A, K rows of B, the rows of
+// C in whole groups of four (those past M are dropped by the range check).
 static bool small_fits(const GemmArgsF64 &g) {
-  const int64_t lim = (int64_t)1 << 31, rows = g.M + 64;
-  return (rows * g.lda + g.K) * 8 < lim && (g.K * g.ldb + g.N) * 8 < lim &&
+  const int64_t lim = (int64_t)1 << 31, rows = (g.M + 3) / 4 * 4;
+  return (g.M * g.lda + g.K) * 8 < lim && (g.K * g.ldb + g.N) * 8 < lim &&
          (rows * g.ldc + g.N) * 8 < lim;
 }
 
@@ -796,7 +800,7 @@ static gemm_status f64_launch(const GemmArgsF64 &g, int cfg, hipStream_t s) {
   }
 }
 
-gemm_status f64_run(const GemmArgsF64 &g, int cfg, hipStream_t s) {
+gemm_status f64_run(const GemmArgsF64 &g, int cfg, bool batched, hipStream_t s) {
   if (cfg >= 3 && cfg <= 5) {
     const int lim = cfg == 3 ? 16 : cfg == 4 ? 32 : 64;
     if (g.M > lim || g.N > lim) {
@@ -813,8 +817,11 @@ gemm_status f64_run(const GemmArgsF64 &g, int cfg, hipStream_t s) {
       return GEMM_STATUS_UNSUPPORTED;
     }
   }
-  // other operands that 32-bit offsets cannot reach take the 64 x 64 tile
+  // other operands that 32-bit offsets cannot reach take the 64 x 64 tile, whose
+  // panels are the smallest (so do those of a batch, whose rule may take 128 x 128
+  // tiles for few problems)
   if ((cfg >= kDirect16 || cfg == 6 || cfg == 7) && !f64::small_fits(g)) cfg = 2;
+  if (cfg == 0 && batched && !f64::tile_reaches(g, 128)) cfg = 2;
   // as many problems to a launch as its lanes allow
   const int tile = cfg >= kDirect16 ? cfg - kDirect16 + 3 : cfg;
   if (tile < 0 || tile >= f64_num_configs()) {

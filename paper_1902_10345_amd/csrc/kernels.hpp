@@ -102,7 +102,7 @@ struct GemmArgsF64 {
 int f64_num_configs();
 const TileConfig &f64_config(int i);
 int f64_default_config(int64_t M, int64_t N, int64_t K, int64_t batch);
-gemm_status f64_run(const GemmArgsF64 &g, int cfg, hipStream_t s);
+gemm_status f64_run(const GemmArgsF64 &g, int cfg, bool batched, hipStream_t s);
 gemm_status scale_c_f64(int64_t M, int64_t N, double beta, double *C, int64_t ldc, int64_t sc,
                         int64_t batch, hipStream_t s);
 
