@@ -578,10 +578,11 @@ __global__ __launch_bounds__(64 * KW) void split_kernel(
       const bool in = k + 2 * lg >= 0;
 #pragma unroll
       for (int i = 0; i < F; ++i)
-        a[0][i][q] = ld1(rA, in && arow[i] >= 0 ? arow[i] + k * 8 : (int)0x80000000, 0);
+        a[0][i][q] = ld1(rA, in && 16 * i + lr < Mr ? arow[i] + k * 8 : (int)0x80000000, 0);
+      // (bcol alone may lie beyond 2^31 where K < 8; the sum does not)
 #pragma unroll
       for (int j = 0; j < F; ++j)
-        b[0][j][q] = ld1(rB, in && bcol[j] >= 0 ? bcol[j] + k * ldb8 : (int)0x80000000, 0);
+        b[0][j][q] = ld1(rB, in && 16 * j + lr < Nr ? bcol[j] + k * ldb8 : (int)0x80000000, 0);
     }
   };
   auto multiply = [&](auto S) {

@@ -309,3 +309,19 @@ def test_few_long_batched_problems_exact(M, N, K, batch):
     C = torch.ones((batch, M, N), device="cuda", dtype=torch.float64)
     mm.gemm_f64_strided_batched(M, N, K, 2.0, A, K, M * K, B, N, K * N, -3.0, C, N, M * N, batch)
     assert torch.equal(C, 2 * torch.stack([a @ b for a, b in zip(A.cpu(), B.cpu())]).cuda() - 3.0)
+
+
+@pytest.mark.parametrize("K", [1, 3, 4])
+def test_few_k_far_apart(K):
+    """Rows of B so far apart that eight of them span more than 2^31 bytes, and
+    fewer of them than that: the k-split tiles address what there is."""
+    import torch
+    import paper_1902_10345_amd as mm
+    M, N, ldb = 20, 37, 60_000_000
+    A = torch.randint(-9, 10, (M, K), device="cuda").double()
+    B = torch.randint(-9, 10, (K, N), device="cuda").double()
+    buf = torch.empty((K - 1) * ldb + N, device="cuda", dtype=torch.float64)
+    buf.as_strided((K, N), (ldb, 1)).copy_(B)
+    C = torch.full((M, N), float("nan"), device="cuda", dtype=torch.float64)
+    mm.gemm_f64(M, N, K, 1.0, A, K, buf, ldb, 0.0, C, N)
+    assert torch.equal(C.cpu(), A.cpu() @ B.cpu())
