@@ -512,13 +512,20 @@ gemm_status bx3_run_splitk(const GemmArgs &g, int n_products, int splits, void *
   const int unit = n_products == 6 ? 32 : 16;
   // 64 x 64 tiles where half of a 128 x 128 tile would be padding (three / six
   // products, us, 128 -> 64: 14 x 3595 x 1168 15.1 -> 12.5, 21 -> 14; 64 x 4096
-  // x 4096 22.5 -> 22, 29 -> 27) or operands are small and a chunk's chain of
-  // slabs is the time (512 x 512 x 2048 18.5 -> 15.8, 23 -> 18).  Larger operands
-  // stream from HBM, three products as fast as that goes: 128-wide tiles read
-  // longer pieces of B's rows (64 x 8192 x 8192 70 -> 65, 100 x 4096 x 4096 32 ->
-  // 25, 120 x 1100 x 7000 22 -> 20).
+  // x 4096 22.5 -> 22, 29 -> 27) or operands are small and 128 x 128 tiles leave
+  // half of the CUs idle (a quarter for six products, whose tiles take longer), so
+  // that a chunk's chain of slabs is the time: 512 x 512 x 2048 on 128 CUs 15.3 ->
+  // 12.6, 19.7 -> 14.7; 384 x 1200 x 1600 on 180 16.1 -> 17.4, 21.8 -> 19.4; 512 x
+  // 1800 x 1024 on 240 17.8 -> 18.3, 22.1 -> 24.7; 1024 x 4096 x 1024 twice on all
+  // 40 -> 48, 56 -> 67.  Larger operands stream from HBM, three products as fast as
+  // that goes: 128-wide tiles read longer pieces of B's rows (64 x 8192 x 8192 70 ->
+  // 65, 100 x 4096 x 4096 32 -> 25, 120 x 1100 x 7000 22 -> 20).
   const int64_t bytes = 4 * (g.M + g.N) * g.K;
-  const bool small = (g.M <= 64 ? n_products == 6 || bytes <= 80000000 : bytes <= 24000000) &&
+  const int64_t deep = ((g.K + splits - 1) / splits + unit - 1) / unit * unit;  // of a chunk
+  const int64_t big = ((g.M + 127) / 128) * ((g.N + 127) / 128) * ((g.K + deep - 1) / deep);
+  const bool idle = big * 4 <= (n_products == 6 ? 3 : 2) * (int64_t)num_cus();
+  const bool small = (g.M <= 64 ? n_products == 6 || bytes <= 80000000
+                                : idle && bytes <= 24000000) &&
                      bx3::offsets_fit<64, 64, 32, false, false>(g) &&
                      kBx3Configs[6].t.per_launch(g.M, g.N) >= splits;
   if (n_products == 6)

@@ -156,3 +156,19 @@ def test_chunks_are_the_single_tile_products_bitwise(M, N, K, splits, n):
         c = c.cpu().numpy()
         want = c if want is None else want + c
     assert np.array_equal(C, want)
+
+
+@pytest.mark.parametrize("M,N,K,splits", [(65, 520, 300, 2), (128, 1152, 1100, 4), (512, 1800, 1024, 4),
+                                          (1024, 1024, 600, 2), (1024, 1024, 2300, 9),
+                                          (1021, 1023, 700, 8), (300, 4100, 1000, 3)])
+@pytest.mark.parametrize("n", [3, 6])
+def test_tile_and_reduction_choices_are_exact(M, N, K, splits, n):
+    """Shapes on both sides of the rules for the tile and for the reduction's
+    reads, with every length of a last group of planes among them; integers, so
+    the result is exact."""
+    import paper_1902_10345_amd as mm
+    A = si.integers((M, K), 3, -50, 50).astype(np.float32)
+    B = si.integers((K, N), 4, -50, 50).astype(np.float32)
+    C0 = si.integers((M, N), 5, -50, 50).astype(np.float32)
+    _, C = _run(mm, A, B, C0, 2.0, -3.0, n, splits)
+    assert np.array_equal(C, 2.0 * (A.astype(np.float64) @ B.astype(np.float64)) - 3.0 * C0)
