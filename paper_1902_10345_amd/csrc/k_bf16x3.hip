@@ -31,11 +31,48 @@ __global__ __launch_bounds__(64 * NW, 1) void gemm_bx3_splitk_kernel(
                                                tn * BN, lds);
 }
 
+// P_0 + P_1 + ... of element q, in plane order.  AHEAD: eight planes are read
+// ahead of their additions, for reductions whose chain of S dependent reads is the
+// time, and no plane is read twice (us, in turn -> eight ahead: 57 x 1856 x 6046 in
+// 23 chunks 23.2 -> 17.3, 64 x 4096 x 4096 in 16 23.4 -> 20.7; 2048 x 2048 x 512 in two
+// chunks 28.5, 29.2 when a short group repeated its last plane).  In turn where
+// 128-bit reads of four or more workgroups per CU keep the memory busy: 256 x 4096 x
+// 2048 in eight 27.3, 28.0 eight ahead, 512 x 4096 x 4096 in nine 86.8, 88.9.
+template <typename V>
+__device__ __forceinline__ V sum_planes(const V *P, int64_t plane, int S, int64_t q, bool ahead) {
+  V acc = P[q];
+  int c = 1;
+  auto add = [&](auto n) {
+    constexpr int kN = decltype(n)::value;
+    V v[kN];
+#pragma unroll
+    for (int u = 0; u < kN; ++u) v[u] = P[(c + u) * plane + q];
+#pragma unroll
+    for (int u = 0; u < kN; ++u) acc += v[u];
+    c += kN;
+  };
+  if (!ahead) {
+    while (c < S) add(std::integral_constant<int, 1>{});
+    return acc;
+  }
+  while (c + 8 <= S) add(std::integral_constant<int, 8>{});
+  switch (S - c) {
+    case 7: add(std::integral_constant<int, 7>{}); break;
+    case 6: add(std::integral_constant<int, 6>{}); break;
+    case 5: add(std::integral_constant<int, 5>{}); break;
+    case 4: add(std::integral_constant<int, 4>{}); break;
+    case 3: add(std::integral_constant<int, 3>{}); break;
+    case 2: add(std::integral_constant<int, 2>{}); break;
+    case 1: add(std::integral_constant<int, 1>{}); break;
+    default: break;
+  }
+  return acc;
+}
+
 // The write-conflict resolution of the chunks: C = alpha * (P_0 + P_1 + ...)
 // + beta * C, summed in chunk order (deterministic), the same epilogue
-// arithmetic as the single-pass kernel.  Eight planes are read ahead of their
-// additions: with so few elements a chain of S dependent reads is the kernel's
-// time (57 x 1856 x 6046 in 23 chunks, with the 128 x 128 tile, 24.8 -> 21.9 us).  VEC: N, ldc multiples of 4 and C 16-byte aligned.
+// arithmetic as the single-pass kernel.  VEC: N, ldc multiples of 4 and C 16-byte
+// aligned.
 template <bool VEC, bool BETA>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(int M, int N, int S,
                                                             const float *__restrict__ P,
@@ -45,16 +82,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(int M, int N, int S,
   if (VEC) {
     const int64_t n4 = plane / 4;
     for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < n4; q += (int64_t)gridDim.x * 256) {
-      float4 acc = reinterpret_cast<const float4 *>(P)[q];
-      for (int c = 1; c < S; c += 8) {
-        float4 v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          v[u] = reinterpret_cast<const float4 *>(P + (c + u < S ? c + u : S - 1) * plane)[q];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (c + u < S) { acc.x += v[u].x; acc.y += v[u].y; acc.z += v[u].z; acc.w += v[u].w; }
-      }
+      const f32x4 acc = sum_planes(reinterpret_cast<const f32x4 *>(P), n4, S, q, gridDim.x < 1024);
       const int64_t e = 4 * q;
       const int64_t i = e / N, j = e - i * N;
       float4 *cp = reinterpret_cast<float4 *>(C + i * ldc + j);
@@ -68,15 +96,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(int M, int N, int S,
     }
   } else {
     for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < plane; e += (int64_t)gridDim.x * 256) {
-      float acc = P[e];
-      for (int c = 1; c < S; c += 8) {
-        float v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = P[(c + u < S ? c + u : S - 1) * plane + e];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (c + u < S) acc += v[u];
-      }
+      const float acc = sum_planes(P, plane, S, e, true);
       const int64_t i = e / N, j = e - i * N;
       float *cp = C + i * ldc + j;
       const float v = alpha * acc;
