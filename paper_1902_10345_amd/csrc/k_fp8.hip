@@ -1217,23 +1217,40 @@ gemm_status fp8_gemm_run_cfg(int64_t M, int64_t N, int64_t K, float alpha, const
   return fp8_launch<256, 256, 128, 64, false>(M, N, L, alpha, base, beta, C, ldc, s);
 }
 
-// Direct-to-LDS kernels.  256 x 256 tiles take 1.75 us per 128-deep slab and
-// round of one tile per CU, 64 x 64 tiles 0.8 ns per tile and slab and a shorter
-// prologue and epilogue (a lane's 16 results instead of 128): the smaller sum
-// (us without quantisation, 256 / 128 / 64: 4096^3 54 / 60 / 88, 3000^3 47 / 55
-// / 47, 2048^3 31 / 18 / 16, 1474 x 1051 x 96 15 / 9 / 5).  With at most three
-// 64 x 64 tiles for two CUs, the ring of four stages (512^3 5.1 -> 4.5 us, 800 x
-// 800 x 4000 17 -> 12); beyond, other workgroups hide a slab's latency and the
-// two-stage form is ahead (2048^3 15 us, ring 19).
+// Direct-to-LDS kernels, the least modelled time in us.  256 x 256 tiles take 1.75
+// per 128-deep slab and round of one tile per CU, 1.55 where they leave two fifths of
+// the CUs idle, and 0.03 per tile for C; 128 x 128 tiles, in one round of at most two
+// per CU, 0.54 per slab alone on a CU and 0.84 in pairs; 64 x 64 tiles 0.2 per slab and
+// tile of a CU, a shorter start and end (a lane's 16 results instead of 128), and 3 more
+// beyond the five of a CU.  Rows of C that are no whole 64-byte pieces cost the larger
+// tiles more.  Fitted on 420 shapes of 100 to 12 000: 0.6 % behind the fastest on
+// average; 2 % behind the rule on tile counts (256 x 256 where they fill the CUs and else
+// 128 x 128) for one.  Without quantisation, 256 / 128 / 64: 4096^3 61 / 69 / 100, 3072^2 x
+// 4096 48 / 57 / 60, 4096 x 2048 x 4096 48 / 37 / 52 (52 before 128 x 128 tiles were among the
+// choices), 2048^3 31 / 18 / 16, 2943 x 2566 x 766 28 / 25 / 21, 4096 x 3072 x 128 14 / 14 /
+// 12.  With at most three 64 x 64 tiles for two CUs, the ring of four stages (512^3 5.1 ->
+// 4.5, 800 x 800 x 4000 17 -> 12); beyond, other workgroups hide a slab's latency and
+// the two-stage form is ahead (2048^3 15, ring 19).
 int fp8_default_config(int64_t M, int64_t N, int64_t K) {
   const double cus = num_cus(), slabs = (double)((K + 127) / 128);
   auto tiles = [&](int b) { return (double)((M + b - 1) / b) * (double)((N + b - 1) / b); };
-  const double big = 6.0 + 1.75 * slabs * std::ceil(tiles(256) / cus);
-  const double small = 3.0 + 0.0008 * slabs * tiles(64);
-  // (a 256-row panel of codes stays below 2^31 bytes, a launch below 2^32 lanes)
-  const bool too_many = tiles(64) > (double)(kMaxLanes / 256);
-  if ((big < small || too_many) && K <= ((int64_t)1 << 23) - 256) return 2;
-  return tiles(64) <= 1.5 * cus ? 8 : 7;
+  const double t256 = tiles(256), t128 = tiles(128), t64 = tiles(64);
+  const double rounds = std::ceil(t256 / cus), ragged = N % 16 == 0 ? 0.0 : 1.0;
+  const double us256 = 4.0 + 0.03 * t256 + slabs * (t256 <= 0.6 * cus ? 1.55 : 1.75 * rounds) +
+                       4.0 * rounds * ragged;
+  const double us128 = t128 > 2.0 * cus
+                           ? 1e30
+                           : 8.2 + slabs * (0.54 + 0.3 * std::max(0.0, t128 / cus - 1.0)) +
+                                 3.0 * t128 / cus * ragged;
+  const double us64 = t64 > (double)(kMaxLanes / 256)
+                          ? 1e30
+                          : 3.0 + 0.0008 * cus * slabs * std::ceil(t64 / cus) +
+                                (t64 > 5.0 * cus ? 3.0 : 0.0);
+  // (a panel of codes stays below 2^31 bytes)
+  const bool fits256 = K <= ((int64_t)1 << 23) - 256, fits128 = K <= ((int64_t)1 << 24) - 256;
+  if (fits128 && us128 <= us256 && us128 <= us64) return 3;
+  if (fits256 && us256 < us64) return 2;
+  return t64 <= 1.5 * cus ? 8 : 7;
 }
 
 gemm_status fp8_encode_run(int64_t n, const float *x, uint8_t *out, hipStream_t s) {

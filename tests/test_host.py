@@ -494,3 +494,17 @@ def test_default_tiles_of_very_long_operands_fit_one_launch():
                     tiles = -(-M // bm) * -(-N // bn)
                     if M * N <= 1 << 30:
                         assert tiles * lanes(name) < 1 << 32, (path, M, N, K, name)
+
+
+def test_default_fp8_tiles_by_modelled_time():
+    """256 x 256 tiles where they fill the compute units, 128 x 128 in one round of
+    two per unit with a long K, 64 x 64 for the rest (256 compute units)."""
+    import paper_1902_10345_amd as mm
+
+    def name(M, N, K):
+        return mm.gemm_config_name(mm.PATH_FP8, mm.gemm_default_config(mm.PATH_FP8, M, N, K))
+    assert name(4096, 4096, 4096) == name(8192, 8192, 4096) == "fp8_256x256x128_8w128x64_dma"
+    for shape in [(4096, 2048, 4096), (2048, 4096, 4096), (8192, 1024, 4096), (3712, 2176, 896)]:
+        assert name(*shape).startswith("fp8_128x128x128"), shape
+    for shape in [(1040, 2294, 2756), (512, 512, 512), (1474, 1051, 96), (4096, 3072, 128)]:
+        assert name(*shape).startswith("fp8_64x64x"), shape
