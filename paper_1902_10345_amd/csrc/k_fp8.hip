@@ -1005,7 +1005,7 @@ __global__ __launch_bounds__(256) void encode_kernel(int64_t n, const float *__r
 size_t fp8_ws_bytes(int64_t M, int64_t N, int64_t K) { return fp8::layout(M, N, K).total; }
 int64_t fp8_kp(int64_t K) { return fp8::layout(0, 0, K).Kp; }
 
-// Row quantisation (Kp > 4096): R rows of K binary32 values (row stride ld) -> per-row
+// Row quantisation on its own: R rows of K binary32 values (row stride ld) -> per-row
 // scales and codes in rows of Kp bytes (k contiguous).  zero: nzero words that
 // the launch also clears when its grid has a thread for each (for a later
 // quant_cols on the same stream); *cleared tells whether it did.
@@ -1028,6 +1028,10 @@ static gemm_status quant_rows(int64_t R, int64_t K, int64_t Kp, const float *P, 
                          0, s, (int)R, (int)K, Kp, P, ld, q, scales, zero, nzero);               \
   } while (0)
   switch (ch) {
+    case 1: MM_QROWS(1); break;
+    case 2: MM_QROWS(2); break;
+    case 3: MM_QROWS(3); break;
+    case 4: MM_QROWS(4); break;
     case 5: MM_QROWS(5); break;
     case 6: MM_QROWS(6); break;
     case 7: MM_QROWS(7); break;
@@ -1105,6 +1109,18 @@ gemm_status fp8_quantize_run(int64_t M, int64_t N, int64_t K, const float *A, in
 #undef MM_QPAIR
       return check_launch("quant_pair_kernel");
     };
+    // Many rows of A: A on its own first, a workgroup to a row.  Behind the columns
+    // of B in one launch its codes and C meet in fewer lines of the caches when the
+    // product reads them (us with the product, beta 0 / 0.5, on its own / in one launch:
+    // 16384 x 4096 x 4096 323 / 393, 323 / 426, 16384 x 4096 x 1024 125 / 206, 125 / 215,
+    // 8192^2 x 4096 328 / 406, 346 / 408, 8192 x 4096 x 4096 176 / 217, 178 / 226, 6144 x 4096 x
+    // 4096 153 / 179, 156 / 182; but 4096^3 102 / 121, 100 / 117, 6144^2 x 4096 224 / 264, 218 /
+    // 253, 4096 x 8192 x 4096 196 / 234, 190 / 233).
+    if (!ta && !tb && L.Kp > 512 && M * L.Kp >= (1 << 24) && (M >= 8192 || M > N) &&
+        M <= kMaxLanes / 256) {
+      if (gemm_status st = quant_rows(M, K, L.Kp, A, lda, qa, sa, s)) return st;
+      return launch(blocks0, 0);  // (ja: the columns of B)
+    }
     // (a launch each where one does not hold both)
     if (blocks0 + blocks1 <= kMaxLanes / 1024) return launch(blocks0, blocks1);
     if (gemm_status st = launch(blocks0, 0)) return st;

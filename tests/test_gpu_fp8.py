@@ -391,3 +391,35 @@ def test_group_products_truncate_toward_zero_on_the_group_grid():
         got = dC.cpu().numpy()[:, 0].astype(np.float64)
         print(mm.gemm_config_name(mm.PATH_FP8, cfg), "got - model:", got - model)
         assert np.array_equal(got, model), (cfg, got - model)
+
+
+@pytest.mark.parametrize("K,lda", [(2048, 2048), (1999, 2003), (3100, 3100), (4096, 4100)])
+def test_many_rows_quantise_as_their_parts(K, lda):
+    """Operands with many rows are quantised in a launch of their own: the codes and
+    scales are those of parts of 4096 rows, which go with the columns in one."""
+    import torch
+    import paper_1902_10345_amd as mm
+    M, N = 8192 + 3, 100
+    g = torch.Generator(device="cuda")
+    g.manual_seed(K)
+    A = torch.randn(M, lda, generator=g, device="cuda")
+    B = torch.randn(K, N, generator=g, device="cuda")
+    A[5, 7], A[4099, :] = float("nan"), 0.0
+
+    def quantised(a):
+        m = a.shape[0]
+        nbytes = mm.gemm_fp8_workspace_bytes(m, N, K)
+        ws = torch.full((nbytes,), 0x55, dtype=torch.uint8, device="cuda")
+        mm.fp8_quantize(m, N, K, a, lda, B, N, ws, nbytes)
+        L = mm.fp8_workspace_layout(m, N, K)
+        rows = ws[L["qa"]:L["qa"] + m * L["Kp"]].view(m, L["Kp"])
+        return (rows, ws[L["sa"]:L["sa"] + 4 * m], ws[L["qb"]:L["qb"] + N * L["Kp"]],
+                ws[L["sb"]:L["sb"] + 4 * N])
+
+    whole = quantised(A)
+    for i in range(0, M, 4096):
+        n = min(4096, M - i)
+        part = quantised(A[i:i + n])
+        assert torch.equal(whole[0][i:i + n], part[0])
+        assert torch.equal(whole[1][4 * i:4 * (i + n)], part[1])
+        assert torch.equal(whole[2], part[2]) and torch.equal(whole[3], part[3])
