@@ -1238,10 +1238,10 @@ gemm_status fp8_gemm_run_cfg(int64_t M, int64_t N, int64_t K, float alpha, const
 // the CUs idle, and 0.03 per tile for C; 128 x 128 tiles, in one round of at most two
 // per CU, 0.54 per slab alone on a CU and 0.84 in pairs; 64 x 64 tiles 0.2 per slab and
 // tile of a CU, a shorter start and end (a lane's 16 results instead of 128), and 3 more
-// beyond the five of a CU.  Rows of C that are no whole 64-byte pieces cost the larger
-// tiles more.  Fitted on 420 shapes of 100 to 12 000: 0.6 % behind the fastest on
-// average; 2 % behind the rule on tile counts (256 x 256 where they fill the CUs and else
-// 128 x 128) for one.  Without quantisation, 256 / 128 / 64: 4096^3 61 / 69 / 100, 3072^2 x
+// and 0.0015 per tile beyond the five of a CU.  Rows of C that are no whole 64-byte pieces cost the larger
+// tiles more.  Fitted on 580 shapes of 100 to 65 536: 0.9 % behind the fastest on
+// average, and for three of them 2 % or more behind the rule on tile counts (256 x 256 where
+// they fill the CUs and else 128 x 128).  Without quantisation, 256 / 128 / 64: 4096^3 61 / 69 / 100, 3072^2 x
 // 4096 48 / 57 / 60, 4096 x 2048 x 4096 48 / 37 / 52 (52 before 128 x 128 tiles were among the
 // choices), 2048^3 31 / 18 / 16, 2943 x 2566 x 766 28 / 25 / 21, 4096 x 3072 x 128 14 / 14 /
 // 12.  With at most three 64 x 64 tiles for two CUs, the ring of four stages (512^3 5.1 ->
@@ -1261,7 +1261,7 @@ int fp8_default_config(int64_t M, int64_t N, int64_t K) {
   const double us64 = t64 > (double)(kMaxLanes / 256)
                           ? 1e30
                           : 3.0 + 0.0008 * cus * slabs * std::ceil(t64 / cus) +
-                                (t64 > 5.0 * cus ? 3.0 : 0.0);
+                                (t64 > 5.0 * cus ? 3.0 + 0.0015 * (t64 - 5.0 * cus) : 0.0);
   // (a panel of codes stays below 2^31 bytes)
   const bool fits256 = K <= ((int64_t)1 << 23) - 256, fits128 = K <= ((int64_t)1 << 24) - 256;
   if (fits128 && us128 <= us256 && us128 <= us64) return 3;
