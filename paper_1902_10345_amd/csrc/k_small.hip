@@ -240,7 +240,9 @@ constexpr int chunk_k(bool staged) {
 // Bound: a wave's chain of chunks (two to four waves per SIMD), each wanting
 // its loads to arrive and its share of the L1's address rate; SETS - 1 chunks
 // of loads are in flight while one is multiplied.
-template <int BM, int BN, int NP, bool STAGED, bool TA, bool TB, bool BETA>
+// FEW: row-major A of at most eight rows is read directly also where B is staged: its
+// rows are few enough for the L1, and turning them through LDS is a detour.
+template <int BM, int BN, int NP, bool STAGED, bool FEW, bool TA, bool TB, bool BETA>
 __global__ __launch_bounds__(64 * KW) void gemm_small_kernel(
     int M, int N, int K, float alpha, const float *__restrict__ A, int lda, int bytes_a,
     const float *__restrict__ B, int ldb, int bytes_b, float beta, float *__restrict__ C,
@@ -252,7 +254,7 @@ __global__ __launch_bounds__(64 * KW) void gemm_small_kernel(
   constexpr int SETS = STAGED ? (BM == 32 ? 2 : 3) : (FM * CK > 16 ? 3 : 4);
   constexpr int BLK = 16 * 64;  // floats of one 32 x 32 accumulator block
   constexpr Read kc = STAGED ? Read::kStaged : Read::kDirect;
-  using OpA = Operand<TA ? Read::kRows : kc, FM, CK, SETS, E>;
+  using OpA = Operand<TA ? Read::kRows : FEW ? Read::kDirect : kc, FM, CK, SETS, E>;
   using OpB = Operand<TB ? kc : Read::kRows, FN, CK, SETS, E>;
   constexpr int TOT = FM * FN * BLK;            // floats of a partial tile
   constexpr int STG = OpA::LDS_FLOATS + OpB::LDS_FLOATS;
@@ -459,17 +461,24 @@ gemm_status launch(const GemmArgs &g, hipStream_t s) {
   // them the bits of the result, are the same for every transpose flag (TN,
   // which has nothing to turn, takes the same chunks).
   const bool staged = g.K >= 1024;
+  // (the same ranges with A read directly: 3 x 6816 x 1920 10.9 -> 10.6 us, 1 x 4000 x 1500 7.5
+  // -> 7.1; at sixteen rows 11.3 -> 11.5, 7.9 -> 8.3)
+  const bool few = BM == 32 && staged && !g.ta && g.M <= 8;
   const bool deal = tiles_m <= 8 && !g.tb && g.ldb % 1024 == 0;
   const bool beta = g.beta != 0.0f;
   const dim3 grid((unsigned)(tiles_m * tiles_n)), block(64 * KW);
-#define MM_SMALL(ST, TA, TB, BT)                                                                   \
-  hipLaunchKernelGGL((gemm_small_kernel<BM, BN, NP, ST, TA, TB, BT>), grid, block, 0, s, (int)g.M, \
-                     (int)g.N, (int)g.K, g.alpha, g.A, (int)g.lda, (int)ea, g.B, (int)g.ldb,       \
-                     (int)eb, g.beta, g.C, g.ldc, (int)tiles_m, (int)tiles_n, deal)
-#define MM_SMALL_BETA(ST, TA, TB) \
-  do { if (beta) MM_SMALL(ST, TA, TB, true); else MM_SMALL(ST, TA, TB, false); } while (0)
-#define MM_SMALL_ST(TA, TB) \
-  do { if (staged) MM_SMALL_BETA(true, TA, TB); else MM_SMALL_BETA(false, TA, TB); } while (0)
+#define MM_SMALL(ST, FEW, TA, TB, BT)                                                             \
+  hipLaunchKernelGGL((gemm_small_kernel<BM, BN, NP, ST, FEW, TA, TB, BT>), grid, block, 0, s,     \
+                     (int)g.M, (int)g.N, (int)g.K, g.alpha, g.A, (int)g.lda, (int)ea, g.B,         \
+                     (int)g.ldb, (int)eb, g.beta, g.C, g.ldc, (int)tiles_m, (int)tiles_n, deal)
+#define MM_SMALL_BETA(ST, FEW, TA, TB) \
+  do { if (beta) MM_SMALL(ST, FEW, TA, TB, true); else MM_SMALL(ST, FEW, TA, TB, false); } while (0)
+#define MM_SMALL_ST(TA, TB)                                       \
+  do {                                                            \
+    if (few) MM_SMALL_BETA(true, (BM == 32 && !TA), TA, TB);      \
+    else if (staged) MM_SMALL_BETA(true, false, TA, TB);          \
+    else MM_SMALL_BETA(false, false, TA, TB);                     \
+  } while (0)
   if (g.ta) { if (g.tb) MM_SMALL_ST(true, true); else MM_SMALL_ST(true, false); }
   else      { if (g.tb) MM_SMALL_ST(false, true); else MM_SMALL_ST(false, false); }
 #undef MM_SMALL_ST

@@ -170,3 +170,12 @@ def test_transpose_flags_return_the_same_bits(M, N, K, path, n):
             outs.append(C)
     for C in outs[1:]:
         assert torch.equal(C, outs[0])
+
+
+@pytest.mark.parametrize("M", [1, 7, 8, 9])
+@pytest.mark.parametrize("N,K", [(70, 1024), (33, 4099)])
+@pytest.mark.parametrize("path,n", [("f32", 3), ("3xbf16", 3), ("3xbf16", 6)])
+def test_few_rows_read_directly_keep_the_bits(M, N, K, path, n):
+    """A of up to eight rows is not turned through LDS: the sums are those of a
+    transposed A, which never is."""
+    test_transpose_flags_return_the_same_bits(M, N, K, path, n)
