@@ -81,7 +81,7 @@ double tile_time(const TileCost &t, int64_t M, int64_t N, int64_t K) {
   const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
   const double steps = (double)((K + 15) / 16);
   const int64_t rest = tiles % slots, deep = (rest + cus - 1) / cus;  // workgroups per CU of the rest
-  double us = (double)(tiles / slots) * (t.fixed + t.full * steps);
+  double us = t.start + (double)(tiles / slots) * (t.fixed + t.full * steps);
   if (rest > 0)
     us += t.fixed + steps * (t.per_cu > 1 ? t.alone + (t.full - t.alone) * (double)(deep - 1) /
                                                           (double)(t.per_cu - 1)

@@ -427,26 +427,30 @@ int bx3_num_configs() { return (int)(sizeof(kBx3Configs) / sizeof(kBx3Configs[0]
 const TileConfig &bx3_config(int i) { return kBx3Configs[i].t; }
 int bx3_config_products(int i) { return kBx3Configs[i].np == 2 ? 3 : 6; }
 
-// The default: the configuration with the least modelled time (tile_time).
-// Costs fitted on 47 shapes of 0.3 to 4.5 thousand per dimension, whole and
-// ragged, every configuration timed on inputs that change from call to call.
-// Against the rules on tile counts that the library had (256 x 256 tiles only
-// when they fill every CU), us: three products 3500^3 369 -> 240, 3800 x 4000 x
-// 1000 102 -> 86, 1280 x 1045 x 3712 75 -> 62; six products 3500^3 665 -> 416,
-// 2500^3 237 -> 167, 2516 x 2228 x 208 31 -> 21, 2048^3 101 -> 90.
+// The default: the configuration with the least modelled time (tile_time) among
+// those whose sums are short enough.  Costs fitted on 434 shapes (six products 254)
+// of 32 to 8192 per dimension, whole and ragged, every configuration timed on inputs
+// that change from call to call: the choice is 0.5 % (0.2 %) behind the fastest on
+// average, costs fitted on long K alone were 3.0 % (0.8 %) behind, with short K the
+// furthest off (1680 x 1792 x 96 13.2 us, now 8.0; six products 2618 x 3313 x 464 73, now
+// 53), and a rule on tile counts 3.2 % (1.9 %), with tiles that do not fill the machine
+// the furthest (256 x 256 ones only where they fill every CU: 3500^3 369 us, 240 by
+// time; six products 665, 416).
 int bx3_default_config(int64_t M, int64_t N, int64_t K, int n_products) {
   const int64_t cus = num_cus();
   auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-  static const TileCost k3[] = {{0, 256, 256, 1, 10.0, 1.05, 1.05}, {2, 256, 128, 1, 7.0, 0.65, 0.65},
-                                {8, 128, 128, 2, 2.5, 0.50, 0.78},  {14, 128, 128, 1, 4.0, 0.39, 0.39},
-                                {6, 64, 64, 5, 2.0, 0.24, 0.80},    {18, 64, 64, 2, 1.0, 0.235, 0.255},
-                                {10, 64, 64, 1, 3.4, 0.152, 0.152}, {9, 32, 32, 2, 1.2, 0.09, 0.11}};
-  static const TileCost k6[] = {{4, 256, 256, 1, 15.0, 1.78, 1.78}, {17, 256, 128, 1, 8.0, 1.0, 1.0},
-                                {15, 128, 128, 2, 3.0, 0.82, 1.2},  {16, 128, 128, 1, 3.0, 0.63, 0.63},
-                                {12, 64, 64, 1, 3.0, 0.20, 0.20},   {11, 32, 32, 2, 1.5, 0.11, 0.135}};
+  static const TileCost k3[] = {
+      {0, 256, 256, 1, 10.03, 0.927, 1.35, 0.0},  {2, 256, 128, 1, 6.38, 0.622, 0.699, 0.0},
+      {8, 128, 128, 2, 3.57, 0.461, 0.712, 1.92}, {14, 128, 128, 1, 3.88, 0.339, 0.407, 2.25},
+      {6, 64, 64, 5, 3.45, 0.205, 0.651, 2.48},   {18, 64, 64, 2, 2.28, 0.186, 0.28, 3.04},
+      {10, 64, 64, 1, 2.72, 0.143, 0.147, 2.52},  {9, 32, 32, 2, 1.09, 0.055, 0.111, 3.56}};
+  static const TileCost k6[] = {
+      {4, 256, 256, 1, 5.44, 1.9, 2.267, 1.74},    {17, 256, 128, 1, 5.91, 1.016, 1.167, 1.75},
+      {15, 128, 128, 2, 2.2, 0.685, 1.189, 2.73},  {16, 128, 128, 1, 4.34, 0.546, 0.676, 1.58},
+      {12, 64, 64, 1, 3.08, 0.169, 0.2, 2.58},     {11, 32, 32, 2, 1.27, 0.071, 0.138, 3.14}};
   // 512 whole 64 x 64 tiles in at most half as many 128 x 128 ones as there are
-  // CUs keep the 64 x 64 LDS tile, a documented default (2048 x 1024 x 4096: 89
-  // us; configuration 18 takes 70)
+  // CUs keep the 64 x 64 LDS tile, which the host tests name for 2048 x 1024 x
+  // 4096 (89 us; configuration 18 takes 70)
   if (n_products == 3 && M % 128 == 0 && N % 128 == 0 && 2 * tiles(128, 128) <= cus &&
       tiles(64, 64) >= 2 * cus)
     return 6;

@@ -269,17 +269,20 @@ int f32_num_configs() { return (int)(sizeof(kF32Configs) / sizeof(kF32Configs[0]
 const TileConfig &f32_config(int i) { return kF32Configs[i]; }
 
 // The default: the matrix-core or small-product tile with the least modelled
-// time (tile_time; costs fitted as the split path's).  Against rules on tile
-// counts alone, us: 3500^3 857 -> 720, 4500^3 2134 -> 1500, 1216 x 3840 x 2224
+// time (tile_time) among those whose sums are short enough; costs fitted as the split
+// path's, on 264 shapes: 0.2 % behind the fastest tile on average (1.3 % with costs
+// fitted on long K: 400 x 1760 x 336 11.2 us, now 9.5; 1216 x 592 x 4026 stays the furthest
+// off, 68 for 59).  Against rules on tile counts alone, us: 3500^3 857 -> 720, 4500^3 2134 -> 1500, 1216 x 3840 x 2224
 // 271 -> 196, 1280 x 1045 x 3712 128 -> 108, 6000 x 4000 x 2000 943 -> 718.
 int f32_default_config(int64_t M, int64_t N, int64_t K) {
   const int64_t cus = num_cus();
   const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128);
-  static const TileCost kCosts[] = {{5, 256, 256, 1, 8.0, 3.8, 3.8},  {6, 128, 128, 2, 4.0, 1.15, 1.95},
-                                    {9, 128, 128, 1, 4.0, 1.04, 1.04}, {8, 64, 64, 1, 3.0, 0.275, 0.275},
-                                    {7, 32, 32, 2, 1.3, 0.14, 0.165}};
+  static const TileCost kCosts[] = {
+      {5, 256, 256, 1, 6.93, 3.806, 3.843, 0.0},  {6, 128, 128, 2, 0.78, 1.119, 1.966, 3.5},
+      {9, 128, 128, 1, 4.46, 1.014, 1.006, 1.61}, {8, 64, 64, 1, 4.12, 0.221, 0.252, 1.57},
+      {7, 32, 32, 2, 0.84, 0.07, 0.152, 3.82}};
   // whole 128 x 128 tiles, more than one and at most two per CU, keep the 128 x
-  // 128 tile, a documented default (2560 x 2048 x 2048: 255 us; the 64 x 64
+  // 128 tile, which the host tests name for 2560 x 2048 x 2048 (255 us; the 64 x 64
   // small tiles take 191)
   if (M % 128 == 0 && N % 128 == 0 && t128 > cus && t128 <= 2 * cus) return 6;
   // The tiles whose sums run over all of K or half of it only where the

@@ -31,13 +31,14 @@ struct TileConfig {
   }
 };
 
-// A tile configuration's time, for the choice among configurations: `fixed` us
-// per round of workgroups plus, per 16 k, `alone` us with one workgroup on each
-// compute unit up to `full` with per_cu of them (linear between).  Whole rounds
-// of per_cu workgroups per compute unit, then the remainder.
+// A tile configuration's time, for the choice among configurations: `start` us,
+// then `fixed` us per round of workgroups plus, per 16 k, `alone` us in a round with
+// one workgroup on each compute unit at most, up to `full` with per_cu of them
+// (linear between; with per_cu 1 `full` is a round on every compute unit).  Whole
+// rounds of per_cu workgroups per compute unit, then the remainder.
 struct TileCost {
   int cfg, bm, bn, per_cu;
-  double fixed, alone, full;
+  double fixed, alone, full, start;
 };
 double tile_time(const TileCost &t, int64_t M, int64_t N, int64_t K);
 // The default configuration of `path` for g, or, where 32-bit offsets of that

@@ -508,3 +508,15 @@ def test_default_fp8_tiles_by_modelled_time():
         assert name(*shape).startswith("fp8_128x128x128"), shape
     for shape in [(1040, 2294, 2756), (512, 512, 512), (1474, 1051, 96), (4096, 3072, 128)]:
         assert name(*shape).startswith("fp8_64x64x"), shape
+
+
+def test_default_tiles_of_short_k():
+    """Shapes of a short K, whose time is a tile's start and end."""
+    import paper_1902_10345_amd as mm
+
+    def name(path, M, N, K):
+        return mm.gemm_config_name(path, mm.gemm_default_config(path, M, N, K))
+    assert name(mm.PATH_3XBF16, 1680, 1792, 96) == "bx3_128x128x16_2x4w64x64_p3_kg2"
+    assert name(mm.PATH_3XBF16, 3088, 2736, 144) == "bx3_256x256x16_8w128x64_p3"
+    assert name(mm.PATH_3XBF16, 254, 2736, 336).startswith("bx3_small")
+    assert name(mm.PATH_F32, 400, 1760, 336) == "f32_small_32x32_8wk"
