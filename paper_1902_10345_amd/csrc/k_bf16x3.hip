@@ -188,7 +188,9 @@ __global__ __launch_bounds__(256) void split_kernel(int64_t n, const float *__re
 // -> 53.9 us.  The same hint on the operand loads was slower.
 constexpr int kStoreNT = 2;
 
-template <int NP, bool BETA, bool TILED>
+// WHOLE: M a multiple of 32, no rows of C to skip (binary32 32 x 32 x 2 x 10 416 with
+// beta 16.3 -> 15.5 us).
+template <int NP, bool BETA, bool TILED, bool WHOLE>
 __global__ __launch_bounds__(256) void small_batched_bx3_kernel(
     int M, int N, int K, float alpha, const float *__restrict__ A, int64_t lda, int64_t sa,
     const float *__restrict__ B, int64_t ldb, int64_t sb, float beta, float *__restrict__ C,
@@ -262,9 +264,11 @@ __global__ __launch_bounds__(256) void small_batched_bx3_kernel(
         b[e] = ld(rB, in && lr < Nr ? bcol + kk * ldb4 : (int)0x80000000, 0);
       };
       // branches around loads that neither lane group needs: worth their cost
-      // only where they save several of the eight (at K = 59, where they save
-      // none, 32 x 32 x 6798 with three products 43 -> 36 us without them)
-      if (K > (NP == 1 ? 10 : 6)) {
+      // only where they save most of the eight (three products, us without / with:
+      // 12 x 32 x 25 423 at K = 2 8.8 / 8.0, 32 x 32 x 8522 at K = 6 8.7 / 9.6, 7 x 9 x 50 000
+      // at K = 6 15.0 / 19.4; binary32, whose lane group 1 begins at k = 4, saves more: 7 x
+      // 9 at K = 10 22.7 / 21.8)
+      if (K > (NP == 1 ? 10 : 3)) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) element(e);
       } else {
@@ -330,7 +334,7 @@ __global__ __launch_bounds__(256) void small_batched_bx3_kernel(
   if (BETA) {
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-      if (8 * q < Mr) {
+      if (WHOLE || 8 * q < Mr) {
 #pragma unroll
         for (int e = 4 * q; e < 4 * q + 4; ++e)
           cold[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
@@ -339,7 +343,7 @@ __global__ __launch_bounds__(256) void small_batched_bx3_kernel(
   }
 #pragma unroll
   for (int q = 0; q < 4; ++q)
-    if (8 * q < Mr) {
+    if (WHOLE || 8 * q < Mr) {
 #pragma unroll
       for (int e = 4 * q; e < 4 * q + 4; ++e) {
         float v = alpha * acc[e];
@@ -371,12 +375,15 @@ gemm_status launch_small_batched(const GemmArgs &g, int64_t sa, int64_t sb, int6
   }
   const bool beta = g.beta != 0.0f;
   const dim3 grid((unsigned)((units + 3) / 4)), block(256);
-#define MM_LAUNCH(BT, TILED)                                                                     \
-  hipLaunchKernelGGL((small_batched_bx3_kernel<NP, BT, TILED>), grid, block, 0, s,                 \
+#define MM_LAUNCH(BT, TILED, WHOLE)                                                              \
+  hipLaunchKernelGGL((small_batched_bx3_kernel<NP, BT, TILED, WHOLE>), grid, block, 0, s,          \
                      (int)g.M, (int)g.N, (int)g.K, g.alpha, g.A, g.lda, sa, g.B, g.ldb, sb,        \
                      g.beta, g.C, g.ldc, sc, batch, (int)tiles_m, (int)tiles_n)
-  if (tiles_m * tiles_n > 1) { if (beta) MM_LAUNCH(true, true); else MM_LAUNCH(false, true); }
-  else                       { if (beta) MM_LAUNCH(true, false); else MM_LAUNCH(false, false); }
+#define MM_LAUNCH_ROWS(BT, TILED) \
+  do { if (g.M % 32 == 0) MM_LAUNCH(BT, TILED, true); else MM_LAUNCH(BT, TILED, false); } while (0)
+  if (tiles_m * tiles_n > 1) { if (beta) MM_LAUNCH_ROWS(true, true); else MM_LAUNCH_ROWS(false, true); }
+  else { if (beta) MM_LAUNCH_ROWS(true, false); else MM_LAUNCH_ROWS(false, false); }
+#undef MM_LAUNCH_ROWS
 #undef MM_LAUNCH
   return check_launch("small_batched_bx3_kernel");
 }
