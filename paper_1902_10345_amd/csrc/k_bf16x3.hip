@@ -575,30 +575,46 @@ gemm_status f32mfma_run(const GemmArgs &g, int which, hipStream_t s) {
 
 // Batched-strided products: the tile with the least modelled time beyond the
 // operands' traffic, which every tile has in common: `fixed` ns per output
-// tile and `step` ns per tile and 16-deep k-step, whole machine, fitted on 46
-// batches whose inputs change from call to call (4 to 512 per dimension, 10 to
-// 190 MB).  The batch takes whole rounds of the workgroups that fit the
-// machine at once while there are few rounds; a round that is not full runs
-// somewhat faster.  Against the tile chosen by the stacked problem's size alone
-// (256 x 256 tiles for any large batch), binary32 / three / six products, us:
-// 100 x 72 x 90 x 2000 232 -> 70, 97 -> 54, 137 -> 55; 144 x 8 x 9 x 5403 217
-// -> 20, 153 -> 18, 236 -> 18; 300^3 x 100 162 -> 67, 50 -> 48, 75 -> 55.
+// tile and `step` ns per tile and 16-deep k-step, whole machine.  The batch takes whole
+// rounds of the workgroups that fit the machine at once while there are few rounds; of a
+// round that is not full, `part` is its latency and the rest goes with the tiles.
+// `ragged`: where rows of C are no whole 64-byte pieces, sub-tiles of one wave each
+// write parts of lines (three products, 53 x 59 x 24 x 2398 17.3 us, 64 x 64 tiles 12.3).
+// Fitted on 390 batches a mode (16 to 2000 per dimension, 8 to 400 MB), every tile timed
+// on inputs that change from call to call: the choice is 1.2 to 1.3 % behind the fastest
+// on average, with costs fitted on 46 batches it was 3.5 to 4.3 %.  Against the
+// tile chosen by the stacked problem's size alone (256 x 256 tiles for any large batch),
+// binary32 / three / six products, us: 100 x 72 x 90 x 2000 232 -> 70, 101 -> 53, 135 ->
+// 55; 144 x 8 x 9 x 5403 217 -> 20, 153 -> 18, 236 -> 18; 300^3 x 100 163 -> 65, 55 -> 47, 84 ->
+// 55.
 namespace {
 struct BatchTile {
   TileConfig t;                // output tile
   int per_cu;                  // tiles per compute unit at once
   double fixed[3], step[3];    // ns: binary32, three products, six products
+  double part[3];
 };
 constexpr BatchTile kBatchTiles[kBatchedTiles] = {
-    {{32, 32, 16, "direct", 64}, 20, {0.1, 0.2, 0.1}, {0.30, 0.14, 0.21}},    // kBatchedDirect
-    {{64, 64, 32, "lds64", 256}, 4, {1.5, 2.5, 5.0}, {1.25, 0.28, 0.42}},     // kBatched64
-    {{128, 128, 16, "lds128", 256}, 2, {3.7, 6.0, 4.0}, {3.05, 0.55, 1.40}},   // kBatched128
-    {{256, 256, 16, "lds256", 512}, 1, {8.0, 8.0, 8.0}, {12.3, 2.3, 5.0}},     // kBatched256
+    // kBatchedDirect, 64, 128, 256
+    {{32, 32, 16, "direct", 64}, 20, {0.036, 0.168, 0.136}, {0.264, 0.14, 0.203}, {0.5, 0.33, 0.44}},
+    {{64, 64, 32, "lds64", 256}, 4, {9.37, 2.51, 7.11}, {1.985, 0.195, 0.6}, {0.15, 0.54, 0.15}},
+    {{128, 128, 16, "lds128", 256}, 2, {2.4, 6.64, 5.78}, {3.36, 0.507, 1.286}, {0.75, 0.48, 0.9}},
+    {{256, 256, 16, "lds256", 512}, 1, {13.5, 25.4, 38.6}, {13.2, 1.32, 3.66}, {0.6, 0.9, 0.9}},
 };
+// `ragged` of a sub-tile, in problems of one 64 x 64 tile, of one 128 x 128 tile
+// (and per step) and in wider ones
+constexpr double kRagged64[3] = {1.0, 2.0, 0.0}, kRagged128[3] = {0.0, 0.23, 0.29},
+                 kRagged128Step[3] = {0.051, 0.0, 0.0}, kRaggedWide[3] = {0.25, 0.22, 0.215};
 }  // namespace
 
 int batched_config(int path, int n_products, int64_t M, int64_t N, int64_t K, int64_t batch) {
   const int mode = path == GEMM_PATH_F32 ? 0 : n_products == 6 ? 2 : 1;
+  const double steps = (double)((K + 15) / 16);
+  double ragged = 0.0;
+  if (N % 16 != 0 && N > 64)
+    ragged = M <= 128 && N <= 128 ? kRagged128[mode] + kRagged128Step[mode] * steps : kRaggedWide[mode];
+  else if (N % 16 != 0 && N > 48 && M > 32 && M <= 64)
+    ragged = kRagged64[mode];
   int best = kBatchedDirect;
   double best_cost = 0.0;
   for (int c = 0; c < kBatchedTiles; ++c) {
@@ -607,8 +623,9 @@ int batched_config(int path, int n_products, int64_t M, int64_t N, int64_t K, in
                          (double)batch;
     const double slots = (double)num_cus() * t.per_cu;
     const double r = tiles / slots;
-    const double rounds = r > 4.0 ? r : r >= 1.0 ? std::ceil(r) : 0.5 + 0.5 * r;
-    const double cost = rounds * slots * (t.fixed[mode] + t.step[mode] * (double)((K + 15) / 16));
+    const double rounds = r > 4.0 ? r : r >= 1.0 ? std::ceil(r) : t.part[mode] + (1.0 - t.part[mode]) * r;
+    const double cost = rounds * slots * (t.fixed[mode] + (c == kBatchedDirect ? ragged : 0.0) +
+                                          t.step[mode] * steps);
     if (c == 0 || cost < best_cost) { best = c; best_cost = cost; }
   }
   return best;
