@@ -554,7 +554,7 @@ gemm_status gemm_strided_batched(int path, int64_t M, int64_t N, int64_t K, floa
   if (alpha == 0.0f || K == 0) return scale_c_batched(M, N, beta, C, ldc, stride_c, batch, stream);
   if (!A) return bad_arg(6, fn, "(A) is NULL");
   if (!B) return bad_arg(9, fn, "(B) is NULL");
-  const int cfg = batched_config(path, n_products, M, N, K, batch);
+  const int cfg = batched_config(path, n_products, M, N, K, batch, beta != 0.0f);
   for (int64_t b0 = 0; b0 < batch; b0 += 65535) {
     const int nb = (int)std::min<int64_t>(65535, batch - b0);
     GemmArgs g{M, N, K, alpha, beta, A + b0 * stride_a, lda, B + b0 * stride_b, ldb,

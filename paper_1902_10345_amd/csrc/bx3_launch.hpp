@@ -123,8 +123,8 @@ __global__ __launch_bounds__(64 * NW, 1) void gemm_batched_kernel(
     int64_t ldc, int64_t sc, int tiles_m, int tiles_n) {
   using G = Cfg<BM, BN, BK, WM, WN, NP, NW>;
   __shared__ __attribute__((aligned(16))) __bf16 lds[G::LDS_BYTES / 2];
-  const int wg = xcd_remap(blockIdx.x, gridDim.x);
   const int tiles = tiles_m * tiles_n;
+  const int wg = tiles > 1 ? xcd_remap(blockIdx.x, gridDim.x) : (int)blockIdx.x;
   const int64_t b = wg / tiles;
   int tm, tn;
   tile_coords(wg - (int)b * tiles, tiles_m, tiles_n, 8, tm, tn);

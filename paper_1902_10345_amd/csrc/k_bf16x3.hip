@@ -164,7 +164,7 @@ __global__ __launch_bounds__(256) void split_kernel(int64_t n, const float *__re
 }
 
 // ---- batched small problems --------------------------------------------------
-// One wave per 32 x 32 sub-tile of a problem, four waves per workgroup,
+// One wave per 32 SB x 32 SB sub-tile of a problem, four waves per workgroup,
 // the sub-tiles of a problem on consecutive waves (its panels meet in the L1
 // and L2 of one CU).  The operands go from memory straight into MFMA fragments
 // (and are split in registers, NP = 2 or 3 planes; NP = 1 is binary32 on the
@@ -188,9 +188,13 @@ __global__ __launch_bounds__(256) void split_kernel(int64_t n, const float *__re
 // -> 53.9 us.  The same hint on the operand loads was slower.
 constexpr int kStoreNT = 2;
 
+// SB = 2 takes whole problems of up to 64 x 64, whose operands it reads once and whose
+// rows of C it writes whole (us, SB = 1 / 2: 48^3 x 5000 33.5 / 30.7 in binary32, 32.8 / 27.3 with
+// three products; 60^3 x 3000 40.6 / 33.1, 39.2 / 29.9); smaller sub-tiles fill the machine
+// better with few problems and cost less padding (33 x 64 x 20 x 5000 17.7 / 19.5, 14.4 / 13.5).
 // WHOLE: M a multiple of 32, no rows of C to skip (binary32 32 x 32 x 2 x 10 416 with
 // beta 16.3 -> 15.5 us).
-template <int NP, bool BETA, bool TILED, bool WHOLE>
+template <int SB, int NP, bool BETA, bool TILED, bool WHOLE>
 __global__ __launch_bounds__(256) void small_batched_bx3_kernel(
     int M, int N, int K, float alpha, const float *__restrict__ A, int64_t lda, int64_t sa,
     const float *__restrict__ B, int64_t ldb, int64_t sb, float beta, float *__restrict__ C,
@@ -201,15 +205,15 @@ __global__ __launch_bounds__(256) void small_batched_bx3_kernel(
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   int prob = (int)blockIdx.x * 4 + wv, m0 = 0, n0 = 0;
   if constexpr (TILED) {
-    // XCD-aware order where a problem spans several waves (its panels meet in
-    // one L2: 160^2 x 16 x 1500 39 -> 26 us); one wave per problem shares
-    // nothing (32^3 x 29 297 is 6 % faster in plain order)
+    // XCD-aware order where a problem spans several workgroups (its panels meet in
+    // one L2: 160^2 x 16 x 1500 39 -> 26 us); plain order where it does not (32^3 x
+    // 29 297 is 6 % faster so, 48^3 x 5000 in binary32 38 -> 34)
     const int tiles = tiles_m * tiles_n;
-    const int unit = xcd_remap(blockIdx.x, gridDim.x) * 4 + wv;
+    const int unit = (tiles > 4 || tiles == 3 ? xcd_remap(blockIdx.x, gridDim.x) : (int)blockIdx.x) * 4 + wv;
     prob = unit / tiles;
     const int sub = unit - prob * tiles, tm = sub / tiles_n;
-    m0 = tm * 32;
-    n0 = (sub - tm * tiles_n) * 32;
+    m0 = tm * 32 * SB;
+    n0 = (sub - tm * tiles_n) * 32 * SB;
   }
   if (prob >= batch) return;
   const int Mr = M - m0, Nr = N - n0;  // valid rows and columns of the sub-tile (may exceed it)
@@ -232,36 +236,55 @@ __global__ __launch_bounds__(256) void small_batched_bx3_kernel(
   // part is in the lane's offset, the rest in the wave-uniform offset.
   constexpr int kGroup = NP == 1 ? 4 : 8;       // first k of lane group 1
   auto koff = [](int e) { return NP == 1 ? 8 * (e >> 2) + (e & 3) : e; };
-  const int arow = lr < Mr ? (lr * (int)lda + kGroup * lg) * 4 : (int)0x80000000;
-  const int bcol = lr < Nr ? lr * 4 + kGroup * lg * ldb4 : (int)0x80000000;
-  f32x16 acc;
+  int arow[SB], bcol[SB];
+  bool col[SB];
 #pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
+  for (int i = 0; i < SB; ++i) {
+    const int x = 32 * i + lr;
+    // (out of range also 16 elements before)
+    arow[i] = x < Mr ? (x * (int)lda + kGroup * lg) * 4 : (int)0x80000040;
+    col[i] = x < Nr;
+    bcol[i] = col[i] ? x * 4 + kGroup * lg * ldb4 : (int)0x80000000;
+  }
+  f32x16 acc[SB][SB];
+#pragma unroll
+  for (int i = 0; i < SB; ++i)
+#pragma unroll
+    for (int j = 0; j < SB; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
   auto ld = [](__amdgpu_buffer_rsrc_t r, int off, int soff) {
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, soff, 0));
   };
   const int KT = (K + 15) / 16;
   const int kbase = K - KT * 16;
-  float a[8], b[8];
+  float a[SB][8], b[SB][8];
   auto load = [&](int s) {
     const int k0 = kbase + 16 * s;
     if (s > 0 || kbase == 0) {
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                      rA, arow, (k0 + koff(4 * h)) * 4, 0));
-        a[4 * h] = v.x; a[4 * h + 1] = v.y;
-        a[4 * h + 2] = v.z; a[4 * h + 3] = v.w;
-      }
+      for (int i = 0; i < SB; ++i)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) b[e] = ld(rB, bcol, (k0 + koff(e)) * ldb4);
+        for (int h = 0; h < 2; ++h) {
+          const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                        rA, arow[i], (k0 + koff(4 * h)) * 4, 0));
+          a[i][4 * h] = v.x; a[i][4 * h + 1] = v.y;
+          a[i][4 * h + 2] = v.z; a[i][4 * h + 3] = v.w;
+        }
+#pragma unroll
+      for (int j = 0; j < SB; ++j)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) b[j][e] = ld(rB, bcol[j], (k0 + koff(e)) * ldb4);
     } else {
       // the partial first step: k in [kbase, kbase + 16) with kbase < 0
       auto element = [&](int e) {
         const int kk = kbase + koff(e);  // the k of lane group 0
-        const bool in = kk + kGroup * lg >= 0;
-        a[e] = ld(rA, in && lr < Mr ? arow + kk * 4 : (int)0x80000000, 0);
-        b[e] = ld(rB, in && lr < Nr ? bcol + kk * ldb4 : (int)0x80000000, 0);
+        const bool in = kk >= -kGroup * lg;
+#pragma unroll
+        for (int i = 0; i < SB; ++i) {
+          a[i][e] = ld(rA, in ? arow[i] + kk * 4 : (int)0x80000000, 0);
+          b[i][e] = ld(rB, (int)in & (int)col[i] ? bcol[i] + kk * ldb4 : (int)0x80000000, 0);
+        }
       };
       // branches around loads that neither lane group needs: worth their cost
       // only where they save most of the eight (three products, us without / with:
@@ -274,7 +297,8 @@ __global__ __launch_bounds__(256) void small_batched_bx3_kernel(
       } else {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          a[e] = b[e] = 0.0f;
+#pragma unroll
+          for (int i = 0; i < SB; ++i) a[i][e] = b[i][e] = 0.0f;
           if (kbase + koff(e) + kGroup >= 0) element(e);
         }
       }
@@ -284,7 +308,11 @@ __global__ __launch_bounds__(256) void small_batched_bx3_kernel(
     if constexpr (NP == 1) {
 #pragma unroll
       for (int e = 0; e < 8; ++e)
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[e], acc, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < SB; ++i)
+#pragma unroll
+          for (int j = 0; j < SB; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], b[j][e], acc[i][j], 0, 0, 0);
     } else {
       // the 8 values of one block as NP bf16 planes (plane 0 the leading part)
       auto split8 = [](const float (&x)[8], bf16x8 (&pl)[NP]) {
@@ -298,11 +326,17 @@ __global__ __launch_bounds__(256) void small_batched_bx3_kernel(
           if constexpr (NP == 3) { pl[2][e] = x2.x; pl[2][e + 1] = x2.y; }
         }
       };
-      bf16x8 pa[NP], pb[NP];
-      split8(a, pa);
-      split8(b, pb);
+      bf16x8 pa[SB][NP], pb[SB][NP];
+#pragma unroll
+      for (int i = 0; i < SB; ++i) split8(a[i], pa[i]);
+#pragma unroll
+      for (int j = 0; j < SB; ++j) split8(b[j], pb[j]);
       auto prod = [&](int qa, int qb) {
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pa[qa], pb[qb], acc, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < SB; ++i)
+#pragma unroll
+          for (int j = 0; j < SB; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pa[i][qa], pb[j][qb], acc[i][j], 0, 0, 0);
       };
       // small products first, the leading product last
       if constexpr (NP == 3) {
@@ -329,29 +363,42 @@ __global__ __launch_bounds__(256) void small_batched_bx3_kernel(
   // that lie past M altogether issue nothing.  With beta != 0 every read of C
   // is issued before the first store.
   const int ldc4 = (int)ldc * 4;
-  const int vb = lr < Nr ? 4 * lg * ldc4 + lr * 4 : (int)0x80000000;
-  float cold[16];
+  int vb[SB];
+#pragma unroll
+  for (int j = 0; j < SB; ++j) vb[j] = col[j] ? 4 * lg * ldc4 + (32 * j + lr) * 4 : (int)0x80000000;
+  // (64 rows with beta: without tests, whose joins hold the stores back: 60^3 x 3000 with
+  // three products 41.5 -> 38.7 us; beta 0 33 x 64 x 20 x 5000 13.3, 13.7 without them)
+  constexpr bool kAllRows = WHOLE || (SB == 2 && BETA);
+  float cold[SB][SB][16];
   if (BETA) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      if (WHOLE || 8 * q < Mr) {
+    for (int i = 0; i < SB; ++i)
 #pragma unroll
-        for (int e = 4 * q; e < 4 * q + 4; ++e)
-          cold[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-                                                  rC, vb, (8 * q + (e & 3)) * ldc4, 0));
-      }
+      for (int q = 0; q < 4; ++q)
+        if (kAllRows || 32 * i + 8 * q < Mr) {
+#pragma unroll
+          for (int j = 0; j < SB; ++j)
+#pragma unroll
+            for (int e = 4 * q; e < 4 * q + 4; ++e)
+              cold[i][j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                            rC, vb[j], (32 * i + 8 * q + (e & 3)) * ldc4, 0));
+        }
   }
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
-    if (WHOLE || 8 * q < Mr) {
+  for (int i = 0; i < SB; ++i)
 #pragma unroll
-      for (int e = 4 * q; e < 4 * q + 4; ++e) {
-        float v = alpha * acc[e];
-        if (BETA) v = fmaf(beta, cold[e], v);
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rC, vb,
-                                              (8 * q + (e & 3)) * ldc4, kStoreNT);
+    for (int q = 0; q < 4; ++q)
+      if (kAllRows || 32 * i + 8 * q < Mr) {
+#pragma unroll
+        for (int e = 4 * q; e < 4 * q + 4; ++e)
+#pragma unroll
+          for (int j = 0; j < SB; ++j) {
+            float v = alpha * acc[i][j][e];
+            if (BETA) v = fmaf(beta, cold[i][j][e], v);
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rC, vb[j],
+                                                  (32 * i + 8 * q + (e & 3)) * ldc4, kStoreNT);
+          }
       }
-    }
 }
 
 // Offsets of the small-problem kernel stay below 2^31: M rows of A, K rows of B,
@@ -363,26 +410,31 @@ bool small_batched_fits(const GemmArgs &g) {
          (rows * g.ldc + g.N) * 4 < lim;
 }
 
-// At most 65535 problems per launch (the caller's chunks).
-template <int NP>
+// At most 65535 problems per launch (the caller's chunks).  SB = 2: problems of up
+// to 64 x 64, one wave each.
+template <int SB, int NP>
 gemm_status launch_small_batched(const GemmArgs &g, int64_t sa, int64_t sb, int64_t sc,
                                  int batch, hipStream_t s) {
-  const int64_t tiles_m = (g.M + 31) / 32, tiles_n = (g.N + 31) / 32;
+  constexpr int kTile = 32 * SB;
+  const int64_t tiles_m = (g.M + kTile - 1) / kTile, tiles_n = (g.N + kTile - 1) / kTile;
   const int64_t units = tiles_m * tiles_n * batch;
-  if (units > kMaxLanes / 64) {
+  if (units > kMaxLanes / 64 || (SB == 2 && tiles_m * tiles_n > 1)) {
     set_error("gemm_strided_batched: too many tiles for one launch");
     return GEMM_STATUS_UNSUPPORTED;
   }
   const bool beta = g.beta != 0.0f;
   const dim3 grid((unsigned)((units + 3) / 4)), block(256);
 #define MM_LAUNCH(BT, TILED, WHOLE)                                                              \
-  hipLaunchKernelGGL((small_batched_bx3_kernel<NP, BT, TILED, WHOLE>), grid, block, 0, s,          \
+  hipLaunchKernelGGL((small_batched_bx3_kernel<SB, NP, BT, TILED, WHOLE>), grid, block, 0, s,      \
                      (int)g.M, (int)g.N, (int)g.K, g.alpha, g.A, g.lda, sa, g.B, g.ldb, sb,        \
                      g.beta, g.C, g.ldc, sc, batch, (int)tiles_m, (int)tiles_n)
 #define MM_LAUNCH_ROWS(BT, TILED) \
-  do { if (g.M % 32 == 0) MM_LAUNCH(BT, TILED, true); else MM_LAUNCH(BT, TILED, false); } while (0)
-  if (tiles_m * tiles_n > 1) { if (beta) MM_LAUNCH_ROWS(true, true); else MM_LAUNCH_ROWS(false, true); }
-  else { if (beta) MM_LAUNCH_ROWS(true, false); else MM_LAUNCH_ROWS(false, false); }
+  do { if (g.M % kTile == 0) MM_LAUNCH(BT, TILED, true); else MM_LAUNCH(BT, TILED, false); } while (0)
+  if (SB == 1 && tiles_m * tiles_n > 1) {
+    if (beta) MM_LAUNCH_ROWS(true, SB == 1); else MM_LAUNCH_ROWS(false, SB == 1);
+  } else {
+    if (beta) MM_LAUNCH_ROWS(true, false); else MM_LAUNCH_ROWS(false, false);
+  }
 #undef MM_LAUNCH_ROWS
 #undef MM_LAUNCH
   return check_launch("small_batched_bx3_kernel");
@@ -590,41 +642,48 @@ gemm_status f32mfma_run(const GemmArgs &g, int which, hipStream_t s) {
 namespace {
 struct BatchTile {
   TileConfig t;                // output tile
-  int per_cu;                  // tiles per compute unit at once
+  double per_cu[3];            // tiles per compute unit at once
   double fixed[3], step[3];    // ns: binary32, three products, six products
   double part[3];
 };
 constexpr BatchTile kBatchTiles[kBatchedTiles] = {
-    // kBatchedDirect, 64, 128, 256
-    {{32, 32, 16, "direct", 64}, 20, {0.036, 0.168, 0.136}, {0.264, 0.14, 0.203}, {0.5, 0.33, 0.44}},
-    {{64, 64, 32, "lds64", 256}, 4, {9.37, 2.51, 7.11}, {1.985, 0.195, 0.6}, {0.15, 0.54, 0.15}},
-    {{128, 128, 16, "lds128", 256}, 2, {2.4, 6.64, 5.78}, {3.36, 0.507, 1.286}, {0.75, 0.48, 0.9}},
-    {{256, 256, 16, "lds256", 512}, 1, {13.5, 25.4, 38.6}, {13.2, 1.32, 3.66}, {0.6, 0.9, 0.9}},
+    // kBatchedDirect, 64, 128, 256, kBatchedWave64
+    {{32, 32, 16, "direct", 64}, {20, 20, 20}, {0.036, 0.168, 0.136}, {0.264, 0.14, 0.203}, {0.5, 0.33, 0.44}},
+    {{64, 64, 32, "lds64", 256}, {4, 4, 4}, {9.37, 2.51, 7.11}, {1.985, 0.195, 0.6}, {0.15, 0.54, 0.15}},
+    {{128, 128, 16, "lds128", 256}, {2, 2, 2}, {2.4, 6.64, 5.78}, {3.36, 0.507, 1.286}, {0.75, 0.48, 0.9}},
+    {{256, 256, 16, "lds256", 512}, {1, 1, 1}, {13.5, 25.4, 38.6}, {13.2, 1.32, 3.66}, {0.6, 0.9, 0.9}},
+    {{64, 64, 16, "direct64", 64}, {12, 4, 8}, {2.34, 0.62, 0.655}, {0.51, 0.447, 0.361}, {0.9, 0.68, 0.9}},
 };
 // `ragged` of a sub-tile, in problems of one 64 x 64 tile, of one 128 x 128 tile
 // (and per step) and in wider ones
-constexpr double kRagged64[3] = {1.0, 2.0, 0.0}, kRagged128[3] = {0.0, 0.23, 0.29},
+constexpr double kRagged64[3] = {0.73, 0.0, 0.2}, kRagged128[3] = {0.0, 0.23, 0.29},
                  kRagged128Step[3] = {0.051, 0.0, 0.0}, kRaggedWide[3] = {0.25, 0.22, 0.215};
+// a 64 x 64 problem's wave that reads C as well: two waves per SIMD (three products, us,
+// with beta, wave / LDS tile: 60^3 x 3000 38 / 36, 64^3 x 4000 54 / 50)
+constexpr double kWave64Beta[3] = {1.5, 1.21, 1.34};
 }  // namespace
 
-int batched_config(int path, int n_products, int64_t M, int64_t N, int64_t K, int64_t batch) {
+int batched_config(int path, int n_products, int64_t M, int64_t N, int64_t K, int64_t batch,
+                   bool reads_c) {
   const int mode = path == GEMM_PATH_F32 ? 0 : n_products == 6 ? 2 : 1;
   const double steps = (double)((K + 15) / 16);
   double ragged = 0.0;
   if (N % 16 != 0 && N > 64)
     ragged = M <= 128 && N <= 128 ? kRagged128[mode] + kRagged128Step[mode] * steps : kRaggedWide[mode];
-  else if (N % 16 != 0 && N > 48 && M > 32 && M <= 64)
+  else if (N % 16 != 0 && N > 32 && M <= 64)
     ragged = kRagged64[mode];
   int best = kBatchedDirect;
   double best_cost = 0.0;
   for (int c = 0; c < kBatchedTiles; ++c) {
     const BatchTile &t = kBatchTiles[c];
+    if (c == kBatchedWave64 && (M > 64 || N > 64 || (M <= 32 && N <= 32))) continue;
     const double tiles = (double)((M + t.t.bm - 1) / t.t.bm) * (double)((N + t.t.bn - 1) / t.t.bn) *
                          (double)batch;
-    const double slots = (double)num_cus() * t.per_cu;
+    const double slots = (double)num_cus() * t.per_cu[mode];
     const double r = tiles / slots;
     const double rounds = r > 4.0 ? r : r >= 1.0 ? std::ceil(r) : t.part[mode] + (1.0 - t.part[mode]) * r;
-    const double cost = rounds * slots * (t.fixed[mode] + (c == kBatchedDirect ? ragged : 0.0) +
+    const double more = c == kBatchedWave64 && reads_c ? kWave64Beta[mode] : 1.0;
+    const double cost = more * rounds * slots * (t.fixed[mode] + (c == kBatchedDirect ? ragged : 0.0) +
                                           t.step[mode] * steps);
     if (c == 0 || cost < best_cost) { best = c; best_cost = cost; }
   }
@@ -635,7 +694,8 @@ template <int NP>
 static gemm_status batched_tile(int cfg, const GemmArgs &g, int64_t sa, int64_t sb, int64_t sc,
                                 int batch, hipStream_t s) {
   switch (cfg) {
-    case kBatchedDirect: return bx3::launch_small_batched<NP>(g, sa, sb, sc, batch, s);
+    case kBatchedDirect: return bx3::launch_small_batched<1, NP>(g, sa, sb, sc, batch, s);
+    case kBatchedWave64: return bx3::launch_small_batched<2, NP>(g, sa, sb, sc, batch, s);
     case kBatched128: return bx3::launch_batched<128, 128, 16, 64, 64, NP, 4>(g, sa, sb, sc, batch, s);
     case kBatched256: return bx3::launch_batched<256, 256, 16, 128, 64, NP, 8>(g, sa, sb, sc, batch, s);
     default: return bx3::launch_batched<64, 64, 32, 32, 32, NP, 4>(g, sa, sb, sc, batch, s);
@@ -651,6 +711,9 @@ gemm_status batched_run(int path, int cfg, const GemmArgs &g, int n_products, in
     if (kBatchTiles[c].t.per_launch(g.M, g.N) < 1) return false;
     switch (c) {
       case kBatchedDirect: return bx3::small_batched_fits(g);
+      case kBatchedWave64:  // (64 rows of C are addressed)
+        return g.M <= 64 && g.N <= 64 && bx3::small_batched_fits(g) &&
+               (64 * g.ldc + g.N) * 4 < ((int64_t)1 << 31);
       case kBatched128: return bx3::offsets_fit<128, 128, 16, false, false>(g);
       case kBatched256: return bx3::offsets_fit<256, 256, 16, false, false>(g);
       default: return bx3::offsets_fit<64, 64, 32, false, false>(g);

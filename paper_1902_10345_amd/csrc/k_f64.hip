@@ -312,8 +312,8 @@ __global__ __launch_bounds__((KG * Cfg<BM, BN, WM, WN>::NT), (Cfg<BM, BN, WM, WN
     int64_t ldc, int64_t sc, int tiles_m, int tiles_n) {
   using G = Cfg<BM, BN, WM, WN>;
   __shared__ __attribute__((aligned(16))) double lds[KG * 2 * G::STAGE];
-  const int wg = xcd_remap(blockIdx.x, gridDim.x);
   const int tiles = tiles_m * tiles_n;
+  const int wg = tiles > 1 ? xcd_remap(blockIdx.x, gridDim.x) : (int)blockIdx.x;
   const int64_t b = wg / tiles;
   int tm, tn;
   tile_coords(wg - (int)b * tiles, tiles_m, tiles_n, 8, tm, tn);
@@ -376,8 +376,8 @@ __global__ __launch_bounds__(256, 2) void small_batched_kernel(
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int tiles = tiles_m * tiles_n;
   int prob = (int)blockIdx.x * 4 + wv, m0 = 0, n0 = 0;
-  if (tiles > 1) {  // XCD-aware order: a problem's panels meet in one L2
-    const int unit = xcd_remap(blockIdx.x, gridDim.x) * 4 + wv;
+  if (tiles > 1) {  // XCD-aware order where a problem spans workgroups: its panels meet in one L2
+    const int unit = (tiles > 4 || tiles == 3 ? xcd_remap(blockIdx.x, gridDim.x) : (int)blockIdx.x) * 4 + wv;
     prob = unit / tiles;
     const int sub = unit - prob * tiles, tm = sub / tiles_n;
     m0 = tm * 16 * F;

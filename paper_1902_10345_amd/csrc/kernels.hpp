@@ -78,11 +78,12 @@ gemm_status bx3_run_splitk(const GemmArgs &g, int n_products, int splits, void *
 // binary32 matrix cores, 2 / 3 = bf16 planes per operand (3 / 6 products).
 gemm_status small_run(const GemmArgs &g, int which, int np, hipStream_t s);
 // Batched-strided products (binary32 or split precision) on the matrix cores:
-// 32 x 32 sub-tiles of one wave each, straight from memory, or LDS-staged
-// tiles of 64 x 64, 128 x 128 or 256 x 256.
+// 32 x 32 sub-tiles of one wave each, straight from memory, or problems of up to
+// 64 x 64 so, one wave each, or LDS-staged tiles of 64 x 64, 128 x 128 or 256 x 256.
 constexpr int kBatchedDirect = 0, kBatched64 = 1, kBatched128 = 2, kBatched256 = 3,
-              kBatchedTiles = 4;
-int batched_config(int path, int n_products, int64_t M, int64_t N, int64_t K, int64_t batch);
+              kBatchedWave64 = 4, kBatchedTiles = 5;
+int batched_config(int path, int n_products, int64_t M, int64_t N, int64_t K, int64_t batch,
+                   bool reads_c);
 gemm_status batched_run(int path, int cfg, const GemmArgs &g, int n_products, int64_t sa,
                         int64_t sb, int64_t sc, int batch, hipStream_t s);
 gemm_status bx3_split(int64_t n, const float *x, uint16_t *p0, uint16_t *p1, uint16_t *p2,

@@ -230,3 +230,26 @@ def test_tiles_of_medium_problems_exact(M, N, K, batch, n):
                             max(n, 3))
     assert torch.equal(C[:, :M * N].view(batch, M, N), want - 6.0)
     assert bool((C[:, M * N:] == 2.0).all())
+
+
+@pytest.mark.parametrize("M,N,K,batch", [(48, 48, 48, 700), (64, 64, 32, 900), (60, 61, 20, 2500),
+                                         (33, 64, 7, 300), (64, 33, 16, 50), (50, 50, 3, 3000)])
+@pytest.mark.parametrize("path,n", [("f32", 3), ("3xbf16", 3), ("3xbf16", 6)])
+def test_one_wave_per_problem_up_to_64(path, n, M, N, K, batch):
+    """Problems between 32 and 64 per dimension, which one wave may take whole:
+    integers, exact; beta, a padded stride of C whose gaps stay untouched."""
+    import torch
+    import paper_1902_10345_amd as mm
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M * N + K)
+    A = torch.randint(-20, 21, (batch, M, K), generator=g, device="cuda").float()
+    B = torch.randint(-20, 21, (batch, K, N), generator=g, device="cuda").float()
+    want = (A.double().cpu() @ B.double().cpu()).float().cuda()
+    sc = M * N + 5
+    C = torch.full((batch, sc), 2.0, device="cuda")
+    code = mm.PATH_F32 if path == "f32" else mm.PATH_3XBF16
+    for alpha, beta, exact in ((2.0, -3.0, 2 * want - 6.0), (1.0, 0.0, want)):
+        mm.gemm_strided_batched(code, M, N, K, alpha, A, K, M * K, B, N, K * N, beta, C, N, sc,
+                                batch, n)
+        assert torch.equal(C[:, :M * N].view(batch, M, N), exact)
+        assert bool((C[:, M * N:] == 2.0).all())
