@@ -61,7 +61,7 @@ static bool config_runs(int path, int cfg, const GemmArgs &g) {
   const bool small = f32 ? cfg == 7 || cfg == 8 : cfg >= 9 && cfg <= 12;
   const bool two_groups = f32 ? cfg == 9 : cfg == 14 || cfg == 16 || cfg == 18;
   if ((two_groups && g.K % 2 != 0) || t.per_launch(g.M, g.N) < 1) return false;
-  if ((g.ta || g.tb) && (f32 ? cfg < 5 : cfg == 1 || cfg == 7 || cfg == 13)) return false;
+  if ((g.ta || g.tb) && (f32 ? cfg < 5 : cfg == 1 || cfg == 5 || cfg == 7 || cfg == 13)) return false;
   const int64_t ra = small ? (g.ta ? g.K : g.M) : (g.ta ? t.bk : t.bm);
   const int64_t rb = small ? (g.tb ? g.N : g.K) : (g.tb ? t.bn : t.bk);
   const int64_t lim = ((int64_t)1 << 31) / 4;
@@ -515,7 +515,7 @@ gemm_status gemm_f64_strided_batched(int64_t M, int64_t N, int64_t K, double alp
   if (!A) return bad_arg(5, fn, "(A) is NULL");
   if (!B) return bad_arg(8, fn, "(B) is NULL");
   const int cfg = f64_default_config(M, N, K, batch);
-  // the grid's second dimension holds at most 65535 problems per launch
+  // the chunks of gemm_strided_batched; a launch's lanes may cut them further
   for (int64_t b0 = 0; b0 < batch; b0 += 65535) {
     const int64_t nb = std::min<int64_t>(65535, batch - b0);
     GemmArgsF64 g{M, N, K, alpha, beta, A + b0 * stride_a, lda, stride_a, B + b0 * stride_b, ldb,

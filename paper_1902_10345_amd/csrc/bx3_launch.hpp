@@ -185,7 +185,7 @@ gemm_status launch_kg(const GemmArgs &g, hipStream_t s) {
 }
 
 // The tile configurations that have transposed-operand variants: the ones the
-// library picks by default (all but 1, 7 and 13), every FP32 matrix-core tile.
+// library picks by default (all but 1, 5, 7 and 13), every FP32 matrix-core tile.
 template <bool TA, bool TB>
 gemm_status bx3_run_trans(const GemmArgs &g, int cfg, hipStream_t s) {
   switch (cfg) {
@@ -193,7 +193,6 @@ gemm_status bx3_run_trans(const GemmArgs &g, int cfg, hipStream_t s) {
     case 2: return launch<256, 128, 32, 64, 64, 2, 8, TA, TB>(g, s);
     case 3: return launch<256, 256, 32, 128, 64, 2, 8, TA, TB>(g, s);
     case 4: return launch<256, 256, 16, 128, 64, 3, 8, TA, TB>(g, s);
-    case 5: return launch<128, 128, 32, 64, 64, 3, 4, TA, TB>(g, s);
     case 6: return launch<64, 64, 32, 32, 32, 2, 4, TA, TB>(g, s);
     case 8: return launch<128, 128, 16, 64, 64, 2, 4, TA, TB>(g, s);
     case 14: return launch_kg<128, 128, 16, 64, 64, 2, 4, TA, TB>(g, s);
