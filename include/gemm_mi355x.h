@@ -69,7 +69,8 @@ const char *gemm_version(void);
  * sum in binary32), or where those would leave compute units idle the
  * small-product tiles (32 x 32 or 64 x 64 outputs per workgroup, the k range
  * split over its eight waves on the same matrix-core instruction, partial
- * tiles summed in wave order).
+ * tiles summed in wave order).  A tile that sums over longer runs of k than the
+ * one that the number of output tiles alone gives is not taken, however fast.
  * The vector-ALU tiles (fused multiply-add accumulation in per-lane register
  * micro-tiles) remain configurations of the path: gemm_run_config selects
  * any of them.
@@ -92,8 +93,9 @@ gemm_status gemm_f32(int64_t M, int64_t N, int64_t K, float alpha,
  * tile is staged into LDS, and
  *   n_products == 3 : acc += a0*b0 + a0*b1 + a1*b0
  *   n_products == 6 : acc += the above + a0*b2 + a1*b1 + a2*b0
- * with binary32 MFMA accumulation.  Arguments as gemm_f32, then
- * 12 n_products (3 or 6), 13 stream.
+ * with binary32 MFMA accumulation.  The default tile splits k into at least as
+ * many partial sums as the tile that the number of output tiles alone gives.
+ * Arguments as gemm_f32, then 12 n_products (3 or 6), 13 stream.
  * ---------------------------------------------------------------------- */
 gemm_status gemm_f32_3xbf16(int64_t M, int64_t N, int64_t K, float alpha,
                             const float *A, int64_t lda, const float *B, int64_t ldb,
@@ -229,9 +231,10 @@ gemm_status gemm_f64_strided_batched(int64_t M, int64_t N, int64_t K, double alp
  * (n_products 3 or 6, as gemm_f32_3xbf16).  Output matrices must not
  * overlap: stride_c >= (M-1)*ldc + N when batch > 1.  Layout and quick
  * returns as gemm_f32; up to 65535 problems per launch.  Problems run as 32 x
- * 32 sub-tiles of one wave each (no LDS staging) or on
- * the LDS-staged tiles, whichever is modelled faster, with results bitwise
- * those of the library's matrix-core tiles of the same arithmetic either way.
+ * 32 sub-tiles of one wave each, up to 64 x 64 as one wave per problem (neither
+ * stages through LDS), or on the LDS-staged tiles, whichever is modelled fastest,
+ * with results bitwise those of the library's matrix-core tiles of the same
+ * arithmetic in each case.
  * Arguments: 1 path,
  * 2 M, 3 N, 4 K, 5 alpha, 6 A, 7 lda, 8 stride_a, 9 B, 10 ldb, 11 stride_b,
  * 12 beta, 13 C, 14 ldc, 15 stride_c, 16 batch, 17 n_products, 18 stream. */

@@ -111,7 +111,7 @@ int grouped_pick_variant(int64_t M, int64_t N, double small_cost) {
 }
 
 size_t grouped_ws_bytes(int count) {
-  const size_t head = 256;
+  const size_t head = 256;  // unused: the size that callers allocate stays as it was
   const size_t descs = ((sizeof(Desc) * (size_t)count + 255) / 256) * 256;
   const size_t starts = sizeof(int) * ((size_t)count + 1);
   return head + descs + starts;

@@ -41,9 +41,10 @@ struct TileCost {
   double fixed, alone, full, start;
 };
 double tile_time(const TileCost &t, int64_t M, int64_t N, int64_t K);
-// The default configuration of `path` for g, or, where 32-bit offsets of that
-// one cannot reach the operands, the configuration that tile counts alone give
-// (large tiles that address one panel at a time).
+// The default configuration of `path` for g, or, where that one cannot run g
+// (32-bit offsets, the lanes of a launch), the configuration that tile counts
+// alone give.  That may be a small tile of a single output tile, which reads its
+// operands at 32-bit offsets too: a g that it cannot reach is refused at launch.
 int addressable_config(int path, int n_products, const GemmArgs &g);
 
 // Plain FP32 vector-ALU path.
